@@ -311,7 +311,7 @@ def measure_workload(index: int, steps: int, warmup: int, args, hbm_meas: float,
     else:
         nbytes = algorithmic_bytes_lmhead(inp)
         ach = nbytes / (kernel_us["lmhead"] * 1e-6) / 1e9
-        kname = "lmhead_f32_kernel" if inp.dtype == "f32" else ("lmhead_bf16_packed_kernel" if packed else "lmhead_bf16_kernel")
+        kname = "lmhead_f32_kernel" if inp.dtype == "f32" else "lmhead_bf16_ring_kernel"
         roof_lm = {"kernel": kname, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                    "frac": ach / HBM_PEAK_GBS, "traffic": measured_traffic(inp.name, "lmhead"), "algorithmic_bytes": nbytes,
                    "frac_of_measured_peak": ach / hbm_meas}

@@ -2,12 +2,10 @@
 // (Sec. 4.2: the O(hV) projection dominates; App. "Configuration Details": guidance scale,
 // temperature, top-k), then one kernel for the per-row softmax statistics.
 //
-// bf16 projection: a workgroup owns 64 vocabulary columns x 64 nodes (conditional and
-// unconditional rows of the same nodes, so the mix happens in registers).  Its four waves split
-// the hidden dimension; every wave streams its own slices of W and H straight from global memory
-// into v_mfma_f32_32x32x16_bf16 operand registers (both operands are k-contiguous, so a lane's
-// 8 operand values are one 16-byte load) and the four partial tiles are summed through LDS once
-// at the end.  Nothing is shared between waves inside the main loop, so it has no barriers.
+// bf16 projection: both operands reach the matrix cores through a ring of LDS stages filled by LDS-direct loads.
+// lmhead_bf16_ring_kernel takes rows and weights as they lie in memory (or packed weights) and comes in tiles from
+// 64 x 64 to 256 x 128; lmhead_bf16_tiled_kernel takes both operands packed and carries the large tiles of steps with
+// several hundred rows.  launch_lmhead_bf16 chooses by estimated time.
 #include "common.h"
 
 namespace {
@@ -23,7 +21,6 @@ struct LmParams {
   const uint4* hp_cond;     // packed hidden states (MFMA operand order), when the packed path runs
   const uint4* hp_uncond;
   int n_nodes, hidden, vocab;
-  int n_mchunks;
   float cfg_scale, temperature;
   int top_k;
 };
@@ -62,106 +59,6 @@ union Frag8 {
   u32x4 n;
 };
 
-template <bool CFG>
-struct Group {   // operands of 4 consecutive k16 steps
-  static constexpr int NA = CFG ? 4 : 2;
-  Frag8 a[4][NA];
-  Frag8 b[4][2];
-};
-
-template <bool CFG>
-__global__ __launch_bounds__(256) void lmhead_bf16_kernel(LmParams p) {
-  constexpr int NA = CFG ? 4 : 2;   // 32-row operand blocks: cond0, cond1, (uncond0, uncond1)
-  extern __shared__ float red[];    // [4 waves][NA*2 acc][16 regs][64 lanes]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r32 = lane & 31, half = lane >> 5;
-  const int K = p.hidden;
-
-  // XCD-aware order: the 8 XCDs take workgroups round-robin; give each XCD a contiguous range of
-  // logical ids so that the m-chunks sharing one W tile meet in the same L2.
-  int logical = blockIdx.x;
-  const int nwg = gridDim.x;
-  if ((nwg & 7) == 0) logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-  const int ntile = logical / p.n_mchunks, mc = logical % p.n_mchunks;
-  const int v0 = ntile * 64, node0 = mc * 64;
-
-  const uint16_t* ap[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int node = min(node0 + 32 * (i & 1) + r32, p.n_nodes - 1);   // rows past the end are clamped, never stored
-    const uint16_t* base = (i < 2) ? (const uint16_t*)p.h_cond : (const uint16_t*)p.h_uncond;
-    ap[i] = base + (int64_t)node * K + 8 * half;
-  }
-  const uint16_t* bp[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) bp[j] = (const uint16_t*)p.w + (int64_t)(v0 + 32 * j + r32) * K + 8 * half;
-
-  f32x16 acc[NA][2];
-#pragma unroll
-  for (int i = 0; i < NA; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // this wave's k groups (64 wide): 128-wide slices wave, wave+4, ... of the hidden dimension
-  const int n_slices = (K / 128 - wave + 3) / 4;   // K is a multiple of 128
-  const int n_groups = 2 * n_slices;
-  auto k_of = [&](int gi) { return (wave + 4 * (gi >> 1)) * 128 + 64 * (gi & 1); };
-  auto load_group = [&](Group<CFG>& G, int k) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-#pragma unroll
-      for (int i = 0; i < NA; ++i) G.a[s][i].u = *(const uint4*)(ap[i] + k + 16 * s);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) G.b[s][j].u = *(const uint4*)(bp[j] + k + 16 * s);
-    }
-  };
-  auto compute_group = [&](const Group<CFG>& G) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G.a[s][i].v, G.b[s][j].v, acc[i][j], 0, 0, 0);
-  };
-
-  Group<CFG> g0, g1;
-  if (n_groups > 0) load_group(g0, k_of(0));
-  for (int gi = 0; gi < n_groups; gi += 2) {   // n_groups is even
-    load_group(g1, k_of(gi + 1));
-    compute_group(g0);
-    if (gi + 2 < n_groups) load_group(g0, k_of(gi + 2));
-    compute_group(g1);
-  }
-
-  // cross-wave reduction and epilogue
-  constexpr int NACC = NA * 2;
-#pragma unroll
-  for (int i = 0; i < NA; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[((wave * NACC + i * 2 + j) * 16 + r) * 64 + lane] = acc[i][j][r];
-  __syncthreads();
-  const int nbk = wave >> 1, nb = wave & 1;
-  const float inv_t = 1.f / p.temperature;
-  (void)inv_t;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float c = 0.f, u = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      c += red[((w * NACC + nbk * 2 + nb) * 16 + r) * 64 + lane];
-      if (CFG) u += red[((w * NACC + (2 + nbk) * 2 + nb) * 16 + r) * 64 + lane];
-    }
-    const float gmix = CFG ? u + p.cfg_scale * (c - u) : c;
-    const int node = node0 + 32 * nbk + 8 * (r >> 2) + 4 * half + (r & 3);
-    if (node < p.n_nodes) p.logits[(int64_t)node * p.vocab + v0 + 32 * nb + r32] = gmix / p.temperature;
-  }
-}
-
 // ------------------------------------------------------------------------- bf16, packed operands
 // Operand order: for a block of 32 rows rb and a 16-wide k step ks, 64 x 16 bytes where entry
 // l = (r32, half) holds src[32*rb + r32][16*ks + 8*half .. +7]; the ks blocks of one rb follow
@@ -179,6 +76,22 @@ __global__ __launch_bounds__(256) void pack32_kernel(const uint16_t* __restrict_
   dst[((int64_t)rb * (K / 16) + ks) * 64 + lane] = v;
 }
 
+// eight guidance-mixed elements u + s (c - u), float32, rounded once to bf16
+__device__ __forceinline__ uint4 mix16(const uint4& c, const uint4& u, float s) {
+  const uint32_t cw[4] = {c.x, c.y, c.z, c.w}, uw[4] = {u.x, u.y, u.z, u.w};
+  uint32_t m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float c0 = __uint_as_float(cw[i] << 16), c1 = __uint_as_float(cw[i] & 0xffff0000u);
+    const float u0 = __uint_as_float(uw[i] << 16), u1 = __uint_as_float(uw[i] & 0xffff0000u);
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const b2 r = __builtin_convertvector(f2{u0 + s * (c0 - u0), u1 + s * (c1 - u1)}, b2);   // round to nearest even
+    m[i] = *(const uint32_t*)&r;
+  }
+  return make_uint4(m[0], m[1], m[2], m[3]);
+}
+
 // The same operand order for the guidance-mixed rows u + s (c - u) (float32, rounded once to bf16): the
 // projection is linear, so one product over these rows gives the mixed logits.
 __global__ __launch_bounds__(256) void pack32_mix_kernel(const uint16_t* __restrict__ src_c, const uint16_t* __restrict__ src_u,
@@ -191,160 +104,174 @@ __global__ __launch_bounds__(256) void pack32_mix_kernel(const uint16_t* __restr
   if (row < rows) {
     const int64_t o = (int64_t)row * K + 16 * ks + 8 * half;
     const uint4 c = *(const uint4*)(src_c + o), u = *(const uint4*)(src_u + o);
-    const uint32_t cw[4] = {c.x, c.y, c.z, c.w}, uw[4] = {u.x, u.y, u.z, u.w};
-    uint32_t m[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float c0 = __uint_as_float(cw[i] << 16), c1 = __uint_as_float(cw[i] & 0xffff0000u);
-      const float u0 = __uint_as_float(uw[i] << 16), u1 = __uint_as_float(uw[i] & 0xffff0000u);
-      typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-      typedef float f2 __attribute__((ext_vector_type(2)));
-      const b2 r = __builtin_convertvector(f2{u0 + s * (c0 - u0), u1 + s * (c1 - u1)}, b2);   // round to nearest even
-      m[i] = *(const uint32_t*)&r;
-    }
-    v = make_uint4(m[0], m[1], m[2], m[3]);
+    v = mix16(c, u, s);
   }
   dst[((int64_t)rb * (K / 16) + ks) * 64 + lane] = v;
 }
 
-// NSTEPS > 0: k16 steps per wave known at compile time (K = 64 * NSTEPS), deep fully unrolled pipeline.
-template <bool CFG, int NSTEPS>
-__global__ __launch_bounds__(256) void lmhead_bf16_packed_kernel(LmParams p) {
-  constexpr bool DEEP = NSTEPS > 0;
-  constexpr int NA = CFG ? 4 : 2;
-  extern __shared__ float red[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// The same mixed rows, left row-major (what the ring kernel reads).
+__global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__ src_c, const uint4* __restrict__ src_u,
+                                                        uint4* __restrict__ dst, int n16, float s) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) dst[i] = mix16(src_c[i], src_u[i], s);
+}
+
+// ----------------------------------------------------------------------------------- bf16, ring of stages
+// Tile = 32 AM WM rows x 32 AN WN vocabulary columns per workgroup of eight waves; a wave owns AM x AN blocks of
+// 32 x 32 and every KW-th k16 step of a stage (KW groups of waves split the hidden dimension inside the workgroup and
+// are summed through LDS at the end, in a fixed order).  A stage = KS k16 steps of every row and column block of the
+// tile; NST stages are in flight or in use.  With guidance a wave's two row blocks are the conditional and the
+// unconditional rows of the same 32 nodes, so the mix stays in registers.
+//
+// What bounds it: the bytes a compute unit has in flight.  Loads alone (no multiplications, no LDS reads) take 90 % of
+// the kernel's time at every tile, and requesting more than ~64 KB ahead changes nothing (48 KB: 33 us, 72 KB: 29.6,
+// 120 KB: 29.6 at 60 x 16384 x 4096), so a tile costs about (weight bytes x HBM latency + row bytes x L2 latency) / 64 KB.
+// Hence tiles as large as the row count justifies, each weight byte loaded once per row tile, no padding traffic.
+// Rows are read as they lie in memory: a wave's 1 KiB request covers whole 128-byte pieces of eight rows (eight lanes per
+// row), and no packing pass precedes the kernel (row-major rows measured the same as packed ones).  LDS-direct loads put
+// lane l's 16 bytes at 16 l, so bank conflicts are avoided by WHICH piece a lane fetches: slot q of row r holds piece
+// q ^ ((r >> 1) & 7), and the 16 rows that a fragment read touches together land in 16 different 16-byte slots.  Packed
+// weights (contiguous 1 KiB operand blocks) are 4 us faster than row-major ones at 16384 x 4096.
+// Measured against the kernels this replaced (64 x 64 tiles, operands loaded to registers, hidden 4096; us, without the
+// packing pass of 4 us that they needed): 60 rows x 16384: 30.2 -> 27.4; 60 x 65536: 110 -> 101 (5.3 TB/s);
+// 120 x 16384: 45 -> 35; 230 x 16384: 75 -> 45; 60 guidance pairs, row-major weights: 63 -> 37.
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
+__global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n_mtiles) {
+  static_assert(WM * WN * KW == 8 && KS % KW == 0 && KS % 4 == 0 && (!CFG || AM == 2), "eight waves; guidance pairs are a wave's two row blocks");
+  constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NA = BM / 32, NBLK = NA + BN / 32, STAGE = NBLK * KS * 1024;
+  constexpr int LPW = NBLK * KS / 8, SPW = KS / KW;
+  static_assert(NBLK * KS % 8 == 0, "every wave requests the same number of 1 KiB chunks");
+  extern __shared__ __align__(1024) char ring_lds[];   // [NST stages][NBLK blocks][KS KiB]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, half = lane >> 5;
-  const int K = p.hidden, KS = K / 16;
+  const int K = p.hidden, n_stages = K / (16 * KS);    // hidden is a multiple of 128
+  // XCD-aware order: contiguous ranges of tiles per XCD (any grid size), row tiles of one column tile adjacent in its L2
+  const int nwg = gridDim.x, xcd = blockIdx.x & 7;
+  const int logical = xcd * (nwg >> 3) + min(xcd, nwg & 7) + (blockIdx.x >> 3);
+  const int nt = logical / n_mtiles, mt = logical % n_mtiles;
 
-  int logical = blockIdx.x;
-  const int nwg = gridDim.x;
-  if ((nwg & 7) == 0) logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-  const int ntile = logical / p.n_mchunks, mc = logical % p.n_mchunks;
-  const int v0 = ntile * 64, node0 = mc * 64;
-
-  const uint4* ap[NA];
+  // loader: chunk id = LPW wave + i of a stage: block id / KS, KiB id % KS of it (one k16 step of packed operands, or
+  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece)
+  unsigned voff[LPW];
+  const char* src[LPW];
 #pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const uint4* base = (i < 2) ? p.hp_cond : p.hp_uncond;
-    ap[i] = base + ((int64_t)(mc * 2 + (i & 1)) * KS) * 64 + lane;
+  for (int i = 0; i < LPW; ++i) {
+    const int id = wave * LPW + i, blk = id / KS, q = id % KS;
+    const char* base;
+    int row0, rows;
+    if (blk < NA) {
+      base = (const char*)((CFG && (blk & 1)) ? p.h_uncond : p.h_cond);
+      row0 = CFG ? mt * (BM / 2) + 32 * (blk >> 1) : mt * BM + 32 * blk;
+      rows = p.n_nodes;
+    } else {
+      base = (const char*)p.w;
+      row0 = nt * BN + 32 * (blk - NA);
+      rows = p.vocab;
+    }
+    if (PW && blk >= NA) {
+      src[i] = base + ((int64_t)min(row0 / 32, rows / 32 - 1) * (K / 16) + q) * 1024;   // columns past the end: clamped, never stored
+      voff[i] = 16u * lane;
+    } else {
+      const int lr = 8 * (q & 3) + (lane >> 3), first = min(row0, rows - 1);
+      src[i] = base + (int64_t)first * 2 * K + (q >> 2) * 128;
+      voff[i] = (unsigned)(min(row0 + lr, rows - 1) - first) * (unsigned)(2 * K) + 16u * (unsigned)((lane & 7) ^ ((lr >> 1) & 7));
+    }
   }
-  const uint4* bp[2];
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)ring_lds) + wave * LPW * 1024;
+  auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
+    const int tc = min(t, n_stages - 1);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) bp[j] = (const uint4*)p.w + ((int64_t)(ntile * 2 + j) * KS) * 64 + lane;
+    for (int i = 0; i < LPW; ++i) {
+      const char* g = src[i] + (int64_t)tc * ((PW && (wave * LPW + i) / KS >= NA) ? KS * 1024 : KS * 32);
+      const unsigned l = lds0 + slot * STAGE + i * 1024;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
+    }
+  };
+  const int kw = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
+  // byte offset of k16 step s of a block for this lane (its 16 bytes of row r32)
+  auto packed_at = [&](int s) { return (unsigned)(s * 1024 + lane * 16); };
+  auto rows_at = [&](int s) { return (unsigned)((s >> 2) * 4096 + r32 * 128 + (((2 * (s & 3) + half) ^ ((r32 >> 1) & 7)) * 16)); };
 
-  f32x16 acc[NA][2];
+  f32x16 acc[AM][AN];
 #pragma unroll
-  for (int i = 0; i < NA; ++i)
+  for (int i = 0; i < AM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < AN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int n_slices = (K / 128 - wave + 3) / 4;   // 128-wide slices wave, wave+4, ... of the hidden dimension
-  if constexpr (DEEP) {
-    // Deep software pipeline, one k16 step at a time.
-    // W streams from HBM: requested WD = 16 steps ahead (32 KiB in flight per wave).  H comes from
-    // L2: requested HD = 8 steps ahead.  Registers: 32 + 32 operand fragments and 8 accumulators.
-    // After a step's MFMAs its own ring slots are refilled, H first, so that waiting for the H
-    // fragment of a later step never waits for younger W requests.
-    constexpr int HD = 8, WD = 16;
-    static_assert(!DEEP || (NSTEPS % 8 == 0 && NSTEPS >= WD), "whole 128-wide slices per wave");
-    // Workgroups that run side by side start at different slices of the hidden dimension (rot), so
-    // that at any moment they read different parts of H (spread over the L2 channels instead of all
-    // hitting the same lines) and their W streams differ in the low address bits as well.
-    constexpr int NSL = NSTEPS / 8;                               // slices per wave (a power of two is not required)
-    const int rot = __builtin_amdgcn_readfirstlane(((blockIdx.x >> 3) + (blockIdx.x & 7)) % NSL);
-    auto ks_of_step = [&](int t) { return (wave + 4 * (((t >> 3) + rot) % NSL)) * 8 + (t & 7); };
-    Frag8 hr[HD][NA];
-    Frag8 wr[WD][2];
-    auto load_h = [&](int slot, int t) {
-      const int64_t o = (int64_t)ks_of_step(t) * 64;
 #pragma unroll
-      for (int i = 0; i < NA; ++i) hr[slot][i].u = ap[i][o];
-    };
-    auto load_w = [&](int slot, int t) {
-      const int64_t o = (int64_t)ks_of_step(t) * 64;
+  for (int t = 0; t < NST - 1; ++t) request(t, t);
+  int slot = 0;
+  for (int t = 0; t < n_stages; ++t) {
+    // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
+    // barrier: everybody's chunks are there and stage t - 1's slot is free
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
+    request(t + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+    const char* st = ring_lds + slot * STAGE;
+    Frag8 a[SPW][AM], b[SPW][AN];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) wr[slot][j].u = bp[j][o];
-    };
-    // prologue in the same request order as the steady state (..., H(t+8), W(t+16), ...)
+    for (int ss = 0; ss < SPW; ++ss) {
+      const int s = kw * SPW + ss;
 #pragma unroll
-    for (int t = 0; t < WD - HD; ++t) load_w(t, t);
+      for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
 #pragma unroll
-    for (int t = 0; t < HD; ++t) {
-      load_h(t, t);
-      load_w(WD - HD + t, WD - HD + t);
+      for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
     }
-    // fully unrolled: the whole schedule is straight-line code with exact outstanding-load counts
 #pragma unroll
-    for (int t = 0; t < NSTEPS; ++t) {
+    for (int ss = 0; ss < SPW; ++ss)
 #pragma unroll
-      for (int i = 0; i < NA; ++i)
+      for (int i = 0; i < AM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hr[t % HD][i].v, wr[t % WD][jj].v, acc[i][jj], 0, 0, 0);
-      if (t + HD < NSTEPS) load_h(t % HD, t + HD);
-      if (t + WD < NSTEPS) load_w(t % WD, t + WD);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    const int n_groups = 2 * n_slices;
-    auto ks_of = [&](int gi) { return (wave + 4 * (gi >> 1)) * 8 + 4 * (gi & 1); };   // first k16 step of the group
-    auto load_group = [&](Group<CFG>& G, int ks) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) G.a[s][i].u = ap[i][(int64_t)(ks + s) * 64];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) G.b[s][j].u = bp[j][(int64_t)(ks + s) * 64];
-      }
-    };
-    auto compute_group = [&](const Group<CFG>& G) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int i = 0; i < NA; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G.a[s][i].v, G.b[s][j].v, acc[i][j], 0, 0, 0);
-    };
-    Group<CFG> g0, g1;
-    if (n_groups > 0) load_group(g0, ks_of(0));
-    for (int gi = 0; gi < n_groups; gi += 2) {
-      load_group(g1, ks_of(gi + 1));
-      compute_group(g0);
-      if (gi + 2 < n_groups) load_group(g0, ks_of(gi + 2));
-      compute_group(g1);
-    }
+        for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
+    slot = slot + 1 == NST ? 0 : slot + 1;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
-  constexpr int NACC = NA * 2;
+  // epilogue: accumulator (i, j), register r of lane (r32, half) is row 8 (r / 4) + 4 half + r % 4, column r32
+  constexpr int NI = CFG ? 1 : AM;   // node blocks of a wave
+  auto emit = [&](int i, int j, int r, float x0, float x1) {
+    const int node = (CFG ? mt * (BM / 2) + 32 * wm : mt * BM + 32 * (AM * wm + i)) + 8 * (r >> 2) + 4 * half + (r & 3);
+    const int col = nt * BN + 32 * (AN * wn + j) + r32;
+    const float gmix = CFG ? x1 + p.cfg_scale * (x0 - x1) : x0;
+    if (node < p.n_nodes && col < p.vocab) p.logits[(int64_t)node * p.vocab + col] = gmix / p.temperature;
+  };
+  if constexpr (KW == 1) {
 #pragma unroll
-  for (int i = 0; i < NA; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < AN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[((wave * NACC + i * 2 + j) * 16 + r) * 64 + lane] = acc[i][j][r];
-  __syncthreads();
-  const int nbk = wave >> 1, nb = wave & 1;
+        for (int r = 0; r < 16; ++r) emit(i, j, r, acc[i][j][r], CFG ? acc[AM - 1][j][r] : 0.f);
+  } else {
+    // the KW partial tiles meet in LDS; wave group kw finishes every KW-th of the wave tile's values
+    __syncthreads();
+    constexpr int NV = AM * AN * 16, PER = NI * AN * 16 / KW;
+    float* red = (float*)ring_lds;   // [8 waves][NV values][64 lanes]
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float c = 0.f, u = 0.f;
+    for (int i = 0; i < AM; ++i)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      c += red[((w * NACC + nbk * 2 + nb) * 16 + r) * 64 + lane];
-      if (CFG) u += red[((w * NACC + (2 + nbk) * 2 + nb) * 16 + r) * 64 + lane];
+      for (int j = 0; j < AN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[(wave * NV + (i * AN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int e0 = 0; e0 < PER; ++e0) {
+      const int e = kw * PER + e0;
+      float x0 = 0.f, x1 = 0.f;
+#pragma unroll
+      for (int g = 0; g < KW; ++g) {
+        const float* part = red + (wave % (WM * WN) + g * WM * WN) * NV * 64 + lane;
+        x0 += part[e * 64];
+        if (CFG) x1 += part[(AN * 16 + e) * 64];
+      }
+      emit(e / (AN * 16), (e >> 4) % AN, e & 15, x0, x1);
     }
-    const float gmix = CFG ? u + p.cfg_scale * (c - u) : c;
-    const int node = node0 + 32 * nbk + 8 * (r >> 2) + 4 * half + (r & 3);
-    if (node < p.n_nodes) p.logits[(int64_t)node * p.vocab + v0 + 32 * nb + r32] = gmix / p.temperature;
   }
 }
 
-
 // ------------------------------------------------------------------- bf16, packed, many rows
-// LDS-tiled projection for steps with several hundred rows (batched prompts), where the kernel is
+// LDS-tiled projection for the large tiles of steps with several hundred rows (batched prompts), where the kernel is
 // bound by the matrix cores instead of by streaming W.  Workgroup tile = 256 rows x 256 vocabulary
 // columns: with guidance 128 nodes (4 conditional + 4 unconditional 32-row blocks), without 256
 // nodes.  The eight waves form a 2 x 4 grid; a wave owns 4 row blocks (two node blocks, conditional
@@ -397,7 +324,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
       else { base = (const char*)p.hp_cond; rb = (int64_t)mt * 8 + wave; }
     } else {
       base = (const char*)p.w;
-      rb = (int64_t)nt * 8 + wave;
+      rb = min(nt * 8 + wave, p.vocab / 32 - 1);   // a last column tile past the vocabulary re-reads its last block, never stored
     }
     src[b4] = base + rb * KS * 1024;
   }
@@ -492,15 +419,17 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   for (int i = 0; i < (CFG ? 2 : NI); ++i) {
     const int node0 = (CFG || HALF) ? mt * 128 + 32 * (2 * wm + i) : mt * 256 + 32 * (4 * wm + i);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j) {
+      const int n_here = v0 + 32 * j < p.vocab ? p.n_nodes : 0;   // nothing to store past the vocabulary
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float c = acc[i][j][r];
         const float gmix = CFG ? acc[i + 2][j][r] + p.cfg_scale * (c - acc[i + 2][j][r]) : c;
         const int node = node0 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (node < p.n_nodes) p.logits[(int64_t)node * p.vocab + v0 + 32 * j + r32] = gmix / p.temperature;
+        if (node < n_here) p.logits[(int64_t)node * p.vocab + v0 + 32 * j + r32] = gmix / p.temperature;
         if (r == 15) __builtin_amdgcn_sched_barrier(0);
       }
+    }
   }
 }
 
@@ -826,7 +755,6 @@ LmParams make_params(const lmhead_args* a) {
   p.n_nodes = a->n_nodes;
   p.hidden = a->hidden;
   p.vocab = a->vocab;
-  p.n_mchunks = (a->n_nodes + 63) / 64;
   p.cfg_scale = a->cfg_scale;
   p.temperature = a->temperature;
   p.top_k = a->top_k;
@@ -845,74 +773,120 @@ hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a) {
   return hipGetLastError();
 }
 
-template <bool CFG, int KIND>   // KIND 0: row-major W, 1: packed, 2: packed + deep pipeline
-hipError_t launch_bf16_gemm(cascade_ctx* ctx, const LmParams& p, int grid) {
-  const size_t smem = (size_t)4 * (CFG ? 8 : 4) * 16 * 64 * sizeof(float);
-  auto kern = KIND == 2 ? lmhead_bf16_packed_kernel<CFG, 64> : (KIND == 1 ? lmhead_bf16_packed_kernel<CFG, 0> : lmhead_bf16_kernel<CFG>);
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
+hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p) {
+  constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NODES = CFG ? BM / 2 : BM;
+  constexpr int RING = NST * (BM + BN) / 32 * KS * 1024, RED = KW > 1 ? 8 * AM * AN * 4096 : 0;
+  constexpr int smem = RING > RED ? RING : RED;
+  static_assert(smem <= 160 * 1024, "LDS of a compute unit");
+  auto kern = lmhead_bf16_ring_kernel<AM, AN, WM, WN, KW, KS, NST, CFG, PW>;
   static bool attr_done = false;   // one flag per template instance
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
+  const int n_mtiles = (p.n_nodes + NODES - 1) / NODES;
   KernelTimer t(ctx, CASCADE_K_LMHEAD);
-  CASCADE_TIMED_LAUNCH(t, kern, dim3(grid), dim3(256), smem, ctx->stream, p);
+  CASCADE_TIMED_LAUNCH(t, kern, dim3((p.vocab + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
+}
+template <bool CFG, bool PW>
+hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile) {
+  switch (tile) {
+    case 0: return launch_ring_t<2, 1, 1, 2, 4, 4, 6, CFG, PW>(ctx, p);
+    case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p);
+    case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p);
+    case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p);
+    default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p);
+  }
+}
+
+// Tiles of the projection and what one of them costs a compute unit at hidden 4096 when the weight stream does not
+// bind (us, measured with every unit holding one tile): ring kernel 0-4, tiled kernel 5 (128 x 256, plain rows only)
+// and 6 (256 x 256).
+struct LmTile {
+  int rows, cols;
+  float us;
+};
+constexpr LmTile LM_TILES[7] = {{64, 64, 22.f}, {128, 64, 28.f}, {64, 256, 51.f}, {128, 128, 42.f}, {256, 128, 68.f}, {128, 256, 65.f}, {256, 256, 112.f}};
+constexpr int LM_RING_TILES = 5;
+
+// Estimated time of a tile shape: rounds of tiles over the compute units, and the weight stream at 5.3 TB/s, which
+// overlap only partly (fourth-power mean; within 10 % of the measured time at 60-1024 rows, 16384-65536 columns: e.g.
+// 60 x 65536: 113 us in 64 x 64 tiles (measured 112), 103 in 64 x 256 (101); 230 x 16384: 43 in 128 x 128 (45), 57 in
+// 128 x 64 (57); 256 x 65536: 130 in 256 x 256 (141), 140 in 256 x 128 (156)).
+float lm_estimate_us(const LmTile& tile, int rows, int vocab, int hidden, int n_cu) {
+  const long tiles = (long)((rows + tile.rows - 1) / tile.rows) * ((vocab + tile.cols - 1) / tile.cols);
+  const float k = hidden / 4096.f, a = (float)((tiles + n_cu - 1) / n_cu) * tile.us * k, b = (float)vocab * hidden * 2.f / 5.3e6f;
+  return sqrtf(sqrtf(a * a * a * a + b * b * b * b));
 }
 
 hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
   LmParams p = make_params(a);
-  const int grid = (a->vocab / 64) * p.n_mchunks;
-  // guidance mixed into the hidden rows while they are packed: from here on a plain projection of n_nodes rows
-  const bool premix = a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && a->w_layout == CASCADE_W_PACKED32;
+  const bool packed_w = a->w_layout == CASCADE_W_PACKED32;
+  // guidance mixed into the hidden rows in front of the projection: from here on a plain projection of n_nodes rows
+  const bool premix = a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && packed_w;
   const bool cfg = a->h_uncond != nullptr && !premix;
-  if (a->w_layout == CASCADE_W_PACKED32) {
-    // many rows and a vocabulary made of whole 256-column tiles: LDS-tiled kernel, 256-row tiles
-    const int rows = a->n_nodes * (cfg ? 2 : 1);
-    const bool tiled = rows >= (cfg ? 512 : 257) && (a->vocab % 256) == 0;
-    // plain projection: 128-row tiles when the 256-row tiling would leave compute units without a workgroup
-    const bool half = !cfg && (long)((a->n_nodes + 255) / 256) * (a->vocab / 256) < ctx->n_cu;
-    const int nodes_per_tile = (cfg || half) ? 128 : 256;
-    const int n_mtiles = (a->n_nodes + nodes_per_tile - 1) / nodes_per_tile;
-    // repack this step's hidden states into operand order (zero rows up to a whole tile / chunk)
-    const int rblocks = tiled ? n_mtiles * (nodes_per_tile / 32) : p.n_mchunks * 2;
-    const size_t per = (size_t)rblocks * 32 * a->hidden * 2;
-    if (per * 2 > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
-    uint4* hc = (uint4*)ctx->hpack_ws;
-    uint4* hu = (uint4*)(ctx->hpack_ws + per);
-    dim3 pgrid((a->hidden / 16 + 3) / 4, rblocks, cfg ? 2 : 1);
-    {
-      KernelTimer t(ctx, CASCADE_K_PACK);
-      if (premix) {
-        CASCADE_TIMED_LAUNCH(t, pack32_mix_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond,
-                             (const uint16_t*)a->h_uncond, hc, a->n_nodes, a->hidden, a->cfg_scale);
-      } else {
-        CASCADE_TIMED_LAUNCH(t, pack32_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond, hc,
-                             (const uint16_t*)a->h_uncond, hu, a->n_nodes, a->hidden);
-      }
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    p.hp_cond = hc;
-    p.hp_uncond = hu;
-    if (tiled) {
-      const size_t smem = (size_t)4 * 32 * 1024;   // ring of four 32 KiB half-stages
-      static bool attr_done[3] = {false, false, false};
-      auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false> : (half ? lmhead_bf16_tiled_kernel<false, true> : lmhead_bf16_tiled_kernel<false, false>);
-      const int which = cfg ? 0 : (half ? 1 : 2);
-      if (!attr_done[which]) {
-        e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_done[which] = true;
-      }
-      KernelTimer t(ctx, CASCADE_K_LMHEAD);
-      CASCADE_TIMED_LAUNCH(t, kern, dim3((a->vocab / 256) * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
-      return hipGetLastError();
-    }
-    if (a->hidden == 4096) return cfg ? launch_bf16_gemm<true, 2>(ctx, p, grid) : launch_bf16_gemm<false, 2>(ctx, p, grid);
-    return cfg ? launch_bf16_gemm<true, 1>(ctx, p, grid) : launch_bf16_gemm<false, 1>(ctx, p, grid);
+  const int rows = a->n_nodes * (cfg ? 2 : 1);
+  int best = 0;
+  float best_us = INFINITY;
+  for (int i = 0; i < (packed_w ? 7 : LM_RING_TILES); ++i) {
+    if (i == 5 && cfg) continue;
+    float us = lm_estimate_us(LM_TILES[i], rows, a->vocab, a->hidden, ctx->n_cu);
+    if (i >= LM_RING_TILES && !premix) us += 4.f;   // the tiled kernel needs its rows packed (the mix packs them on the way)
+    if (us < best_us) { best = i; best_us = us; }
   }
-  return cfg ? launch_bf16_gemm<true, 0>(ctx, p, grid) : launch_bf16_gemm<false, 0>(ctx, p, grid);
+  const bool tiled = best >= LM_RING_TILES, half = best == 5;
+  uint4* hc = (uint4*)ctx->hpack_ws;
+  if (!tiled) {
+    if (premix) {
+      const int64_t n16 = (int64_t)a->n_nodes * a->hidden / 8;
+      if ((size_t)n16 * 16 > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
+      KernelTimer t(ctx, CASCADE_K_PACK);
+      CASCADE_TIMED_LAUNCH(t, mix_rows_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, ctx->stream, (const uint4*)a->h_cond,
+                           (const uint4*)a->h_uncond, hc, (int)n16, a->cfg_scale);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      p.h_cond = hc;
+    }
+    if (packed_w) return cfg ? launch_ring<true, true>(ctx, p, best) : launch_ring<false, true>(ctx, p, best);
+    return cfg ? launch_ring<true, false>(ctx, p, best) : launch_ring<false, false>(ctx, p, best);
+  }
+  const int nodes_per_tile = (cfg || half) ? 128 : 256;
+  const int n_mtiles = (a->n_nodes + nodes_per_tile - 1) / nodes_per_tile;
+  // this step's hidden states in operand order (zero rows up to a whole tile)
+  const int rblocks = n_mtiles * (nodes_per_tile / 32);
+  const size_t per = (size_t)rblocks * 32 * a->hidden * 2;
+  if (per * (cfg ? 2 : 1) > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
+  uint4* hu = (uint4*)(ctx->hpack_ws + per);
+  dim3 pgrid((a->hidden / 16 + 3) / 4, rblocks, cfg ? 2 : 1);
+  {
+    KernelTimer t(ctx, CASCADE_K_PACK);
+    if (premix) {
+      CASCADE_TIMED_LAUNCH(t, pack32_mix_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond,
+                           (const uint16_t*)a->h_uncond, hc, a->n_nodes, a->hidden, a->cfg_scale);
+    } else {
+      CASCADE_TIMED_LAUNCH(t, pack32_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond, hc,
+                           (const uint16_t*)a->h_uncond, hu, a->n_nodes, a->hidden);
+    }
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  p.hp_cond = hc;
+  p.hp_uncond = hu;
+  const size_t smem = (size_t)4 * 32 * 1024;   // ring of four 32 KiB half-stages
+  static bool attr_done[3] = {false, false, false};
+  auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false> : (half ? lmhead_bf16_tiled_kernel<false, true> : lmhead_bf16_tiled_kernel<false, false>);
+  const int which = cfg ? 0 : (half ? 1 : 2);
+  if (!attr_done[which]) {
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_done[which] = true;
+  }
+  KernelTimer t(ctx, CASCADE_K_LMHEAD);
+  CASCADE_TIMED_LAUNCH(t, kern, dim3((a->vocab + 255) / 256 * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
+  return hipGetLastError();
 }
 
 hipError_t launch_pack_w(cascade_ctx* ctx, const void* w, int vocab, int hidden, void* w_packed) {

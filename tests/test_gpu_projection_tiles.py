@@ -1,0 +1,52 @@
+"""Every tile of the bf16 projection at its edges (ragged last row and column tiles, one- and two-stage hidden sizes,
+guidance pairs, packed and row-major weights) against the same product in float64.
+
+Bound: the kernels sum K exact bf16 products in float32 in some order, so an element is off by at most
+K 2^-24 sum |h| |w| (and the guidance mix adds its own two roundings, which the same bound covers with the factor of
+the mix applied to |h|); rows mixed before the product carry one bf16 rounding (2^-8 of the element) in addition."""
+import pytest
+import torch
+
+from paper_2605_07230_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+# rows of the product, vocabulary, hidden: the tile that 256 compute units choose (see launch_lmhead_bf16)
+SHAPES = [
+    (1, 64, 128), (33, 16384, 128), (64, 16320, 384),          # 64 x 64
+    (65, 16384, 256), (127, 16320, 640),                       # 128 x 64
+    (3, 65536, 256), (64, 33088, 384), (120, 65472, 128),      # 64 x 256, the last column tile ragged
+    (129, 16384, 256), (230, 16320, 384),                      # 128 x 128
+    (257, 16384, 256), (490, 16448, 128), (513, 33088, 256),   # 256 x 128 / 128 x 256 / 256 x 256
+    (700, 33088, 256), (256, 65472, 128),
+]
+
+
+@pytest.mark.parametrize("rows,vocab,hidden", SHAPES)
+@pytest.mark.parametrize("mode", ["plain", "pairs", "mixed"])
+@pytest.mark.parametrize("packed", [True, False])
+def test_projection_tiles(rows, vocab, hidden, mode, packed):
+    n = max(1, rows // 2) if mode == "pairs" else rows
+    print(f"[projection] nodes={n} vocab={vocab} hidden={hidden} {mode} packed={packed}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows * 131 + vocab + hidden)
+    w = (0.02 * torch.randn(vocab, hidden, device="cuda", generator=gen)).bfloat16()
+    c = torch.randn(n, hidden, device="cuda", generator=gen).bfloat16()
+    u = (c.float() + 0.5 * torch.randn(n, hidden, device="cuda", generator=gen)).bfloat16()
+    ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=hidden, vocab=vocab)
+    logits = torch.full((n, vocab), float("nan"), device="cuda")
+    stats = [torch.empty(n, device="cuda") for _ in range(3)]
+    s, temp = 3.0, 0.8
+    binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=None if mode == "plain" else u, w=binding.cascade_pack_lmhead_w(ctx, w) if packed else w,
+                               w_layout=binding.W_PACKED32 if packed else binding.W_ROWMAJOR, cfg_scale=s, temperature=temp, top_k=50,
+                               logits=logits, row_max=stats[0], row_thr=stats[1], row_lse=stats[2],
+                               cfg_mix=binding.CFG_MIX_HIDDEN if mode == "mixed" else binding.CFG_MIX_LOGITS)
+    cd, ud = c.double(), u.double()
+    x = cd if mode == "plain" else ud + s * (cd - ud)
+    mag = cd.abs() if mode == "plain" else ud.abs() + s * (cd.abs() + ud.abs())
+    ref, bound = x @ w.double().t() / temp, hidden * 2.0 ** -24 * (mag @ w.double().abs().t()) / temp
+    if mode == "mixed" and packed:
+        bound = bound + 2.0 ** -8 * (x.abs() @ w.double().abs().t()) / temp
+    bad = ~((logits.double() - ref).abs() <= bound + 1e-6)      # NaN (an unwritten element) is bad
+    assert not bad.any(), (int(bad.sum()), torch.nonzero(bad)[0].tolist())
+    assert torch.equal(stats[0], logits.max(1).values)
