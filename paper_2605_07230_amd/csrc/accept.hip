@@ -7,7 +7,7 @@
 // a . x (row of a) and every |x|^2 (diagonal) at once.  For bf16 hidden states the tile runs on
 // v_mfma_f32_16x16x32_bf16 with the four waves splitting the hidden dimension (operands loaded
 // straight from global memory as 16-byte k-contiguous pieces); f32 rows (and logit-space
-// similarity) use wave-wide dot products.  The probabilities of the siblings' and children's
+// similarity) are swept once for eight others at a time on the vector ALU.  The probabilities of the siblings' and children's
 // tokens under the parent's distribution are gathered while the rows are still in flight; the sets
 // I_a and C_a, the distinct-token masses and all outputs then need only ballots and LDS.
 #include "common.h"
@@ -26,25 +26,6 @@ __device__ __forceinline__ float prob_of(const float* logits_row, float thr, flo
 
 __device__ __forceinline__ float cos_from(float ab, float aa, float bb) {
   return (aa > 0.f && bb > 0.f) ? ab / (sqrtf(aa) * sqrtf(bb)) : 0.f;
-}
-
-__device__ __forceinline__ float dot_rows(const float* a, const float* b, int h, int lane) {
-  float s = 0.f;
-  for (int k = lane; k < h; k += 64) s = fmaf(a[k], b[k], s);
-  return wave_sum(s);
-}
-__device__ __forceinline__ float dot_rows(const uint16_t* a, const uint16_t* b, int h, int lane) {
-  float s = 0.f;
-  for (int k = lane * 8; k < h; k += 64 * 8) {   // h is a multiple of 8
-    const uint4 ua = *(const uint4*)(a + k), ub = *(const uint4*)(b + k);
-    const uint32_t wa[4] = {ua.x, ua.y, ua.z, ua.w}, wb[4] = {ub.x, ub.y, ub.z, ub.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s = fmaf(__uint_as_float(wa[i] << 16), __uint_as_float(wb[i] << 16), s);
-      s = fmaf(__uint_as_float(wa[i] & 0xffff0000u), __uint_as_float(wb[i] & 0xffff0000u), s);
-    }
-  }
-  return wave_sum(s);
 }
 
 union Frag8 {
@@ -93,54 +74,77 @@ __device__ __forceinline__ f32x4 gram_tile_deep(const uint16_t* row, int k0, int
   return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
-// a . x and x . x in one pass (generic rows)
-__device__ __forceinline__ void dot2_rows(const float* a, const float* x, int h, int lane, float& ax, float& xx) {
-  float s = 0.f, t = 0.f;
-  for (int k = lane; k < h; k += 64) {
-    const float xv = x[k];
-    s = fmaf(a[k], xv, s);
-    t = fmaf(xv, xv, t);
-  }
-  ax = wave_sum(s);
-  xx = wave_sum(t);
-}
-__device__ __forceinline__ void dot2_rows(const uint16_t* a, const uint16_t* x, int h, int lane, float& ax, float& xx) {
-  float s = 0.f, t = 0.f;
-  for (int k = lane * 8; k < h; k += 64 * 8) {   // h is a multiple of 8
-    const uint4 ua = *(const uint4*)(a + k), ux = *(const uint4*)(x + k);
-    const uint32_t wa[4] = {ua.x, ua.y, ua.z, ua.w}, wx[4] = {ux.x, ux.y, ux.z, ux.w};
+// Rows that do not go through the matrix cores (f32; bf16 of a width that is no multiple of 128): the whole workgroup
+// sweeps the row of a once per group of DG other rows and keeps a.x, x.x of each in registers, NT x 16 bytes of every
+// row per step.  Bound by the bytes a compute unit has in flight (each node reads all of its relatives' rows): the former
+// one-row-per-wave loop had one 4-byte load per lane and row in flight - 235 us for 120 nodes x 16384 logits, now 19.
+constexpr int DG = 8;
+template <typename T> struct Piece;   // 16 bytes of a row, or one element of rows that are not 16-byte aligned
+template <> struct Piece<float> {
+  static constexpr int N = 4;
+  static __device__ __forceinline__ void get(const float* p, float (&x)[N]) { const float4 v = *(const float4*)p; x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
+};
+template <> struct Piece<uint16_t> {
+  static constexpr int N = 8;
+  static __device__ __forceinline__ void get(const uint16_t* p, float (&x)[N]) {
+    const uint4 v = *(const uint4*)p;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x0 = __uint_as_float(wx[i] << 16), x1 = __uint_as_float(wx[i] & 0xffff0000u);
-      s = fmaf(__uint_as_float(wa[i] << 16), x0, s);
-      s = fmaf(__uint_as_float(wa[i] & 0xffff0000u), x1, s);
-      t = fmaf(x0, x0, t);
-      t = fmaf(x1, x1, t);
+    for (int i = 0; i < 4; ++i) { x[2 * i] = __uint_as_float(w[i] << 16); x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
+  }
+};
+// sums over this thread's share of the row: s[2 j] = a.x_j, s[2 j + 1] = x_j.x_j, s[2 DG] = a.a
+template <int NT, typename T>
+__device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[DG], int h, bool aligned, int tid, float (&s)[2 * DG + 1]) {
+  constexpr int N = Piece<T>::N;
+#pragma unroll
+  for (int j = 0; j < 2 * DG + 1; ++j) s[j] = 0.f;
+  if (aligned) {
+#pragma unroll 2
+    for (int k = tid * N; k < h; k += NT * N) {   // h is a multiple of N
+      float av[N], xv[DG][N];
+      Piece<T>::get(a + k, av);
+#pragma unroll
+      for (int j = 0; j < DG; ++j) Piece<T>::get(x[j] + k, xv[j]);
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        s[2 * DG] = fmaf(av[c], av[c], s[2 * DG]);
+#pragma unroll
+        for (int j = 0; j < DG; ++j) { s[2 * j] = fmaf(av[c], xv[j][c], s[2 * j]); s[2 * j + 1] = fmaf(xv[j][c], xv[j][c], s[2 * j + 1]); }
+      }
+    }
+  } else {
+    for (int k = tid; k < h; k += NT) {
+      const float av = load_f32(a + k);
+      s[2 * DG] = fmaf(av, av, s[2 * DG]);
+#pragma unroll
+      for (int j = 0; j < DG; ++j) {
+        const float xv = load_f32(x[j] + k);
+        s[2 * j] = fmaf(av, xv, s[2 * j]);
+        s[2 * j + 1] = fmaf(xv, xv, s[2 * j + 1]);
+      }
     }
   }
-  ax = wave_sum(s);
-  xx = wave_sum(t);
 }
 
 constexpr int MAXO = 2 * MAXW;   // others of a node: parent + (siblings - 1) + children <= 1 + 63 + 64
 
-template <typename T>
-__global__ __launch_bounds__(256) void accept_node_kernel(accept_args a, int* dev_status) {
-  __shared__ float gq[4][256];          // K-quarter partial Gram tiles
+template <typename T, int NT>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
+__global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev_status) {
+  __shared__ float gq[4][256];          // K-quarter partial Gram tiles; generic path: the waves' partial sums
   __shared__ float s_cos[MAXO];         // cos(a, other)
   __shared__ int s_other[MAXO];         // node index of every other row: parent, siblings (without a), children
   __shared__ int s_stok[MAXW], s_ctok[MAXW];   // tokens of the siblings (by rank, a included) and of the children
   __shared__ int s_sib[MAXW], s_chl[MAXW];     // node indices of the siblings (by rank, a included) and of the children
   __shared__ float s_sq[MAXW], s_cq[MAXW];     // their probabilities under the parent's distribution
   __shared__ int s_ks, s_kc, s_rank;
-  __shared__ float s_aa;                       // |a|^2 (generic path)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.y, node = blockIdx.x;
   const int lo = a.node_off[b], Tn = a.node_off[b + 1] - lo;
   if (node == 0 && Tn > (int)gridDim.x) {
     // the launch was sized for smaller trees: the nodes beyond it are flagged and written as zeros
     if (tid == 0) atomicOr(dev_status, CASCADE_FLAG_TREE_SIZE);
-    for (int j = (int)gridDim.x + tid; j < Tn && lo + j < a.n_nodes_total; j += 256) {
+    for (int j = (int)gridDim.x + tid; j < Tn && lo + j < a.n_nodes_total; j += NT) {
       a.q_tok[lo + j] = 0.f; a.m_int[lo + j] = 0.f; a.cos_parent[lo + j] = 0.f; a.n_int[lo + j] = 0;
       a.m_conv[lo + j] = 0.f; a.n_conv[lo + j] = 0;
     }
@@ -279,16 +283,33 @@ __global__ __launch_bounds__(256) void accept_node_kernel(accept_args a, int* de
   }
   if (!mfma_done) {
     gather_q();
-    if (wave == 0) {
-      float aa, dummy;
-      dot2_rows(row_a, row_a, h, lane, dummy, aa);
-      if (lane == 0) s_aa = aa;
-    }
-    __syncthreads();
-    for (int oi = wave; oi < n_other; oi += 4) {
-      float ax, xx;
-      dot2_rows(row_a, H + (int64_t)(lo + s_other[oi]) * h, h, lane, ax, xx);
-      if (lane == 0) s_cos[oi] = cos_from(ax, s_aa, xx);
+    float* part = &gq[0][0];   // [NT / 64 waves][2 DG + 1]
+    static_assert(NT / 64 * (2 * DG + 1) <= 1024, "partial sums fit");
+    const bool aligned = (h * sizeof(T)) % 16 == 0 && ((uintptr_t)H & 15) == 0;
+    for (int o0 = 0; o0 < n_other; o0 += DG) {
+      const T* x[DG];
+#pragma unroll
+      for (int j = 0; j < DG; ++j)   // past the end: the last one again
+        x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
+      float s[2 * DG + 1];
+      dot_group<NT>(row_a, x, h, aligned, tid, s);
+      if (o0 > 0) __syncthreads();   // the previous group's sums have been consumed
+#pragma unroll
+      for (int j = 0; j < 2 * DG + 1; ++j) {
+        const float t = wave_sum(s[j]);
+        if (lane == 0) part[wave * (2 * DG + 1) + j] = t;
+      }
+      __syncthreads();
+      if (tid < DG && o0 + tid < n_other) {
+        float ax = 0.f, xx = 0.f, aa = 0.f;
+        for (int w = 0; w < NT / 64; ++w) {
+          const float* q = part + w * (2 * DG + 1);
+          ax += q[2 * tid];
+          xx += q[2 * tid + 1];
+          aa += q[2 * DG];
+        }
+        s_cos[o0 + tid] = cos_from(ax, aa, xx);
+      }
     }
   }
   if (own_sib) { s_stok[tid] = my_tok; s_sq[tid] = my_q; }
@@ -346,7 +367,7 @@ __global__ __launch_bounds__(256) void accept_node_kernel(accept_args a, int* de
 hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   KernelTimer t(ctx, CASCADE_K_ACCEPT);
   dim3 grid(ctx->lim.max_nodes_per_tree, a->n_prompts);
-  if (a->h_dtype == CASCADE_BF16) CASCADE_TIMED_LAUNCH(t, accept_node_kernel<uint16_t>, grid, dim3(256), 0, ctx->stream, *a, ctx->dev_status);
-  else CASCADE_TIMED_LAUNCH(t, accept_node_kernel<float>, grid, dim3(256), 0, ctx->stream, *a, ctx->dev_status);
+  if (a->h_dtype == CASCADE_BF16) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<uint16_t, 256>), grid, dim3(256), 0, ctx->stream, *a, ctx->dev_status);
+  else CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<float, 512>), grid, dim3(512), 0, ctx->stream, *a, ctx->dev_status);
   return hipGetLastError();
 }
