@@ -452,13 +452,13 @@ __device__ __forceinline__ float key_f32(uint32_t k) {
 // (A row whose entries all share one bin, e.g. all equal, serialises on one LDS address: slow, exact.)
 template <int BPT>   // bins per thread; the workgroup's 1024 threads cover 1024 * BPT bins, highest first
 __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int tid, int lane, int wave, int* s_wsum, int* s_bin,
-                                                  int* s_above, int pad_bin, int pad) {   // pad entries of bin pad_bin are not part of the row
+                                                  int* s_above) {
   constexpr int NB = 1024 * BPT;
   int hb[BPT], loc = 0;
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
     const int b = NB - 1 - (BPT * tid + i);
-    hb[i] = hist[b] - (b == pad_bin ? pad : 0);
+    hb[i] = hist[b];
     loc += hb[i];
   }
   const int incl = wave_scan_incl_i(loc);
@@ -504,6 +504,10 @@ struct RowStatsSmem {
 // Workgroups are persistent: workgroup b takes rows b, b + gridDim.x, ...; the loads of its next row are issued
 // as soon as the registers of the current one are no longer needed, so that they overlap the row's tail (list
 // processing, candidate ranking, reductions).
+// VPT = values per thread: 4, 8, 16, 24, 32, 40, 48 or 64 (rows that are not 16-byte aligned: 4, 16 or 64), the smallest
+// that holds the row.  A chunk that the row does not fill files only its real entries: 33088 entries in a 65536-entry
+// frame used to send 32448 padding entries through LDS atomics on one bin, one after the other (78 us for 343 rows, now
+// 22; 46 -> 10 us for 200 x 24000).
 template <int VPT, bool VEC>   // VEC: rows start on 16-byte boundaries and V is a multiple of 4
 __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   extern __shared__ __align__(1024) char rs_smem_raw[];
@@ -512,6 +516,8 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   const int V = p.vocab;
   const bool topk = p.top_k > 0 && p.top_k < V;
   constexpr int NCH = VPT / 4;
+  // chunks that the row fills for sure (it did not fit the next smaller frame)
+  constexpr int SURE = VEC ? (VPT == 64 ? 12 : (VPT == 16 ? 2 : (VPT >= 24 ? NCH - 2 : (VPT == 8 ? 1 : 0)))) : (VPT == 64 ? 4 : (VPT == 16 ? 1 : 0));
   // Long rows: the last NPRE 16 KiB chunks of the NEXT row are fetched into LDS (LDS-direct loads, no registers
   // needed) while the current row's registers are still in use - HBM would otherwise idle between the end of a
   // row's loads and the moment its registers are free.  A thread reads back exactly the 16 bytes its own lane
@@ -525,6 +531,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   // NREG .. NCH-1 come from LDS and are swept last.  Entries past V are masked to -inf before use.  Every load
   // is unconditional (addresses clamped into the row): all of them are in flight at once.
   auto mch = [](int jj) { return jj; };
+  const bool whole = V == VPT * 1024;   // workgroup-uniform: a full row needs no masking
   float x[VPT];
   // (The thread index is passed through an empty asm so that the per-chunk offsets and masks below are recomputed
   // where they are used instead of being kept in registers across the whole row loop.)
@@ -555,11 +562,11 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     }
   };
   auto mask_chunks = [&](int jj0, int jj1) {
-    if (V != VPT * 1024) {   // workgroup-uniform: a full row needs no masking
+    if (!whole) {
       int t = tid;
       asm volatile("" : "+v"(t));
 #pragma unroll
-      for (int jj = jj0; jj < jj1; ++jj)
+      for (int jj = jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + 1024 * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
     }
@@ -594,13 +601,26 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
 
     float mx = -INFINITY;
     auto sweep = [&](int jj0, int jj1) {   // row maximum and first-round histogram of x-chunks jj0 .. jj1-1
-      if (fast) {
+      auto chunk = [&](int jj, auto in_row) {
 #pragma unroll
-        for (int i = 4 * jj0; i < 4 * jj1; ++i) {
-          mx = fmaxf(mx, x[i]);
-          const float t = __builtin_amdgcn_fmed3f(fmaf(x[i], bs, bc), 0.f, 4095.f);
-          atomicAdd(&sm.hist1[(int)t], 1);
-          if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // keep the unrolled sweep from piling up temporaries
+        for (int c = 0; c < 4; ++c) {
+          mx = fmaxf(mx, x[4 * jj + c]);
+          const float t = __builtin_amdgcn_fmed3f(fmaf(x[4 * jj + c], bs, bc), 0.f, 4095.f);
+          if (in_row(c)) atomicAdd(&sm.hist1[(int)t], 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // keep the unrolled sweep from piling up temporaries
+      };
+      auto always = [](int) { return true; };
+      if (fast && whole) {
+#pragma unroll
+        for (int jj = jj0; jj < jj1; ++jj) chunk(jj, always);
+      } else if (fast) {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+#pragma unroll
+        for (int jj = jj0; jj < jj1; ++jj) {
+          if (jj < SURE || 4096 * (jj + 1) <= V) chunk(jj, always);   // workgroup-uniform
+          else chunk(jj, [&](int c) { return 4 * (t + 1024 * jj) + c < V; });
         }
       } else {
 #pragma unroll
@@ -635,8 +655,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     bool done = false;
     int cnt = 0, B = 0, n_c = 0, k = p.top_k;
     if (fast) {
-      // the -inf padding past V went to bin 0 with everything else at or below the sample's minimum
-      find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above, 0, VPT * 1024 - V);
+      find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       B = sm.s_bin;
       n_c = sm.hist1[B];
       k -= sm.s_above;                     // rank of the k-th largest inside bin B, 1 = largest
@@ -701,7 +720,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
         k = p.top_k;
         for (int v = tid; v < V; v += 1024) atomicAdd(&sm.hist1[f32_key(g[v]) >> 20], 1);
         __syncthreads();
-        find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above, 0, 0);
+        find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
         const uint32_t b1 = (uint32_t)sm.s_bin;
         k -= sm.s_above;
         __syncthreads();   // s_bin / s_above are rewritten by the next round
@@ -710,7 +729,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
           if ((key >> 20) == b1) atomicAdd(&sm.hist2[(key >> 10) & 1023u], 1);
         }
         __syncthreads();
-        find_bin_from_top<1>(sm.hist2, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above, 0, 0);
+        find_bin_from_top<1>(sm.hist2, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
         const uint32_t b12 = (b1 << 10) | (uint32_t)sm.s_bin;
         k -= sm.s_above;
         __syncthreads();
@@ -719,7 +738,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
           if ((key >> 10) == b12) atomicAdd(&sm.hist3[key & 1023u], 1);
         }
         __syncthreads();
-        find_bin_from_top<1>(sm.hist3, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above, 0, 0);
+        find_bin_from_top<1>(sm.hist3, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
         thr_key = (b12 << 10) | (uint32_t)sm.s_bin;
         thr = key_f32(thr_key);
       }
@@ -918,7 +937,14 @@ hipError_t launch_row_stats(cascade_ctx* ctx, const lmhead_args* a) {
   const int V = a->vocab;
   // 16-byte loads need every row to start on a 16-byte boundary
   const bool vec = V % 4 == 0 && ((uintptr_t)a->logits & 15u) == 0;
-  if (V <= 4096) return vec ? launch_row_stats_t<4, true>(ctx, p) : launch_row_stats_t<4, false>(ctx, p);
-  if (V <= 16384) return vec ? launch_row_stats_t<16, true>(ctx, p) : launch_row_stats_t<16, false>(ctx, p);
-  return vec ? launch_row_stats_t<64, true>(ctx, p) : launch_row_stats_t<64, false>(ctx, p);
+  if (!vec) return V <= 4096 ? launch_row_stats_t<4, false>(ctx, p) : (V <= 16384 ? launch_row_stats_t<16, false>(ctx, p) : launch_row_stats_t<64, false>(ctx, p));
+  switch ((V + 8191) / 8192) {
+    case 1: return V <= 4096 ? launch_row_stats_t<4, true>(ctx, p) : launch_row_stats_t<8, true>(ctx, p);
+    case 2: return launch_row_stats_t<16, true>(ctx, p);
+    case 3: return launch_row_stats_t<24, true>(ctx, p);
+    case 4: return launch_row_stats_t<32, true>(ctx, p);
+    case 5: return launch_row_stats_t<40, true>(ctx, p);
+    case 6: return launch_row_stats_t<48, true>(ctx, p);
+    default: return launch_row_stats_t<64, true>(ctx, p);
+  }
 }
