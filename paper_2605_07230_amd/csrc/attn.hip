@@ -16,7 +16,7 @@
 // writes split-KV partials to the workspace for a small merge kernel when the keys must be split across
 // workgroups to fill the GPU.
 //
-// f32 path: a plain one-workgroup-per-(node, head) kernel, used by the small fp32 configuration.
+// f32 path: one kernel on the f32 matrix instructions, 16 query rows per workgroup, used by the small fp32 configuration.
 #include <type_traits>
 
 #include "common.h"
@@ -48,79 +48,178 @@ struct AttnParams {
   float scale_log2e;
 };
 
+// 2^x for x <= 0 or -inf (v_exp_f32; no range handling needed here)
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // ------------------------------------------------------------------------------------------ f32
-// grid (N, Hq); 256 threads.  Keys are visited in chunks of 256 with a running max / sum.
-template <int DMAX>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p, int n_rows, int D) {
-  __shared__ float qs[DMAX];
-  __shared__ float sc[256];
-  __shared__ int anc[CASCADE_MAX_DEPTH + 2];
-  __shared__ float red[8];
-  __shared__ int s_row, s_nanc;
-  const int node = blockIdx.x, head = blockIdx.y, tid = threadIdx.x;
-  const int kvh = head / p.group;
-  if (tid == 0) {
-    int s = 0;
-    while (s + 1 < n_rows && p.node_off[s + 1] <= node) ++s;
-    s_row = s;
-    int lo = p.node_off[s];
-    int i = node - lo, n = 0;
-    while (i >= 0 && n < CASCADE_MAX_DEPTH + 1) {
-      anc[n++] = i;
-      int pi = p.parent[lo + i];
-      if (pi >= i) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); break; }
-      i = pi;
+// Workgroup = (16 query rows of one row of the batch, kv head); its NW waves take every NW-th tile of 16 keys and meet in
+// LDS.  Both products run on v_mfma_f32_16x16x4_f32 (one value per lane and operand, k = lane / 16 = g):
+//   S^T = K Q^T   lane (l16, g) loads 16 bytes at d = 16 ks + 4 g of key / query l16 and feeds element c of both to the
+//                 c-th product; the result holds keys 4 g + r of query l16;
+//   O^T = V^T P^T product r takes P^T straight from register r of that result, and key 4 g + r's value at d = 16 db + l16.
+// Nothing passes through LDS before the merge.  Latency-bound: the fixed part (row lookup, queries and
+// parents, barrier, merge) is 8.6 us of the 10.2 at 15 nodes x 8 heads x 64 and a 256-key prefix (48.5 us with one
+// workgroup per (node, head) and one key per thread); 8 instead of 16 waves, or the first tile requested before the
+// parent array is staged, change nothing.
+// DB = 16-wide blocks of head_dim; VEC: rows can be read 16 bytes at a time (otherwise element by element).
+template <int DB, int NW, bool VEC>
+__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_rows, int D) {
+  extern __shared__ __align__(16) float f32_smem[];   // [NW][16 queries][16 DB + 4] partial outputs, [NW][16][2] (m, l)
+  __shared__ int s_parent[CASCADE_MAX_TREE];
+  constexpr int OP = 16 * DB + 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g = lane >> 4, kvh = blockIdx.y, G = p.group;
+  // which row of the batch this query block belongs to: the grid counts the blocks of all rows
+  int s = -1, lo = 0, T = 0, P = 0, sb = blockIdx.x;
+  for (int base = 0; base < n_rows && s < 0; base += 64) {
+    const int r = base + lane;
+    const int lo_l = r < n_rows ? p.node_off[r] : 0, t_l = r < n_rows ? p.node_off[r + 1] - lo_l : 0;
+    const int p_l = r < n_rows ? p.prefix_len[r] : 0;
+    const int nb = (t_l * G + 15) / 16, incl = wave_scan_incl_i(nb);
+    const unsigned long long hit = __ballot(sb < incl);
+    if (hit) {
+      const int l = __ffsll((long long)hit) - 1;
+      s = base + l;
+      lo = __builtin_amdgcn_readlane(lo_l, l);
+      T = __builtin_amdgcn_readlane(t_l, l);
+      P = __builtin_amdgcn_readlane(p_l, l);
+      sb -= __builtin_amdgcn_readlane(incl - nb, l);
+    } else {
+      sb -= __builtin_amdgcn_readlane(incl, 63);
     }
-    if (i >= 0 && n == CASCADE_MAX_DEPTH + 1) atomicOr(p.dev_status, CASCADE_FLAG_DEPTH);
-    s_nanc = n;
   }
-  const float* q = (const float*)p.q + ((int64_t)node * p.n_heads + head) * D;
-  for (int d = tid; d < D; d += 256) qs[d] = q[d];
-  __syncthreads();
-  const int s = s_row, lo = p.node_off[s], P = p.prefix_len[s], nanc = s_nanc;
-  const int L = P + nanc;
+  if (s < 0) return;   // the grid is an upper bound of the number of blocks
+  const int M = T * G;
+  if (T > CASCADE_MAX_TREE) {   // flagged, zeros (the same for every block of the row)
+    if (tid == 0) atomicOr(p.dev_status, CASCADE_FLAG_TREE_SIZE);
+    for (int r = 16 * sb + tid; r < min(16 * sb + 16, M); r += 64 * NW) {
+      const int64_t rowg = (int64_t)(lo + r % T) * p.n_heads + kvh * G + r / T;
+      for (int d = 0; d < D; ++d) ((float*)p.out)[rowg * D + d] = 0.f;
+      if (p.lse) p.lse[rowg] = -INFINITY;
+    }
+    return;
+  }
+  const int qr = min(16 * sb + l16, M - 1);   // rows past the end repeat the last one, never stored
+  const int qi = qr % T;
+  const int64_t q_row = (int64_t)(lo + qi) * p.n_heads + kvh * G + qr / T;
+  const int n_pt = (P + 15) / 16, nt = n_pt + (T + 15) / 16;
+  auto load4 = [&](const float* row, int d) {
+    if (VEC) return d < D ? *(const f32x4*)(row + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 x;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = d + c < D ? row[d + c] : 0.f;
+    return x;
+  };
   const float* kc = (const float*)p.k_cache + s * p.sr + kvh * p.sh;
   const float* vc = (const float*)p.v_cache + s * p.sr + kvh * p.sh;
-  const float* kt = (const float*)p.k_tree;
-  const float* vt = (const float*)p.v_tree;
-  float m = -INFINITY, l = 0.f, acc = 0.f;  // acc: output element tid (tid < D)
-  for (int base = 0; base < L; base += 256) {
-    const int j = base + tid;
-    float z = -INFINITY;
-    if (j < L) {
-      const float* kp = (j < P) ? kc + (int64_t)j * p.sp
-                                : kt + ((int64_t)(lo + anc[j - P]) * p.n_kv_heads + kvh) * D;
-      float dot = 0.f;
-      for (int d = 0; d < D; ++d) dot = fmaf(qs[d], kp[d], dot);
-      z = dot * p.scale_log2e;
+  const float* ktr = (const float*)p.k_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
+  const float* vtr = (const float*)p.v_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
+  const int64_t tree_pitch = (int64_t)p.n_kv_heads * D;
+  // tile registers; keys past the end of the tile's source: clamped, masked below
+  f32x4 q[DB], ot[DB], k[DB];
+  float v[4][DB];
+  auto request_k = [&](int t) {
+    const bool tree = t >= n_pt;
+    const int key = min(16 * (tree ? t - n_pt : t) + l16, (tree ? T : P) - 1);
+    const float* row = (tree ? ktr : kc) + (int64_t)key * (tree ? tree_pitch : p.sp);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) k[db] = load4(row, 16 * db + 4 * g);
+  };
+  auto request_v = [&](int t) {
+    const bool tree = t >= n_pt;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int key = min(16 * (tree ? t - n_pt : t) + 4 * g + r, (tree ? T : P) - 1);
+      const float* row = (tree ? vtr : vc) + (int64_t)key * (tree ? tree_pitch : p.sp);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) v[r][db] = row[min(16 * db + l16, D - 1)];
     }
-    float cm = wave_max(z);
-    if ((tid & 63) == 0) red[tid >> 6] = cm;
-    __syncthreads();
-    cm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    const float m_new = fmaxf(m, cm);
-    const float alpha = exp2f(m - m_new);   // m = -inf on the first chunk gives 0
-    const float e = (j < L) ? exp2f(z - m_new) : 0.f;
-    sc[tid] = e;
-    float cs = wave_sum(e);
-    if ((tid & 63) == 0) red[4 + (tid >> 6)] = cs;
-    __syncthreads();
-    l = l * alpha + (red[4] + red[5] + red[6] + red[7]);
-    m = m_new;
-    if (tid < D) {
-      acc *= alpha;
-      const int cnt = min(256, L - base);
-      for (int jj = 0; jj < cnt; ++jj) {
-        const int j2 = base + jj;
-        const float* vp = (j2 < P) ? vc + (int64_t)j2 * p.sp
-                                   : vt + ((int64_t)(lo + anc[j2 - P]) * p.n_kv_heads + kvh) * D;
-        acc = fmaf(sc[jj], vp[tid], acc);
-      }
-    }
-    __syncthreads();
+  };
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    q[db] = load4((const float*)p.q + q_row * D, 16 * db + 4 * g);
+    ot[db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (tid < D) ((float*)p.out)[((int64_t)node * p.n_heads + head) * D + tid] = acc / l;
-  if (tid == 0 && p.lse) p.lse[(int64_t)node * p.n_heads + head] = m * LN2 + logf(l);
+  for (int i = tid; i < T; i += 64 * NW) {
+    int pi = p.parent[lo + i];
+    if (pi >= i || pi < -1) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // keeps the climb finite
+    s_parent[i] = pi;
+  }
+  __syncthreads();
+  if (wave < nt) { request_k(wave); request_v(wave); }
+  float m = -INFINITY, l = 0.f;
+  for (int t = wave; t < nt; t += NW) {
+    const bool tree = t >= n_pt;
+    const int kb = 16 * (tree ? t - n_pt : t), last = (tree ? T : P) - 1;
+    // keys of the tile that query l16 sees
+    unsigned bits;
+    if (tree) {
+      bits = 0;
+      int a = qi, steps = 0;
+      while (a >= kb) {
+        if (a - kb < 16) bits |= 1u << (a - kb);
+        if (++steps > CASCADE_MAX_DEPTH + 1) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); break; }
+        a = s_parent[a];   // smaller than a, or -1
+      }
+    } else {
+      bits = last - kb >= 15 ? 0xffffu : (1u << (last - kb + 1)) - 1u;
+    }
+    f32x4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) st = __builtin_amdgcn_mfma_f32_16x16x4f32(k[db][c], q[db][c], st, 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      st[r] = ((bits >> (4 * g + r)) & 1u) ? st[r] * p.scale_log2e : -INFINITY;
+      mx = fmaxf(mx, st[r]);
+    }
+    const float m_new = fmaxf(m, rows4_max(mx)), m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = fast_exp2(m - m_use);
+    float ls = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      st[r] = fast_exp2(st[r] - m_use);
+      ls += st[r];
+    }
+    l = l * alpha + ls;
+    m = m_new;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      ot[db] *= alpha;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][db], st[r], ot[db], 0, 0, 0);
+    }
+    if (t + NW < nt) { request_k(t + NW); request_v(t + NW); }
+  }
+  // merge: lane (l16, g) holds d = 16 db + 4 g + c of query l16
+  l = rows4_sum(l);
+  float* mo = f32_smem + (wave * 16 + l16) * OP;
+  float* ml = f32_smem + NW * 16 * OP;
+#pragma unroll
+  for (int db = 0; db < DB; ++db) *(f32x4*)(mo + 16 * db + 4 * g) = ot[db];
+  if (g == 0) {
+    ml[(wave * 16 + l16) * 2] = m;
+    ml[(wave * 16 + l16) * 2 + 1] = l;
+  }
+  __syncthreads();
+  const int rows = min(16, M - 16 * sb);
+  for (int e = tid; e < rows * D; e += 64 * NW) {
+    const int r = e / D, d = e % D, row = 16 * sb + r;
+    float mm = -INFINITY, o = 0.f, ll = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mm = fmaxf(mm, ml[(w * 16 + r) * 2]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = fast_exp2(ml[(w * 16 + r) * 2] - mm);   // a wave without visible keys: 0
+      ll = fmaf(f, ml[(w * 16 + r) * 2 + 1], ll);
+      o = fmaf(f, f32_smem[(w * 16 + r) * OP + d], o);
+    }
+    const int64_t rowg = (int64_t)(lo + row % T) * p.n_heads + kvh * G + row / T;
+    ((float*)p.out)[rowg * D + d] = o / ll;
+    if (d == 0 && p.lse) p.lse[rowg] = mm * LN2 + logf(ll);
+  }
 }
 
 // ----------------------------------------------------------------------------------------- bf16
@@ -209,8 +308,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   const bf16x2_t v = __builtin_convertvector(f32x2_t{a, b}, bf16x2_t);
   return *(const uint32_t*)&v;
 }
-// 2^x for x <= 0 or -inf (v_exp_f32; no range handling needed here)
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 union Frag8 {
   bf16x8 v;
@@ -1566,12 +1663,30 @@ hipError_t launch_split_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
 
 }  // namespace
 
+template <int DB, int NW, bool VEC>
+hipError_t launch_f32_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid, int n_rows, int D) {
+  constexpr int smem = (NW * 16 * (16 * DB + 4) + NW * 32) * 4;
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute((const void*)attn_f32_kernel<DB, NW, VEC>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  KernelTimer t(ctx, CASCADE_K_ATTN);
+  CASCADE_TIMED_LAUNCH(t, (attn_f32_kernel<DB, NW, VEC>), grid, dim3(64 * NW), smem, ctx->stream, p, n_rows, D);
+  return hipGetLastError();
+}
+
 hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
   AttnParams p = make_params(ctx, a);
-  dim3 grid(a->n_nodes_total, a->n_heads);
-  KernelTimer t(ctx, CASCADE_K_ATTN);
-  CASCADE_TIMED_LAUNCH(t, (attn_f32_kernel<256>), grid, dim3(256), 0, ctx->stream, p, a->n_rows, a->head_dim);
-  return hipGetLastError();
+  const int D = a->head_dim;
+  // blocks of 16 query rows: at most one partly filled one per row of the batch
+  dim3 grid((unsigned)((int64_t)a->n_nodes_total * p.group / 16 + a->n_rows), a->n_kv_heads);
+  const bool vec = D % 4 == 0 && ((a->cache_stride_row | a->cache_stride_head | a->cache_stride_pos) & 3) == 0 &&
+                   (((uintptr_t)a->q | (uintptr_t)a->k_tree | (uintptr_t)a->k_cache) & 15) == 0;
+  if (D <= 64) return vec ? launch_f32_t<4, 16, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<4, 16, false>(ctx, p, grid, a->n_rows, D);
+  if (D <= 128) return vec ? launch_f32_t<8, 8, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<8, 8, false>(ctx, p, grid, a->n_rows, D);
+  return vec ? launch_f32_t<16, 4, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<16, 4, false>(ctx, p, grid, a->n_rows, D);
 }
 
 // CAN_SPLIT: the dispatcher may split the keys across workgroups for this instantiation (it never does when

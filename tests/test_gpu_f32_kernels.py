@@ -1,0 +1,96 @@
+"""The f32 projection and tree attention at the edges of their 16-wide blocks, with widths that cannot be read 16 bytes at a
+time, against float64.
+
+Bounds: a float32 sum of K products in some order is off by at most K 2^-24 sum|a||b|.  For attention that is the error d
+of a score (times the scale); probabilities are then off by 2 d relative, and the weighted sum of L values adds
+(L + 8) 2^-24, all relative to the largest |v|."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_07230_amd import binding
+from paper_2605_07230_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nodes", [1, 15, 16, 17, 64, 65, 130])
+@pytest.mark.parametrize("hidden,vocab", [(1, 5), (3, 16), (64, 17), (97, 300), (256, 1000), (512, 4100)])
+@pytest.mark.parametrize("guided", [False, True])
+def test_f32_projection(nodes, hidden, vocab, guided):
+    print(f"[f32 projection] {nodes} x {hidden} x {vocab} guided={guided}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nodes + 1000 * hidden + vocab)
+    w, c, u = (torch.randn(k, hidden, device="cuda", generator=gen) for k in (vocab, nodes, nodes))
+    ctx = binding.Context(max_rows=1, max_nodes_total=nodes, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=hidden, vocab=vocab)
+    g = torch.full((nodes, vocab), float("nan"), device="cuda")
+    st = [torch.empty(nodes, device="cuda") for _ in range(3)]
+    binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=u if guided else None, w=w, cfg_scale=3.0, temperature=0.7, top_k=0, logits=g,
+                               row_max=st[0], row_thr=st[1], row_lse=st[2])
+    wd, cd, ud = w.double(), c.double(), u.double()
+    x, mag = (ud + 3 * (cd - ud), ud.abs() + 3 * (cd.abs() + ud.abs())) if guided else (cd, cd.abs())
+    err = (g.double() - x @ wd.t() / 0.7).abs()
+    assert torch.all(err <= (hidden + 4) * 2.0 ** -24 * (mag @ wd.abs().t()) / 0.7 + 1e-30)
+
+
+def _attend(q, k, v, see, scale):
+    z = (q.double() @ k.double().t()) * scale
+    z = z.masked_fill(~see, -float("inf"))
+    l = torch.logsumexp(z, 1)
+    return torch.exp(z - l[:, None]) @ v.double(), l
+
+
+@pytest.mark.parametrize("head_dim", [1, 6, 20, 64, 100, 128, 256])
+@pytest.mark.parametrize("heads,kv_heads", [(2, 2), (6, 2)])
+@pytest.mark.parametrize("sizes,prefix,depth", [([1], [0], 1), ([15, 16, 17], [16, 1, 33], 5), ([70, 3], [0, 300], 40), ([2] * 70, list(range(70)), 1)])
+def test_f32_attention(head_dim, heads, kv_heads, sizes, prefix, depth):
+    print(f"[f32 attention] d={head_dim} heads={heads}/{kv_heads} sizes={sizes[:4]} prefix={prefix[:4]}", flush=True)
+    rng = np.random.default_rng(head_dim + heads)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(head_dim * 10 + heads)
+    trees = [wl.grow_tree(rng, n, min(depth, n - 1)) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n, S, cap = int(off[-1]), len(sizes), max(max(prefix), 1)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen)  # noqa: E731
+    q, kt, vt = r(n, heads, head_dim), r(n, kv_heads, head_dim), r(n, kv_heads, head_dim)
+    kc, vc = r(S, kv_heads, cap, head_dim), r(S, kv_heads, cap, head_dim)
+    out, lse = torch.full_like(q, float("nan")), torch.full((n, heads), float("nan"), device="cuda")
+    ctx = binding.Context(max_rows=S, max_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix=cap, n_heads=heads, head_dim=head_dim, hidden=64, vocab=64)
+    dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
+    binding.tree_verify_attn(ctx, node_off=dev(off), parent=dev(np.concatenate(trees)), prefix_len=dev(prefix), q=q, k_tree=kt, v_tree=vt,
+                             k_cache=kc, v_cache=vc, out=out, lse=lse, max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix))
+    assert ctx.device_status() == binding.OK
+    scale = head_dim ** -0.5
+    for s in range(S):
+        lo, hi, T = int(off[s]), int(off[s + 1]), sizes[s]
+        see = torch.zeros(T, prefix[s] + T, dtype=torch.bool)
+        see[:, :prefix[s]] = True
+        for i in range(T):
+            a = i
+            while a >= 0:
+                see[i, prefix[s] + a] = True
+                a = int(trees[s][a])
+        for h in range(heads):
+            kv = h // (heads // kv_heads)
+            k, v = torch.cat([kc[s, kv, :prefix[s]], kt[lo:hi, kv]]), torch.cat([vc[s, kv, :prefix[s]], vt[lo:hi, kv]])
+            ref, rl = _attend(q[lo:hi, h], k, v, see.cuda(), scale)
+            d = head_dim * 2.0 ** -24 * scale * float(q[lo:hi, h].double().norm(dim=1).max() * k.double().norm(dim=1).max())
+            bound = (2 * d + (prefix[s] + T + 8) * 2.0 ** -24) * float(v.abs().max()) + 1e-30
+            assert float((out[lo:hi, h].double() - ref).abs().max()) <= bound
+            assert float((lse[lo:hi, h].double() - rl).abs().max()) <= 2 * d + (prefix[s] + T + 8) * 2.0 ** -24 * (1 + float(rl.abs().max()))
+
+
+def test_f32_attention_flags_bad_parents_and_overlong_paths():
+    def status(parent):
+        n = len(parent)
+        ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=n, max_prefix=1, n_heads=1, head_dim=8, hidden=64, vocab=64)
+        dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
+        t = [torch.randn(n, 1, 8, device="cuda") for _ in range(3)]
+        c = torch.randn(1, 1, 1, 8, device="cuda")
+        binding.tree_verify_attn(ctx, node_off=dev([0, n]), parent=dev(parent), prefix_len=dev([1]), q=t[0], k_tree=t[1], v_tree=t[2], k_cache=c,
+                                 v_cache=c, out=torch.empty_like(t[0]), max_nodes_per_tree=n, max_prefix_len=1)
+        return ctx.device_status()
+    assert status([-1, 0, 1, 1]) == binding.OK
+    assert status([-1, 0, 5, 1]) == binding.ETREE
+    assert status(list(range(-1, 64))) == binding.OK          # 64 levels below the root
+    assert status(list(range(-1, 70))) == binding.ETREE       # deeper than the library's limit
