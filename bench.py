@@ -323,16 +323,11 @@ def measure_workload(index: int, steps: int, warmup: int, args, hbm_meas: float,
                 "frac": ach / HBM_PEAK_GBS, "traffic": traffic, "algorithmic_bytes": nbytes,
                 "frac_of_measured_peak": ach / hbm_meas, "avg_launch_us": us}
 
+    # 256-row workgroups (the ring kernel) when they fill the chip, smaller ones of the same scheme otherwise
     max_tree = int((inp.node_off[1:] - inp.node_off[:-1]).max())
     m_rows = max_tree * (inp.n_heads // inp.n_kv_heads)
-    units = inp.n_rows * inp.n_kv_heads * ((m_rows + 63) // 64)
-    if inp.dtype == "f32":
-        attn_kernel = "attn_f32_kernel"
-    elif m_rows > 128:
-        # 256 query rows per workgroup; the ring kernel unless the keys are split to fill an idle GPU
-        attn_kernel = "attn_bf16_kernel" if "attn_merge" in kernel_us else "attn_bf16_ring_kernel"
-    else:
-        attn_kernel = "attn_bf16_qsplit_kernel" if units <= 128 else "attn_bf16_ksplit_kernel"
+    fills = m_rows > 128 and inp.n_rows * inp.n_kv_heads * ((m_rows + 255) // 256) >= 256
+    attn_kernel = "attn_f32_kernel" if inp.dtype == "f32" else ("attn_bf16_ring_kernel" if fills else "attn_bf16_rows_kernel")
     attn_us = kernel_us.get("attn", 0.0) + kernel_us.get("attn_merge", 0.0)
     t_attn, t_merge = measured_traffic(inp.name, "attn"), measured_traffic(inp.name, "attn_merge")
     if t_attn is not None and "attn_merge" in kernel_us:

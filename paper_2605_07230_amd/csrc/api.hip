@@ -191,6 +191,7 @@ namespace {
 
 constexpr int MAX_STATIC_DEVICES = 64;
 unsigned char* g_scratch_ptr[MAX_STATIC_DEVICES];   // device address of `scratch`, per device (null until first use)
+int g_static_n_cu[MAX_STATIC_DEVICES];              // compute units, per device (set with the address)
 std::mutex g_scratch_mutex;
 
 // first word of the scratch array: cleared before the launch, copied out after it
@@ -199,8 +200,9 @@ __global__ void static_status_kernel(int* flag, int* copy_to) {
   else *flag = 0;
 }
 
-// device address of this device's copy of the array (looked up once per device, with that device current)
-int static_scratch(int device, unsigned char** out) {
+// device address of this device's copy of the array and the device's compute units (looked up once per device, with that
+// device current)
+int static_scratch(int device, unsigned char** out, int* n_cu) {
   if (device < 0 || device >= MAX_STATIC_DEVICES) return CASCADE_ESHAPE;
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
   if (!g_scratch_ptr[device]) {
@@ -208,8 +210,11 @@ int static_scratch(int device, unsigned char** out) {
     hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
     if (!ptr) return CASCADE_EHIP;
+    e = hipDeviceGetAttribute(&g_static_n_cu[device], hipDeviceAttributeMultiprocessorCount, device);
+    if (e != hipSuccess || g_static_n_cu[device] <= 0) return hip_fail(e != hipSuccess ? e : hipErrorInvalidDevice);
     g_scratch_ptr[device] = (unsigned char*)ptr;
   }
+  *n_cu = g_static_n_cu[device];
   *out = g_scratch_ptr[device];
   return CASCADE_OK;
 }
@@ -228,13 +233,15 @@ int tree_verify_attn_static(void* hip_stream, const tree_attn_args* a, int32_t* 
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return hip_fail(e);
   unsigned char* base = nullptr;
-  int st = static_scratch(device, &base);
+  int n_cu = 0;
+  int st = static_scratch(device, &base, &n_cu);
   if (st != CASCADE_OK) return st;
   // a context on the stack that points into the static array: no workspace of its own, no timing events
   cascade_ctx local;
   memset(&local, 0, sizeof(local));
   local.stream = (hipStream_t)hip_stream;
   local.device = device;
+  local.n_cu = n_cu;
   local.lim.max_rows = a->n_rows;
   local.lim.max_nodes_total = a->n_nodes_total;
   local.lim.max_nodes_per_tree = a->max_nodes_per_tree;

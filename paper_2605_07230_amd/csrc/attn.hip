@@ -9,12 +9,11 @@
 // transposed in memory.  Scores are produced TRANSPOSED, S^T = K Q^T, with v_mfma_f32_16x16x32_bf16: a
 // lane then owns one query column, so the online-softmax statistics are per-lane scalars and the
 // probabilities are already laid out as the B operand of O^T = V^T P^T.  The ancestor mask of the 64
-// tree keys of a tile is one 64-bit word per query, built in LDS by climbing parent pointers.  Four
-// kernels share this scheme and differ in how work is cut: query rows split over waves (tiny batches),
-// key groups inside the workgroup (small trees), 256 query rows per workgroup on a three-deep LDS ring
-// filled by LDS-direct loads (large trees), and the double-buffered predecessor of the latter, which
-// writes split-KV partials to the workspace for a small merge kernel when the keys must be split across
-// workgroups to fill the GPU.
+// tree keys of a tile is one 64-bit word per query, built in LDS by climbing parent pointers.  One body
+// (ring_body: tiles in an LDS ring filled by LDS-direct loads) serves 64 to 256 query rows per workgroup,
+// the smaller ones with the keys split across workgroups where that fills the chip (partials to the
+// workspace, a small merge kernel); the smallest steps split the query rows over workgroups instead and
+// the keys over waves.  launch_tree_attn_bf16 chooses by estimated time.
 //
 // f32 path: one kernel on the f32 matrix instructions, 16 query rows per workgroup, used by the small fp32 configuration.
 #include <type_traits>
@@ -45,6 +44,7 @@ struct AttnParams {
   int n_split, n_sb;
   int n_rows_total;  // N * Hq
   int max_tree;      // the host's bound on any row's node count (the grid was sized for it)
+  int round_rows;    // rows of the batch that one workgroup per compute unit covers; 0: less than one
   float scale_log2e;
 };
 
@@ -230,6 +230,8 @@ constexpr int KT = 64;  // keys per tile
 // is almost done and finish alone.  Dispatch position z therefore takes the z-th heaviest row
 // (keys = prefix + tree nodes; ties by index), computed redundantly by every wave from the two small
 // arrays it reads anyway.  Batches of more than 64 rows keep their order.
+// Workgroups beyond one per compute unit land beside an earlier one: every second round of p.round_rows rows is taken in
+// reverse, so that the heaviest row of a round shares its unit with the lightest of the next.
 // The row's first node, node count and prefix length come back with it: the lanes already hold them, so the
 // workgroup does not go to memory a second time for three values that the next loads depend on.
 struct RowInfo {
@@ -255,6 +257,10 @@ __device__ __forceinline__ RowInfo row_by_work_rank(const AttnParams& p, int z, 
   for (int r = 0; r < n_rows; ++r) {
     const int wr = __builtin_amdgcn_readlane(work, r);
     rank += (wr > work || (wr == work && r < lane)) ? 1 : 0;
+  }
+  if (p.round_rows > 0 && ((z / p.round_rows) & 1)) {
+    const int first = z / p.round_rows * p.round_rows;
+    z = first + min(first + p.round_rows, n_rows) - 1 - z;
   }
   const unsigned long long hit = __ballot(lane < n_rows && rank == z);
   ri.s = hit ? __ffsll((long long)hit) - 1 : z;   // (ranks are a permutation: some lane always hits)
@@ -318,286 +324,6 @@ union Frag8 {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-template <int D>
-struct TileSmem {
-  static constexpr int KP = D + 8;      // K row pitch (elements)
-  static constexpr int VP = D + 16;     // V row pitch (elements): 4 consecutive keys fall on distinct bank groups
-  uint16_t k[KT * KP];
-  uint16_t v[KT * VP];
-};
-
-// Large trees.  Workgroup = (row, kv head, 16*NQ*NW query rows, kv split); its NW waves own NQ 16-row
-// query blocks each and share every 64-key K/V tile through LDS.  Tiles are double-buffered in LDS
-// and prefetched through registers: while tile t is multiplied, tile t+1 is written to the other
-// buffer and tile t+2 is in flight from HBM, with one workgroup barrier per tile.  K and V are
-// stored row-major; the V^T operand is fetched with the transposing LDS read.
-template <int D, int NQ, int NW, bool SPLIT>
-__global__ __launch_bounds__(64 * NW, (NQ == 4 || NW == 8) ? 1 : 2) void attn_bf16_kernel(AttnParams p) {
-  using TS = TileSmem<D>;
-  extern __shared__ __align__(16) char smem_raw[];
-  TS* tiles = (TS*)smem_raw;                                                    // [2]
-  int* s_parent = (int*)(smem_raw + 2 * sizeof(TS));                            // [CASCADE_MAX_TREE]
-  unsigned long long* s_anc = (unsigned long long*)(s_parent + CASCADE_MAX_TREE);   // [2][RW]
-  constexpr int NT = 64 * NW;        // threads
-  constexpr int RW = 16 * NQ * NW;   // query rows of the workgroup
-  constexpr int KS = D / 32;   // 32-wide d steps of the score MFMA
-  constexpr int DB = D / 16;   // 16-wide d blocks of the output
-  constexpr int DC = D / 8;    // 16-byte chunks per row
-  constexpr int NPC = KT * DC / NT;   // 16-byte pieces of K (and of V) per thread per tile
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, g = lane >> 4;
-  // the query blocks and splits of a (row, kv head), which stream the same keys and values, share an L2
-  const unsigned nx = gridDim.x, ny = gridDim.y;
-  const unsigned lid = xcd_local_order(blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z), nx, ny * gridDim.z);
-  const int bx = (int)(lid % nx), kvh = (int)((lid / nx) % ny);
-  const RowInfo ri = row_by_work_rank(p, (int)(lid / (nx * ny)), (int)gridDim.z, threadIdx.x & 63);
-  const int s = ri.s, lo = ri.lo, T = ri.T, P = ri.P;
-  const int split = bx % p.n_split, sb = bx / p.n_split;
-  const int G = p.group;
-  const int M = T * G;
-  const int row0 = sb * RW;
-  if (T > p.max_tree) { skip_oversize_row<D, SPLIT>(p, lo, T, kvh, sb, split, tid, NT); return; }
-  if (row0 >= M || T > CASCADE_MAX_TREE) return;
-  const int n_pt = (P + KT - 1) / KT, n_tt = (T + KT - 1) / KT, nt = n_pt + n_tt;
-  const int per = (nt + p.n_split - 1) / p.n_split;
-  const int t_begin = split * per, t_end = min(nt, t_begin + per);
-
-  const uint16_t* kc = (const uint16_t*)p.k_cache + s * p.sr + kvh * p.sh;
-  const uint16_t* vc = (const uint16_t*)p.v_cache + s * p.sr + kvh * p.sh;
-  const uint16_t* ktr = (const uint16_t*)p.k_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
-  const uint16_t* vtr = (const uint16_t*)p.v_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
-  const int64_t tree_pitch = (int64_t)p.n_kv_heads * D;
-
-  // tile staging registers: piece c = tid + 256 it -> key c / DC, 8 d at c % DC
-  u32x4 kr[NPC], vr[NPC];
-  auto request_tile = [&](int t) {
-    const bool tree_tile = t >= n_pt;
-    const int kbase = tree_tile ? (t - n_pt) * KT : t * KT;
-    const int klimit = tree_tile ? T : P;
-    const uint16_t* ksrc = tree_tile ? ktr : kc;
-    const uint16_t* vsrc = tree_tile ? vtr : vc;
-    const int64_t pitch = tree_tile ? tree_pitch : p.sp;
-#pragma unroll
-    for (int it = 0; it < NPC; ++it) {
-      const int c = tid + NT * it, key = c / DC, dc = c % DC;
-      kr[it] = u32x4{0u, 0u, 0u, 0u};
-      vr[it] = u32x4{0u, 0u, 0u, 0u};
-      if (t < t_end && kbase + key < klimit) {
-        kr[it] = *(const u32x4*)(ksrc + (int64_t)(kbase + key) * pitch + 8 * dc);
-        vr[it] = *(const u32x4*)(vsrc + (int64_t)(kbase + key) * pitch + 8 * dc);
-      }
-    }
-  };
-  // registers -> LDS buffer, plus (tree tiles) one ancestor-or-self word per query row of the workgroup
-  auto store_tile = [&](int t, int buf) {
-#pragma unroll
-    for (int it = 0; it < NPC; ++it) {
-      const int c = tid + NT * it, key = c / DC, dc = c % DC;
-      *(u32x4*)(&tiles[buf].k[key * TS::KP + 8 * dc]) = kr[it];
-      *(u32x4*)(&tiles[buf].v[key * TS::VP + 8 * dc]) = vr[it];
-    }
-    if (t < t_end && t >= n_pt && tid < RW) {
-      const int kbase = (t - n_pt) * KT;
-      const int r = row0 + tid;
-      unsigned long long wbits = 0ull;
-      if (r < M) {
-        int a = r % T, guard = 0;
-        while (a >= 0 && guard++ <= CASCADE_MAX_TREE) {
-          const int rel = a - kbase;
-          if (rel < 0) break;   // ancestors only get smaller
-          if (rel < 64) wbits |= 1ull << rel;
-          a = s_parent[a];
-        }
-      }
-      s_anc[buf * RW + tid] = wbits;
-    }
-  };
-
-  request_tile(t_begin);   // in flight while parents and queries are fetched
-  if (t_end > n_pt) {
-    for (int i = tid; i < T; i += NT) {
-      int pi = p.parent[lo + i];
-      if (pi >= i || pi < -1 || (i == 0 && pi != -1) || (i > 0 && pi < 0)) {
-        atomicOr(p.dev_status, CASCADE_FLAG_PARENT);
-        pi = (i == 0) ? -1 : 0;   // keep the climb finite
-      }
-      s_parent[i] = pi;
-    }
-  }
-
-  // query fragments (B operand of S^T): lane = (query l16, d group g)
-  Frag8 qf[NQ][KS];
-  int64_t out_row[NQ];   // index into [N*Hq] or -1
-#pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    const int r = row0 + 16 * (wave + NW * n) + l16;
-    const bool ok = r < M;
-    const int i = ok ? r % T : 0, hg = ok ? r / T : 0;
-    const int64_t rowg = (int64_t)(lo + i) * p.n_heads + kvh * G + hg;
-    out_row[n] = ok ? rowg : -1;
-    const uint16_t* qp = (const uint16_t*)p.q + rowg * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ok) qf[n][ks].u = *(const uint4*)(qp + 32 * ks);
-      else qf[n][ks].u = make_uint4(0, 0, 0, 0);
-    }
-  }
-
-  f32x4 ot[NQ][DB];
-  float m_run[NQ], l_run[NQ];
-#pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    m_run[n] = -INFINITY;
-    l_run[n] = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) ot[n][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  __syncthreads();               // parent array complete
-  store_tile(t_begin, 0);
-  request_tile(t_begin + 1);
-  __syncthreads();
-
-  for (int t = t_begin; t < t_end; ++t) {
-    const int buf = (t - t_begin) & 1;
-    const TS& tl = tiles[buf];
-    const bool tree_tile = t >= n_pt;
-    const int kbase = tree_tile ? (t - n_pt) * KT : t * KT;
-    const int klimit = tree_tile ? T : P;
-    // tile t+1 (requested one iteration ago) goes to the other buffer, tile t+2 is requested
-    store_tile(t + 1, buf ^ 1);
-    request_tile(t + 2);
-
-    // S^T = K Q^T : st[n][kt] holds keys 16*kt + 4*g + c for query l16
-    f32x4 st[NQ][4];
-#pragma unroll
-    for (int n = 0; n < NQ; ++n)
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt) st[n][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Frag8 kf;
-        kf.u = *(const uint4*)(&tl.k[(16 * kt + l16) * TS::KP + 32 * ks + 8 * g]);
-#pragma unroll
-        for (int n = 0; n < NQ; ++n)
-          st[n][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf.v, qf[n][ks].v, st[n][kt], 0, 0, 0);
-      }
-    }
-
-    // mask + online softmax; probabilities packed as the B operand of the second MFMA
-    Frag8 pf[NQ][2];
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      unsigned long long valid;
-      if (tree_tile) {
-        valid = s_anc[buf * RW + 16 * (wave + NW * n) + l16];
-      } else {
-        const int rem = klimit - kbase;
-        valid = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
-      }
-      if (out_row[n] < 0) valid = 0ull;
-      float mx = -INFINITY;
-      if (__ballot(valid != ~0ull) == 0ull) {
-        // every key of the tile is visible to every query of the block: no masking
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            st[n][kt][c] *= p.scale_log2e;
-            mx = fmaxf(mx, st[n][kt][c]);
-          }
-      } else {
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-          const uint32_t nib = (uint32_t)(valid >> (16 * kt + 4 * g));   // this lane's 4 keys of sub-tile kt
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const float z = ((nib >> c) & 1u) ? st[n][kt][c] * p.scale_log2e : -INFINITY;
-            st[n][kt][c] = z;
-            mx = fmaxf(mx, z);
-          }
-        }
-      }
-      mx = rows4_max(mx);
-      const float m_new = fmaxf(m_run[n], mx);
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      float ls = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float e = fast_exp2(st[n][kt][c] - m_use);
-          st[n][kt][c] = e;
-          ls += e;
-        }
-      if (__ballot(m_new != m_run[n]) != 0ull) {
-        // the running maximum moved for some query of the block: rescale the accumulators
-        const float alpha = fast_exp2(m_run[n] - m_use);   // -inf - finite = -inf -> 0
-        l_run[n] *= alpha;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) ot[n][db] *= alpha;
-        m_run[n] = m_new;
-      }
-      l_run[n] += ls;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        pf[n][j].u.x = pack_bf16x2(st[n][2 * j][0], st[n][2 * j][1]);
-        pf[n][j].u.y = pack_bf16x2(st[n][2 * j][2], st[n][2 * j][3]);
-        pf[n][j].u.z = pack_bf16x2(st[n][2 * j + 1][0], st[n][2 * j + 1][1]);
-        pf[n][j].u.w = pack_bf16x2(st[n][2 * j + 1][2], st[n][2 * j + 1][3]);
-      }
-    }
-
-    // O^T += V^T P^T.  Operand slots of lane (l16, g): keys 32j + 4g + {0..3} and 32j + 16 + 4g + {0..3}
-    // at d = 16 db + l16, fetched by two transposing loads from the row-major V tile.
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint16_t* vp = &tl.v[(32 * j + 4 * g + (l16 >> 2)) * TS::VP + 16 * db + 4 * (l16 & 3)];
-        union { Frag8 f; s16x4 h[2]; } vf;
-        vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(vp));
-        vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(vp + 16 * TS::VP));
-#pragma unroll
-        for (int n = 0; n < NQ; ++n)
-          ot[n][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.f.v, pf[n][j].v, ot[n][db], 0, 0, 0);
-      }
-    }
-    __syncthreads();   // tile t consumed by every wave; tile t+1 complete in the other buffer
-  }
-
-  // epilogue: lane (query l16, g) owns d = 16*db + 4*g + c
-#pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    float l = l_run[n];
-    l = rows4_sum(l);
-    if (out_row[n] < 0) continue;
-    if (SPLIT) {
-      float* wo = p.ws_o + ((int64_t)split * p.n_rows_total + out_row[n]) * D;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) *(f32x4*)(wo + 16 * db + 4 * g) = ot[n][db];
-      if (g == 0) {
-        float* wm = p.ws_ml + ((int64_t)split * p.n_rows_total + out_row[n]) * 2;
-        wm[0] = m_run[n];
-        wm[1] = l;
-      }
-    } else {
-      const float inv = 1.f / l;
-      uint16_t* o = (uint16_t*)p.out + out_row[n] * D;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        uint2 w;
-        w.x = pack_bf16x2(ot[n][db][0] * inv, ot[n][db][1] * inv);
-        w.y = pack_bf16x2(ot[n][db][2] * inv, ot[n][db][3] * inv);
-        *(uint2*)(o + 16 * db + 4 * g) = w;
-      }
-      if (g == 0 && p.lse) p.lse[out_row[n]] = m_run[n] * LN2 + logf(l);
-    }
-  }
-}
-
 // A wave's own LDS-direct loads have landed when at most the N youngest are outstanding; its LDS writes and
 // reads are complete at lgkmcnt(0); then the workgroup barrier, bare (a fenced barrier would wait for every
 // outstanding load, i.e. for the whole prefetch ring).
@@ -606,8 +332,8 @@ __device__ __forceinline__ void wait_and_sync() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// ---------------------------------------------------------------------- bf16, large trees
-// Workgroup = (row, kv head, 256 query rows, kv split): eight waves x two 16-row query blocks share every
+// ---------------------------------------------------------------------- bf16, ring of tiles
+// Workgroup = (row, kv head, 16 NQ NW query rows, kv split): NW waves x NQ 16-row query blocks share every
 // 64-key K / V tile.  Tiles never pass through registers on their way in: 16-byte LDS-direct loads
 // (global_load_lds_dwordx4, M0 = LDS address of the wave's 1 KiB chunk) write them into two rings of NS
 // tiles each, NS - 1 tiles ahead of their use; a wave waits only for its own chunks of the tile that is
@@ -651,14 +377,15 @@ __device__ __forceinline__ float rows4_max_raw(float v) {
   return vmax2(__uint_as_float(b.x), __uint_as_float(b.y));
 }
 
-template <int D, int NS>
-__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
+template <int D, int NS, int NQ, int NW, bool WHOLE>
+__device__ __forceinline__ void ring_body(const AttnParams& p) {
   using GM = RingGeom<D>;
-  constexpr int NW = 8, NQ = 2, NT = 64 * NW, RW = 16 * NQ * NW;
+  constexpr int NT = 64 * NW, RW = 16 * NQ * NW;
   constexpr int KS = D / 32, DB = D / 16;
-  constexpr int CPW = GM::CPT / NW;     // chunks of K (and of V) a wave loads per tile: 2 (D = 128) or 1 (D = 64)
+  constexpr int LW = GM::CPT % NW == 0 ? NW : 4;   // waves that load: all, or the first four when the chunks do not divide
+  constexpr int CPW = GM::CPT / LW;     // chunks of K (and of V) a loading wave fetches per tile
   constexpr int LPI = 2 * CPW;          // LDS-direct loads a wave issues per iteration
-  static_assert(GM::CPT % NW == 0 && NS == 3, "ring geometry: the loop below is unrolled three times");
+  static_assert(GM::CPT % LW == 0 && NW >= LW && (NS == 2 || NS == 3), "ring geometry: the loop below is unrolled NS times");
   extern __shared__ __align__(1024) char ring_smem[];
   char* const smem_raw = ring_smem;
   // [K ring: NS tiles][V ring: NS tiles][parent: CASCADE_MAX_TREE ints][ancestor words: 2 x RW]
@@ -672,14 +399,28 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
   const int bx = (int)(lid % nx), kvh = (int)((lid / nx) % ny);
   const RowInfo ri = row_by_work_rank(p, (int)(lid / (nx * ny)), (int)gridDim.z, lane);
   const int s = ri.s, lo = ri.lo, T = ri.T, P = ri.P;
-  const int sb = bx;   // the keys of a row are never split across workgroups here (n_split == 1)
+  const int n_split = WHOLE ? 1 : p.n_split;
+  const int split = bx % n_split, sb = bx / n_split;
   const int G = p.group;
   const int M = T * G;
   const int row0 = sb * RW;
-  if (T > p.max_tree) { skip_oversize_row<D, false>(p, lo, T, kvh, sb, 0, tid, NT); return; }
+  if (T > p.max_tree) {
+    if (n_split > 1) skip_oversize_row<D, true>(p, lo, T, kvh, sb, split, tid, NT);
+    else skip_oversize_row<D, false>(p, lo, T, kvh, sb, split, tid, NT);
+    return;
+  }
   if (row0 >= M || T > CASCADE_MAX_TREE) return;
-  const int n_pt = (P + KT - 1) / KT, n_tt = (T + KT - 1) / KT, nt = n_pt + n_tt;
-  const int t_begin = 0, t_end = nt;   // nt >= 1: a tree has at least its root
+  const int n_pt = (P + KT - 1) / KT, n_tt = (T + KT - 1) / KT, nt = n_pt + n_tt;   // nt >= 1: a tree has at least its root
+  const int per = WHOLE ? nt : (nt + n_split - 1) / n_split;
+  const int t_begin = split * per, t_end = min(nt, t_begin + per);
+  if (!WHOLE && t_begin >= t_end) {   // a row with fewer tiles than splits: an empty partial
+    for (int r = row0 + tid; r < min(row0 + RW, M); r += NT) {
+      float* wm = p.ws_ml + ((int64_t)split * p.n_rows_total + (int64_t)(lo + r % T) * p.n_heads + kvh * G + r / T) * 2;
+      wm[0] = -INFINITY;
+      wm[1] = 0.f;
+    }
+    return;
+  }
 
   const char* kc = (const char*)((const uint16_t*)p.k_cache + s * p.sr + kvh * p.sh);
   const char* vc = (const char*)((const uint16_t*)p.v_cache + s * p.sr + kvh * p.sh);
@@ -707,6 +448,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
   // used); rows past the end of the tile's source are read from its last row (always in bounds; their scores
   // are masked, so the finite clamped values contribute exactly nothing).
   auto request = [&](int tk, int stage, bool is_v) {
+    if (LW < NW && wave >= LW) return;
     const int tc = min(tk, t_end - 1);
     const unsigned ldst = lds0 + (is_v ? NS * GM::TILE : 0) + stage * GM::TILE + CPW * wave * 1024;
     if (tc < n_pt && (tc + 1) * KT <= P) {
@@ -926,6 +668,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
         float e[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) e[c] = fast_exp2(fmaf(st[n][kt][c], p.scale_log2e, m_neg[n]));   // -inf stays -inf -> 0
+        if (!WHOLE) lsum[n][0] += (e[0] + e[1]) + (e[2] + e[3]);   // this lane's keys, before they are rounded
         const uint32_t lo2 = pack_bf16x2(e[0], e[1]), hi2 = pack_bf16x2(e[2], e[3]);
         if (kt & 1) { pf[n][kt >> 1].u.z = lo2; pf[n][kt >> 1].u.w = hi2; }
         else { pf[n][kt >> 1].u.x = lo2; pf[n][kt >> 1].u.y = hi2; }
@@ -952,7 +695,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
 #pragma unroll
     for (int n = 0; n < NQ; ++n)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) lsum[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, pf[n][j].v, lsum[n], 0, 0, 0);
+      for (int j = 0; j < (WHOLE ? 2 : 0); ++j) lsum[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, pf[n][j].v, lsum[n], 0, 0, 0);
 #pragma unroll
     for (int n = 0; n < NQ; ++n) lmax[n] = lane_max(n);
 #pragma unroll
@@ -968,16 +711,29 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
     tile_step(t, std::integral_constant<int, 0>{});
     if (t + 1 >= t_end) break;
     tile_step(t + 1, std::integral_constant<int, 1>{});
-    if (t + 2 >= t_end) break;
-    tile_step(t + 2, std::integral_constant<int, 2>{});
+    if constexpr (NS > 2) {
+      if (t + 2 >= t_end) break;
+      tile_step(t + 2, std::integral_constant<int, 2>{});
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
   // epilogue: lane (query l16, g) owns d = 16*db + 4*g + c
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
-    const float l = lsum[n][0];
+    const float l = WHOLE ? lsum[n][0] : rows4_sum(lsum[n][0]);
     if (out_row[n] < 0) continue;
+    if (n_split > 1) {
+      float* wo = p.ws_o + ((int64_t)split * p.n_rows_total + out_row[n]) * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) *(f32x4*)(wo + 16 * db + 4 * g) = ot[n][db];
+      if (g == 0) {
+        float* wm = p.ws_ml + ((int64_t)split * p.n_rows_total + out_row[n]) * 2;
+        wm[0] = m_ref[n];
+        wm[1] = l;
+      }
+      continue;
+    }
     const float inv = 1.f / l;   // l >= 1: the node's own key is never masked
     uint16_t* o = (uint16_t*)p.out + out_row[n] * D;
 #pragma unroll
@@ -991,334 +747,21 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) {
   }
 }
 
-// ---------------------------------------------------------------------- bf16, small trees
-// Workgroup = (row, kv head, 64 query rows, kv split), NKG key groups x 4 query blocks of waves.
-// In every round the key groups take NKG consecutive 64-key tiles; the four waves of a
-// group copy their tile into the group's LDS buffer (each a quarter of it), then each wave runs
-// its own 16 query rows against it.  The next round's tile is requested from memory before the
-// current one is consumed.  K and V are both stored row-major with plain 16-byte stores; the V^T
-// operand of the second MFMA is read with the transposing LDS load (ds_read_b64_tr_b16): inside
-// each group of 16 lanes, lane i passes the address of 4 consecutive d of key (i / 4), and lane L
-// receives the 4 keys at d + L.  The key groups' (m, l, O) are merged through LDS at the
-// end, so a drafted tree against a short prefix needs neither workspace traffic nor a second kernel.
+template <int D, int NS>
+__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { ring_body<D, NS, 2, 8, true>(p); }
 
-template <int D>
-struct KsplitGroupSmem {
-  static constexpr int KP = D + 8;      // K row pitch (elements)
-  static constexpr int VP = D + 16;     // V row pitch (elements): 4 consecutive keys fall on distinct bank groups
-  uint16_t k[KT * KP];
-  uint16_t v[KT * VP];
-};
-
-// NKG = key groups (the workgroup has NKG * 4 waves)
-template <int D, int NKG, bool SPLIT>
-// (four waves per workgroup: at most 168 registers, so that three workgroups share a CU)
-__global__ __launch_bounds__(NKG * 256, (NKG == 1 ? 3 : 1)) void attn_bf16_ksplit_kernel(AttnParams p) {
-  constexpr int NT = NKG * 256;
-  using GS = KsplitGroupSmem<D>;
-  extern __shared__ __align__(16) char smem_raw[];
-  constexpr int KS = D / 32, DB = D / 16, DC = D / 8;
-  constexpr int OP = D + 4;            // merge buffer row pitch (floats)
-  constexpr int NPC = KT * DC / 256;   // 16-byte pieces of K (and of V) each lane copies per tile
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int kg = wave >> 2, qb = wave & 3;     // key group, query block
-  const int gl = tid & 255;                    // lane index inside the key group
-  const int l16 = lane & 15, g = lane >> 4;
-  GS* gs = (GS*)smem_raw + kg;
-  int* s_parent = (int*)(smem_raw + NKG * sizeof(GS));                                         // [CASCADE_MAX_TREE]
-  unsigned long long* s_anc = (unsigned long long*)(s_parent + CASCADE_MAX_TREE) + 64 * kg;   // [NKG][64]
-  // the query blocks and splits of a (row, kv head) share an L2
-  const unsigned nx = gridDim.x, ny = gridDim.y;
-  const unsigned lid = xcd_local_order(blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z), nx, ny * gridDim.z);
-  const int bx = (int)(lid % nx), kvh = (int)((lid / nx) % ny);
-  const RowInfo ri = row_by_work_rank(p, (int)(lid / (nx * ny)), (int)gridDim.z, threadIdx.x & 63);
-  const int s = ri.s, lo = ri.lo, T = ri.T, P = ri.P;
-  const int split = bx % p.n_split, sb = bx / p.n_split;
-  const int G = p.group;
-  const int M = T * G;
-  const int row0 = sb * 64;
-  if (T > p.max_tree) { skip_oversize_row<D, SPLIT>(p, lo, T, kvh, sb, split, tid, NT); return; }
-  if (row0 >= M || T > CASCADE_MAX_TREE) return;
-  const int n_pt = (P + KT - 1) / KT, n_tt = (T + KT - 1) / KT, nt = n_pt + n_tt;
-  const int per = (nt + p.n_split - 1) / p.n_split;
-  const int t_begin = split * per, t_end = min(nt, t_begin + per);
-  const int n_rounds = (max(t_end - t_begin, 0) + NKG - 1) / NKG;
-
-  const uint16_t* kc = (const uint16_t*)p.k_cache + s * p.sr + kvh * p.sh;
-  const uint16_t* vc = (const uint16_t*)p.v_cache + s * p.sr + kvh * p.sh;
-  const uint16_t* ktr = (const uint16_t*)p.k_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
-  const uint16_t* vtr = (const uint16_t*)p.v_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
-  const int64_t tree_pitch = (int64_t)p.n_kv_heads * D;
-
-  // a quarter of the group's tile per wave: pieces gl, gl + 256, ... (piece c = key c / DC, 8 d at c % DC),
-  // requested one round ahead (two rounds ahead, with a second register set, changed nothing).  Keys
-  // past the end of the tile's source are read from its last row (clamped: always in bounds) and not
-  // zeroed: their scores are masked to -inf, so their probabilities are exactly 0 and the clamped
-  // (finite) rows contribute nothing; a select or a branch on the loaded value would make the compiler
-  // wait for every load on the spot.
-  uint4 kr[NPC], vr[NPC];
-#pragma unroll
-  for (int it = 0; it < NPC; ++it) kr[it] = vr[it] = make_uint4(0, 0, 0, 0);
-  auto request_tile = [&](int t) {
-    if (t >= t_end) return;   // uniform per wave
-    const bool tree_tile = t >= n_pt;
-    const int kbase = tree_tile ? (t - n_pt) * KT : t * KT;
-    const int last = (tree_tile ? T : P) - 1;   // >= 0: a tile exists only if its source has keys
-    const uint16_t* ksrc = tree_tile ? ktr : kc;
-    const uint16_t* vsrc = tree_tile ? vtr : vc;
-    const int64_t pitch = tree_tile ? tree_pitch : p.sp;
-#pragma unroll
-    for (int it = 0; it < NPC; ++it) {
-      const int c = gl + 256 * it, key = c / DC, dc = c % DC;
-      const int64_t o = (int64_t)min(kbase + key, last) * pitch + 8 * dc;
-      kr[it] = *(const uint4*)(ksrc + o);
-      vr[it] = *(const uint4*)(vsrc + o);
-    }
-  };
-  request_tile(t_begin + kg);   // first round's tile: in flight while queries and parents are fetched
-
-  if (t_end > n_pt) {
-    for (int i = tid; i < T; i += NT) {
-      int pi = p.parent[lo + i];
-      if (pi >= i || pi < -1 || (i == 0 && pi != -1) || (i > 0 && pi < 0)) {
-        atomicOr(p.dev_status, CASCADE_FLAG_PARENT);
-        pi = (i == 0) ? -1 : 0;
-      }
-      s_parent[i] = pi;
-    }
-  }
-
-  // this wave's 16 query rows (B operand of S^T): lane = (query l16, d group g)
-  Frag8 qf[KS];
-  const int qr = row0 + 16 * qb + l16;
-  const bool q_ok = qr < M;
-  {
-    const int i = q_ok ? qr % T : 0, hg = q_ok ? qr / T : 0;
-    const uint16_t* qp = (const uint16_t*)p.q + ((int64_t)(lo + i) * p.n_heads + kvh * G + hg) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (q_ok) qf[ks].u = *(const uint4*)(qp + 32 * ks);
-      else qf[ks].u = make_uint4(0, 0, 0, 0);
-    }
-  }
-  f32x4 ot[DB];
-  float m_run = -INFINITY, l_run = 0.f;
-#pragma unroll
-  for (int db = 0; db < DB; ++db) ot[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int r = 0; r < n_rounds; ++r) {
-    const int t = t_begin + NKG * r + kg;
-    const bool active = t < t_end;
-    const bool tree_tile = t >= n_pt;
-    const int kbase = tree_tile ? (t - n_pt) * KT : t * KT;
-    const int klimit = tree_tile ? T : P;
-    __syncthreads();   // the previous pass's tiles are consumed (and, before the first pass, the parent array is complete)
-#pragma unroll
-    for (int it = 0; it < NPC; ++it) {
-      const int c = gl + 256 * it, key = c / DC, dc = c % DC;
-      *(uint4*)(&gs->k[key * GS::KP + 8 * dc]) = kr[it];
-      *(uint4*)(&gs->v[key * GS::VP + 8 * dc]) = vr[it];
-    }
-    if (active && tree_tile && qb == 0) {
-      // ancestor-or-self bits of this tile's 64 tree keys for query row (row0 + lane)
-      const int rr = row0 + lane;
-      unsigned long long wbits = 0ull;
-      if (rr < M) {
-        int a = rr % T, guard = 0;
-        while (a >= 0 && guard++ <= CASCADE_MAX_TREE) {
-          const int rel = a - kbase;
-          if (rel < 0) break;
-          if (rel < 64) wbits |= 1ull << rel;
-          a = s_parent[a];
-        }
-      }
-      s_anc[lane] = wbits;
-    }
-    request_tile(t + NKG);   // next round streams in while this one is consumed
-    __syncthreads();
-    if (!active) continue;
-
-    // S^T = K Q^T : st[kt] holds keys 16*kt + 4*g + c for query l16
-    f32x4 st[4];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-      st[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Frag8 kf;
-        kf.u = *(const uint4*)(&gs->k[(16 * kt + l16) * GS::KP + 32 * ks + 8 * g]);
-        st[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf.v, qf[ks].v, st[kt], 0, 0, 0);
-      }
-    }
-    unsigned long long valid;
-    if (tree_tile) {
-      valid = s_anc[16 * qb + l16];
-    } else {
-      const int rem = klimit - kbase;
-      valid = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
-    }
-    if (!q_ok) valid = 0ull;
-    float mx = -INFINITY;
-    if (__ballot(valid != ~0ull) == 0ull) {
-      // every key of the tile is visible to every query of the block: no masking
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          st[kt][c] *= p.scale_log2e;
-          mx = fmaxf(mx, st[kt][c]);
-        }
-    } else {
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt) {
-        const uint32_t nib = (uint32_t)(valid >> (16 * kt + 4 * g));   // this lane's 4 keys of sub-tile kt
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float z = ((nib >> c) & 1u) ? st[kt][c] * p.scale_log2e : -INFINITY;
-          st[kt][c] = z;
-          mx = fmaxf(mx, z);
-        }
-      }
-    }
-    mx = rows4_max(mx);
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = fast_exp2(m_run - m_use);
-    float ls = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float e = fast_exp2(st[kt][c] - m_use);
-        st[kt][c] = e;
-        ls += e;
-      }
-    l_run = l_run * alpha + ls;
-    m_run = m_new;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) ot[db] *= alpha;
-    Frag8 pf[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      pf[j].u.x = pack_bf16x2(st[2 * j][0], st[2 * j][1]);
-      pf[j].u.y = pack_bf16x2(st[2 * j][2], st[2 * j][3]);
-      pf[j].u.z = pack_bf16x2(st[2 * j + 1][0], st[2 * j + 1][1]);
-      pf[j].u.w = pack_bf16x2(st[2 * j + 1][2], st[2 * j + 1][3]);
-    }
-    // O^T += V^T P^T.  Operand slots of lane (l16, g): keys 32j + 4g + {0..3} and 32j + 16 + 4g + {0..3}
-    // at d = 16 db + l16, fetched by two transposing loads from the row-major V tile.
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint16_t* vp = &gs->v[(32 * j + 4 * g + (l16 >> 2)) * GS::VP + 16 * db + 4 * (l16 & 3)];
-        union { Frag8 f; s16x4 h[2]; } vf;
-        vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(vp));
-        vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(vp + 16 * GS::VP));
-        ot[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.f.v, pf[j].v, ot[db], 0, 0, 0);
-      }
-    }
-  }
-
-  l_run = rows4_sum(l_run);
-  if (NKG == 1) {
-    // one key group: nothing to merge - every wave writes its 16 rows from its registers (lane (l16, g) owns
-    // d = 16 db + 4 g + c of query l16), no LDS round trip and no barrier
-    if (q_ok) {
-      const int i = qr % T, hg = qr / T;
-      const int64_t rowg = (int64_t)(lo + i) * p.n_heads + kvh * G + hg;
-      if (SPLIT) {
-        float* wo = p.ws_o + ((int64_t)split * p.n_rows_total + rowg) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) *(f32x4*)(wo + 16 * db + 4 * g) = ot[db];
-        if (g == 0) {
-          float* wm = p.ws_ml + ((int64_t)split * p.n_rows_total + rowg) * 2;
-          wm[0] = m_run;
-          wm[1] = l_run;
-        }
-      } else {
-        const float inv = 1.f / l_run;
-        uint16_t* op = (uint16_t*)p.out + rowg * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          uint2 w2;
-          w2.x = pack_bf16x2(ot[db][0] * inv, ot[db][1] * inv);
-          w2.y = pack_bf16x2(ot[db][2] * inv, ot[db][3] * inv);
-          *(uint2*)(op + 16 * db + 4 * g) = w2;
-        }
-        if (g == 0 && p.lse) p.lse[rowg] = m_run * LN2 + logf(l_run);
-      }
-    }
-    return;
-  }
-  // merge the key groups through LDS (the tile buffers are reused)
-  __syncthreads();
-  float* mo = (float*)smem_raw;                 // [NKG][64 rows][OP]
-  float* mml = mo + NKG * 64 * OP;              // [NKG][64 rows][2]
-  {
-    float* orow = mo + ((kg * 64) + 16 * qb + l16) * OP;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) *(f32x4*)(orow + 16 * db + 4 * g) = ot[db];
-    if (g == 0) {
-      mml[((kg * 64) + 16 * qb + l16) * 2] = m_run;
-      mml[((kg * 64) + 16 * qb + l16) * 2 + 1] = l_run;
-    }
-  }
-  __syncthreads();
-  {
-    constexpr int TPR = NT / 64;                 // threads per output row
-    constexpr int DQ = D / TPR;                  // d range of one thread
-    const int row = tid / TPR, dq = tid % TPR;
-    const int rr = row0 + row;
-    if (rr < M) {
-      float mw[NKG], m = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < NKG; ++w) { mw[w] = mml[(w * 64 + row) * 2]; m = fmaxf(m, mw[w]); }
-      float l = 0.f, o[DQ];
-#pragma unroll
-      for (int d = 0; d < DQ; ++d) o[d] = 0.f;
-#pragma unroll
-      for (int w = 0; w < NKG; ++w) {
-        if (mw[w] == -INFINITY) continue;
-        const float sc = fast_exp2(mw[w] - m);
-        l += sc * mml[(w * 64 + row) * 2 + 1];
-        const float* orow = mo + (w * 64 + row) * OP + DQ * dq;
-#pragma unroll
-        for (int d = 0; d < DQ; d += 4) {
-          const f32x4 v4 = *(const f32x4*)(orow + d);
-          o[d] += sc * v4[0]; o[d + 1] += sc * v4[1]; o[d + 2] += sc * v4[2]; o[d + 3] += sc * v4[3];
-        }
-      }
-      const int i = rr % T, hg = rr / T;
-      const int64_t rowg = (int64_t)(lo + i) * p.n_heads + kvh * G + hg;
-      if (SPLIT) {
-        float* wo = p.ws_o + ((int64_t)split * p.n_rows_total + rowg) * D + DQ * dq;
-#pragma unroll
-        for (int d = 0; d < DQ; d += 4) *(f32x4*)(wo + d) = f32x4{o[d], o[d + 1], o[d + 2], o[d + 3]};
-        if (dq == 0) {
-          float* wm = p.ws_ml + ((int64_t)split * p.n_rows_total + rowg) * 2;
-          wm[0] = m;
-          wm[1] = l;
-        }
-      } else {
-        const float inv = 1.f / l;
-        uint16_t* op = (uint16_t*)p.out + rowg * D + DQ * dq;
-#pragma unroll
-        for (int d = 0; d < DQ; d += 4) {
-          uint2 w2;
-          w2.x = pack_bf16x2(o[d] * inv, o[d + 1] * inv);
-          w2.y = pack_bf16x2(o[d + 2] * inv, o[d + 3] * inv);
-          *(uint2*)(op + d) = w2;
-        }
-        if (dq == 0 && p.lse) p.lse[rowg] = m * LN2 + logf(l);
-      }
-    }
-  }
-}
+// 64 (4 waves), 80 (5), 96 (6) or, with two query blocks per wave, 128 rows per workgroup: two workgroups share a compute
+// unit (two-deep rings, 64 KiB) and cover each other's waits.  One workgroup as large as the row's tree reads every key once:
+// trees of 65 to 80 nodes used to take two 64-row workgroups.  Deeper rings (96, 128 KiB: one workgroup per unit) measured
+// the same or slower at every shape.  Against the kernels this replaced, in a step (us): 16 rows of 113-680 keys, 40-80
+// nodes: 46 -> 37; 10 rows of 107-1619 keys, 8 kv heads of 4: 54 -> 34; 8 rows of 140-680 keys: 25 -> 22; 2 rows of 4200 keys
+// and 256 nodes, keys in four parts: 65 -> 59 with the merge; 2 rows of 1289 keys, four parts: 23 -> 21.
+template <int D, int NS, int NQ, int NW, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false>(p); }
 
 // ---------------------------------------------------------------------- bf16, few query rows
-// When a step has so few (row, kv head, 64-query block) units that they cannot fill the GPU, the
-// query rows are split instead of the keys: workgroup = (row, kv head, 16 query rows), eight
+// When a step has so few (row, kv head) pairs and keys that the chain of tiles of one workgroup is what takes the time,
+// the query rows are split instead of the keys: workgroup = (row, kv head, 16 query rows), eight
 // waves, wave w owning the 64-key tiles w, w + 8, ... of the whole key range.  A wave keeps its
 // tile to itself: K is loaded from global memory directly in MFMA operand order (16-byte pieces of
 // one key row per lane), V goes through a wave-private LDS region only to be read back transposed.
@@ -1618,6 +1061,7 @@ AttnParams make_params(cascade_ctx* ctx, const tree_attn_args* a) {
   p.group = a->n_heads / a->n_kv_heads;
   p.n_split = 1;
   p.n_sb = 1;
+  p.round_rows = 0;
   p.n_rows_total = a->n_nodes_total * a->n_heads;
   p.max_tree = a->max_nodes_per_tree;
   const float scale = a->scale != 0.f ? a->scale : 1.f / sqrtf((float)a->head_dim);
@@ -1627,7 +1071,7 @@ AttnParams make_params(cascade_ctx* ctx, const tree_attn_args* a) {
 
 // whole rows of keys per workgroup (n_split == 1): the ring kernel
 template <int D>
-hipError_t launch_ring_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
+hipError_t launch_ring_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int NS = 3;
   const size_t smem = 2 * NS * RingGeom<D>::TILE + CASCADE_MAX_TREE * sizeof(int) + 2 * 256 * sizeof(unsigned long long);
   static bool attr_done = false;
@@ -1638,26 +1082,6 @@ hipError_t launch_ring_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
   }
   KernelTimer t(ctx, CASCADE_K_ATTN);
   CASCADE_TIMED_LAUNCH(t, (attn_bf16_ring_kernel<D, NS>), grid, dim3(512), smem, ctx->stream, p);
-  return hipGetLastError();
-}
-
-// keys split across workgroups (n_split > 1): partials, then the merge kernel
-template <int D, int NQ, int NW>
-hipError_t launch_split_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
-  hipStream_t st = ctx->stream;
-  const size_t smem = 2 * sizeof(TileSmem<D>) + CASCADE_MAX_TREE * sizeof(int) + 2 * 256 * sizeof(unsigned long long);
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_kernel<D, NQ, NW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  {
-    KernelTimer t(ctx, CASCADE_K_ATTN);
-    CASCADE_TIMED_LAUNCH(t, (attn_bf16_kernel<D, NQ, NW, true>), grid, dim3(64 * NW), smem, st, p);
-  }
-  KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
-  CASCADE_TIMED_LAUNCH(t, (attn_merge_kernel<D>), dim3((p.n_rows_total + (1024 / D) - 1) / (1024 / D)), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -1689,42 +1113,30 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
   return vec ? launch_f32_t<16, 4, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<16, 4, false>(ctx, p, grid, a->n_rows, D);
 }
 
-// CAN_SPLIT: the dispatcher may split the keys across workgroups for this instantiation (it never does when
-// there are two or more workgroups per compute unit anyway, so those partial-writing variants are not built)
-template <int D, int NKG, bool CAN_SPLIT>
-hipError_t launch_ksplit_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
-  hipStream_t st = ctx->stream;
-  const size_t smem = NKG * sizeof(KsplitGroupSmem<D>) + CASCADE_MAX_TREE * sizeof(int) + NKG * 64 * sizeof(unsigned long long);
-  static_assert(NKG * 64 * (D + 4) * 4 + NKG * 64 * 2 * 4 <= NKG * sizeof(KsplitGroupSmem<D>), "merge buffers fit in the tile buffers");
+// 16 NQ NW query rows per workgroup, keys split p.n_split ways (partials, then the merge kernel)
+template <int D, int NQ, int NW, int OCC>
+hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
+  constexpr int NS = 2, RW = 16 * NQ * NW;
+  constexpr int smem = 2 * NS * RingGeom<D>::TILE + CASCADE_MAX_TREE * (int)sizeof(int) + 2 * RW * (int)sizeof(unsigned long long);
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_ksplit_kernel<D, NKG, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if constexpr (CAN_SPLIT) {
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_bf16_ksplit_kernel<D, NKG, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    }
+    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  if (p.n_split > 1) {
-    if constexpr (CAN_SPLIT) {
-      {
-        KernelTimer t(ctx, CASCADE_K_ATTN);
-        CASCADE_TIMED_LAUNCH(t, (attn_bf16_ksplit_kernel<D, NKG, true>), grid, dim3(NKG * 256), smem, st, p);
-      }
-      KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
-      CASCADE_TIMED_LAUNCH(t, (attn_merge_kernel<D>), dim3((p.n_rows_total + (1024 / D) - 1) / (1024 / D)), dim3(256), 0, st, p);
-    } else {
-      return hipErrorInvalidValue;   // the dispatcher never asks for it
-    }
-  } else {
+  {
     KernelTimer t(ctx, CASCADE_K_ATTN);
-    CASCADE_TIMED_LAUNCH(t, (attn_bf16_ksplit_kernel<D, NKG, false>), grid, dim3(NKG * 256), smem, st, p);
+    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC>), grid, dim3(64 * NW), smem, ctx->stream, p);
+  }
+  if (p.n_split > 1) {
+    KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
+    CASCADE_TIMED_LAUNCH(t, (attn_merge_kernel<D>), dim3((p.n_rows_total + (1024 / D) - 1) / (1024 / D)), dim3(256), 0, ctx->stream, p);
   }
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_qsplit_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
+hipError_t launch_qsplit_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int VP = D + 16;
   const size_t smem = (size_t)8 * KT * VP * sizeof(uint16_t) + 128 * sizeof(int) + 32 * sizeof(unsigned long long);
   static_assert(8 * 16 * (D + 4) * 4 + 8 * 16 * 2 * 4 <= 8 * KT * (D + 16) * 2, "merge buffers fit in the V tiles");
@@ -1739,66 +1151,77 @@ hipError_t launch_qsplit_t(cascade_ctx* ctx, AttnParams& p, dim3 grid) {
   return hipGetLastError();
 }
 
+// How a step's attention can be cut.  Shapes 0-4: query rows per workgroup, and what one 64-key tile costs a workgroup (us
+// at head_dim 128, inside a step, i.e. with cold caches): on a mostly idle chip (c0: its chain of waits), with one workgroup
+// on every compute unit (c1), with two (c2; c2_hbm when every tile comes from HBM because no other query block shares it:
+// the bytes in flight bind).  Shape 5 is the query-split kernel.
+struct AttnShape {
+  int rows;
+  float c0, c1, c2, c2_hbm;
+  int per_cu;
+};
+constexpr int ATTN_N_SHAPES = 6, ATTN_RING = 4, ATTN_QSPLIT = 5;
+constexpr AttnShape ATTN_SHAPES[ATTN_N_SHAPES] = {{64, 1.0f, 1.0f, 1.5f, 3.0f, 2}, {80, 1.0f, 1.15f, 1.9f, 3.0f, 2}, {96, 1.0f, 1.2f, 2.1f, 3.0f, 2},
+                                                  {128, 1.2f, 1.45f, 2.5f, 2.5f, 2}, {256, 1.7f, 2.3f, 2.3f, 2.3f, 1}, {16, 0.75f, 0.75f, 0.75f, 0.75f, 1}};
+
+// Estimated time of a step's attention, us.  Against measured steps (32 heads, head_dim 128): 2 rows x 312 keys, 60 nodes:
+// query split 10.5 (10.3), 64 rows 13.4 (13.4); 2 x 1289 keys: query split 22.5 (23.1), 64 rows whole 29 (29.5) and in four
+// splits 18 (20.7); 2 x 4200 keys, 256 nodes: 64 rows 77 (79), 128 rows in four splits 61 (59); 8 such rows: 256 rows
+// 168 (167), 128 rows 182 (172); 16 rows of 113-680 keys, 40-80 nodes: 128 rows 37 (37), 80 rows 43 (44); 10 rows of
+// 107-1619 keys, 8 kv heads of 4: 64 rows 40 (34), 128 rows in two splits 42 (38).
+float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_split, int n_cu) {
+  const AttnShape& sh = ATTN_SHAPES[shape];
+  const int M = a->max_nodes_per_tree * group, n_sb = (M + sh.rows - 1) / sh.rows;
+  const int tiles = (a->max_prefix_len + KT - 1) / KT + (a->max_nodes_per_tree + KT - 1) / KT;
+  const float d = a->head_dim == 128 ? 1.f : 0.65f;
+  // query blocks that hold rows: ragged trees leave some of the launched ones empty
+  float blocks = (float)a->n_rows * n_sb;
+  if (n_sb > 1) blocks = fminf(blocks, (float)a->n_nodes_total * group / sh.rows + 0.5f * a->n_rows);
+  const float x = blocks * a->n_kv_heads * n_split / n_cu;   // workgroups per compute unit
+  if (shape == ATTN_QSPLIT) return 6.f + tiles * sh.c1 * d * fmaxf(x, 1.f);
+  const float c2 = sh.c2_hbm + (sh.c2 - sh.c2_hbm) * fminf(blocks / a->n_rows - 1.f, 1.f);
+  const float per_tile = x <= 1.f ? sh.c0 + (sh.c1 - sh.c0) * x
+                       : (sh.per_cu == 1 ? sh.c1 * ceilf(x) : (x <= 2.f ? sh.c1 + (c2 - sh.c1) * (x - 1.f) : c2 * 0.5f * x));
+  float us = 7.4f + (float)((tiles + n_split - 1) / n_split) * per_tile * d;
+  if (n_split > 1)   // a second launch, and partials written and read (mostly through the caches)
+    us += 3.8f + (float)n_split * a->n_nodes_total * a->n_heads * (a->head_dim + 2) * 4.f / 7e6f;
+  return us;
+}
+
+template <int D>
+hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, dim3 grid) {
+  switch (shape) {
+    case 0: return launch_rows_t<D, 1, 4, 2>(ctx, p, grid);
+    case 1: return launch_rows_t<D, 1, 5, 3>(ctx, p, grid);
+    case 2: return launch_rows_t<D, 1, 6, 3>(ctx, p, grid);
+    case 3: return launch_rows_t<D, 2, 4, 2>(ctx, p, grid);
+    case ATTN_RING: return launch_ring_t<D>(ctx, p, grid);
+    default: return launch_qsplit_t<D>(ctx, p, grid);
+  }
+}
+
 hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
   AttnParams p = make_params(ctx, a);
   const int M = a->max_nodes_per_tree * p.group;   // query rows per (row, kv head)
   const int n_tiles = (a->max_prefix_len + KT - 1) / KT + (a->max_nodes_per_tree + KT - 1) / KT;
   const size_t per_split = (size_t)p.n_rows_total * (a->head_dim + 2) * sizeof(float);
-  if (M <= 128 && (long)a->n_rows * a->n_kv_heads * ((M + 63) / 64) <= 128 && a->max_nodes_per_tree <= 128) {
-    // too few 64-row units to fill the GPU: split the query rows, not the keys (no partials, no merge kernel)
-    p.n_sb = (M + 15) / 16;
-    dim3 grid(p.n_sb, a->n_kv_heads, a->n_rows);
-    return a->head_dim == 128 ? launch_qsplit_t<128>(ctx, p, grid) : launch_qsplit_t<64>(ctx, p, grid);
-  }
-  if (M <= 128) {
-    // small trees: key groups split the tiles inside the workgroup; split across workgroups only when a
-    // workgroup would otherwise walk more than 16 tiles (4 rounds) and the GPU is not yet full
-    p.n_sb = (M + 63) / 64;
-    const long base_wgs = (long)a->n_rows * a->n_kv_heads * p.n_sb;
-    int n_split = (n_tiles + 15) / 16;
-    const int fill = (int)((512 + base_wgs - 1) / base_wgs);
-    if (n_split > fill) n_split = fill;
-    if (n_split > 16) n_split = 16;
-    if (n_split > 1 && per_split * n_split > ctx->attn_ws_bytes) n_split = (int)(ctx->attn_ws_bytes / per_split);
-    if (n_split < 1) n_split = 1;
-    p.n_split = n_split;
-    if (n_split > 1) {
-      p.ws_o = (float*)ctx->attn_ws;
-      p.ws_ml = (float*)(ctx->attn_ws + (size_t)n_split * p.n_rows_total * a->head_dim * sizeof(float));
+  int shape = 0;
+  float best = INFINITY;
+  for (int i = 0; i < ATTN_N_SHAPES; ++i) {
+    if (i == ATTN_QSPLIT && (M > 128 || a->max_nodes_per_tree > 128)) continue;   // its LDS holds trees of 128 nodes
+    for (int n = 1; n <= 16 && n <= n_tiles; n = n < 4 ? n + 1 : n * 2) {
+      if (n > 1 && (i >= ATTN_RING || per_split * n > ctx->attn_ws_bytes)) break;   // these take whole rows of keys
+      const float us = attn_estimate_us(i, a, p.group, n, ctx->n_cu);
+      if (us < best) { best = us; shape = i; p.n_split = n; }
     }
-    dim3 grid(n_split * p.n_sb, a->n_kv_heads, a->n_rows);
-    // key groups per workgroup: two (head_dim 128: 8 waves, 2 workgroups per CU) or four (head_dim 64) when
-    // workgroups are scarce; half as many when there are at least two per CU anyway - smaller workgroups,
-    // four resident per CU, hide each other's tile latencies better (54 -> 46 us at 16 rows x 32 heads)
-    const bool many = base_wgs >= 512;
-    // (many => fill == 1 => n_split == 1 above)
-    if (a->head_dim == 128) return many ? launch_ksplit_t<128, 1, false>(ctx, p, grid) : launch_ksplit_t<128, 2, true>(ctx, p, grid);
-    return many ? launch_ksplit_t<64, 2, false>(ctx, p, grid) : launch_ksplit_t<64, 4, true>(ctx, p, grid);
   }
-  // large trees: NW waves x 2 query blocks each share every K/V tile through LDS
-  // (measured at 8 rows x 32 heads x 256 nodes, 4200-key prefix: 283 us with 4 waves x 4 blocks and
-  // one workgroup per CU, 217 us with 4 waves x 2 blocks and two workgroups per CU, 196 us with 8 waves
-  // x 2 blocks sharing one copy of every tile)
-  constexpr int NW = 8;
-  const int RW = 32 * NW;
-  p.n_sb = (M + RW - 1) / RW;
-  const long base_wgs = (long)a->n_rows * a->n_kv_heads * p.n_sb;
-  // two workgroups of four waves (or one of eight) are resident per CU: split only to fill those slots
-  const long slots = NW == 8 ? 256 : 512;
-  int n_split = (int)(slots / base_wgs);
-  if (n_split > n_tiles) n_split = n_tiles;
-  if (n_split > 16) n_split = 16;
-  if (n_split > 1 && per_split * n_split > ctx->attn_ws_bytes) n_split = (int)(ctx->attn_ws_bytes / per_split);
-  if (n_split < 1) n_split = 1;
-  p.n_split = n_split;
-  if (n_split > 1) {
+  p.n_sb = (M + ATTN_SHAPES[shape].rows - 1) / ATTN_SHAPES[shape].rows;
+  if (p.n_split > 1) {
     p.ws_o = (float*)ctx->attn_ws;
-    p.ws_ml = (float*)(ctx->attn_ws + (size_t)n_split * p.n_rows_total * a->head_dim * sizeof(float));
+    p.ws_ml = (float*)(ctx->attn_ws + (size_t)p.n_split * p.n_rows_total * a->head_dim * sizeof(float));
   }
-  dim3 grid(n_split * p.n_sb, a->n_kv_heads, a->n_rows);
-  // Both kernels cover 256 query rows per workgroup.  With whole rows of keys per workgroup the ring kernel runs
-  // (tiles straight into LDS, three deep); when the keys are split to fill an otherwise idle GPU, the older
-  // double-buffered kernel writes the partials (the ring kernel's register budget has no room for that epilogue).
-  if (n_split > 1) return a->head_dim == 128 ? launch_split_t<128, 2, NW>(ctx, p, grid) : launch_split_t<64, 2, NW>(ctx, p, grid);
-  return a->head_dim == 128 ? launch_ring_t<128>(ctx, p, grid) : launch_ring_t<64>(ctx, p, grid);
+  dim3 grid(p.n_split * p.n_sb, a->n_kv_heads, a->n_rows);
+  // rows of the batch that one round of workgroups over the compute units covers (see row_by_work_rank)
+  p.round_rows = ctx->n_cu / (int)(grid.x * grid.y);
+  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, grid) : launch_bf16_t<64>(ctx, p, shape, grid);
 }

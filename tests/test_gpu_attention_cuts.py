@@ -1,0 +1,74 @@
+"""bf16 tree attention in every way the dispatcher cuts it (64 / 80 / 96 / 128 / 256 query rows per workgroup, keys split or
+whole, query-split) at head_dim 64 and 128: ragged trees around the cuts' edges, empty prefixes, one-node trees, prefixes
+around the 64-key tiles; every output against float64.
+
+Bound per output, with m = sum p |v|: rounding to bf16 (8 significant bits, to nearest) moves a value by at most u = 2^-8 of
+it.  Probabilities are rounded before the second product (u m), their sum may be taken after that rounding (u m), the output
+is rounded (u m), and a score's float32 error d moves every probability by at most 2 d.  The log-sum-exp carries d, the
+rounded sum (u) and L 2^-24."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_07230_amd import binding
+from paper_2605_07230_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths
+    "64 rows, keys in 16 parts": (2, 1, [60, 41, 64, 17, 55], [1500, 37, 700, 1100, 260]),
+    "64 rows, whole": (32, 1, [60, 41, 64, 17, 55], [800, 0, 64, 513, 300]),
+    "64 rows, grouped heads, ragged blocks": (2, 3, [100, 33, 64], [1900, 130, 0]),
+    "80 rows": (32, 1, [70, 80, 65, 3, 64, 63, 79, 16, 1], [90, 200, 64, 0, 333, 128, 1, 65, 63]),
+    "96 rows": (32, 1, [90, 96, 81, 3, 64, 63, 79, 16, 1], [90, 200, 64, 0, 333, 128, 1, 65, 63]),
+    "128 rows": (32, 1, [100, 128, 97, 33, 64, 63, 79, 16, 1, 2, 127, 65, 17, 111, 20, 7],
+                 [90, 20, 64, 0, 133, 128, 1, 65, 63, 10, 5, 70, 30, 100, 40, 200]),
+    "128 rows, keys in parts": (32, 1, [256, 130], [4000, 64]),
+    "256 rows": (32, 1, [256, 255, 130, 200, 140, 199, 250, 256], [70, 1, 0, 64, 65, 130, 200, 31]),
+    "query split": (2, 1, [20, 17], [400, 63]),
+    "query split, one node": (1, 1, [1], [0]),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_attention_cuts(name, head_dim):
+    kv_heads, group, sizes, prefix = CASES[name]
+    print(f"[attention cuts] {name}, head_dim {head_dim}", flush=True)
+    rng = np.random.default_rng(head_dim + len(sizes))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(head_dim + kv_heads)
+    trees = [wl.grow_tree(rng, n, min(7, n - 1)) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n, S, cap, heads = int(off[-1]), len(sizes), max(max(prefix), 1), kv_heads * group
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()  # noqa: E731
+    q, kt, vt = r(n, heads, head_dim), r(n, kv_heads, head_dim), r(n, kv_heads, head_dim)
+    kc, vc = r(S, kv_heads, cap, head_dim), r(S, kv_heads, cap, head_dim)
+    out, lse = torch.full_like(q, float("nan")), torch.full((n, heads), float("nan"), device="cuda")
+    ctx = binding.Context(max_rows=S, max_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix=cap, n_heads=heads, head_dim=head_dim, hidden=128, vocab=64)
+    dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
+    binding.tree_verify_attn(ctx, node_off=dev(off), parent=dev(np.concatenate(trees)), prefix_len=dev(prefix), q=q, k_tree=kt, v_tree=vt,
+                             k_cache=kc, v_cache=vc, out=out, lse=lse, max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix))
+    assert ctx.device_status() == binding.OK
+    scale = head_dim ** -0.5
+    for s in range(S):
+        lo, hi, T, P = int(off[s]), int(off[s + 1]), sizes[s], prefix[s]
+        see = torch.zeros(T, P + T, dtype=torch.bool)
+        see[:, :P] = True
+        for i in range(T):
+            a = i
+            while a >= 0:
+                see[i, P + a] = True
+                a = int(trees[s][a])
+        see = see.cuda()
+        for kv in range(kv_heads):
+            k, v = torch.cat([kc[s, kv, :P], kt[lo:hi, kv]]).double(), torch.cat([vc[s, kv, :P], vt[lo:hi, kv]]).double()
+            for h in range(kv * group, (kv + 1) * group):
+                qd = q[lo:hi, h].double()
+                z = ((qd @ k.t()) * scale).masked_fill(~see, -float("inf"))
+                rl = torch.logsumexp(z, 1)
+                p = torch.exp(z - rl[:, None])
+                d = head_dim * 2.0 ** -24 * scale * float(qd.norm(dim=1).max() * k.norm(dim=1).max())
+                bound = (3 * 2.0 ** -8 + 2 * d) * (p @ v.abs()) + 1e-30
+                assert torch.all((out[lo:hi, h].double() - p @ v).abs() <= bound), (s, h)
+                assert torch.all((lse[lo:hi, h].double() - rl).abs() <= 2 * d + 2.0 ** -8 + (P + T) * 2.0 ** -24), (s, h)
