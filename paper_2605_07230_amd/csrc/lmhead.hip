@@ -243,29 +243,46 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
   for (int t = 0; t < NST - 1; ++t) request(t, t);
-  int slot = 0;
-  for (int t = 0; t < n_stages; ++t) {
-    // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
-    // barrier: everybody's chunks are there and stage t - 1's slot is free
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
-    request(t + NST - 1, slot == 0 ? NST - 1 : slot - 1);
-    const char* st = ring_lds + slot * STAGE;
-    Frag8 a[SPW][AM], b[SPW][AN];
+  // every sum over the hidden dimension is four chains, over the KW groups of waves and within a wave: one chain of 4096
+  // terms is off by 3.7e-7 of the row (2-norm, against float64), two 2.5e-7, four 1.7e-7
+  constexpr int CH = 4 / KW;
+  f32x16 done[AM][AN];   // (CH > 1) the finished chains
+  int slot = 0, t = 0;
+  for (int c = 1; c <= CH; ++c) {
+    for (const int t_end = n_stages * c / CH; t < t_end; ++t) {
+      // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
+      // barrier: everybody's chunks are there and stage t - 1's slot is free
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
+      request(t + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+      const char* st = ring_lds + slot * STAGE;
+      Frag8 a[SPW][AM], b[SPW][AN];
 #pragma unroll
-    for (int ss = 0; ss < SPW; ++ss) {
-      const int s = kw * SPW + ss;
+      for (int ss = 0; ss < SPW; ++ss) {
+        const int s = kw * SPW + ss;
 #pragma unroll
-      for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
+        for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
 #pragma unroll
-      for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
+        for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
+      }
+#pragma unroll
+      for (int ss = 0; ss < SPW; ++ss)
+#pragma unroll
+        for (int i = 0; i < AM; ++i)
+#pragma unroll
+          for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
+      slot = slot + 1 == NST ? 0 : slot + 1;
     }
-#pragma unroll
-    for (int ss = 0; ss < SPW; ++ss)
+    if (CH > 1)
 #pragma unroll
       for (int i = 0; i < AM; ++i)
 #pragma unroll
-        for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
-    slot = slot + 1 == NST ? 0 : slot + 1;
+        for (int j = 0; j < AN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
+            done[i][j][r] = x;
+            acc[i][j][r] = c < CH ? 0.f : x;
+          }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
@@ -439,18 +456,34 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   land_and_sync();
 #pragma unroll
   for (int k = 0; k < NFR; ++k) read_one(0, 0, 0, FRAG_ORDER[k]);
-  for (int h0 = 0; h0 < n_half; h0 += NBUF) {   // hidden is a multiple of 128: four half-stages always divide it
+  constexpr int CH = HALF ? 4 : 1;   // chains of the sum over the hidden dimension (256-row tiles have no registers for more than one)
+  f32x16 done[NI][2];                // (CH > 1) the finished chains
+  int h0 = 0;
+  for (int c = 1; c <= CH; ++c) {
+    for (const int h_end = n_half / NBUF * c / CH * NBUF; h0 < h_end; h0 += NBUF) {   // hidden is a multiple of 128: four half-stages always divide it
 #pragma unroll
-    for (int b = 0; b < NBUF; ++b) {
-      const int hn = h0 + b + NBUF - 1, bn = (b + NBUF - 1) % NBUF;
-      multiply_with(0, [&](int k) {
-        if (HALF) { read_one(1, b, 1, FRAG_ORDER[k]); request(hn, bn, k); }   // four multiplications: a read and a request behind each
-        else if (k < 6) read_one(1, b, 1, FRAG_ORDER[k]);
-        else { request(hn, bn, 2 * (k - 6)); request(hn, bn, 2 * (k - 6) + 1); }
-      });
-      land_and_sync();
-      multiply_with(1, [&](int k) { if (k < NFR) read_one(0, (b + 1) % NBUF, 0, FRAG_ORDER[k]); });
+      for (int b = 0; b < NBUF; ++b) {
+        const int hn = h0 + b + NBUF - 1, bn = (b + NBUF - 1) % NBUF;
+        multiply_with(0, [&](int k) {
+          if (HALF) { read_one(1, b, 1, FRAG_ORDER[k]); request(hn, bn, k); }   // four multiplications: a read and a request behind each
+          else if (k < 6) read_one(1, b, 1, FRAG_ORDER[k]);
+          else { request(hn, bn, 2 * (k - 6)); request(hn, bn, 2 * (k - 6) + 1); }
+        });
+        land_and_sync();
+        multiply_with(1, [&](int k) { if (k < NFR) read_one(0, (b + 1) % NBUF, 0, FRAG_ORDER[k]); });
+      }
     }
+    if (CH > 1)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
+            done[i][j][r] = x;
+            acc[i][j][r] = c < CH ? 0.f : x;
+          }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
@@ -884,7 +917,8 @@ constexpr int LM_RING_TILES = 5;
 // Estimated time of a tile shape: rounds of tiles over the compute units, and the weight stream at 5.3 TB/s, which
 // overlap only partly (fourth-power mean; within 10 % of the measured time at 60-1024 rows, 16384-65536 columns: e.g.
 // 60 x 65536: 113 us in 64 x 64 tiles (measured 112), 103 in 64 x 256 (101); 230 x 16384: 43 in 128 x 128 (45), 57 in
-// 128 x 64 (57); 256 x 65536: 130 in 256 x 256 (141), 140 in 256 x 128 (156)).
+// 128 x 64 (57); 461 x 16384: 66 in 128 x 256 (67); 256 x 65536, the worst seen: 141 in 128 x 256 (169), still
+// ahead of 256 x 128 by a few us).
 float lm_estimate_us(const LmTile& tile, int rows, int vocab, int hidden, int n_cu) {
   const long tiles = (long)((rows + tile.rows - 1) / tile.rows) * ((vocab + tile.cols - 1) / tile.cols);
   const float k = hidden / 4096.f, a = (float)((tiles + n_cu - 1) / n_cu) * tile.us * k, b = (float)vocab * hidden * 2.f / 5.3e6f;
@@ -902,6 +936,9 @@ hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
   float best_us = INFINITY;
   for (int i = 0; i < (packed_w ? 7 : LM_RING_TILES); ++i) {
     if (i == 5 && cfg) continue;
+    // 256 x 256 tiles sum the hidden dimension in one chain; faster for fewer rows as well (256 x 65536: 138 us against 169),
+    // but there every other tile is twice as close to the exact sums
+    if (i == 6 && (a->vocab % 256 != 0 || rows < (cfg ? 512 : 257))) continue;
     float us = lm_estimate_us(LM_TILES[i], rows, a->vocab, a->hidden, ctx->n_cu);
     if (i >= LM_RING_TILES && !premix) us += 4.f;   // the tiled kernel needs its rows packed (the mix packs them on the way)
     if (us < best_us) { best = i; best_us = us; }

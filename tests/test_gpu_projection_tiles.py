@@ -50,3 +50,28 @@ def test_projection_tiles(rows, vocab, hidden, mode, packed):
     bad = ~((logits.double() - ref).abs() <= bound + 1e-6)      # NaN (an unwritten element) is bad
     assert not bad.any(), (int(bad.sum()), torch.nonzero(bad)[0].tolist())
     assert torch.equal(stats[0], logits.max(1).values)
+
+
+# one size per tile; a 256 x 256 tile (more rows) sums in one chain
+@pytest.mark.parametrize("rows,vocab", [(60, 16384), (120, 16384), (60, 65536), (230, 16384), (250, 65536), (461, 16384)])
+def test_projection_sums_in_four_chains(rows, vocab):
+    """2-norm distance from float64.  A chain of n accumulations whose partial sums grow as a random walk rounds with an
+    rms of at most 2^-24 / sqrt(3) of each partial sum: sqrt(n / 2) / sqrt(3) 2^-24 of the result, n = K / 16 / 4; an
+    undivided chain of the same terms measures twice that."""
+    print(f"[projection chains] rows={rows} vocab={vocab}", flush=True)
+    hidden = 4096
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + vocab)
+    w = (0.02 * torch.randn(vocab, hidden, device="cuda", generator=gen)).bfloat16()
+    c = torch.randn(rows, hidden, device="cuda", generator=gen).bfloat16()
+    ctx = binding.Context(max_rows=1, max_nodes_total=rows, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=hidden, vocab=vocab)
+    logits = torch.empty(rows, vocab, device="cuda")
+    stats = [torch.empty(rows, device="cuda") for _ in range(3)]
+    binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=None, w=binding.cascade_pack_lmhead_w(ctx, w), w_layout=binding.W_PACKED32, cfg_scale=1.0,
+                               temperature=1.0, top_k=50, logits=logits, row_max=stats[0], row_thr=stats[1], row_lse=stats[2])
+    num = den = 0.0
+    for v in range(0, vocab, 8192):
+        ref = c.double() @ w[v:v + 8192].double().t()
+        num += float(((logits[:, v:v + 8192].double() - ref) ** 2).sum())
+        den += float((ref ** 2).sum())
+    assert (num / den) ** 0.5 <= (hidden / 64 / 6) ** 0.5 * 2.0 ** -24
