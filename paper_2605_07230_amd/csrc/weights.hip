@@ -11,6 +11,7 @@
 namespace {
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr int MAX_RUN = 128;   // pairs of a run (their partial sums wait in LDS)
 
 template <typename T> struct Acc;
 template <> struct Acc<float> {
@@ -37,83 +38,96 @@ template <> struct Acc<uint16_t> {   // bf16 pairs packed in 32-bit words
   }
 };
 
-// NV = 16-byte vectors per lane (row bytes <= NV * 1024)
-template <typename T, int NV>
-__global__ __launch_bounds__(256) void conv_weight_kernel(conv_weight_args a, int runs_per_seq, int RUN) {
-  const int lane = threadIdx.x & 63;
-  const long long wave_id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int seq = (int)(wave_id / runs_per_seq), run = (int)(wave_id % runs_per_seq);
-  if (seq >= a.n_seqs) return;
+// CS waves share a run of consecutive rows, each with every CS-th KiB of a row (NV of them), and the next R - 1 rows
+// requested; a workgroup of four waves holds 4 / CS runs.  Each wave leaves its part of every row's norm and of every
+// pair's product in LDS, and they are added once at the end of the run, so the loop has no barrier.
+template <typename T, int NV, int CS, int R>
+__global__ __launch_bounds__(256) void conv_weight_kernel(conv_weight_args a, int runs_per_seq, int run_len) {
+  constexpr int RUNS = 4 / CS;
+  __shared__ float s_dot[RUNS][CS][MAX_RUN], s_norm[RUNS][CS][MAX_RUN + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int part = wave % CS, mine = wave / CS;
+  const long long run_id = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * RUNS + mine;
+  const bool exists = run_id < (long long)a.n_seqs * runs_per_seq;
+  const int seq = exists ? (int)(run_id / runs_per_seq) : 0, run = exists ? (int)(run_id % runs_per_seq) : 0;
   const int K = a.seq_len;
   const int nvec = a.hidden * (int)sizeof(T) / 16;   // 16-byte vectors per row
   const u32x4* base = (const u32x4*)a.features + (long long)seq * K * nvec;
-  float* wout = a.weights + (long long)seq * K;
-  float* cout = a.cos_next ? a.cos_next + (long long)seq * K : nullptr;
-  const int k0 = run * RUN, k1 = min(k0 + RUN, K - 1);   // pairs (k, k+1) for k in [k0, k1)
+  const int k0 = run * run_len, n = exists ? min(run_len, K - 1 - k0) : 0;   // pairs (k, k+1) for k in [k0, k0 + n)
 
-  auto load_row = [&](int k, u32x4 (&dst)[NV]) {
-    const u32x4* row = base + (long long)k * nvec;
+  if (n > 0) {
+    u32x4 r[R][NV];
+    auto load_row = [&](int i, u32x4 (&dst)[NV]) {   // row i of the run; past its end the last one again (a cache hit)
+      const u32x4* row = base + (long long)(k0 + min(i, n)) * nvec;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int idx = v * 64 + lane;
-      const u32x4 x = row[min(idx, nvec - 1)];   // clamped, zeroed below
-      dst[v] = idx < nvec ? x : u32x4{0u, 0u, 0u, 0u};
-    }
-  };
-
-  if (k0 < k1) {
-    u32x4 prev[NV], cur[NV], nxt[NV];
-    load_row(k0, prev);
-    load_row(k0 + 1, cur);
+      for (int v = 0; v < NV; ++v) {
+        const int idx = (v * CS + part) * 64 + lane;
+        const u32x4 x = row[min(idx, nvec - 1)];   // clamped, zeroed below
+        dst[v] = idx < nvec ? x : u32x4{0u, 0u, 0u, 0u};
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < R; ++i) load_row(i, r[i]);
     float pp = 0.f, dummy = 0.f;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Acc<T>::dot(prev[v], prev[v], dummy, pp);
+    for (int v = 0; v < NV; ++v) Acc<T>::dot(r[0][v], r[0][v], dummy, pp);
     pp = wave_sum(pp);
-    for (int k = k0; k < k1; ++k) {
-      const int kn = min(k + 2, k1);   // next row to fetch; at the end of the run the last row again (a cache hit)
-      load_row(kn, nxt);
-      float ab = 0.f, bb = 0.f;
+    if (lane == 0) s_norm[mine][part][0] = pp;
+    for (int i0 = 0; i0 < n; i0 += R) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Acc<T>::dot(prev[v], cur[v], ab, bb);
-      ab = wave_sum(ab);
-      bb = wave_sum(bb);
-      const float cs = (pp > 0.f && bb > 0.f) ? ab / (sqrtf(pp) * sqrtf(bb)) : 0.f;
-      if (lane == 0) {
-        wout[k] = cs >= a.tau_seq ? a.c : 1.f;
-        if (cout) cout[k] = cs;
+      for (int u = 0; u < R; ++u) {
+        const int i = i0 + u;
+        if (i >= n) break;
+        float ab = 0.f, bb = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Acc<T>::dot(r[u][v], r[(u + 1) % R][v], ab, bb);
+        load_row(i + R, r[u]);
+        ab = wave_sum(ab);
+        bb = wave_sum(bb);
+        if (lane == 0) { s_dot[mine][part][i] = ab; s_norm[mine][part][i + 1] = bb; }
       }
-      pp = bb;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) { prev[v] = cur[v]; cur[v] = nxt[v]; }
     }
   }
-  if (run == runs_per_seq - 1 && lane == 0) {   // the last position has no successor
+  __syncthreads();
+  float* wout = a.weights + (long long)seq * K;
+  float* cout = a.cos_next ? a.cos_next + (long long)seq * K : nullptr;
+  for (int i = part * 64 + lane; i < n; i += 64 * CS) {
+    float ab = 0.f, aa = 0.f, bb = 0.f;
+#pragma unroll
+    for (int c = 0; c < CS; ++c) { ab += s_dot[mine][c][i]; aa += s_norm[mine][c][i]; bb += s_norm[mine][c][i + 1]; }
+    const float cs = (aa > 0.f && bb > 0.f) ? ab / (sqrtf(aa) * sqrtf(bb)) : 0.f;
+    wout[k0 + i] = cs >= a.tau_seq ? a.c : 1.f;
+    if (cout) cout[k0 + i] = cs;
+  }
+  if (exists && run == runs_per_seq - 1 && part == 0 && lane == 0) {   // the last position has no successor
     wout[K - 1] = 1.f;
     if (cout) cout[K - 1] = 0.f;
   }
 }
 
+template <typename T, int NV, int CS, int R>
+hipError_t launch_cs(cascade_ctx* ctx, const conv_weight_args* a) {
+  // one run per group of CS waves with eight waves on every compute unit: long runs re-read fewer boundary rows
+  const long long pairs = (long long)a->n_seqs * (a->seq_len - 1), groups = (long long)ctx->n_cu * 8 / CS;
+  long long run_len = (pairs + groups - 1) / groups;
+  run_len = run_len < 4 ? 4 : (run_len > MAX_RUN ? MAX_RUN : run_len);
+  const int runs_per_seq = a->seq_len > 1 ? (int)((a->seq_len - 1 + run_len - 1) / run_len) : 1;
+  const long long blocks = ((long long)a->n_seqs * runs_per_seq + 4 / CS - 1) / (4 / CS);
+  const long long gy = (blocks + (1 << 22) - 1) >> 22;   // a grid dimension holds fewer than 2^32 threads
+  KernelTimer t(ctx, CASCADE_K_WEIGHTS);
+  CASCADE_TIMED_LAUNCH(t, (conv_weight_kernel<T, NV, CS, R>), dim3((unsigned)((blocks + gy - 1) / gy), (unsigned)gy), dim3(256), 0, ctx->stream, *a,
+                       runs_per_seq, (int)run_len);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_t(cascade_ctx* ctx, const conv_weight_args* a) {
-  const int row_bytes = a->hidden * (int)sizeof(T);
-  const int nv = (row_bytes + 1023) / 1024;
-  // pairs per wavefront: long runs re-read fewer boundary rows, short runs give more wavefronts in
-  // flight; aim at eight wavefronts per compute unit, between 8 and 32 pairs each
-  const long long pairs = (long long)a->n_seqs * (a->seq_len > 1 ? a->seq_len - 1 : 0);
-  int RUN = (int)(pairs / (256 * 8));
-  RUN = RUN < 8 ? 8 : (RUN > 32 ? 32 : RUN);
-  const int runs_per_seq = a->seq_len > 1 ? (a->seq_len - 1 + RUN - 1) / RUN : 1;
-  const long long waves = (long long)a->n_seqs * runs_per_seq;
-  dim3 grid((unsigned)((waves + 3) / 4));
-  KernelTimer t(ctx, CASCADE_K_WEIGHTS);
-#define CASCADE_LAUNCH_CW(NV) CASCADE_TIMED_LAUNCH(t, (conv_weight_kernel<T, NV>), grid, dim3(256), 0, ctx->stream, *a, runs_per_seq, RUN)
-  if (nv <= 1) CASCADE_LAUNCH_CW(1);
-  else if (nv <= 2) CASCADE_LAUNCH_CW(2);
-  else if (nv <= 4) CASCADE_LAUNCH_CW(4);
-  else if (nv <= 8) CASCADE_LAUNCH_CW(8);
-  else CASCADE_LAUNCH_CW(16);
-#undef CASCADE_LAUNCH_CW
-  return hipGetLastError();
+  const int kib = (a->hidden * (int)sizeof(T) + 1023) / 1024;   // at most 16
+  if (kib <= 1) return launch_cs<T, 1, 1, 8>(ctx, a);
+  if (kib <= 2) return launch_cs<T, 1, 2, 8>(ctx, a);
+  if (kib <= 4) return launch_cs<T, 1, 4, 8>(ctx, a);
+  if (kib <= 8) return launch_cs<T, 2, 4, 8>(ctx, a);
+  return launch_cs<T, 4, 4, 4>(ctx, a);
 }
 
 }  // namespace
