@@ -5,7 +5,7 @@
 // bf16 projection: both operands reach the matrix cores through a ring of LDS stages filled by LDS-direct loads.
 // lmhead_bf16_ring_kernel takes rows and weights as they lie in memory (or packed weights) and comes in tiles from
 // 64 x 64 to 256 x 128; lmhead_bf16_tiled_kernel takes both operands packed and carries the large tiles of steps with
-// several hundred rows.  launch_lmhead_bf16 chooses by estimated time.
+// several hundred rows.  lm_plan chooses by estimated time, and gives the columns that do not fill a round a smaller tile.
 #include "common.h"
 
 namespace {
@@ -21,6 +21,7 @@ struct LmParams {
   const uint4* hp_cond;     // packed hidden states (MFMA operand order), when the packed path runs
   const uint4* hp_uncond;
   int n_nodes, hidden, vocab;
+  int col0;                 // first vocabulary column of the launch
   float cfg_scale, temperature;
   int top_k;
 };
@@ -134,9 +135,9 @@ __device__ __forceinline__ uint4 mix16(const uint4& c, const uint4& u, float s) 
 }
 
 // The same operand order for the guidance-mixed rows u + s (c - u) (float32, rounded once to bf16): the
-// projection is linear, so one product over these rows gives the mixed logits.
+// projection is linear, so one product over these rows gives the mixed logits.  dst_rows: the rows as they lie, too.
 __global__ __launch_bounds__(256) void pack32_mix_kernel(const uint16_t* __restrict__ src_c, const uint16_t* __restrict__ src_u,
-                                                          uint4* __restrict__ dst, int rows, int K, float s) {
+                                                          uint4* __restrict__ dst, uint4* __restrict__ dst_rows, int rows, int K, float s) {
   const int lane = threadIdx.x & 63, r32 = lane & 31, half = lane >> 5;
   const int ks = blockIdx.x * 4 + (threadIdx.x >> 6), rb = blockIdx.y;
   if (ks >= K / 16) return;
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(256) void pack32_mix_kernel(const uint16_t* __restr
     const int64_t o = (int64_t)row * K + 16 * ks + 8 * half;
     const uint4 c = *(const uint4*)(src_c + o), u = *(const uint4*)(src_u + o);
     v = mix16(c, u, s);
+    if (dst_rows) dst_rows[o / 8] = v;
   }
   dst[((int64_t)rb * (K / 16) + ks) * 64 + lane] = v;
 }
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       rows = p.n_nodes;
     } else {
       base = (const char*)p.w;
-      row0 = nt * BN + 32 * (blk - NA);
+      row0 = p.col0 + nt * BN + 32 * (blk - NA);
       rows = p.vocab;
     }
     if (PW && blk >= NA) {
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   constexpr int NI = CFG ? 1 : AM;   // node blocks of a wave
   auto emit = [&](int i, int j, int r, float x0, float x1) {
     const int node = (CFG ? mt * (BM / 2) + 32 * wm : mt * BM + 32 * (AM * wm + i)) + 8 * (r >> 2) + 4 * half + (r & 3);
-    const int col = nt * BN + 32 * (AN * wn + j) + r32;
+    const int col = p.col0 + nt * BN + 32 * (AN * wn + j) + r32;
     const float gmix = CFG ? x1 + p.cfg_scale * (x0 - x1) : x0;
     if (node < p.n_nodes && col < p.vocab) p.logits[(int64_t)node * p.vocab + col] = gmix / p.temperature;
   };
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
       else { base = (const char*)p.hp_cond; rb = (int64_t)mt * 8 + wave; }
     } else {
       base = (const char*)p.w;
-      rb = min(nt * 8 + wave, p.vocab / 32 - 1);   // a last column tile past the vocabulary re-reads its last block, never stored
+      rb = min(p.col0 / 32 + nt * 8 + wave, p.vocab / 32 - 1);   // a last column tile past the vocabulary re-reads its last block, never stored
     }
     src[b4] = base + rb * KS * 1024;
   }
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
   // epilogue: accumulator (i, j), register r of lane (r32, half) is row 8 (r / 4) + 4 half + r % 4, column r32
-  const int v0 = nt * 256 + 64 * wn;
+  const int v0 = p.col0 + nt * 256 + 64 * wn;
 #pragma unroll
   for (int i = 0; i < (CFG ? 2 : NI); ++i) {
     const int node0 = (CFG || HALF) ? mt * 128 + 32 * (2 * wm + i) : mt * 256 + 32 * (4 * wm + i);
@@ -848,6 +850,7 @@ LmParams make_params(const lmhead_args* a) {
   p.n_nodes = a->n_nodes;
   p.hidden = a->hidden;
   p.vocab = a->vocab;
+  p.col0 = 0;
   p.cfg_scale = a->cfg_scale;
   p.temperature = a->temperature;
   p.top_k = a->top_k;
@@ -876,7 +879,7 @@ hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a) {
 }
 
 template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
-hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p) {
+hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols) {
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NODES = CFG ? BM / 2 : BM;
   constexpr int RING = NST * (BM + BN) / 32 * KS * 1024, RED = KW > 1 ? 8 * AM * AN * 4096 : 0;
   constexpr int smem = RING > RED ? RING : RED;
@@ -890,39 +893,108 @@ hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p) {
   }
   const int n_mtiles = (p.n_nodes + NODES - 1) / NODES;
   KernelTimer t(ctx, CASCADE_K_LMHEAD);
-  CASCADE_TIMED_LAUNCH(t, kern, dim3((p.vocab + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
+  CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
 }
 template <bool CFG, bool PW>
-hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile) {
+hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols) {
   switch (tile) {
-    case 0: return launch_ring_t<2, 1, 1, 2, 4, 4, 6, CFG, PW>(ctx, p);
-    case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p);
-    case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p);
-    case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p);
-    default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p);
+    case 0: return launch_ring_t<2, 1, 1, 2, 4, 4, 6, CFG, PW>(ctx, p, n_cols);
+    case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p, n_cols);
+    case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p, n_cols);
+    case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p, n_cols);
+    default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p, n_cols);
   }
 }
 
-// Tiles of the projection and what one of them costs a compute unit at hidden 4096 when the weight stream does not
-// bind (us, measured with every unit holding one tile): ring kernel 0-4, tiled kernel 5 (128 x 256, plain rows only)
-// and 6 (256 x 256).
+// Tiles of the projection: ring kernel 0-4, tiled kernel 5 (128 x 256, plain rows only) and 6 (256 x 256).  us = one tile
+// on every compute unit, hidden 4096, the weight stream aside; a last round that fills few units costs `few` of that plus
+// the filled share of the rest (the clock rises when units idle), a tile of padding rows only `pad` (zeros draw less
+// power).  Fitted to 100 sizes (16-1024 rows, 16384-65536 columns, plain, pairs and row-major weights), all seven tiles each.
 struct LmTile {
   int rows, cols;
-  float us;
+  float us, few, pad;
 };
-constexpr LmTile LM_TILES[7] = {{64, 64, 22.f}, {128, 64, 28.f}, {64, 256, 51.f}, {128, 128, 42.f}, {256, 128, 68.f}, {128, 256, 65.f}, {256, 256, 112.f}};
+constexpr LmTile LM_TILES[7] = {{64, 64, 17.6f, 1.f, 0.83f}, {128, 64, 26.8f, 1.f, 0.64f}, {64, 256, 46.5f, 0.91f, 1.f}, {128, 128, 41.f, 0.83f, 0.8f},
+                                {256, 128, 72.f, 0.77f, 0.9f}, {128, 256, 68.5f, 0.87f, 0.77f}, {256, 256, 115.4f, 0.66f, 0.58f}};
 constexpr int LM_RING_TILES = 5;
 
-// Estimated time of a tile shape: rounds of tiles over the compute units, and the weight stream at 5.3 TB/s, which
-// overlap only partly (fourth-power mean; within 10 % of the measured time at 60-1024 rows, 16384-65536 columns: e.g.
-// 60 x 65536: 113 us in 64 x 64 tiles (measured 112), 103 in 64 x 256 (101); 230 x 16384: 43 in 128 x 128 (45), 57 in
-// 128 x 64 (57); 461 x 16384: 66 in 128 x 256 (67); 256 x 65536, the worst seen: 141 in 128 x 256 (169), still
-// ahead of 256 x 128 by a few us).
-float lm_estimate_us(const LmTile& tile, int rows, int vocab, int hidden, int n_cu) {
-  const long tiles = (long)((rows + tile.rows - 1) / tile.rows) * ((vocab + tile.cols - 1) / tile.cols);
-  const float k = hidden / 4096.f, a = (float)((tiles + n_cu - 1) / n_cu) * tile.us * k, b = (float)vocab * hidden * 2.f / 5.3e6f;
-  return sqrtf(sqrtf(a * a * a * a + b * b * b * b));
+// Time of the tiles of a launch over n_cols columns: rounds over the compute units.
+float lm_rounds_us(const LmTile& tile, int rows, int n_cols, int hidden, int n_cu) {
+  const int n_mtiles = (rows + tile.rows - 1) / tile.rows;
+  const long tiles = (long)n_mtiles * ((n_cols + tile.cols - 1) / tile.cols);
+  const float last = (float)(tiles % n_cu) / n_cu, used = (float)rows / ((float)n_mtiles * tile.rows);
+  const float rounds = (float)(tiles / n_cu) + (last > 0.f ? tile.few + (1.f - tile.few) * last : 0.f);
+  return rounds * tile.us * (tile.pad + (1.f - tile.pad) * used) * (hidden / 4096.f);
+}
+// Estimated time of the whole projection: that, and the weight stream at 6.2 TB/s, which overlap only partly.  Over those
+// sizes the single tile chosen is 1.2 % behind the fastest one in the mean.
+float lm_estimate_us(float a, int vocab, int hidden) {
+  const float b = (float)vocab * hidden * 2.f / 6.2e6f;
+  return sqrtf(a * a + b * b);
+}
+
+// How a projection is cut: columns [0, split) in tiles of one shape, [split, vocab) in tiles of another (split = vocab: one
+// launch).  A last round that fills few compute units costs as much as a full one, so the columns that fill whole rounds
+// take the large tile and the rest a smaller one in a second launch: 686 rows (guidance pairs) x 33088 x 2048 are 777
+// tiles of 256 x 128, four rounds of 256 units (133 us); 768 of them and 55 of 64 x 64: 122 us.  Over those 100 sizes the
+// cut that is chosen is 5 % faster than the fastest single tile in the mean, 29 % at 461 rows x 33024 (193 -> 137 us),
+// and at worst 14 % behind it (850 rows x 24000: 235 us in 128 x 256 against 207 in 256 x 128).
+struct LmPlan {
+  int main, rest, split;
+  float us;
+};
+constexpr float LM_SECOND_LAUNCH_US = 4.f;
+
+LmPlan lm_plan(const lmhead_args* a, bool packed_w, bool premix, bool cfg, int n_cu) {
+  const int rows = a->n_nodes * (cfg ? 2 : 1), V = a->vocab;
+  auto usable = [&](int i) {
+    if (i >= LM_RING_TILES && !packed_w) return false;
+    if (i == 5) return !cfg;
+    // 256 x 256 tiles sum the hidden dimension in one chain; faster for fewer rows as well (256 x 65536: 138 us against 169),
+    // but there every other tile is twice as close to the exact sums
+    return i != 6 || (V % 256 == 0 && rows >= (cfg ? 512 : 257));
+  };
+  LmPlan best = {0, 0, V, INFINITY};
+  for (int i = 0; i < 7; ++i) {
+    if (!usable(i)) continue;
+    const float pack = i >= LM_RING_TILES && !premix ? 4.f : 0.f;   // the tiled kernel needs its rows packed (the mix packs them on the way)
+    const LmTile& t = LM_TILES[i];
+    const float whole = lm_estimate_us(lm_rounds_us(t, rows, V, a->hidden, n_cu), V, a->hidden) + pack;
+    if (whole < best.us) best = {i, i, V, whole};
+    const int n_mtiles = (rows + t.rows - 1) / t.rows, n_ntiles = (V + t.cols - 1) / t.cols;
+    const int full = (int)((long)n_mtiles * n_ntiles / n_cu) * n_cu / n_mtiles;   // column tiles in whole rounds
+    if (full == 0 || full * t.cols >= V) continue;
+    for (int j = 0; j < 7; ++j) {
+      if (!usable(j) || (i < LM_RING_TILES && j >= LM_RING_TILES)) continue;
+      const float c = lm_rounds_us(t, rows, full * t.cols, a->hidden, n_cu) + lm_rounds_us(LM_TILES[j], rows, V - full * t.cols, a->hidden, n_cu);
+      const float us = lm_estimate_us(c, V, a->hidden) + pack + LM_SECOND_LAUNCH_US;
+      if (us < best.us) best = {i, j, full * t.cols, us};
+    }
+  }
+  return best;
+}
+
+// one launch over columns [p.col0, p.col0 + n_cols)
+hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cfg, bool packed_w, int n_cols) {
+  if (tile < LM_RING_TILES) {
+    if (packed_w) return cfg ? launch_ring<true, true>(ctx, p, tile, n_cols) : launch_ring<false, true>(ctx, p, tile, n_cols);
+    return cfg ? launch_ring<true, false>(ctx, p, tile, n_cols) : launch_ring<false, false>(ctx, p, tile, n_cols);
+  }
+  const bool half = tile == 5;
+  const int nodes_per_tile = (cfg || half) ? 128 : 256, n_mtiles = (p.n_nodes + nodes_per_tile - 1) / nodes_per_tile;
+  const size_t smem = (size_t)4 * 32 * 1024;   // ring of four 32 KiB half-stages
+  static bool attr_done[3] = {false, false, false};
+  auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false> : (half ? lmhead_bf16_tiled_kernel<false, true> : lmhead_bf16_tiled_kernel<false, false>);
+  const int which = cfg ? 0 : (half ? 1 : 2);
+  if (!attr_done[which]) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_done[which] = true;
+  }
+  KernelTimer t(ctx, CASCADE_K_LMHEAD);
+  CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + 255) / 256 * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
+  return hipGetLastError();
 }
 
 hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
@@ -931,68 +1003,42 @@ hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
   // guidance mixed into the hidden rows in front of the projection: from here on a plain projection of n_nodes rows
   const bool premix = a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && packed_w;
   const bool cfg = a->h_uncond != nullptr && !premix;
-  const int rows = a->n_nodes * (cfg ? 2 : 1);
-  int best = 0;
-  float best_us = INFINITY;
-  for (int i = 0; i < (packed_w ? 7 : LM_RING_TILES); ++i) {
-    if (i == 5 && cfg) continue;
-    // 256 x 256 tiles sum the hidden dimension in one chain; faster for fewer rows as well (256 x 65536: 138 us against 169),
-    // but there every other tile is twice as close to the exact sums
-    if (i == 6 && (a->vocab % 256 != 0 || rows < (cfg ? 512 : 257))) continue;
-    float us = lm_estimate_us(LM_TILES[i], rows, a->vocab, a->hidden, ctx->n_cu);
-    if (i >= LM_RING_TILES && !premix) us += 4.f;   // the tiled kernel needs its rows packed (the mix packs them on the way)
-    if (us < best_us) { best = i; best_us = us; }
-  }
-  const bool tiled = best >= LM_RING_TILES, half = best == 5;
+  const LmPlan plan = lm_plan(a, packed_w, premix, cfg, ctx->n_cu);
   uint4* hc = (uint4*)ctx->hpack_ws;
-  if (!tiled) {
+  if (plan.main < LM_RING_TILES) {
     if (premix) {
       const int64_t n16 = (int64_t)a->n_nodes * a->hidden / 8;
       if ((size_t)n16 * 16 > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
       KernelTimer t(ctx, CASCADE_K_PACK);
       CASCADE_TIMED_LAUNCH(t, mix_rows_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, ctx->stream, (const uint4*)a->h_cond,
                            (const uint4*)a->h_uncond, hc, (int)n16, a->cfg_scale);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
       p.h_cond = hc;
     }
-    if (packed_w) return cfg ? launch_ring<true, true>(ctx, p, best) : launch_ring<false, true>(ctx, p, best);
-    return cfg ? launch_ring<true, false>(ctx, p, best) : launch_ring<false, false>(ctx, p, best);
-  }
-  const int nodes_per_tile = (cfg || half) ? 128 : 256;
-  const int n_mtiles = (a->n_nodes + nodes_per_tile - 1) / nodes_per_tile;
-  // this step's hidden states in operand order (zero rows up to a whole tile)
-  const int rblocks = n_mtiles * (nodes_per_tile / 32);
-  const size_t per = (size_t)rblocks * 32 * a->hidden * 2;
-  if (per * (cfg ? 2 : 1) > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
-  uint4* hu = (uint4*)(ctx->hpack_ws + per);
-  dim3 pgrid((a->hidden / 16 + 3) / 4, rblocks, cfg ? 2 : 1);
-  {
+  } else {
+    // this step's hidden states in operand order (zero rows up to a whole tile)
+    const int rblocks = (a->n_nodes + 255) / 256 * 8;
+    const size_t per = (size_t)rblocks * 32 * a->hidden * 2;
+    if (per * (cfg ? 2 : 1) > ctx->hpack_ws_bytes) return hipErrorInvalidValue;
+    uint4* hu = (uint4*)(ctx->hpack_ws + per);
+    dim3 pgrid((a->hidden / 16 + 3) / 4, rblocks, cfg ? 2 : 1);
     KernelTimer t(ctx, CASCADE_K_PACK);
     if (premix) {
       CASCADE_TIMED_LAUNCH(t, pack32_mix_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond,
-                           (const uint16_t*)a->h_uncond, hc, a->n_nodes, a->hidden, a->cfg_scale);
+                           (const uint16_t*)a->h_uncond, hc, plan.rest < LM_RING_TILES ? hu : nullptr, a->n_nodes, a->hidden, a->cfg_scale);
+      if (plan.rest < LM_RING_TILES) p.h_cond = hu;
     } else {
       CASCADE_TIMED_LAUNCH(t, pack32_kernel, pgrid, dim3(256), 0, ctx->stream, (const uint16_t*)a->h_cond, hc,
                            (const uint16_t*)a->h_uncond, hu, a->n_nodes, a->hidden);
     }
+    p.hp_cond = hc;
+    p.hp_uncond = hu;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  p.hp_cond = hc;
-  p.hp_uncond = hu;
-  const size_t smem = (size_t)4 * 32 * 1024;   // ring of four 32 KiB half-stages
-  static bool attr_done[3] = {false, false, false};
-  auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false> : (half ? lmhead_bf16_tiled_kernel<false, true> : lmhead_bf16_tiled_kernel<false, false>);
-  const int which = cfg ? 0 : (half ? 1 : 2);
-  if (!attr_done[which]) {
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done[which] = true;
-  }
-  KernelTimer t(ctx, CASCADE_K_LMHEAD);
-  CASCADE_TIMED_LAUNCH(t, kern, dim3((a->vocab + 255) / 256 * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
-  return hipGetLastError();
+  e = launch_lm_tile(ctx, p, plan.main, cfg, packed_w, plan.split);
+  if (e != hipSuccess || plan.split == a->vocab) return e;
+  p.col0 = plan.split;
+  return launch_lm_tile(ctx, p, plan.rest, cfg, packed_w, a->vocab - plan.split);
 }
 
 hipError_t launch_pack_w(cascade_ctx* ctx, const void* w, int vocab, int hidden, void* w_packed) {

@@ -2,10 +2,11 @@
 // consecutive positions (k, k+1) of a target-generated sequence: cos(F_k, F_{k+1}) >= tau_seq (the
 // convergence set of Eq. 2 between neighbours) gives weight c, otherwise 1.
 //
-// Bandwidth-bound: every feature row should cross HBM once.  One wavefront walks a run of
-// consecutive pairs with the previous row held in registers (16-byte vectors, lane-interleaved so
-// that every load instruction covers 1 KiB of contiguous memory), the next row already requested
-// while the current one is reduced; only the first row of a run is read by two wavefronts.
+// Bandwidth-bound: every feature row should cross HBM once.  A run of consecutive pairs belongs to the waves that share
+// its rows: the four waves of a workgroup take a quarter of every row each (narrow rows: fewer waves per run), in 1 KiB
+// pieces, with seven rows requested ahead.  Only the first row of a run is read twice.  8 sequences x 2356 x 4096 bf16:
+// 30.3 us (154 MB, 5.1 TB/s); with whole rows per wave the chip filled only with runs of 9 pairs, 11 % of the rows were
+// read twice, and it took 36.0.
 #include "common.h"
 
 namespace {

@@ -26,10 +26,25 @@ SHAPES = [
 @pytest.mark.parametrize("mode", ["plain", "pairs", "mixed"])
 @pytest.mark.parametrize("packed", [True, False])
 def test_projection_tiles(rows, vocab, hidden, mode, packed):
-    n = max(1, rows // 2) if mode == "pairs" else rows
+    _check(max(1, rows // 2) if mode == "pairs" else rows, vocab, hidden, mode, packed)
+
+
+# columns cut into whole rounds of one tile and a rest in another (tiles by number, as the launcher counts them)
+@pytest.mark.parametrize("n,vocab,mode,packed", [
+    (65, 33024, "plain", True), (200, 33024, "plain", True), (257, 33088, "plain", True), (461, 24000, "plain", True),   # 3+0, 4+0, 5+2, 4+3
+    (600, 33024, "plain", True), (343, 24000, "plain", True),                                                           # 6+5, 5+0
+    (257, 33088, "mixed", True), (200, 41024, "mixed", True), (600, 41024, "mixed", True), (257, 33024, "mixed", True), # 5+2, 5+3, 5+1, 6+0
+    (65, 33024, "pairs", True), (343, 24000, "pairs", True), (300, 33024, "pairs", True), (461, 33024, "pairs", True),  # 2+3, 4+1, 6+3, 6+0
+    (65, 33024, "pairs", False), (100, 33024, "pairs", False), (200, 41024, "pairs", False),                            # 2+3, 4+0, 4+2
+])
+def test_projection_split_columns(n, vocab, mode, packed):
+    _check(n, vocab, 2048, mode, packed)
+
+
+def _check(n, vocab, hidden, mode, packed):
     print(f"[projection] nodes={n} vocab={vocab} hidden={hidden} {mode} packed={packed}", flush=True)
     gen = torch.Generator(device="cuda")
-    gen.manual_seed(rows * 131 + vocab + hidden)
+    gen.manual_seed(n * 131 + vocab + hidden)
     w = (0.02 * torch.randn(vocab, hidden, device="cuda", generator=gen)).bfloat16()
     c = torch.randn(n, hidden, device="cuda", generator=gen).bfloat16()
     u = (c.float() + 0.5 * torch.randn(n, hidden, device="cuda", generator=gen)).bfloat16()
