@@ -66,17 +66,34 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
       const int nch = (Tn + 63) >> 6;
       int par[TCH], tok[TCH];
       float qv[TCH], mi[TCH], mc[TCH], up[TCH];
+      // the loads of several chunks are in flight together (all of them in trees of at most 256 nodes): clamped, because a
+      // branch per chunk made every chunk wait for its own
+      constexpr int GC = TCH > 4 ? 2 : TCH;
 #pragma unroll
-      for (int c = 0; c < TCH; ++c) {
-        const int j = c * 64 + lane;
-        par[c] = -2; tok[c] = -1; qv[c] = 0.f; mi[c] = 0.f; mc[c] = 0.f; up[c] = 0.f;
-        if (c < nch && j < Tn) {
-          par[c] = a.parent[lo + j];
-          tok[c] = a.token[lo + j];
-          qv[c] = a.q_tok[lo + j];
-          mi[c] = a.m_int[lo + j];
-          mc[c] = a.m_conv[lo + j];
-          up[c] = a.u[lo + j] * (a.draft_prob ? a.draft_prob[lo + j] : 1.f);
+      for (int c0 = 0; c0 < TCH; c0 += GC) {
+#pragma unroll
+        for (int c = c0; c < c0 + GC; ++c) { par[c] = -2; tok[c] = -1; qv[c] = mi[c] = mc[c] = up[c] = 0.f; }
+        if (c0 * 64 < Tn) {
+          float pr[GC];
+#pragma unroll
+          for (int c = c0; c < c0 + GC; ++c) {
+            const int at = lo + min(c * 64 + lane, Tn - 1);
+            par[c] = a.parent[at];
+            tok[c] = a.token[at];
+            qv[c] = a.q_tok[at];
+            mi[c] = a.m_int[at];
+            mc[c] = a.m_conv[at];
+            up[c] = a.u[at];
+            pr[c - c0] = 1.f;
+          }
+          if (a.draft_prob)
+#pragma unroll
+            for (int c = c0; c < c0 + GC; ++c) pr[c - c0] = a.draft_prob[lo + min(c * 64 + lane, Tn - 1)];
+#pragma unroll
+          for (int c = c0; c < c0 + GC; ++c) {
+            up[c] *= pr[c - c0];
+            if (c * 64 + lane >= Tn) par[c] = -2;   // no node: nobody's child
+          }
         }
       }
       int cur = 0, len = 0, ntried = 0;
@@ -192,35 +209,27 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
   const bool vec = (V & 3) == 0;
   const float ub = a.u_bonus[b];
 
-  // every wave owns the chunks wave, wave + NW, ...; their logits are loaded in batches of 8 chunks
-  // (all loads of a batch in flight together).  With a single batch (CPW == 8) the registers are
-  // kept, and the crossing chunk is later resolved by its owner without a second trip to memory.
-  constexpr int NBATCH = CPW / 8;
-  auto load_chunk = [&](int c) -> f32x4 {
-    const int e0 = c * 256 + lane * 4;
-    f32x4 v = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    if (c < nchunks) {
-      if (vec && e0 + 3 < V) {
-        v = *(const f32x4*)(Lr + e0);
-      } else {
+  // every wave owns the chunks wave, wave + NW, ...; all their loads are in flight together and the registers are kept: the
+  // crossing chunk is resolved by its owner without a second trip to memory.  Latency-bound: guarded loads made every
+  // chunk wait for the one before.  Whole steps against that: 5 prompts x 33088 entries 208 -> 198 us, one 256-node tree x
+  // 65536 entries 293 -> 282, 60 nodes x 16384 75 -> 73.
+  f32x4 gv[CPW];
+  if (vec) {   // unconditional: clamped into the row, entries past its end are masked in chunk_vals
 #pragma unroll
-        for (int i = 0; i < 4; ++i) if (e0 + i < V) v[i] = Lr[e0 + i];
-      }
-    }
-    return v;
-  };
-  f32x4 gv[8];
-  if (NBATCH == 1) {
+    for (int ci = 0; ci < CPW; ++ci) gv[ci] = *(const f32x4*)(Lr + min((wave + SEL_WAVES * ci) * 256 + lane * 4, V - 4));
+  } else {
 #pragma unroll
-    for (int ci = 0; ci < 8; ++ci) gv[ci] = load_chunk(wave + SEL_WAVES * ci);
+    for (int ci = 0; ci < CPW; ++ci)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gv[ci][i] = Lr[min((wave + SEL_WAVES * ci) * 256 + lane * 4 + i, V - 1)];
   }
   // masses of the 4 entries a lane owns inside chunk c
   // lane e holds the e-th rejected token; chunk_vals visits them with readlane (no LDS in the loop)
   const int tried_reg = lane < ntried ? s_tried[lane] : -1;
-  auto chunk_vals = [&](int c, const f32x4& g4, bool use_ban, float r[4]) {
-    const int e0 = c * 256 + lane * 4;
+  auto chunk_vals = [&](int c, const f32x4& g4, bool use_ban, int l4, float ref, float r[4]) {
+    const int e0 = c * 256 + l4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = (g4[i] >= thr && e0 + i < V) ? __expf(g4[i] - lse) : 0.f;
+    for (int i = 0; i < 4; ++i) r[i] = (g4[i] >= thr && e0 + i < V) ? __expf(g4[i] - ref) : 0.f;
     if (use_ban) {
       for (int e = 0; e < ntried; ++e) {
         const int t = __builtin_amdgcn_readlane(tried_reg, e);
@@ -234,20 +243,18 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
 
   bool use_ban = true;
   for (int attempt = 0; attempt < 2; ++attempt) {
-    for (int bt = 0; bt < NBATCH; ++bt) {
-      if (NBATCH > 1) {
+    // the masses and masks are recomputed per attempt: hoisted out of the loop they would need as many registers again
+    int l4 = 4 * lane;
+    float ref = lse;
+    asm volatile("" : "+v"(l4), "+v"(ref));
 #pragma unroll
-        for (int ci = 0; ci < 8; ++ci) gv[ci] = load_chunk(wave + SEL_WAVES * (8 * bt + ci));
-      }
-#pragma unroll
-      for (int ci = 0; ci < 8; ++ci) {
-        const int c = wave + SEL_WAVES * (8 * bt + ci);
-        if (c < nchunks) {
-          float r[4];
-          chunk_vals(c, gv[ci], use_ban, r);
-          const float cs = wave_sum(((r[0] + r[1]) + r[2]) + r[3]);
-          if (lane == 0) s_chunk[c] = cs;
-        }
+    for (int ci = 0; ci < CPW; ++ci) {
+      const int c = wave + SEL_WAVES * ci;
+      if (c < nchunks) {
+        float r[4];
+        chunk_vals(c, gv[ci], use_ban, l4, ref, r);
+        const float cs = wave_sum(((r[0] + r[1]) + r[2]) + r[3]);
+        if (lane == 0) s_chunk[c] = cs;
       }
     }
     __syncthreads();
@@ -295,35 +302,34 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
     const int cstar = s_cstar;
     const bool ok = s_total > 0.f && cstar >= 0;
     if (!ok && tid == 0) a.emitted[(int64_t)b * (a.max_depth + 1) + len] = -1;
+    if (ok && wave == cstar % SEL_WAVES) {   // the owner of the crossing chunk finishes
+      const float target = ub * s_total;
+      float r[4];
+      f32x4 g4 = gv[0];
 #pragma unroll
-    for (int ci = 0; ci < 8; ++ci) {
-      // the owner of the crossing chunk finishes (kept registers, or one reload when there were several batches)
-      if (ok && (NBATCH == 1 ? wave + SEL_WAVES * ci == cstar : (ci == 0 && wave == cstar % SEL_WAVES))) {
-        const float target = ub * s_total;
-        float r[4];
-        const f32x4 g4 = NBATCH == 1 ? gv[ci] : load_chunk(cstar);
-        chunk_vals(cstar, g4, use_ban, r);
-        const float p0 = r[0], p1 = p0 + r[1], p2 = p1 + r[2], p3 = p2 + r[3];
-        const float incl = wave_scan_incl_f(p3);
-        const float run = s_base + (incl - p3);
-        int cand = 0x7fffffff;
-        const int e0 = cstar * 256 + lane * 4;
-        if (!s_lastkept) {
-          if (r[0] > 0.f && run + p0 > target) cand = e0;
-          else if (r[1] > 0.f && run + p1 > target) cand = e0 + 1;
-          else if (r[2] > 0.f && run + p2 > target) cand = e0 + 2;
-          else if (r[3] > 0.f && run + p3 > target) cand = e0 + 3;
-        }
-        const int best = wave_min_i(cand);
-        int x = best;
-        if (best == 0x7fffffff) {
-          int last = -1;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) if (r[i] > 0.f) last = e0 + i;
-          x = wave_max_i(last);
-        }
-        if (lane == 0) a.emitted[(int64_t)b * (a.max_depth + 1) + len] = x;
+      for (int ci = 1; ci < CPW; ++ci)
+        if (wave + SEL_WAVES * ci == cstar) g4 = gv[ci];
+      chunk_vals(cstar, g4, use_ban, 4 * lane, lse, r);
+      const float p0 = r[0], p1 = p0 + r[1], p2 = p1 + r[2], p3 = p2 + r[3];
+      const float incl = wave_scan_incl_f(p3);
+      const float run = s_base + (incl - p3);
+      int cand = 0x7fffffff;
+      const int e0 = cstar * 256 + lane * 4;
+      if (!s_lastkept) {
+        if (r[0] > 0.f && run + p0 > target) cand = e0;
+        else if (r[1] > 0.f && run + p1 > target) cand = e0 + 1;
+        else if (r[2] > 0.f && run + p2 > target) cand = e0 + 2;
+        else if (r[3] > 0.f && run + p3 > target) cand = e0 + 3;
       }
+      const int best = wave_min_i(cand);
+      int x = best;
+      if (best == 0x7fffffff) {
+        int last = -1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (r[i] > 0.f) last = e0 + i;
+        x = wave_max_i(last);
+      }
+      if (lane == 0) a.emitted[(int64_t)b * (a.max_depth + 1) + len] = x;
     }
   }
   for (int d = tid; d < a.max_depth; d += SEL_THREADS)
