@@ -47,24 +47,25 @@ MEASURED_TRAFFIC_KIB = {
     ("stress_1024px", "pack_h"): (8196.5, 8192.0),
     ("stress_1024px", "row_stats"): (131197.7, 98.2),
     ("stress_1024px", "select"): (588.3, 0.9),
-    ("janus_batched", "accept"): (7529.7, 83.8),
-    ("janus_batched", "attn"): (49856.9, 8118.1),
-    ("janus_batched", "lmhead"): (82009.7, 28864.0),
-    ("janus_batched", "pack_h"): (3612.5, 4096.0),
-    ("janus_batched", "row_stats"): (14507.5, 42.3),
-    ("janus_batched", "select"): (424.0, 1.4),
-    ("janus_pro_7b", "accept"): (989.2, 11.2),
-    ("janus_pro_7b", "attn"): (6521.0, 1080.0),
-    ("janus_pro_7b", "lmhead"): (67752.2, 3840.0),
-    ("janus_pro_7b", "pack_h"): (484.5, 512.0),
-    ("janus_pro_7b", "row_stats"): (1995.8, 5.6),
-    ("janus_pro_7b", "select"): (52.8, 0.2),
-    ("lumina_mgpt_7b_768", "accept"): (997.8, 11.2),
-    ("lumina_mgpt_7b_768", "attn"): (22158.7, 1080.0),
-    ("lumina_mgpt_7b_768", "lmhead"): (264994.3, 15360.0),
-    ("lumina_mgpt_7b_768", "pack_h"): (484.5, 512.0),
-    ("lumina_mgpt_7b_768", "row_stats"): (7804.2, 5.6),
-    ("lumina_mgpt_7b_768", "select"): (144.2, 0.2),
+    ("janus_batched", "accept"): (7526.2, 83.9),
+    ("janus_batched", "attn"): (49376.5, 8118.1),
+    ("janus_batched", "lmhead"): (82017.2, 28864.0),
+    ("janus_batched", "pack_h"): (3621.0, 4096.0),
+    ("janus_batched", "row_stats"): (14504.0, 42.3),
+    ("janus_batched", "select"): (392.1, 1.4),
+    ("janus_pro_7b", "accept"): (985.7, 11.2),
+    ("janus_pro_7b", "attn"): (6521.1, 1080.0),
+    ("janus_pro_7b", "lmhead"): (67491.0, 3840.0),
+    ("janus_pro_7b", "pack_h"): (491.0, 480.0),
+    ("janus_pro_7b", "row_stats"): (1992.0, 5.6),
+    ("janus_pro_7b", "select"): (48.7, 0.2),
+    ("lumina_mgpt_7b_768", "accept"): (994.3, 11.2),
+    ("lumina_mgpt_7b_768", "attn"): (22182.4, 8160.0),
+    ("lumina_mgpt_7b_768", "attn_merge"): (3975.5, 975.0),
+    ("lumina_mgpt_7b_768", "lmhead"): (264147.3, 15360.0),
+    ("lumina_mgpt_7b_768", "pack_h"): (491.0, 480.0),
+    ("lumina_mgpt_7b_768", "row_stats"): (7798.0, 5.6),
+    ("lumina_mgpt_7b_768", "select"): (151.0, 0.2),
 }
 
 
