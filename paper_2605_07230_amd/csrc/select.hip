@@ -209,20 +209,32 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
   const bool vec = (V & 3) == 0;
   const float ub = a.u_bonus[b];
 
-  // every wave owns the chunks wave, wave + NW, ...; all their loads are in flight together and the registers are kept: the
-  // crossing chunk is resolved by its owner without a second trip to memory.  Latency-bound: guarded loads made every
-  // chunk wait for the one before.  Whole steps against that: 5 prompts x 33088 entries 208 -> 198 us, one 256-node tree x
-  // 65536 entries 293 -> 282, 60 nodes x 16384 75 -> 73.
-  f32x4 gv[CPW];
-  if (vec) {   // unconditional: clamped into the row, entries past its end are masked in chunk_vals
+  // every wave owns the chunks wave, wave + NW, ...; their logits are loaded in batches of 8 chunks, all loads of a batch in
+  // flight together: clamped into the row (entries past its end are masked in chunk_vals), because a guard around every
+  // load made every chunk wait for the one before.  With a single batch (CPW == 8) the registers are kept, and the crossing
+  // chunk is resolved by its owner without a second trip to memory.  Latency-bound: 60 nodes x 16384 entries 9.0 -> 7.6 us,
+  // x 65536 12.9 -> 11.4, four 256-node trees x 65536 16.1 -> 14.5.  Sixteen chunks in registers instead of two batches were
+  // slower (65536 entries: 13.6 and 17.3): a lone workgroup runs through straight-line code that it has to fetch first.
+  constexpr int NBATCH = CPW / 8;
+  auto load_chunk = [&](int c) -> f32x4 {
+    const int e0 = c * 256 + lane * 4;
+    if (vec) return *(const f32x4*)(Lr + min(e0, V - 4));
+    f32x4 v;
 #pragma unroll
-    for (int ci = 0; ci < CPW; ++ci) gv[ci] = *(const f32x4*)(Lr + min((wave + SEL_WAVES * ci) * 256 + lane * 4, V - 4));
-  } else {
+    for (int i = 0; i < 4; ++i) v[i] = Lr[min(e0 + i, V - 1)];
+    return v;
+  };
+  f32x4 gv[8];
+  auto load_batch = [&](int bt) {
+    if (vec) {
 #pragma unroll
-    for (int ci = 0; ci < CPW; ++ci)
+      for (int ci = 0; ci < 8; ++ci) gv[ci] = *(const f32x4*)(Lr + min((wave + SEL_WAVES * (8 * bt + ci)) * 256 + lane * 4, V - 4));
+    } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gv[ci][i] = Lr[min((wave + SEL_WAVES * ci) * 256 + lane * 4 + i, V - 1)];
-  }
+      for (int ci = 0; ci < 8; ++ci) gv[ci] = load_chunk(wave + SEL_WAVES * (8 * bt + ci));
+    }
+  };
+  if (NBATCH == 1) load_batch(0);
   // masses of the 4 entries a lane owns inside chunk c
   // lane e holds the e-th rejected token; chunk_vals visits them with readlane (no LDS in the loop)
   const int tried_reg = lane < ntried ? s_tried[lane] : -1;
@@ -247,14 +259,17 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
     int l4 = 4 * lane;
     float ref = lse;
     asm volatile("" : "+v"(l4), "+v"(ref));
+    for (int bt = 0; bt < NBATCH; ++bt) {
+      if (NBATCH > 1) load_batch(bt);
 #pragma unroll
-    for (int ci = 0; ci < CPW; ++ci) {
-      const int c = wave + SEL_WAVES * ci;
-      if (c < nchunks) {
-        float r[4];
-        chunk_vals(c, gv[ci], use_ban, l4, ref, r);
-        const float cs = wave_sum(((r[0] + r[1]) + r[2]) + r[3]);
-        if (lane == 0) s_chunk[c] = cs;
+      for (int ci = 0; ci < 8; ++ci) {
+        const int c = wave + SEL_WAVES * (8 * bt + ci);
+        if (c < nchunks) {
+          float r[4];
+          chunk_vals(c, gv[ci], use_ban, l4, ref, r);
+          const float cs = wave_sum(((r[0] + r[1]) + r[2]) + r[3]);
+          if (lane == 0) s_chunk[c] = cs;
+        }
       }
     }
     __syncthreads();
@@ -306,9 +321,11 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
       const float target = ub * s_total;
       float r[4];
       f32x4 g4 = gv[0];
+      if (NBATCH > 1) g4 = load_chunk(cstar);
+      else
 #pragma unroll
-      for (int ci = 1; ci < CPW; ++ci)
-        if (wave + SEL_WAVES * ci == cstar) g4 = gv[ci];
+        for (int ci = 1; ci < 8; ++ci)
+          if (wave + SEL_WAVES * ci == cstar) g4 = gv[ci];
       chunk_vals(cstar, g4, use_ban, 4 * lane, lse, r);
       const float p0 = r[0], p1 = p0 + r[1], p2 = p1 + r[2], p3 = p2 + r[3];
       const float incl = wave_scan_incl_f(p3);
