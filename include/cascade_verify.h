@@ -150,7 +150,7 @@ typedef struct {
   const int32_t* parent;      /* [N] DEVICE, local indices */
   const int32_t* prefix_len;  /* [n_rows] DEVICE */
   int32_t n_nodes_total;      /* HOST copy of node_off[n_rows] */
-  int32_t max_nodes_per_tree; /* HOST upper bound on any row's node count */
+  int32_t max_nodes_per_tree; /* HOST upper bound on any row's node count (bf16: 0 with nodes is CASCADE_ESHAPE) */
   int32_t max_prefix_len;     /* HOST upper bound on any prefix_len[s] */
   cascade_dtype dtype;
   int32_t n_heads, n_kv_heads, head_dim;

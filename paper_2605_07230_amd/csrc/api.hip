@@ -175,6 +175,8 @@ int tree_verify_attn(cascade_ctx* ctx, const tree_attn_args* a) {
   }
   if (a->cache_stride_pos < a->head_dim && a->max_prefix_len > 1) return CASCADE_ESHAPE;
   if (a->n_rows == 0 || a->n_nodes_total == 0) return CASCADE_OK;
+  // the bf16 grids are sized by the bound: nodes without one are a contradiction (the f32 grid counts the nodes themselves)
+  if (a->dtype == CASCADE_BF16 && a->max_nodes_per_tree == 0) return CASCADE_ESHAPE;
   hipError_t e = (a->dtype == CASCADE_BF16) ? launch_tree_attn_bf16(ctx, a) : launch_tree_attn_f32(ctx, a);
   return e == hipSuccess ? CASCADE_OK : hip_fail(e);
 }
