@@ -143,6 +143,9 @@ int cascade_measure_mfma_bf16(cascade_ctx* ctx, int32_t iters, double* tflop_per
  *                      + pos*cache_stride_pos + d   (d contiguous; strides multiples of 8 for bf16)
  *     lse              [N, n_heads] float32, log-sum-exp of the scaled scores over J; may be NULL
  * out is written in dtype (bf16: round to nearest even); accumulation and softmax are float32.
+ * f32: a node's output depends on the keys and values in its J alone, infinities and NaN elsewhere in
+ * the row included.  bf16: values are expected to be finite - one that is not makes the same element of
+ * every node of its row (and heads) NaN, whether the node attends to it or not.
  */
 typedef struct {
   int32_t n_rows;

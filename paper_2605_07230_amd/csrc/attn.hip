@@ -185,11 +185,36 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
     }
     l = l * alpha + ls;
     m = m_new;
+    // A masked key has probability 0, but 0 x inf and 0 x NaN are NaN: a tile that some query does not see whole is looked
+    // through for such values, and if it holds any its keys are added one at a time, to the queries that see them.
+    bool whole_keys = true;
+    if (__any(bits != 0xffffu)) {
+      float z = 0.f;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      ot[db] *= alpha;
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][db], st[r], ot[db], 0, 0, 0);
+        for (int db = 0; db < DB; ++db) z = fmaf(v[r][db], 0.f, z);
+      whole_keys = !__any(z != 0.f);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) ot[db] *= alpha;
+    if (whole_keys) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][db], st[r], ot[db], 0, 0, 0);
+    } else {
+      for (int kg = 0; kg < 4; ++kg)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool sees = (bits >> (4 * kg + r)) & 1u;
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {
+            const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? v[r][db] : 0.f, st[r], ot[db], 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) ot[db][c] = sees ? o[c] : ot[db][c];
+          }
+        }
     }
     if (t + NW < nt) { request_k(t + NW); request_v(t + NW); }
   }

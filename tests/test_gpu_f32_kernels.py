@@ -80,6 +80,60 @@ def test_f32_attention(head_dim, heads, kv_heads, sizes, prefix, depth):
             assert float((lse[lo:hi, h].double() - rl).abs().max()) <= 2 * d + (prefix[s] + T + 8) * 2.0 ** -24 * (1 + float(rl.abs().max()))
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("head_dim", [6, 64, 128, 256])
+@pytest.mark.parametrize("sizes,prefix", [([20, 15], [33, 0]), ([1, 40], [5, 48])])
+def test_f32_attention_keeps_non_finite_values_with_the_nodes_that_see_them(value, head_dim, sizes, prefix):
+    """A value row that is not finite - of a node in the middle of its tree, of the last node (whose row stands in for the
+    keys past the tree's end) or of the last prefix key - reaches the nodes that attend to it and changes no other output."""
+    print(f"[f32 non-finite] {value} d={head_dim} sizes={sizes} prefix={prefix}", flush=True)
+    rng = np.random.default_rng(head_dim)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(head_dim)
+    trees = [wl.grow_tree(rng, n, min(4, n - 1)) if n > 1 else np.array([-1], np.int32) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n, S, cap, heads = int(off[-1]), len(sizes), max(prefix), 2
+    r = lambda *s: torch.randn(*s, device="cuda", generator=gen)  # noqa: E731
+    q, kt, vt, kc, vc = r(n, heads, head_dim), r(n, heads, head_dim), r(n, heads, head_dim), r(S, heads, cap, head_dim), r(S, heads, cap, head_dim)
+    dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
+    ctx = binding.Context(max_rows=S, max_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix=cap, n_heads=heads, head_dim=head_dim, hidden=64, vocab=64)
+
+    def attend(vt, vc):
+        out, lse = torch.full_like(q, 7.0), torch.full((n, heads), 7.0, device="cuda")
+        binding.tree_verify_attn(ctx, node_off=dev(off), parent=dev(np.concatenate(trees)), prefix_len=dev(prefix), q=q, k_tree=kt, v_tree=vt,
+                                 k_cache=kc, v_cache=vc, out=out, lse=lse, max_nodes_per_tree=max(sizes), max_prefix_len=cap)
+        assert ctx.device_status() == binding.OK
+        return out, lse
+
+    clean, lse0 = attend(vt, vc)
+    for s in range(S):
+        T, lo = sizes[s], int(off[s])
+        for x in {T - 1, T // 2}:      # a node's value, one element of it
+            bad = vt.clone()
+            bad[lo + x, 1, head_dim - 1] = value
+            out, lse = attend(bad, vc)
+            sees = torch.zeros(n, dtype=torch.bool)
+            for i in range(T):
+                a = i
+                while a >= 0:
+                    if a == x:
+                        sees[lo + i] = True
+                    a = int(trees[s][a])
+            hit = torch.zeros_like(out, dtype=torch.bool)
+            hit[:, 1, head_dim - 1] = sees.cuda()
+            assert torch.equal(~torch.isfinite(out), hit), (s, x)
+            assert torch.all(out[hit] == value) or value != value
+            # a tile that holds such a value adds its keys in another order: 16 of up to 89 keys, each a few 2^-24 of |v|
+            assert torch.all((out - clean)[~hit].abs() <= 64 * 2.0 ** -24 * float(vt.abs().max())) and torch.equal(lse, lse0)
+        if prefix[s]:
+            bad = vc.clone()
+            bad[s, 0, prefix[s] - 1, 0] = value
+            out, _ = attend(vt, bad)
+            hit = torch.zeros_like(out, dtype=torch.bool)
+            hit[lo:lo + T, 0, 0] = True
+            assert torch.equal(~torch.isfinite(out), hit) and (value != value or torch.all(out[hit] == value))
+
+
 def test_f32_attention_flags_bad_parents_and_overlong_paths():
     def status(parent):
         n = len(parent)
