@@ -142,7 +142,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   }
   for (int i = tid; i < T; i += 64 * NW) {
     int pi = p.parent[lo + i];
-    if (pi >= i || pi < -1) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // keeps the climb finite
+    if (pi >= i) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // keeps the climb finite; any negative parent ends it
     s_parent[i] = pi;
   }
   __syncthreads();
@@ -156,10 +156,10 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
     if (tree) {
       bits = 0;
       int a = qi, steps = 0;
-      while (a >= kb) {
-        if (a - kb < 16) bits |= 1u << (a - kb);
+      while (a >= kb) {   // the node and its MAX_DEPTH nearest ancestors; a longer path is flagged
         if (++steps > CASCADE_MAX_DEPTH + 1) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); break; }
-        a = s_parent[a];   // smaller than a, or -1
+        if (a - kb < 16) bits |= 1u << (a - kb);
+        a = s_parent[a];   // smaller than a, or negative
       }
     } else {
       bits = last - kb >= 15 ? 0xffffu : (1u << (last - kb + 1)) - 1u;
