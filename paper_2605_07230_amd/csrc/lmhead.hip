@@ -178,7 +178,12 @@ __global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__
 // Measured against the kernels this replaced (64 x 64 tiles, operands loaded to registers, hidden 4096; us, without the
 // packing pass of 4 us that they needed): 60 rows x 16384: 30.2 -> 27.4; 60 x 65536: 110 -> 101 (5.3 TB/s);
 // 120 x 16384: 45 -> 35; 230 x 16384: 75 -> 45; 60 guidance pairs, row-major weights: 63 -> 37.
-template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
+// DIRECT = false: rows or weights that do not start on a 16-byte boundary.  LDS-direct loads are counted on for aligned
+// addresses only; ordinary loads take any, pass through registers and are stored to the same places, one stage ahead in two
+// slots (so the stages are twice as long).  60 rows x 16384 x 4096: 26 us aligned, 38 with rows at 8 bytes past a boundary,
+// 47 with packed weights 2 bytes past one (36 in the register-staged kernel); 60 pairs, row-major: 36, 62, 78 (93); 230 rows:
+// 44, 58, 78 (109).
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT>
 __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n_mtiles) {
   static_assert(WM * WN * KW == 8 && KS % KW == 0 && KS % 4 == 0 && (!CFG || AM == 2), "eight waves; guidance pairs are a wave's two row blocks");
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NA = BM / 32, NBLK = NA + BN / 32, STAGE = NBLK * KS * 1024;
@@ -222,11 +227,17 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
     }
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)ring_lds) + wave * LPW * 1024;
+  u32x4 held[DIRECT ? 1 : LPW];   // (ordinary loads) the stage on its way
+  auto store_held = [&](int slot) {   // complete before the next barrier, which waits for the wave's LDS operations
+#pragma unroll
+    for (int i = 0; i < (DIRECT ? 0 : LPW); ++i) *(u32x4*)(ring_lds + (wave * LPW + i) * 1024 + slot * STAGE + 16 * lane) = held[i];
+  };
   auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
     const int tc = min(t, n_stages - 1);
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
       const char* g = src[i] + (int64_t)tc * ((PW && (wave * LPW + i) / KS >= NA) ? KS * 1024 : KS * 32);
+      if constexpr (!DIRECT) { __builtin_memcpy(&held[i], g + voff[i], 16); continue; }
       const unsigned l = lds0 + slot * STAGE + i * 1024;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
     }
@@ -244,7 +255,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
-  for (int t = 0; t < NST - 1; ++t) request(t, t);
+  for (int t = 0; t < NST - 1; ++t) { request(t, t); store_held(t); }
   // every sum over the hidden dimension is four chains, over the KW groups of waves and within a wave: one chain of 4096
   // terms is off by 3.7e-7 of the row (2-norm, against float64), two 2.5e-7, four 1.7e-7
   constexpr int CH = 4 / KW;
@@ -255,7 +266,9 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
       // barrier: everybody's chunks are there and stage t - 1's slot is free
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
-      request(t + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+      const int free_slot = slot == 0 ? NST - 1 : slot - 1;
+      request(t + NST - 1, free_slot);
+      if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
       const char* st = ring_lds + slot * STAGE;
       Frag8 a[SPW][AM], b[SPW][AN];
 #pragma unroll
@@ -272,6 +285,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
         for (int i = 0; i < AM; ++i)
 #pragma unroll
           for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
+      store_held(free_slot);
       slot = slot + 1 == NST ? 0 : slot + 1;
     }
     if (CH > 1)
@@ -878,13 +892,13 @@ hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a) {
   return hipGetLastError();
 }
 
-template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT = true>
 hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols) {
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NODES = CFG ? BM / 2 : BM;
   constexpr int RING = NST * (BM + BN) / 32 * KS * 1024, RED = KW > 1 ? 8 * AM * AN * 4096 : 0;
   constexpr int smem = RING > RED ? RING : RED;
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-  auto kern = lmhead_bf16_ring_kernel<AM, AN, WM, WN, KW, KS, NST, CFG, PW>;
+  auto kern = lmhead_bf16_ring_kernel<AM, AN, WM, WN, KW, KS, NST, CFG, PW, DIRECT>;
   static bool attr_done = false;   // one flag per template instance
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
@@ -896,6 +910,7 @@ hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols) {
   CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
 }
+constexpr int LM_UNALIGNED = -1;   // ordinary loads: 64 x 64 or 128 x 128
 template <bool CFG, bool PW>
 hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols) {
   switch (tile) {
@@ -903,6 +918,8 @@ hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols
     case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p, n_cols);
     case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p, n_cols);
     case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p, n_cols);
+    case LM_UNALIGNED: return p.n_nodes * (CFG ? 2 : 1) <= 64 ? launch_ring_t<2, 1, 1, 2, 4, 8, 2, CFG, PW, false>(ctx, p, n_cols)
+                                                              : launch_ring_t<2, 2, 2, 2, 2, 8, 2, CFG, PW, false>(ctx, p, n_cols);
     default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p, n_cols);
   }
 }
@@ -1003,7 +1020,11 @@ hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
   // guidance mixed into the hidden rows in front of the projection: from here on a plain projection of n_nodes rows
   const bool premix = a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && packed_w;
   const bool cfg = a->h_uncond != nullptr && !premix;
-  const LmPlan plan = lm_plan(a, packed_w, premix, cfg, ctx->n_cu);
+  LmPlan plan = lm_plan(a, packed_w, premix, cfg, ctx->n_cu);
+  // (mixed and packed rows lie in the workspace; both passes that write them read the caller's rows with ordinary loads)
+  const bool rows_direct = !premix && (plan.main < LM_RING_TILES || plan.rest < LM_RING_TILES);
+  if (((uintptr_t)a->w | (rows_direct ? (uintptr_t)a->h_cond | (uintptr_t)(cfg ? a->h_uncond : nullptr) : 0)) & 15)
+    plan.main = plan.rest = LM_UNALIGNED, plan.split = a->vocab;
   uint4* hc = (uint4*)ctx->hpack_ws;
   if (plan.main < LM_RING_TILES) {
     if (premix) {

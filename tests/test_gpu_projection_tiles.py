@@ -41,8 +41,22 @@ def test_projection_split_columns(n, vocab, mode, packed):
     _check(n, vocab, 2048, mode, packed)
 
 
-def _check(n, vocab, hidden, mode, packed):
-    print(f"[projection] nodes={n} vocab={vocab} hidden={hidden} {mode} packed={packed}", flush=True)
+# buffers that start 2, 8 and 14 bytes past a 16-byte boundary: sizes that take one ring tile, two, packed rows, and both
+@pytest.mark.parametrize("n,vocab,hidden", [(1, 64, 128), (60, 4096, 384), (200, 16448, 128), (257, 33088, 256), (520, 16384, 128)])
+@pytest.mark.parametrize("mode", ["plain", "pairs", "mixed"])
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("shift_h,shift_w", [(1, 0), (0, 4), (7, 1)])
+def test_projection_of_buffers_off_the_16_byte_grid(n, vocab, hidden, mode, packed, shift_h, shift_w):
+    _check(n, vocab, hidden, mode, packed, shift_h, shift_w)
+
+
+def _shifted(x, elements):
+    y = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)[elements:elements + x.numel()].view(x.shape)
+    return y.copy_(x)
+
+
+def _check(n, vocab, hidden, mode, packed, shift_h=0, shift_w=0):
+    print(f"[projection] nodes={n} vocab={vocab} hidden={hidden} {mode} packed={packed} shift={shift_h},{shift_w}", flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n * 131 + vocab + hidden)
     w = (0.02 * torch.randn(vocab, hidden, device="cuda", generator=gen)).bfloat16()
@@ -52,7 +66,11 @@ def _check(n, vocab, hidden, mode, packed):
     logits = torch.full((n, vocab), float("nan"), device="cuda")
     stats = [torch.empty(n, device="cuda") for _ in range(3)]
     s, temp = 3.0, 0.8
-    binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=None if mode == "plain" else u, w=binding.cascade_pack_lmhead_w(ctx, w) if packed else w,
+    wp = binding.cascade_pack_lmhead_w(ctx, w) if packed else w
+    if shift_h or shift_w:
+        c, u, wp = _shifted(c, shift_h), _shifted(u, shift_h), _shifted(wp, shift_w)
+        assert c.data_ptr() % 16 == 2 * shift_h and wp.data_ptr() % 16 == 2 * shift_w
+    binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=None if mode == "plain" else u, w=wp,
                                w_layout=binding.W_PACKED32 if packed else binding.W_ROWMAJOR, cfg_scale=s, temperature=temp, top_k=50,
                                logits=logits, row_max=stats[0], row_thr=stats[1], row_lse=stats[2],
                                cfg_mix=binding.CFG_MIX_HIDDEN if mode == "mixed" else binding.CFG_MIX_LOGITS)
