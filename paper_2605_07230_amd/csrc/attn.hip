@@ -90,15 +90,6 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   }
   if (s < 0) return;   // the grid is an upper bound of the number of blocks
   const int M = T * G;
-  if (T > CASCADE_MAX_TREE) {   // flagged, zeros (the same for every block of the row)
-    if (tid == 0) atomicOr(p.dev_status, CASCADE_FLAG_TREE_SIZE);
-    for (int r = 16 * sb + tid; r < min(16 * sb + 16, M); r += 64 * NW) {
-      const int64_t rowg = (int64_t)(lo + r % T) * p.n_heads + kvh * G + r / T;
-      for (int d = 0; d < D; ++d) ((float*)p.out)[rowg * D + d] = 0.f;
-      if (p.lse) p.lse[rowg] = -INFINITY;
-    }
-    return;
-  }
   const int qr = min(16 * sb + l16, M - 1);   // rows past the end repeat the last one, never stored
   const int qi = qr % T;
   const int64_t q_row = (int64_t)(lo + qi) * p.n_heads + kvh * G + qr / T;
@@ -143,8 +134,14 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   for (int i = tid; i < T; i += 64 * NW) {
     int pi = p.parent[lo + i];
     if (pi >= i) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // keeps the climb finite; any negative parent ends it
-    s_parent[i] = pi;
+    if (i < CASCADE_MAX_TREE) s_parent[i] = pi;
   }
+  // node a's parent: smaller than a, or negative.  Nothing but the array in LDS bounds a tree here; nodes past it read memory.
+  auto parent_of = [&](int a) {
+    if (a < CASCADE_MAX_TREE) return s_parent[a];
+    const int pi = p.parent[lo + a];
+    return pi >= a ? -1 : pi;
+  };
   __syncthreads();
   if (wave < nt) { request_k(wave); request_v(wave); }
   float m = -INFINITY, l = 0.f;
@@ -159,7 +156,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
       while (a >= kb) {   // the node and its MAX_DEPTH nearest ancestors; a longer path is flagged
         if (++steps > CASCADE_MAX_DEPTH + 1) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); break; }
         if (a - kb < 16) bits |= 1u << (a - kb);
-        a = s_parent[a];   // smaller than a, or negative
+        a = parent_of(a);
       }
     } else {
       bits = last - kb >= 15 ? 0xffffu : (1u << (last - kb + 1)) - 1u;

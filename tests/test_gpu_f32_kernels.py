@@ -137,12 +137,13 @@ def test_f32_attention_keeps_non_finite_values_with_the_nodes_that_see_them(valu
 def test_f32_attention_flags_bad_parents_and_overlong_paths():
     def status(parent, see=None):
         n = len(parent)
-        ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=n, max_prefix=1, n_heads=1, head_dim=8, hidden=64, vocab=64)
+        bound = min(n, 1024)
+        ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=bound, max_prefix=1, n_heads=1, head_dim=8, hidden=64, vocab=64)
         dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
         t = [torch.randn(n, 1, 8, device="cuda") for _ in range(3)]
         c = torch.randn(1, 1, 1, 8, device="cuda")
         binding.tree_verify_attn(ctx, node_off=dev([0, n]), parent=dev(parent), prefix_len=dev([1]), q=t[0], k_tree=t[1], v_tree=t[2], k_cache=c,
-                                 v_cache=c, out=(out := torch.empty_like(t[0])), max_nodes_per_tree=n, max_prefix_len=1)
+                                 v_cache=c, out=(out := torch.empty_like(t[0])), max_nodes_per_tree=bound, max_prefix_len=1)
         if see is not None:
             mask = torch.tensor([[True] + [see(i, j) for j in range(n)] for i in range(n)]).cuda()
             ref, _ = _attend(t[0][:, 0], torch.cat([c[0, 0], t[1][:, 0]]), torch.cat([c[0, 0], t[2][:, 0]]), mask, 8 ** -0.5)
@@ -154,4 +155,10 @@ def test_f32_attention_flags_bad_parents_and_overlong_paths():
     assert status(list(range(-1, 70))) == binding.ETREE       # deeper than the library's limit
     # a flagged path still counts: the node and its 64 nearest ancestors
     assert status(list(range(-1, 70)), lambda i, j: i - 65 < j <= i) == binding.ETREE
+    # nothing in the f32 path is sized by the largest tree: 1024 nodes are no limit
+    wide = [-1] + [i % 40 for i in range(39)] + [0] * 984 + [1023, 1024, 7] + [1025] * 40
+    path = [set() for _ in wide]
+    for i, pi in enumerate(wide):
+        path[i] = {i} | (path[pi] if pi >= 0 else set())
+    assert status(wide, lambda i, j: j in path[i]) == binding.OK
     assert status([-1, 0, -2, 2], lambda i, j: i == j or (i, j) in ((1, 0), (3, 2))) == binding.OK   # a negative parent ends a path
