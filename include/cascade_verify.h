@@ -58,7 +58,8 @@ typedef enum { CASCADE_F32 = 0, CASCADE_BF16 = 1 } cascade_dtype;
 
 /* SEQUENTIAL is Alg. 2 as printed (siblings tried in order, first accepted child descends).
  * LONGEST simulates the same rule along every root-to-leaf path on its own and keeps the path
- * with the longest accepted prefix (ties: smallest leaf index). */
+ * with the longest accepted prefix (ties: smallest leaf index); if no path accepts anything the walk
+ * stays at the root as if nothing had been tried (tvd_used 0, no token removed from the root's row). */
 typedef enum { CASCADE_WALK_SEQUENTIAL = 0, CASCADE_WALK_LONGEST = 1 } cascade_walk_mode;
 
 #define CASCADE_MAX_WIDTH 64      /* children per node */
