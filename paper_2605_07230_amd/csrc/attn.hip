@@ -401,7 +401,11 @@ __device__ __forceinline__ float rows4_max_raw(float v) {
   return vmax2(__uint_as_float(b.x), __uint_as_float(b.y));
 }
 
-template <int D, int NS, int NQ, int NW, bool WHOLE>
+//
+// DIRECT = false: keys and values that do not start on a 16-byte boundary, or positions more than 64 MiB apart.  LDS-direct
+// loads are counted on for aligned addresses only and take 32-bit offsets inside a tile; ordinary loads with 64-bit addresses
+// take any.  They pass through registers and are stored to the same places at the end of the step that requested them.
+template <int D, int NS, int NQ, int NW, bool WHOLE, bool DIRECT = true>
 __device__ __forceinline__ void ring_body(const AttnParams& p) {
   using GM = RingGeom<D>;
   constexpr int NT = 64 * NW, RW = 16 * NQ * NW;
@@ -409,6 +413,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
   constexpr int LW = GM::CPT % NW == 0 ? NW : 4;   // waves that load: all, or the first four when the chunks do not divide
   constexpr int CPW = GM::CPT / LW;     // chunks of K (and of V) a loading wave fetches per tile
   constexpr int LPI = 2 * CPW;          // LDS-direct loads a wave issues per iteration
+  static_assert(DIRECT || LW == NW, "every wave stores what it has requested");
   static_assert(GM::CPT % LW == 0 && NW >= LW && (NS == 2 || NS == 3), "ring geometry: the loop below is unrolled NS times");
   extern __shared__ __align__(1024) char ring_smem[];
   char* const smem_raw = ring_smem;
@@ -471,9 +476,25 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
   // extra requests keep the per-iteration load count fixed; their data lands in a free stage and is never
   // used); rows past the end of the tile's source are read from its last row (always in bounds; their scores
   // are masked, so the finite clamped values contribute exactly nothing).
+  u32x4 held[2][DIRECT ? 1 : CPW];   // (ordinary loads) K and V on their way
+  auto store_held = [&](int stage, bool is_v) {
+#pragma unroll
+    for (int i = 0; i < (DIRECT ? 0 : CPW); ++i)
+      *(u32x4*)(smem_raw + (is_v ? NS * GM::TILE : 0) + stage * GM::TILE + (CPW * wave + i) * 1024 + 16 * lane) = held[is_v][i];
+  };
   auto request = [&](int tk, int stage, bool is_v) {
     if (LW < NW && wave >= LW) return;
     const int tc = min(tk, t_end - 1);
+    if constexpr (!DIRECT) {
+      const bool tree_tile = tc >= n_pt;
+      const int kb = tree_tile ? (tc - n_pt) * KT : tc * KT;
+      const int lim = (tree_tile ? T : P) - 1 - kb;                 // last valid row of the tile, >= 0
+      const int64_t pitch_b = tree_tile ? (int64_t)tree_pitch_b : 2 * p.sp;
+      const char* src = (is_v ? (tree_tile ? vtr : vc) : (tree_tile ? ktr : kc)) + (int64_t)kb * pitch_b;
+#pragma unroll
+      for (int i = 0; i < CPW; ++i) __builtin_memcpy(&held[is_v][i], src + min(ld_row[i], lim) * pitch_b + (is_v ? ld_vpiece[i] : ld_kpiece[i]), 16);
+      return;
+    }
     const unsigned ldst = lds0 + (is_v ? NS * GM::TILE : 0) + stage * GM::TILE + CPW * wave * 1024;
     if (tc < n_pt && (tc + 1) * KT <= P) {
       // a whole tile of the prefix: nothing to clamp, the per-lane offsets are constants
@@ -519,10 +540,13 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
 
   // ---- prologue: K(t_begin) first, then the steady-state order K(t + NS), V(t + NS - 1) of iterations -NS+1 .. -1
   request(t_begin, 0, false);
+  store_held(0, false);
 #pragma unroll
   for (int i = 1 - NS; i < 0; ++i) {
     request(t_begin + i + NS, (i + NS) % NS, false);
+    store_held((i + NS) % NS, false);
     request(t_begin + i + NS - 1, (i + NS - 1) % NS, true);
+    store_held((i + NS - 1) % NS, true);
   }
   if (t_end > n_pt) {
     for (int i = tid; i < T; i += NT) {
@@ -640,6 +664,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     wait_and_sync<LPI * (NS - 2)>();   // K(t+1), V(t) landed everywhere; K(t), V(t-1) free
     request(t + NS, ST, false);
     request(t + NS - 1, ST_VNEW, true);
+    if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
     Frag8 kf[2][KS];
     load_kfrags(kf[0], ST_K, 0);       // in flight during the reference check
     if (t + 1 < t_end && t + 1 >= n_pt) build_mask(t + 1);   // read after the next barrier
@@ -730,6 +755,8 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
       if (i + VW < NVS) load_vfrag(vf[i % VW], ST, i + VW);
       __builtin_amdgcn_sched_barrier(0);   // keeps the read of step i + VW here, VW steps ahead of its use
     }
+    store_held(ST, false);       // K(t) and V(t - 1) are free (see above); complete before the next barrier, which waits for LDS
+    store_held(ST_VNEW, true);
   };
 
   for (int t = t_begin; t < t_end; t += NS) {
@@ -781,8 +808,8 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { 
 // the same or slower at every shape.  Against the kernels this replaced, in a step (us): 16 rows of 113-680 keys, 40-80
 // nodes: 46 -> 37; 10 rows of 107-1619 keys, 8 kv heads of 4: 54 -> 34; 8 rows of 140-680 keys: 25 -> 22; 2 rows of 4200 keys
 // and 256 nodes, keys in four parts: 65 -> 59 with the merge; 2 rows of 1289 keys, four parts: 23 -> 21.
-template <int D, int NS, int NQ, int NW, int OCC>
-__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false>(p); }
+template <int D, int NS, int NQ, int NW, int OCC, bool DIRECT>
+__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false, DIRECT>(p); }
 
 // ---------------------------------------------------------------------- bf16, few query rows
 // When a step has so few (row, kv head) pairs and keys that the chain of tiles of one workgroup is what takes the time,
@@ -1139,19 +1166,19 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
 }
 
 // 16 NQ NW query rows per workgroup, keys split p.n_split ways (partials, then the merge kernel)
-template <int D, int NQ, int NW, int OCC>
+template <int D, int NQ, int NW, int OCC, bool DIRECT = true>
 hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int NS = 2, RW = 16 * NQ * NW;
   constexpr int smem = 2 * NS * RingGeom<D>::TILE + CASCADE_MAX_TREE * (int)sizeof(int) + 2 * RW * (int)sizeof(unsigned long long);
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   {
     KernelTimer t(ctx, CASCADE_K_ATTN);
-    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC>), grid, dim3(64 * NW), smem, ctx->stream, p);
+    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, DIRECT>), grid, dim3(64 * NW), smem, ctx->stream, p);
   }
   if (p.n_split > 1) {
     KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
@@ -1213,8 +1240,13 @@ float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_spli
   return us;
 }
 
+// shapes that exist with ordinary loads as well (the query-split kernel has no others)
+bool attn_shape_loads_any(int shape) { return shape == 0 || shape == 3 || shape == ATTN_QSPLIT; }
+
 template <int D>
-hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, dim3 grid) {
+hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, bool direct, dim3 grid) {
+  if (!direct && shape != ATTN_QSPLIT)
+    return shape == 0 ? launch_rows_t<D, 1, 4, 2, false>(ctx, p, grid) : launch_rows_t<D, 1, 8, 2, false>(ctx, p, grid);
   switch (shape) {
     case 0: return launch_rows_t<D, 1, 4, 2>(ctx, p, grid);
     case 1: return launch_rows_t<D, 1, 5, 3>(ctx, p, grid);
@@ -1230,9 +1262,13 @@ hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
   const int M = a->max_nodes_per_tree * p.group;   // query rows per (row, kv head)
   const int n_tiles = (a->max_prefix_len + KT - 1) / KT + (a->max_nodes_per_tree + KT - 1) / KT;
   const size_t per_split = (size_t)p.n_rows_total * (a->head_dim + 2) * sizeof(float);
+  // keys and values are fetched by LDS-direct loads where their addresses allow it (strides are multiples of 16 bytes)
+  const bool direct = (((uintptr_t)a->k_tree | (uintptr_t)a->v_tree | (uintptr_t)a->k_cache | (uintptr_t)a->v_cache) & 15) == 0 &&
+                      a->cache_stride_pos <= (int64_t)1 << 25;
   int shape = 0;
   float best = INFINITY;
   for (int i = 0; i < ATTN_N_SHAPES; ++i) {
+    if (!direct && !attn_shape_loads_any(i)) continue;
     if (i == ATTN_QSPLIT && (M > 128 || a->max_nodes_per_tree > 128)) continue;   // its LDS holds trees of 128 nodes
     for (int n = 1; n <= 16 && n <= n_tiles; n = n < 4 ? n + 1 : n * 2) {
       if (n > 1 && (i >= ATTN_RING || per_split * n > ctx->attn_ws_bytes)) break;   // these take whole rows of keys
@@ -1248,5 +1284,5 @@ hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
   dim3 grid(p.n_split * p.n_sb, a->n_kv_heads, a->n_rows);
   // rows of the batch that one round of workgroups over the compute units covers (see row_by_work_rank)
   p.round_rows = ctx->n_cu / (int)(grid.x * grid.y);
-  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, grid) : launch_bf16_t<64>(ctx, p, shape, grid);
+  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, direct, grid) : launch_bf16_t<64>(ctx, p, shape, direct, grid);
 }

@@ -33,8 +33,35 @@ CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths
 @pytest.mark.parametrize("name", CASES)
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_attention_cuts(name, head_dim):
-    kv_heads, group, sizes, prefix = CASES[name]
-    print(f"[attention cuts] {name}, head_dim {head_dim}", flush=True)
+    _check(head_dim, *CASES[name])
+
+
+# buffers 2, 8 and 14 bytes past a 16-byte boundary, and positions further apart than a 32-bit offset of a tile reaches:
+# loads that need neither, in the cuts they come in (64 and 128 query rows per workgroup, keys whole and in parts, query split)
+LOADS = {
+    "64 rows, keys in parts": (2, 1, [60, 41, 64, 17, 55], [1500, 37, 700, 1100, 260]),
+    "64 rows, grouped heads": (2, 3, [100, 33, 64], [900, 130, 0]),
+    "128 rows": (32, 1, [100, 128, 97, 33, 64, 63, 79, 16, 1, 2, 127, 65, 17, 111, 20, 7], [90, 20, 64, 0, 133, 128, 1, 65, 63, 10, 5, 70, 30, 100, 40, 200]),
+    "128 rows, keys in parts": (32, 1, [256, 130], [2000, 64]),
+    "query split": (2, 1, [20, 17], [400, 63]),
+}
+
+
+@pytest.mark.parametrize("name", LOADS)
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("shift", [1, 4, 7])
+def test_attention_of_buffers_off_the_16_byte_grid(name, head_dim, shift):
+    _check(head_dim, *LOADS[name], shift=shift)
+
+
+@pytest.mark.parametrize("sizes,prefix", [([20, 70], [5, 66]), ([150], [40])])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_attention_of_positions_far_apart(sizes, prefix, head_dim):
+    _check(head_dim, 2, 1, sizes, prefix, pos_stride=(1 << 25) + 8)
+
+
+def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None):
+    print(f"[attention cuts] heads {kv_heads} x {group}, trees {sizes}, prefixes {prefix}, head_dim {head_dim}, shift {shift}", flush=True)
     rng = np.random.default_rng(head_dim + len(sizes))
     gen = torch.Generator(device="cuda")
     gen.manual_seed(head_dim + kv_heads)
@@ -44,6 +71,18 @@ def test_attention_cuts(name, head_dim):
     r = lambda *s: torch.randn(*s, device="cuda", generator=gen).bfloat16()  # noqa: E731
     q, kt, vt = r(n, heads, head_dim), r(n, kv_heads, head_dim), r(n, kv_heads, head_dim)
     kc, vc = r(S, kv_heads, cap, head_dim), r(S, kv_heads, cap, head_dim)
+    if shift:
+        def moved(x):
+            y = torch.empty(x.numel() + 8, dtype=x.dtype, device="cuda")[shift:shift + x.numel()].view(x.shape)
+            assert y.data_ptr() % 16 == 2 * shift
+            return y.copy_(x)
+        q, kt, vt, kc, vc = (moved(x) for x in (q, kt, vt, kc, vc))
+    if pos_stride:   # [position][row][head][head_dim] with a gap behind every position
+        def spread(x):
+            size = (S, kv_heads, cap, head_dim)
+            y = torch.empty(cap * pos_stride, dtype=x.dtype, device="cuda").as_strided(size, (kv_heads * head_dim, head_dim, pos_stride, 1))
+            return y.copy_(x)
+        kc, vc = spread(kc), spread(vc)
     out, lse = torch.full_like(q, float("nan")), torch.full((n, heads), float("nan"), device="cuda")
     ctx = binding.Context(max_rows=S, max_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix=cap, n_heads=heads, head_dim=head_dim, hidden=128, vocab=64)
     dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
