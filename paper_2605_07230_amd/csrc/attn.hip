@@ -369,8 +369,10 @@ __device__ __forceinline__ void wait_and_sync() {
 // The running maximum that the exponentials refer to is only moved when a row's maximum has grown by
 // more than 2^8 (the result does not depend on the reference, p <= 256 is exact enough in bf16 and far
 // from overflow in the float accumulators), so the accumulator rescale is a rarely taken branch.  That holds
-// for the 256-row kernel; the smaller ones keep the running maximum itself, whose probability is exactly 1 and
-// whose neighbours round finest: 2.16e-3 (2-norm, against float64) instead of 2.28e-3 for 1 us at 37.
+// for the 256-row kernel.  The smaller ones move it with every new maximum, whose probability is then exactly 1 and whose
+// neighbours round finest; with FINE the exponentials of a tile refer to the tile's own maximum, and its sums and products
+// are scaled to the running one in float32 when they are added.  2-norm against float64: 2.08e-3 with FINE at every shape
+// measured (1 to 16 rows, 90-4200 keys), 2.14e-3 to 2.25e-3 without, 2.34e-3 in the 256-row kernel.
 template <int D>
 struct RingGeom {
   static constexpr int RB = 2 * D;        // bytes per key row
@@ -405,11 +407,12 @@ __device__ __forceinline__ float rows4_max_raw(float v) {
 // DIRECT = false: keys and values that do not start on a 16-byte boundary, or positions more than 64 MiB apart.  LDS-direct
 // loads are counted on for aligned addresses only and take 32-bit offsets inside a tile; ordinary loads with 64-bit addresses
 // take any.  They pass through registers and are stored to the same places at the end of the step that requested them.
-template <int D, int NS, int NQ, int NW, bool WHOLE, bool DIRECT = true>
+template <int D, int NS, int NQ, int NW, bool WHOLE, bool FINE, bool DIRECT>
 __device__ __forceinline__ void ring_body(const AttnParams& p) {
   using GM = RingGeom<D>;
   constexpr int NT = 64 * NW, RW = 16 * NQ * NW;
   constexpr int KS = D / 32, DB = D / 16;
+  static_assert(!(WHOLE && FINE), "the 256-row kernel lets the reference lag");
   constexpr int LW = GM::CPT % NW == 0 ? NW : 4;   // waves that load: all, or the first four when the chunks do not divide
   constexpr int CPW = GM::CPT / LW;     // chunks of K (and of V) a loading wave fetches per tile
   constexpr int LPI = 2 * CPW;          // LDS-direct loads a wave issues per iteration
@@ -640,7 +643,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
   __syncthreads();                    // parent array complete (the compiler's own waits cover its loads)
   if (t_begin >= n_pt) build_mask(t_begin);
   wait_and_sync<LPI * (NS - 1)>();    // K(t_begin) everywhere (and the first mask)
-  float lmax[NQ];                     // lane_max of the scores in st (valid for tiles that need no mask)
+  float lmax[NQ];                     // lane_max of the scores in st (FINE: the row's), for tiles that need no mask
   {
     Frag8 kf[2][KS];
     load_kfrags(kf[0], 0, 0);
@@ -650,7 +653,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
       score_kt(kf[kt & 1], kt);
     }
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) lmax[n] = lane_max(n);
+    for (int n = 0; n < NQ; ++n) lmax[n] = FINE ? rows4_max_raw(lane_max(n)) : lane_max(n);
   }
 
   // One tile.  ST = ring stage of tile t (compile time: the loop below is unrolled NS times).
@@ -682,19 +685,23 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
 #pragma unroll
           for (int c = 0; c < 4; ++c) st[n][kt][c] = ((nib >> c) & 1u) ? st[n][kt][c] : -INFINITY;
         }
-        lmax[n] = lane_max(n);
+        lmax[n] = FINE ? rows4_max_raw(lane_max(n)) : lane_max(n);
       }
     }
     // a lane sees 16 of its row's 64 scores; if none of a wave's lanes exceeds its row's reference by more than
     // the step, no row does, and the reference stays (scale > 0: the maximum commutes with it)
     constexpr float STEP = WHOLE ? RESCALE_STEP : 0.f;
+    float m_tile[NQ];
     bool moved = false;
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) moved |= lmax[n] * p.scale_log2e > m_ref[n] + STEP;   // -inf + 8 = -inf: a first finite score always moves it
+    for (int n = 0; n < NQ; ++n) {
+      m_tile[n] = lmax[n] * p.scale_log2e;   // FINE: the row's in this tile, otherwise this lane's
+      moved |= m_tile[n] > m_ref[n] + STEP;   // -inf + 8 = -inf: a first finite score always moves it
+    }
     if (__ballot(moved) != 0ull) {
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
-        const float mx = rows4_max_raw(lmax[n]) * p.scale_log2e;
+        const float mx = FINE ? m_tile[n] : rows4_max_raw(lmax[n]) * p.scale_log2e;
         const float m_new = (mx > m_ref[n] + STEP) ? mx : m_ref[n];
         const float use_new = (m_new == -INFINITY) ? 0.f : m_new;
         const float alpha = fast_exp2(m_ref[n] - use_new);   // -inf - finite = -inf -> 0 ; equal -> 1
@@ -704,9 +711,14 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
         m_ref[n] = m_new;
       }
     }
-    float m_neg[NQ];
+    float m_neg[NQ], beta[NQ], ltile[NQ];   // (FINE) 2^(the tile's maximum - the running one); this lane's part of the tile's row sums
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) m_neg[n] = (m_ref[n] == -INFINITY) ? 0.f : -m_ref[n];
+    for (int n = 0; n < NQ; ++n) {
+      const float m = FINE ? m_tile[n] : m_ref[n];
+      m_neg[n] = (m == -INFINITY) ? 0.f : -m;
+      if (FINE) beta[n] = (m == -INFINITY) ? 0.f : fast_exp2(m - m_ref[n]);   // no visible key: nothing to add
+      ltile[n] = 0.f;
+    }
 
     // ---- probabilities of tile t and scores of tile t+1.  Sub-tile kt's scores are consumed by the exponentials
     // (and packed as the B operand of the second MFMA) before the MFMAs of tile t+1 overwrite the same registers,
@@ -718,7 +730,9 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
         float e[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) e[c] = fast_exp2(fmaf(st[n][kt][c], p.scale_log2e, m_neg[n]));   // -inf stays -inf -> 0
-        if (!WHOLE) lsum[n][0] += (e[0] + e[1]) + (e[2] + e[3]);   // this lane's keys, before they are rounded
+        const float sum = (e[0] + e[1]) + (e[2] + e[3]);   // this lane's keys, before they are rounded
+        if (FINE) ltile[n] += sum;
+        else if (!WHOLE) lsum[n][0] += sum;
         const uint32_t lo2 = pack_bf16x2(e[0], e[1]), hi2 = pack_bf16x2(e[2], e[3]);
         if (kt & 1) { pf[n][kt >> 1].u.z = lo2; pf[n][kt >> 1].u.w = hi2; }
         else { pf[n][kt >> 1].u.x = lo2; pf[n][kt >> 1].u.y = hi2; }
@@ -746,15 +760,34 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     for (int n = 0; n < NQ; ++n)
 #pragma unroll
       for (int j = 0; j < (WHOLE ? 2 : 0); ++j) lsum[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, pf[n][j].v, lsum[n], 0, 0, 0);
+    if (FINE)
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) lsum[n][0] = fmaf(beta[n], ltile[n], lsum[n][0]);
 #pragma unroll
     for (int n = 0; n < NQ; ++n) lmax[n] = lane_max(n);
+    f32x4 pv[2][NQ];   // (FINE) the tile's product for this d block and the one before, which is added meanwhile
+    auto add_pv = [&](int db) {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ot[n][db][c] = fmaf(beta[n], pv[db & 1][n][c], ot[n][db][c]);
+    };
 #pragma unroll
     for (int i = 0; i < NVS; ++i) {
+      if (FINE && i == 2)   // under the products' cover: nothing else stands between the barrier and the exponentials
 #pragma unroll
-      for (int n = 0; n < NQ; ++n) ot[n][i >> 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VW].f.v, pf[n][i & 1].v, ot[n][i >> 1], 0, 0, 0);
+        for (int n = 0; n < NQ; ++n) lmax[n] = rows4_max_raw(lmax[n]);
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        f32x4& o = FINE ? pv[(i >> 1) & 1][n] : ot[n][i >> 1];
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VW].f.v, pf[n][i & 1].v, FINE && (i & 1) == 0 ? zero : o, 0, 0, 0);
+      }
+      if (FINE && (i & 1) && i > 1) add_pv((i >> 1) - 1);
       if (i + VW < NVS) load_vfrag(vf[i % VW], ST, i + VW);
       __builtin_amdgcn_sched_barrier(0);   // keeps the read of step i + VW here, VW steps ahead of its use
     }
+    if (FINE) add_pv(DB - 1);
     store_held(ST, false);       // K(t) and V(t - 1) are free (see above); complete before the next barrier, which waits for LDS
     store_held(ST_VNEW, true);
   };
@@ -800,7 +833,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
 }
 
 template <int D, int NS>
-__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { ring_body<D, NS, 2, 8, true>(p); }
+__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { ring_body<D, NS, 2, 8, true, false, true>(p); }
 
 // 64 (4 waves), 80 (5), 96 (6) or, with two query blocks per wave, 128 rows per workgroup: two workgroups share a compute
 // unit (two-deep rings, 64 KiB) and cover each other's waits.  One workgroup as large as the row's tree reads every key once:
@@ -808,8 +841,8 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { 
 // the same or slower at every shape.  Against the kernels this replaced, in a step (us): 16 rows of 113-680 keys, 40-80
 // nodes: 46 -> 37; 10 rows of 107-1619 keys, 8 kv heads of 4: 54 -> 34; 8 rows of 140-680 keys: 25 -> 22; 2 rows of 4200 keys
 // and 256 nodes, keys in four parts: 65 -> 59 with the merge; 2 rows of 1289 keys, four parts: 23 -> 21.
-template <int D, int NS, int NQ, int NW, int OCC, bool DIRECT>
-__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false, DIRECT>(p); }
+template <int D, int NS, int NQ, int NW, int OCC, bool FINE, bool DIRECT>
+__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false, FINE, DIRECT>(p); }
 
 // ---------------------------------------------------------------------- bf16, few query rows
 // When a step has so few (row, kv head) pairs and keys that the chain of tiles of one workgroup is what takes the time,
@@ -1166,19 +1199,19 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
 }
 
 // 16 NQ NW query rows per workgroup, keys split p.n_split ways (partials, then the merge kernel)
-template <int D, int NQ, int NW, int OCC, bool DIRECT = true>
+template <int D, int NQ, int NW, int OCC, bool FINE, bool DIRECT>
 hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int NS = 2, RW = 16 * NQ * NW;
   constexpr int smem = 2 * NS * RingGeom<D>::TILE + CASCADE_MAX_TREE * (int)sizeof(int) + 2 * RW * (int)sizeof(unsigned long long);
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, FINE, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   {
     KernelTimer t(ctx, CASCADE_K_ATTN);
-    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, DIRECT>), grid, dim3(64 * NW), smem, ctx->stream, p);
+    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, FINE, DIRECT>), grid, dim3(64 * NW), smem, ctx->stream, p);
   }
   if (p.n_split > 1) {
     KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
@@ -1243,18 +1276,34 @@ float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_spli
 // shapes that exist with ordinary loads as well (the query-split kernel has no others)
 bool attn_shape_loads_any(int shape) { return shape == 0 || shape == 3 || shape == ATTN_QSPLIT; }
 
-template <int D>
-hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, bool direct, dim3 grid) {
-  if (!direct && shape != ATTN_QSPLIT)
-    return shape == 0 ? launch_rows_t<D, 1, 4, 2, false>(ctx, p, grid) : launch_rows_t<D, 1, 8, 2, false>(ctx, p, grid);
+// Whether a tile's exponentials refer to its own maximum (see ring_body).  On a full chip that costs time: it adds 1.2 us to a
+// step of 16 rows of 113-680 keys (153 us), 3.2 to one of 10 rows of 107-1619 keys with 8 kv heads of 4 (210), 4.4 to one of
+// 2 rows of 4200 keys and 256 nodes in four parts (290).  Fewer workgroups mostly wait (0.5 us of 161 at 2 rows of 1289 keys,
+// 0.9 of 94 at 4 rows of 240-560), and one running maximum rounds more coarsely there than the 2 to 16 groups of waves, each
+// with a maximum of its own, that such steps' keys were cut into before (2.16e-3 against 2.12e-3 and 2.17e-3 against 2.14e-3
+// from float64; 2.08e-3 so).  It is taken there, unless 256-row workgroups that fill the chip would have no more parts.
+bool attn_fine(const tree_attn_args* a, int group, int n_split, int n_cu) {
+  const long M = (long)a->max_nodes_per_tree * group, heads = (long)a->n_rows * a->n_kv_heads;
+  if (M <= 128) return a->head_dim == 64 || heads * ((M + 63) / 64) < 2 * n_cu;
+  return n_split < n_cu / (heads * ((M + 255) / 256));
+}
+
+template <int D, bool FINE>
+hipError_t launch_rows(cascade_ctx* ctx, const AttnParams& p, int shape, dim3 grid) {
   switch (shape) {
-    case 0: return launch_rows_t<D, 1, 4, 2>(ctx, p, grid);
-    case 1: return launch_rows_t<D, 1, 5, 3>(ctx, p, grid);
-    case 2: return launch_rows_t<D, 1, 6, 3>(ctx, p, grid);
-    case 3: return launch_rows_t<D, 2, 4, 2>(ctx, p, grid);
-    case ATTN_RING: return launch_ring_t<D>(ctx, p, grid);
-    default: return launch_qsplit_t<D>(ctx, p, grid);
+    case 0: return launch_rows_t<D, 1, 4, 2, FINE, true>(ctx, p, grid);
+    case 1: return launch_rows_t<D, 1, 5, 3, FINE, true>(ctx, p, grid);
+    case 2: return launch_rows_t<D, 1, 6, 3, FINE, true>(ctx, p, grid);
+    default: return launch_rows_t<D, 2, 4, 2, FINE, true>(ctx, p, grid);
   }
+}
+
+template <int D>
+hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, bool fine, bool direct, dim3 grid) {
+  if (shape == ATTN_RING) return launch_ring_t<D>(ctx, p, grid);
+  if (shape == ATTN_QSPLIT) return launch_qsplit_t<D>(ctx, p, grid);
+  if (!direct) return shape == 0 ? launch_rows_t<D, 1, 4, 2, true, false>(ctx, p, grid) : launch_rows_t<D, 1, 8, 2, true, false>(ctx, p, grid);
+  return fine ? launch_rows<D, true>(ctx, p, shape, grid) : launch_rows<D, false>(ctx, p, shape, grid);
 }
 
 hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
@@ -1284,5 +1333,6 @@ hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
   dim3 grid(p.n_split * p.n_sb, a->n_kv_heads, a->n_rows);
   // rows of the batch that one round of workgroups over the compute units covers (see row_by_work_rank)
   p.round_rows = ctx->n_cu / (int)(grid.x * grid.y);
-  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, direct, grid) : launch_bf16_t<64>(ctx, p, shape, direct, grid);
+  const bool fine = attn_fine(a, p.group, p.n_split, ctx->n_cu);
+  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, fine, direct, grid) : launch_bf16_t<64>(ctx, p, shape, fine, direct, grid);
 }

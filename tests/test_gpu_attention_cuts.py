@@ -5,7 +5,14 @@ around the 64-key tiles; every output against float64.
 Bound per output, with m = sum p |v|: rounding to bf16 (8 significant bits, to nearest) moves a value by at most u = 2^-8 of
 it.  Probabilities are rounded before the second product (u m), their sum may be taken after that rounding (u m), the output
 is rounded (u m), and a score's float32 error d moves every probability by at most 2 d.  The log-sum-exp carries d, the
-rounded sum (u) and L 2^-24."""
+rounded sum (u) and L 2^-24.
+
+That bound would not see probabilities rounded more coarsely, so the 2-norm distance from float64 is compared with that of a
+copy of the finest rounding: every tile of 64 keys refers to its own maximum, probabilities are rounded once, the output is
+rounded once.  float32 instead of float64 before a rounding flips 2^-24 / 2^-9 of them, 3e-5, so both distances agree to 3e-3
+where the kernel rounds like that (steps of few workgroups, head_dim 64, and the query split up to eight tiles).  A reference
+that is not the tile's spreads the mantissas of the heavy probabilities, at worst evenly over an octave: sqrt(2) times the
+distance of a copy without rounded probabilities, 1.17 times this one's; a running maximum measures 1.03 to 1.08."""
 import numpy as np
 import pytest
 import torch
@@ -33,7 +40,8 @@ CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths
 @pytest.mark.parametrize("name", CASES)
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_attention_cuts(name, head_dim):
-    _check(head_dim, *CASES[name])
+    full_chip = name in ("256 rows", "128 rows, keys in parts") or (head_dim == 128 and name in ("80 rows", "96 rows", "128 rows"))
+    _check(head_dim, *CASES[name], further=(1.17 if name == "256 rows" else 1.08) if full_chip else 1.003)
 
 
 # buffers 2, 8 and 14 bytes past a 16-byte boundary, and positions further apart than a 32-bit offset of a tile reaches:
@@ -60,7 +68,7 @@ def test_attention_of_positions_far_apart(sizes, prefix, head_dim):
     _check(head_dim, 2, 1, sizes, prefix, pos_stride=(1 << 25) + 8)
 
 
-def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None):
+def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None, further=None):
     print(f"[attention cuts] heads {kv_heads} x {group}, trees {sizes}, prefixes {prefix}, head_dim {head_dim}, shift {shift}", flush=True)
     rng = np.random.default_rng(head_dim + len(sizes))
     gen = torch.Generator(device="cuda")
@@ -90,6 +98,7 @@ def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None):
                              k_cache=kc, v_cache=vc, out=out, lse=lse, max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix))
     assert ctx.device_status() == binding.OK
     scale = head_dim ** -0.5
+    far = far_copy = 0.0
     for s in range(S):
         lo, hi, T, P = int(off[s]), int(off[s + 1]), sizes[s], prefix[s]
         see = torch.zeros(T, P + T, dtype=torch.bool)
@@ -111,3 +120,11 @@ def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None):
                 bound = (3 * 2.0 ** -8 + 2 * d) * (p @ v.abs()) + 1e-30
                 assert torch.all((out[lo:hi, h].double() - p @ v).abs() <= bound), (s, h)
                 assert torch.all((lse[lo:hi, h].double() - rl).abs() <= 2 * d + 2.0 ** -8 + (P + T) * 2.0 ** -24), (s, h)
+                if further:
+                    num = torch.zeros_like(p @ v)
+                    for first, end in [(i, min(i + 64, P)) for i in range(0, P, 64)] + [(P + i, min(P + i + 64, P + T)) for i in range(0, T, 64)]:
+                        m = z[:, first:end].max(1, keepdim=True).values.clamp(min=-1e30)     # a tile without visible keys adds nothing
+                        num += torch.exp(m - rl[:, None]) * (torch.exp(z[:, first:end] - m).bfloat16().double() @ v[first:end])
+                    far += float(((out[lo:hi, h].double() - p @ v) ** 2).sum())
+                    far_copy += float(((num.bfloat16().double() - p @ v) ** 2).sum())
+    assert not further or far ** 0.5 <= further * far_copy ** 0.5, (far ** 0.5 / max(far_copy, 1e-30) ** 0.5)
