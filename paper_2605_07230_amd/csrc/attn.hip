@@ -1249,6 +1249,13 @@ constexpr int ATTN_N_SHAPES = 6, ATTN_RING = 4, ATTN_QSPLIT = 5;
 constexpr AttnShape ATTN_SHAPES[ATTN_N_SHAPES] = {{64, 1.0f, 1.0f, 1.5f, 3.0f, 2}, {80, 1.0f, 1.15f, 1.9f, 3.0f, 2}, {96, 1.0f, 1.2f, 2.1f, 3.0f, 2},
                                                   {128, 1.2f, 1.45f, 2.5f, 2.5f, 2}, {256, 1.7f, 2.3f, 2.3f, 2.3f, 1}, {16, 0.75f, 0.75f, 0.75f, 0.75f, 1}};
 
+// head_dim 64: the tile's cost against that at 128, shape by shape (half the bytes and products, the same exponentials and
+// waits).  Fitted, with the fixed part, to every cut of 20 steps (1-16 rows, 90-4200 keys, 16-256 nodes, 1 or 4 heads per kv
+// head, cold caches): the cut chosen is 2 % behind the fastest in the mean, 5 % with one factor of 0.65.  2 rows x 1289 keys,
+// 60 nodes: query split 16.9 us, 64 rows in four splits 18.9; 4 x 2000 keys, 256 nodes, 8 kv heads of 4: 64 rows 47.0, 128 rows
+// 51.6; 2 x 2400 keys, 128 nodes: 64 rows in four splits 28.3, 128 rows in eight 33.4.
+constexpr float ATTN_NARROW[ATTN_N_SHAPES] = {0.75f, 0.75f, 0.75f, 0.83f, 0.62f, 0.73f};
+
 // Estimated time of a step's attention, us.  Against measured steps (32 heads, head_dim 128): 2 rows x 312 keys, 60 nodes:
 // query split 10.5 (10.3), 64 rows 13.4 (13.4); 2 x 1289 keys: query split 22.5 (23.1), 64 rows whole 29 (29.5) and in four
 // splits 18 (20.7); 2 x 4200 keys, 256 nodes: 64 rows 77 (79), 128 rows in four splits 61 (59); 8 such rows: 256 rows
@@ -1258,7 +1265,8 @@ float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_spli
   const AttnShape& sh = ATTN_SHAPES[shape];
   const int M = a->max_nodes_per_tree * group, n_sb = (M + sh.rows - 1) / sh.rows;
   const int tiles = (a->max_prefix_len + KT - 1) / KT + (a->max_nodes_per_tree + KT - 1) / KT;
-  const float d = a->head_dim == 128 ? 1.f : 0.65f;
+  const bool narrow = a->head_dim == 64;
+  const float d = narrow ? ATTN_NARROW[shape] : 1.f;
   // query blocks that hold rows: ragged trees leave some of the launched ones empty
   float blocks = (float)a->n_rows * n_sb;
   if (n_sb > 1) blocks = fminf(blocks, (float)a->n_nodes_total * group / sh.rows + 0.5f * a->n_rows);
@@ -1267,7 +1275,7 @@ float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_spli
   const float c2 = sh.c2_hbm + (sh.c2 - sh.c2_hbm) * fminf(blocks / a->n_rows - 1.f, 1.f);
   const float per_tile = x <= 1.f ? sh.c0 + (sh.c1 - sh.c0) * x
                        : (sh.per_cu == 1 ? sh.c1 * ceilf(x) : (x <= 2.f ? sh.c1 + (c2 - sh.c1) * (x - 1.f) : c2 * 0.5f * x));
-  float us = 7.4f + (float)((tiles + n_split - 1) / n_split) * per_tile * d;
+  float us = (narrow ? 9.3f : 7.4f) + (float)((tiles + n_split - 1) / n_split) * per_tile * d;
   if (n_split > 1)   // a second launch, and partials written and read (mostly through the caches)
     us += 3.8f + (float)n_split * a->n_nodes_total * a->n_heads * (a->head_dim + 2) * 4.f / 7e6f;
   return us;
