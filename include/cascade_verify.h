@@ -167,6 +167,11 @@ typedef struct {
   float* lse;                 /* nullable */
 } tree_attn_args;
 int tree_verify_attn(cascade_ctx* ctx, const tree_attn_args* args);
+/* How a bf16 call with these (valid, non-empty) arguments is cut, for benchmarks and tests: HOST only, nothing
+ * is enqueued and pointers are looked at for alignment alone.  query_rows: rows of a workgroup (64, 80, 96, 128,
+ * 256; 16: the query rows are split over workgroups and the keys over waves); key_parts: parts that the keys are
+ * cut in.  ctx NULL: as on 256 compute units with all the workspace that a cut could use.  f32: CASCADE_EDTYPE. */
+int cascade_attention_cut(const cascade_ctx* ctx, const tree_attn_args* args, int32_t* query_rows, int32_t* key_parts);
 
 /* tree_verify_attn_static — tree_verify_attn for callers that cannot allocate device memory and so
  * cannot hold a cascade_ctx: code under HIP graph capture, tight serving loops, harnesses that
@@ -241,6 +246,10 @@ typedef struct {
   float *row_max, *row_thr, *row_lse;
 } lmhead_args;
 int lmhead_softmax_cfg(cascade_ctx* ctx, const lmhead_args* args);
+/* The tiles of a bf16 call's projection, likewise: 0 to 4 of the kernel that reads rows as they lie (64 x 64,
+ * 128 x 64, 64 x 256, 128 x 128, 256 x 128 rows x columns), 5 and 6 of the one that takes them packed (128 x 256,
+ * 256 x 256), -1 for ordinary loads; columns from rest_column on, if that is below vocab, run in rest_tile. */
+int cascade_projection_tiles(const cascade_ctx* ctx, const lmhead_args* args, int32_t* tile, int32_t* rest_tile, int32_t* rest_column);
 
 /* ---------------------------------------------------------------------------------------------
  * cascade_accept — what the relaxed acceptance rule needs at every non-root node a with parent p

@@ -1,6 +1,7 @@
 // C ABI of the tree-verification library: context, argument validation, dispatch.
 // Validation uses host-visible values only and happens before anything is enqueued.
 #include <math.h>
+#include <stdint.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -181,6 +182,16 @@ int tree_verify_attn(cascade_ctx* ctx, const tree_attn_args* a) {
   return e == hipSuccess ? CASCADE_OK : hip_fail(e);
 }
 
+int cascade_attention_cut(const cascade_ctx* ctx, const tree_attn_args* a, int32_t* query_rows, int32_t* key_parts) {
+  if (!a || !query_rows || !key_parts) return CASCADE_EINVAL;
+  if (a->dtype != CASCADE_BF16) return CASCADE_EDTYPE;
+  if (a->n_rows <= 0 || a->n_nodes_total <= 0 || a->max_nodes_per_tree <= 0 || a->max_prefix_len < 0 || a->n_kv_heads <= 0 ||
+      a->n_heads < a->n_kv_heads || (a->head_dim != 64 && a->head_dim != 128))
+    return CASCADE_EINVAL;
+  plan_tree_attn_bf16(a, ctx ? ctx->n_cu : 256, ctx ? ctx->attn_ws_bytes : SIZE_MAX, query_rows, key_parts);
+  return CASCADE_OK;
+}
+
 // --------------------------------------------------------------------------------------------
 // tree_verify_attn_static: the same attention for callers that cannot allocate.  Everything the
 // kernels need beyond inputs and outputs (the precondition flag word and the split-KV partials)
@@ -292,6 +303,14 @@ int lmhead_softmax_cfg(cascade_ctx* ctx, const lmhead_args* a) {
   if (e != hipSuccess) return hip_fail(e);
   e = launch_row_stats(ctx, a);
   return e == hipSuccess ? CASCADE_OK : hip_fail(e);
+}
+
+int cascade_projection_tiles(const cascade_ctx* ctx, const lmhead_args* a, int32_t* tile, int32_t* rest_tile, int32_t* rest_column) {
+  if (!a || !tile || !rest_tile || !rest_column) return CASCADE_EINVAL;
+  if (a->dtype != CASCADE_BF16) return CASCADE_EDTYPE;
+  if (a->n_nodes <= 0 || a->hidden <= 0 || a->vocab <= 0) return CASCADE_EINVAL;
+  plan_lmhead_bf16(a, ctx ? ctx->n_cu : 256, tile, rest_tile, rest_column);
+  return CASCADE_OK;
 }
 
 int cascade_pack_lmhead_w(cascade_ctx* ctx, const void* w, int32_t vocab, int32_t hidden, void* w_packed) {

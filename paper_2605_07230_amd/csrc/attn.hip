@@ -13,7 +13,7 @@
 // (ring_body: tiles in an LDS ring filled by LDS-direct loads) serves 64 to 256 query rows per workgroup,
 // the smaller ones with the keys split across workgroups where that fills the chip (partials to the
 // workspace, a small merge kernel); the smallest steps split the query rows over workgroups instead and
-// the keys over waves.  launch_tree_attn_bf16 chooses by estimated time.
+// the keys over waves.  attn_choose chooses by estimated time.
 //
 // f32 path: one kernel on the f32 matrix instructions, 16 query rows per workgroup, used by the small fp32 configuration.
 #include <type_traits>
@@ -1314,26 +1314,44 @@ hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, bool 
   return fine ? launch_rows<D, true>(ctx, p, shape, grid) : launch_rows<D, false>(ctx, p, shape, grid);
 }
 
-hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
-  AttnParams p = make_params(ctx, a);
-  const int M = a->max_nodes_per_tree * p.group;   // query rows per (row, kv head)
+struct AttnCut {
+  int shape, n_split;
+  bool fine, direct;
+};
+
+AttnCut attn_choose(const tree_attn_args* a, int n_cu, size_t ws_bytes) {
+  const int group = a->n_heads / a->n_kv_heads, M = a->max_nodes_per_tree * group;   // query rows per (row, kv head)
   const int n_tiles = (a->max_prefix_len + KT - 1) / KT + (a->max_nodes_per_tree + KT - 1) / KT;
-  const size_t per_split = (size_t)p.n_rows_total * (a->head_dim + 2) * sizeof(float);
+  const size_t per_split = (size_t)a->n_nodes_total * a->n_heads * (a->head_dim + 2) * sizeof(float);
+  AttnCut cut = {0, 1, false, true};
   // keys and values are fetched by LDS-direct loads where their addresses allow it (strides are multiples of 16 bytes)
-  const bool direct = (((uintptr_t)a->k_tree | (uintptr_t)a->v_tree | (uintptr_t)a->k_cache | (uintptr_t)a->v_cache) & 15) == 0 &&
-                      a->cache_stride_pos <= (int64_t)1 << 25;
-  int shape = 0;
+  cut.direct = (((uintptr_t)a->k_tree | (uintptr_t)a->v_tree | (uintptr_t)a->k_cache | (uintptr_t)a->v_cache) & 15) == 0 &&
+               a->cache_stride_pos <= (int64_t)1 << 25;
   float best = INFINITY;
   for (int i = 0; i < ATTN_N_SHAPES; ++i) {
-    if (!direct && !attn_shape_loads_any(i)) continue;
+    if (!cut.direct && !attn_shape_loads_any(i)) continue;
     if (i == ATTN_QSPLIT && (M > 128 || a->max_nodes_per_tree > 128)) continue;   // its LDS holds trees of 128 nodes
     for (int n = 1; n <= 16 && n <= n_tiles; n = n < 4 ? n + 1 : n * 2) {
-      if (n > 1 && (i >= ATTN_RING || per_split * n > ctx->attn_ws_bytes)) break;   // these take whole rows of keys
-      const float us = attn_estimate_us(i, a, p.group, n, ctx->n_cu);
-      if (us < best) { best = us; shape = i; p.n_split = n; }
+      if (n > 1 && (i >= ATTN_RING || per_split * n > ws_bytes)) break;   // these take whole rows of keys
+      const float us = attn_estimate_us(i, a, group, n, n_cu);
+      if (us < best) { best = us; cut.shape = i; cut.n_split = n; }
     }
   }
-  p.n_sb = (M + ATTN_SHAPES[shape].rows - 1) / ATTN_SHAPES[shape].rows;
+  cut.fine = attn_fine(a, group, cut.n_split, n_cu);
+  return cut;
+}
+
+void plan_tree_attn_bf16(const tree_attn_args* a, int n_cu, size_t ws_bytes, int32_t* query_rows, int32_t* key_parts) {
+  const AttnCut cut = attn_choose(a, n_cu, ws_bytes);
+  *query_rows = ATTN_SHAPES[cut.shape].rows;
+  *key_parts = cut.n_split;
+}
+
+hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
+  AttnParams p = make_params(ctx, a);
+  const AttnCut cut = attn_choose(a, ctx->n_cu, ctx->attn_ws_bytes);
+  p.n_split = cut.n_split;
+  p.n_sb = (a->max_nodes_per_tree * p.group + ATTN_SHAPES[cut.shape].rows - 1) / ATTN_SHAPES[cut.shape].rows;
   if (p.n_split > 1) {
     p.ws_o = (float*)ctx->attn_ws;
     p.ws_ml = (float*)(ctx->attn_ws + (size_t)p.n_split * p.n_rows_total * a->head_dim * sizeof(float));
@@ -1341,6 +1359,6 @@ hipError_t launch_tree_attn_bf16(cascade_ctx* ctx, const tree_attn_args* a) {
   dim3 grid(p.n_split * p.n_sb, a->n_kv_heads, a->n_rows);
   // rows of the batch that one round of workgroups over the compute units covers (see row_by_work_rank)
   p.round_rows = ctx->n_cu / (int)(grid.x * grid.y);
-  const bool fine = attn_fine(a, p.group, p.n_split, ctx->n_cu);
-  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, shape, fine, direct, grid) : launch_bf16_t<64>(ctx, p, shape, fine, direct, grid);
+  return a->head_dim == 128 ? launch_bf16_t<128>(ctx, p, cut.shape, cut.fine, cut.direct, grid)
+                            : launch_bf16_t<64>(ctx, p, cut.shape, cut.fine, cut.direct, grid);
 }

@@ -992,6 +992,21 @@ LmPlan lm_plan(const lmhead_args* a, bool packed_w, bool premix, bool cfg, int n
   return best;
 }
 
+// guidance mixed into the hidden rows in front of the projection: from there on a plain projection of n_nodes rows
+bool lm_premix(const lmhead_args* a) {
+  return a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && a->w_layout == CASCADE_W_PACKED32;
+}
+
+LmPlan lm_choose(const lmhead_args* a, int n_cu) {
+  const bool premix = lm_premix(a), cfg = a->h_uncond != nullptr && !premix;
+  LmPlan plan = lm_plan(a, a->w_layout == CASCADE_W_PACKED32, premix, cfg, n_cu);
+  // (mixed and packed rows lie in the workspace; both passes that write them read the caller's rows with ordinary loads)
+  const bool rows_direct = !premix && (plan.main < LM_RING_TILES || plan.rest < LM_RING_TILES);
+  if (((uintptr_t)a->w | (rows_direct ? (uintptr_t)a->h_cond | (uintptr_t)(cfg ? a->h_uncond : nullptr) : 0)) & 15)
+    plan.main = plan.rest = LM_UNALIGNED, plan.split = a->vocab;
+  return plan;
+}
+
 // one launch over columns [p.col0, p.col0 + n_cols)
 hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cfg, bool packed_w, int n_cols) {
   if (tile < LM_RING_TILES) {
@@ -1014,17 +1029,18 @@ hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cf
   return hipGetLastError();
 }
 
+void plan_lmhead_bf16(const lmhead_args* a, int n_cu, int32_t* tile, int32_t* rest_tile, int32_t* rest_column) {
+  const LmPlan plan = lm_choose(a, n_cu);
+  *tile = plan.main;
+  *rest_tile = plan.rest;
+  *rest_column = plan.split;
+}
+
 hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a) {
   LmParams p = make_params(a);
   const bool packed_w = a->w_layout == CASCADE_W_PACKED32;
-  // guidance mixed into the hidden rows in front of the projection: from here on a plain projection of n_nodes rows
-  const bool premix = a->h_uncond != nullptr && a->cfg_mix == CASCADE_CFG_MIX_HIDDEN && packed_w;
-  const bool cfg = a->h_uncond != nullptr && !premix;
-  LmPlan plan = lm_plan(a, packed_w, premix, cfg, ctx->n_cu);
-  // (mixed and packed rows lie in the workspace; both passes that write them read the caller's rows with ordinary loads)
-  const bool rows_direct = !premix && (plan.main < LM_RING_TILES || plan.rest < LM_RING_TILES);
-  if (((uintptr_t)a->w | (rows_direct ? (uintptr_t)a->h_cond | (uintptr_t)(cfg ? a->h_uncond : nullptr) : 0)) & 15)
-    plan.main = plan.rest = LM_UNALIGNED, plan.split = a->vocab;
+  const bool premix = lm_premix(a), cfg = a->h_uncond != nullptr && !premix;
+  const LmPlan plan = lm_choose(a, ctx->n_cu);
   uint4* hc = (uint4*)ctx->hpack_ws;
   if (plan.main < LM_RING_TILES) {
     if (premix) {

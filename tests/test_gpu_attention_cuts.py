@@ -22,7 +22,7 @@ from paper_2605_07230_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths
+CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths (cuts: CUTS, below)
     "64 rows, keys in 16 parts": (2, 1, [60, 41, 64, 17, 55], [1500, 37, 700, 1100, 260]),
     "64 rows, whole": (32, 1, [60, 41, 64, 17, 55], [800, 0, 64, 513, 300]),
     "64 rows, grouped heads, ragged blocks": (2, 3, [100, 33, 64], [1900, 130, 0]),
@@ -31,16 +31,25 @@ CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths
     "128 rows": (32, 1, [100, 128, 97, 33, 64, 63, 79, 16, 1, 2, 127, 65, 17, 111, 20, 7],
                  [90, 20, 64, 0, 133, 128, 1, 65, 63, 10, 5, 70, 30, 100, 40, 200]),
     "128 rows, keys in parts": (32, 1, [256, 130], [4000, 64]),
+    "128 rows, long keys in parts": (32, 1, [256, 240], [4200, 4100]),
     "256 rows": (32, 1, [256, 255, 130, 200, 140, 199, 250, 256], [70, 1, 0, 64, 65, 130, 200, 31]),
     "query split": (2, 1, [20, 17], [400, 63]),
     "query split, one node": (1, 1, [1], [0]),
+}
+
+# (query rows per workgroup, parts of the keys) that 256 compute units choose, at head_dim 64 and 128
+CUTS = {
+    "64 rows, keys in 16 parts": ((64, 16), (64, 16)), "64 rows, whole": ((64, 1), (64, 1)),
+    "64 rows, grouped heads, ragged blocks": ((64, 16), (64, 16)), "80 rows": ((80, 1), (80, 1)), "96 rows": ((96, 1), (96, 1)),
+    "128 rows": ((128, 1), (128, 1)), "128 rows, keys in parts": ((96, 4), (128, 4)), "128 rows, long keys in parts": ((128, 4), (128, 4)),
+    "256 rows": ((256, 1), (256, 1)), "query split": ((16, 1), (16, 1)), "query split, one node": ((16, 1), (16, 1)),
 }
 
 
 @pytest.mark.parametrize("name", CASES)
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_attention_cuts(name, head_dim):
-    full_chip = name in ("256 rows", "128 rows, keys in parts") or (head_dim == 128 and name in ("80 rows", "96 rows", "128 rows"))
+    full_chip = name in ("256 rows", "128 rows, keys in parts", "128 rows, long keys in parts") or (head_dim == 128 and name in ("80 rows", "96 rows", "128 rows"))
     _check(head_dim, *CASES[name], further=(1.17 if name == "256 rows" else 1.08) if full_chip else 1.003)
 
 
@@ -93,6 +102,10 @@ def _check(head_dim, kv_heads, group, sizes, prefix, shift=0, pos_stride=None, f
         kc, vc = spread(kc), spread(vc)
     out, lse = torch.full_like(q, float("nan")), torch.full((n, heads), float("nan"), device="cuda")
     ctx = binding.Context(max_rows=S, max_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix=cap, n_heads=heads, head_dim=head_dim, hidden=128, vocab=64)
+    if (kv_heads, group, sizes, prefix) in CASES.values() and not shift:
+        name = next(k for k, c in CASES.items() if c == (kv_heads, group, sizes, prefix))
+        assert binding.attention_cut(n_rows=S, n_nodes_total=n, max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix), n_heads=heads,
+                                     n_kv_heads=kv_heads, head_dim=head_dim, ctx=ctx) == CUTS[name][head_dim == 128]
     dev = lambda x: torch.from_numpy(np.asarray(x, np.int32)).cuda()  # noqa: E731
     binding.tree_verify_attn(ctx, node_off=dev(off), parent=dev(np.concatenate(trees)), prefix_len=dev(prefix), q=q, k_tree=kt, v_tree=vt,
                              k_cache=kc, v_cache=vc, out=out, lse=lse, max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix))

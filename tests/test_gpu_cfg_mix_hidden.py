@@ -56,8 +56,8 @@ def test_streaming_projection_with_mixed_rows(index, seed):
 
 @pytest.mark.parametrize("hidden,sizes", [(128, [100, 97, 63]), (384, [130, 128, 1]), (640, [200, 200, 130])])
 def test_half_tiles_with_mixed_rows_every_logit(hidden, sizes):
-    """260 / 259 / 530 mixed rows in 128-row tiles (the last one with 4, 3 and 18 rows) at hidden sizes of one,
-    three and five ring rounds; every logit against the definition and against the single product."""
+    """260 / 259 / 530 mixed rows at short hidden sizes and a small vocabulary; every logit against the definition and
+    against the single product.  (Steps this small take the 64 x 64 tile; the large tiles have their own tests.)"""
     rng = np.random.default_rng(21)
     trees = [wl.grow_tree(rng, n, 6, 8) if n > 1 else np.array([-1], np.int32) for n in sizes]
     inp = wl.make_inputs(seed=21, name="edge", dtype="bf16", n_prompts=3, cfg=True, n_heads=4, n_kv_heads=2, head_dim=64,
@@ -71,8 +71,8 @@ def test_half_tiles_with_mixed_rows_every_logit(hidden, sizes):
 
 @pytest.mark.parametrize("seed", range(6))
 def test_tiled_projection_random_shapes_both_mixes(seed):
-    """Random row counts (257-700 nodes in 3-6 prompts), hidden sizes and vocabularies through both guidance
-    mixes: guidance-pair tiles, plain 256-row tiles and 128-row tiles with ragged last tiles; every logit compared."""
+    """Random row counts (257-700 nodes in 3-6 prompts), short hidden sizes and small vocabularies through both guidance
+    mixes, with ragged last tiles; every logit compared."""
     rng = np.random.default_rng(100 + seed)
     n_prompts = int(rng.integers(3, 7))
     total = int(rng.integers(257, 701))

@@ -159,8 +159,8 @@ def test_temperature_and_no_guidance(packed):
 
 @pytest.mark.parametrize("hidden,cfg", [(128, True), (384, True), (640, False)])
 def test_tiled_projection_short_hidden_and_ragged_row_tiles(hidden, cfg):
-    """The LDS-tiled projection (>= 512 rows) at hidden sizes of one, three and five ring rounds,
-    with a last row tile that is almost empty; every logit is compared."""
+    """520 and 530 rows at short hidden sizes and a small vocabulary; every logit is compared.  (Steps this small take the
+    64 x 64 tile; the large tiles have their own tests.)"""
     rng = np.random.default_rng(11)
     sizes = [100, 97, 63] if cfg else [200, 200, 130]          # 260 nodes x 2 rows / 530 rows: three row tiles
     trees = [wl.grow_tree(rng, n, 6, 8) for n in sizes]

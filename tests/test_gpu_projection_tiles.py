@@ -11,14 +11,15 @@ from paper_2605_07230_amd import binding
 
 pytestmark = pytest.mark.gpu
 
-# rows of the product, vocabulary, hidden: the tile that 256 compute units choose (see launch_lmhead_bf16)
+# rows of the product, vocabulary, hidden: the tile that 256 compute units choose for plain rows (mixed rows and row-major
+# weights may take a neighbour; tests/test_dispatch.py counts what these lists reach)
 SHAPES = [
     (1, 64, 128), (33, 16384, 128), (64, 16320, 384),          # 64 x 64
     (65, 16384, 256), (127, 16320, 640),                       # 128 x 64
     (3, 65536, 256), (64, 33088, 384), (120, 65472, 128),      # 64 x 256, the last column tile ragged
     (129, 16384, 256), (230, 16320, 384),                      # 128 x 128
-    (257, 16384, 256), (490, 16448, 128), (513, 33088, 256),   # 256 x 128 / 128 x 256 / 256 x 256
-    (700, 33088, 256), (256, 65472, 128),
+    (257, 16384, 256), (700, 33088, 256), (256, 65472, 128),   # 256 x 128 (mixed rows: 128 x 256)
+    (490, 16448, 128), (513, 33088, 256),                      # 128 x 128 again: whole rounds
 ]
 
 
@@ -29,16 +30,31 @@ def test_projection_tiles(rows, vocab, hidden, mode, packed):
     _check(max(1, rows // 2) if mode == "pairs" else rows, vocab, hidden, mode, packed)
 
 
-# columns cut into whole rounds of one tile and a rest in another (tiles by number, as the launcher counts them)
-@pytest.mark.parametrize("n,vocab,mode,packed", [
-    (65, 33024, "plain", True), (200, 33024, "plain", True), (257, 33088, "plain", True), (461, 24000, "plain", True),   # 3+0, 4+0, 5+2, 4+3
-    (600, 33024, "plain", True), (343, 24000, "plain", True),                                                           # 6+5, 5+0
-    (257, 33088, "mixed", True), (200, 41024, "mixed", True), (600, 41024, "mixed", True), (257, 33024, "mixed", True), # 5+2, 5+3, 5+1, 6+0
-    (65, 33024, "pairs", True), (343, 24000, "pairs", True), (300, 33024, "pairs", True), (461, 33024, "pairs", True),  # 2+3, 4+1, 6+3, 6+0
-    (65, 33024, "pairs", False), (100, 33024, "pairs", False), (200, 41024, "pairs", False),                            # 2+3, 4+0, 4+2
+# the large tiles, with one row in the last of them, at hidden sizes of one, three and five rounds of their rings (and the
+# 256 x 128 ring tile at as many): nodes, vocabulary, hidden, mode, tile
+@pytest.mark.parametrize("n,vocab,hidden,mode,tile", [
+    (129, 24576, 128, "plain", 4), (129, 24576, 384, "plain", 4), (129, 24576, 640, "plain", 4),
+    (257, 16448, 128, "mixed", 5), (257, 16448, 384, "mixed", 5), (257, 16448, 640, "mixed", 5),
+    (257, 24576, 128, "mixed", 6), (257, 24576, 384, "mixed", 6), (257, 24576, 640, "mixed", 6), (257, 65536, 384, "plain", 6),
+    (513, 49152, 128, "pairs", 6), (257, 33024, 384, "pairs", 6), (257, 33024, 640, "pairs", 6),
 ])
-def test_projection_split_columns(n, vocab, mode, packed):
-    _check(n, vocab, 2048, mode, packed)
+def test_large_tiles_short_hidden(n, vocab, hidden, mode, tile):
+    _check(n, vocab, hidden, mode, True, tiles=(tile, tile))
+
+
+# columns cut into whole rounds of one tile and a rest in another (tiles by number, as the launcher counts them)
+SPLITS = [
+    (65, 33024, "plain", True, (3, 0)), (200, 33024, "plain", True, (4, 0)), (257, 33088, "plain", True, (5, 2)), (461, 24000, "plain", True, (4, 3)),
+    (600, 33024, "plain", True, (6, 5)), (343, 24000, "plain", True, (5, 0)),
+    (257, 33088, "mixed", True, (5, 2)), (200, 41024, "mixed", True, (5, 3)), (600, 41024, "mixed", True, (5, 1)), (257, 33024, "mixed", True, (6, 0)),
+    (65, 33024, "pairs", True, (2, 3)), (343, 24000, "pairs", True, (4, 1)), (300, 33024, "pairs", True, (6, 3)), (461, 33024, "pairs", True, (6, 0)),
+    (65, 33024, "pairs", False, (2, 3)), (100, 33024, "pairs", False, (4, 0)), (200, 41024, "pairs", False, (4, 2)),
+]
+
+
+@pytest.mark.parametrize("n,vocab,mode,packed,tiles", SPLITS)
+def test_projection_split_columns(n, vocab, mode, packed, tiles):
+    _check(n, vocab, 2048, mode, packed, tiles=tiles)
 
 
 # buffers that start 2, 8 and 14 bytes past a 16-byte boundary: sizes that take one ring tile, two, packed rows, and both
@@ -55,7 +71,7 @@ def _shifted(x, elements):
     return y.copy_(x)
 
 
-def _check(n, vocab, hidden, mode, packed, shift_h=0, shift_w=0):
+def _check(n, vocab, hidden, mode, packed, shift_h=0, shift_w=0, tiles=None):
     print(f"[projection] nodes={n} vocab={vocab} hidden={hidden} {mode} packed={packed} shift={shift_h},{shift_w}", flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n * 131 + vocab + hidden)
@@ -63,6 +79,11 @@ def _check(n, vocab, hidden, mode, packed, shift_h=0, shift_w=0):
     c = torch.randn(n, hidden, device="cuda", generator=gen).bfloat16()
     u = (c.float() + 0.5 * torch.randn(n, hidden, device="cuda", generator=gen)).bfloat16()
     ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=hidden, vocab=vocab)
+    if tiles:
+        got = binding.projection_tiles(n_nodes=n, hidden=hidden, vocab=vocab, guided=mode != "plain", ctx=ctx,
+                                       w_layout=binding.W_PACKED32 if packed else binding.W_ROWMAJOR,
+                                       cfg_mix=binding.CFG_MIX_HIDDEN if mode == "mixed" else binding.CFG_MIX_LOGITS)
+        assert got[:2] == tiles and (got[2] == vocab) == (tiles[0] == tiles[1])
     logits = torch.full((n, vocab), float("nan"), device="cuda")
     stats = [torch.empty(n, device="cuda") for _ in range(3)]
     s, temp = 3.0, 0.8
@@ -86,8 +107,8 @@ def _check(n, vocab, hidden, mode, packed, shift_h=0, shift_w=0):
 
 
 # one size per tile; a 256 x 256 tile (more rows) sums in one chain
-@pytest.mark.parametrize("rows,vocab", [(60, 16384), (120, 16384), (60, 65536), (230, 16384), (250, 65536), (461, 16384)])
-def test_projection_sums_in_four_chains(rows, vocab):
+@pytest.mark.parametrize("rows,vocab,tile", [(60, 16384, 0), (120, 16384, 1), (60, 65536, 2), (230, 16384, 3), (250, 32768, 4), (250, 65536, 5)])
+def test_projection_sums_in_four_chains(rows, vocab, tile):
     """2-norm distance from float64.  A chain of n accumulations whose partial sums grow as a random walk rounds with an
     rms of at most 2^-24 / sqrt(3) of each partial sum: sqrt(n / 2) / sqrt(3) 2^-24 of the result, n = K / 16 / 4; an
     undivided chain of the same terms measures twice that."""
@@ -98,6 +119,7 @@ def test_projection_sums_in_four_chains(rows, vocab):
     w = (0.02 * torch.randn(vocab, hidden, device="cuda", generator=gen)).bfloat16()
     c = torch.randn(rows, hidden, device="cuda", generator=gen).bfloat16()
     ctx = binding.Context(max_rows=1, max_nodes_total=rows, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=hidden, vocab=vocab)
+    assert binding.projection_tiles(n_nodes=rows, hidden=hidden, vocab=vocab, guided=False, w_layout=binding.W_PACKED32, ctx=ctx) == (tile, tile, vocab)
     logits = torch.empty(rows, vocab, device="cuda")
     stats = [torch.empty(rows, device="cuda") for _ in range(3)]
     binding.lmhead_softmax_cfg(ctx, h_cond=c, h_uncond=None, w=binding.cascade_pack_lmhead_w(ctx, w), w_layout=binding.W_PACKED32, cfg_scale=1.0,
