@@ -284,7 +284,7 @@ def measure_workload(index: int, steps: int, warmup: int, args, hbm_meas: float,
     # second pass over the same steps with the dispatch's own begin / end timestamps on every launch
     # (HIP events on the library's stream, handed to the launch itself)
     ds.ctx.set_kernel_timing(True)
-    n_timed = min(steps, 2000)
+    n_timed = min(steps, 1000)     # (2048 launches of a kernel are kept; a projection cut at a column is two per step)
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     for i in range(n_timed):
@@ -295,40 +295,42 @@ def measure_workload(index: int, steps: int, warmup: int, args, hbm_meas: float,
     for kid, name in KERNEL_NAMES.items():
         ms, n = ds.ctx.read_kernel_timing(kid)
         if n:
-            kernel_us[name] = ms * 1e3 / n
+            kernel_us[name] = ms * 1e3 / n_timed     # per step, whatever the number of launches
     ds.ctx.set_kernel_timing(False)
 
     rows = inp.n_nodes * (2 if (inp.h_uncond is not None and not premix) else 1)   # rows the projection multiplies
-    guidance_pairs = inp.h_uncond is not None and not premix
-    tiled = packed and rows >= (512 if guidance_pairs else 257) and inp.vocab % 256 == 0   # the library's own rule
-    # projection: bound by the matrix cores when the step has several hundred rows, by the W stream otherwise
-    if tiled:
+    kname, tile = "lmhead_f32_kernel", -1
+    if inp.dtype == "bf16":        # what the library's own rule launches
+        tile, rest, _ = binding.projection_tiles(n_nodes=inp.n_nodes, hidden=inp.hidden, vocab=inp.vocab, guided=inp.h_uncond is not None, w_layout=layout,
+                                                 cfg_mix=ds.cfg_mix, ctx=ds.ctx)
+        kname = " + ".join(dict.fromkeys("lmhead_bf16_tiled_kernel" if t >= 5 else "lmhead_bf16_ring_kernel" for t in (tile, rest)))
+    # projection: bound by the matrix cores when the step has several hundred rows (the packed tiles), by the W stream otherwise
+    if tile >= 5:
         flops = 2 * rows * inp.hidden * inp.vocab      # executed: with the hidden-row mix half of the two-product count
         ach = flops / (kernel_us["lmhead"] * 1e-6) / 1e12
-        roof_lm = {"kernel": "lmhead_bf16_tiled_kernel", "bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS,
+        roof_lm = {"kernel": kname, "bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS,
                    "unit": "TFLOP/s", "frac": ach / MFMA_BF16_PEAK_TFLOPS, "traffic": measured_traffic(inp.name, "lmhead"),
                    "algorithmic_flops": flops, "flops_two_products": algorithmic_flops_lmhead(inp),
                    "algorithmic_bytes": algorithmic_bytes_lmhead(inp), "frac_of_measured_peak": ach / mfma_meas}
     else:
         nbytes = algorithmic_bytes_lmhead(inp)
         ach = nbytes / (kernel_us["lmhead"] * 1e-6) / 1e9
-        kname = "lmhead_f32_kernel" if inp.dtype == "f32" else "lmhead_bf16_ring_kernel"
         roof_lm = {"kernel": kname, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                    "frac": ach / HBM_PEAK_GBS, "traffic": measured_traffic(inp.name, "lmhead"), "algorithmic_bytes": nbytes,
                    "frac_of_measured_peak": ach / hbm_meas}
-    roof_lm["avg_launch_us"] = kernel_us["lmhead"]
+    roof_lm["us_per_step"] = kernel_us["lmhead"]
 
     def hbm_block(kernel, nbytes, us, traffic):
         ach = nbytes / (us * 1e-6) / 1e9
         return {"kernel": kernel, "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": ach / HBM_PEAK_GBS, "traffic": traffic, "algorithmic_bytes": nbytes,
-                "frac_of_measured_peak": ach / hbm_meas, "avg_launch_us": us}
+                "frac_of_measured_peak": ach / hbm_meas, "us_per_step": us}
 
-    # 256-row workgroups (the ring kernel) when they fill the chip, smaller ones of the same scheme otherwise
-    max_tree = int((inp.node_off[1:] - inp.node_off[:-1]).max())
-    m_rows = max_tree * (inp.n_heads // inp.n_kv_heads)
-    fills = m_rows > 128 and inp.n_rows * inp.n_kv_heads * ((m_rows + 255) // 256) >= 256
-    attn_kernel = "attn_f32_kernel" if inp.dtype == "f32" else ("attn_bf16_ring_kernel" if fills else "attn_bf16_rows_kernel")
+    attn_kernel = "attn_f32_kernel"
+    if inp.dtype == "bf16":
+        q_rows, _ = binding.attention_cut(n_rows=inp.n_rows, n_nodes_total=inp.q.shape[0], max_nodes_per_tree=ds.max_tree, max_prefix_len=int(inp.prefix_len.max()),
+                                          n_heads=inp.n_heads, n_kv_heads=inp.n_kv_heads, head_dim=inp.head_dim, ctx=ds.ctx)
+        attn_kernel = {256: "attn_bf16_ring_kernel", 16: "attn_bf16_qsplit_kernel"}.get(q_rows, "attn_bf16_rows_kernel")
     attn_us = kernel_us.get("attn", 0.0) + kernel_us.get("attn_merge", 0.0)
     t_attn, t_merge = measured_traffic(inp.name, "attn"), measured_traffic(inp.name, "attn_merge")
     if t_attn is not None and "attn_merge" in kernel_us:
