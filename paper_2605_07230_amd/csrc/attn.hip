@@ -522,7 +522,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     }
   };
 
-  // ancestor-or-self words of tree tile tt (tile index in the workgroup's numbering) for the 256 query rows
+  // ancestor-or-self words of tree tile tt (tile index in the workgroup's numbering) for the workgroup's query rows
   auto build_mask = [&](int tt) {
     if (tid < RW) {
       const int kbase = (tt - n_pt) * KT;

@@ -87,3 +87,47 @@ def test_row_statistics_prefetch_uses_m0_only_for_its_loads(tmp_path):
     m0 = [l.strip() for l in body.splitlines() if re.search(r"\bm0\b", l)]
     assert m0 and all(l.startswith("s_mov_b32 m0,") for l in m0), (name, m0[:5])
     assert body.count("global_load_lds_dwordx4") >= 8 and "scratch_" not in body
+
+
+LDS_DIRECT = {"s_waitcnt", "s_barrier", "s_mov_b32", "s_nop", "global_load_lds_dwordx4"}
+
+
+def _bodies(text, kernel):
+    return re.findall(rf"^(_ZN\S*{kernel}\S*):[^\n]*\n(.*?)s_endpgm", text, flags=re.S | re.M)
+
+
+def _check_lds_direct(name, body, direct):
+    """M0 has no user but the LDS-direct loads (the compiler is not told), none of which an instance with ordinary loads holds;
+    nothing passes through scratch; inline assembly is those loads, waits and barriers."""
+    m0 = [l.strip() for l in body.splitlines() if re.search(r"\bm0\b", l)]
+    assert bool(m0) == direct and all(l.startswith("s_mov_b32 m0,") for l in m0), (name, m0[:5])
+    assert len(m0) == body.count("global_load_lds_dwordx4") and "scratch_" not in body, name
+    inline = re.findall(r";;#ASMSTART\n(.*?);;#ASMEND", body, flags=re.S)
+    ops = {l.split()[0] for blk in inline for l in blk.strip().splitlines()}
+    assert ops <= LDS_DIRECT, (name, ops)
+
+
+def test_ring_projection_m0_and_waits(tmp_path):
+    """Every instance of the ring projection: five tiles and, with ordinary loads, two, for pairs or not and packed weights or
+    not.  With LDS-direct loads two to five stages stay in flight, so the loop holds no wait for ALL outstanding loads."""
+    _, text = _kernel_stats("lmhead.hip", tmp_path)
+    bodies = _bodies(text, "lmhead_bf16_ring_kernel")
+    assert len(bodies) == 28
+    for name, body in bodies:
+        direct = "ELb1EEEv" in name
+        _check_lds_direct(name, body, direct)
+        loop = body[body.index("Loop Header"):body.rindex("vmcnt(0)")]      # up to the drain behind it
+        assert "s_barrier" in loop and "v_mfma_f32_32x32x16_bf16" in loop, name
+        assert not direct or "vmcnt(0)" not in loop, name
+
+
+def test_row_cut_attention_m0(tmp_path):
+    """Every instance of the smaller attention cuts: four at two head widths with the running or the tile's maximum, and two
+    with ordinary loads.  Their rings are two deep: a tile is waited for whole, one barrier each."""
+    _, text = _kernel_stats("attn.hip", tmp_path)
+    bodies = _bodies(text, "attn_bf16_rows_kernel")
+    assert len(bodies) == 20
+    for name, body in bodies:
+        _check_lds_direct(name, body, "ELb1EEEv" in name)
+        loop = body[body.index("=>This Loop Header: Depth=1"):body.rindex("vmcnt(0)")]
+        assert loop.count("s_barrier") == 2, name
