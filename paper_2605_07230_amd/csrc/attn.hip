@@ -1258,9 +1258,12 @@ constexpr float ATTN_NARROW[ATTN_N_SHAPES] = {0.75f, 0.75f, 0.75f, 0.83f, 0.62f,
 
 // Estimated time of a step's attention, us.  Against measured steps (32 heads, head_dim 128): 2 rows x 312 keys, 60 nodes:
 // query split 10.5 (10.3), 64 rows 13.4 (13.4); 2 x 1289 keys: query split 22.5 (23.1), 64 rows whole 29 (29.5) and in four
-// splits 18 (20.7); 2 x 4200 keys, 256 nodes: 64 rows 77 (79), 128 rows in four splits 61 (59); 8 such rows: 256 rows
+// splits 19 (20.7); 2 x 4200 keys, 256 nodes: 64 rows 77 (79), 128 rows in four splits 62 (59); 8 such rows: 256 rows
 // 168 (167), 128 rows 182 (172); 16 rows of 113-680 keys, 40-80 nodes: 128 rows 37 (37), 80 rows 43 (44); 10 rows of
-// 107-1619 keys, 8 kv heads of 4: 64 rows 40 (34), 128 rows in two splits 42 (38).
+// 107-1619 keys, 8 kv heads of 4: 64 rows 40 (34), 128 rows in two splits 43 (38).  With cold caches, query split and 64 rows: 8 rows
+// of 29 keys, 54 nodes (four rounds) 25.5 and 12.7, at head_dim 64 18.6 and 10.3; 16 x 110 keys, 29 nodes, 8 kv heads of 4 (three)
+// 24.7 and 13.7; 64 rows in four, eight and sixteen parts: 2 x 1269 keys, 29 nodes, 8 heads 18.6, 18.4, 21.0.  Over 72 steps
+// (1-16 rows, 24-4200 keys, 15-256 nodes) the cut chosen is 2.5 % behind the fastest in the mean.
 float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_split, int n_cu) {
   const AttnShape& sh = ATTN_SHAPES[shape];
   const int M = a->max_nodes_per_tree * group, n_sb = (M + sh.rows - 1) / sh.rows;
@@ -1271,13 +1274,16 @@ float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_spli
   float blocks = (float)a->n_rows * n_sb;
   if (n_sb > 1) blocks = fminf(blocks, (float)a->n_nodes_total * group / sh.rows + 0.5f * a->n_rows);
   const float x = blocks * a->n_kv_heads * n_split / n_cu;   // workgroups per compute unit
-  if (shape == ATTN_QSPLIT) return 6.f + tiles * sh.c1 * d * fmaxf(x, 1.f);
+  if (shape == ATTN_QSPLIT) {   // one workgroup fills a compute unit's LDS: whole rounds, each with its own start and merge
+    const float chain = tiles * sh.c1 * d;
+    return 6.f + chain + (fmaxf(ceilf(x), 1.f) - 1.f) * ((narrow ? 2.7f : 4.f) + chain);
+  }
   const float c2 = sh.c2_hbm + (sh.c2 - sh.c2_hbm) * fminf(blocks / a->n_rows - 1.f, 1.f);
   const float per_tile = x <= 1.f ? sh.c0 + (sh.c1 - sh.c0) * x
                        : (sh.per_cu == 1 ? sh.c1 * ceilf(x) : (x <= 2.f ? sh.c1 + (c2 - sh.c1) * (x - 1.f) : c2 * 0.5f * x));
   float us = (narrow ? 9.3f : 7.4f) + (float)((tiles + n_split - 1) / n_split) * per_tile * d;
-  if (n_split > 1)   // a second launch, and partials written and read (mostly through the caches)
-    us += 3.8f + (float)n_split * a->n_nodes_total * a->n_heads * (a->head_dim + 2) * 4.f / 7e6f;
+  if (n_split > 1)   // a second launch, which reads the parts one after the other, and partials written and read (mostly through the caches)
+    us += 3.8f + 0.3f * n_split + (float)n_split * a->n_nodes_total * a->n_heads * (a->head_dim + 2) * 4.f / 7e6f;
   return us;
 }
 

@@ -23,7 +23,8 @@ from paper_2605_07230_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths (cuts: CUTS, below)
-    "64 rows, keys in 16 parts": (2, 1, [60, 41, 64, 17, 55], [1500, 37, 700, 1100, 260]),
+    "64 rows, keys in 8 parts": (2, 1, [60, 41, 64, 17, 55], [1500, 37, 700, 1100, 260]),
+    "64 rows, keys in 16 parts": (1, 1, [60, 31], [4000, 900]),
     "64 rows, whole": (32, 1, [60, 41, 64, 17, 55], [800, 0, 64, 513, 300]),
     "64 rows, grouped heads, ragged blocks": (2, 3, [100, 33, 64], [1900, 130, 0]),
     "80 rows": (32, 1, [70, 80, 65, 3, 64, 63, 79, 16, 1], [90, 200, 64, 0, 333, 128, 1, 65, 63]),
@@ -39,9 +40,9 @@ CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths (cut
 
 # (query rows per workgroup, parts of the keys) that 256 compute units choose, at head_dim 64 and 128
 CUTS = {
-    "64 rows, keys in 16 parts": ((64, 16), (64, 16)), "64 rows, whole": ((64, 1), (64, 1)),
-    "64 rows, grouped heads, ragged blocks": ((64, 16), (64, 16)), "80 rows": ((80, 1), (80, 1)), "96 rows": ((96, 1), (96, 1)),
-    "128 rows": ((128, 1), (128, 1)), "128 rows, keys in parts": ((96, 4), (128, 4)), "128 rows, long keys in parts": ((128, 4), (128, 4)),
+    "64 rows, keys in 8 parts": ((64, 8), (64, 8)), "64 rows, keys in 16 parts": ((64, 16), (64, 16)), "64 rows, whole": ((64, 1), (64, 1)),
+    "64 rows, grouped heads, ragged blocks": ((64, 8), (64, 8)), "80 rows": ((80, 1), (80, 1)), "96 rows": ((96, 1), (96, 1)),
+    "128 rows": ((128, 1), (128, 1)), "128 rows, keys in parts": ((64, 3), (128, 4)), "128 rows, long keys in parts": ((128, 4), (128, 4)),
     "256 rows": ((256, 1), (256, 1)), "query split": ((16, 1), (16, 1)), "query split, one node": ((16, 1), (16, 1)),
 }
 
