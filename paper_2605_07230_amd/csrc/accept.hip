@@ -7,7 +7,7 @@
 // a . x (row of a) and every |x|^2 (diagonal) at once.  For bf16 hidden states the tile runs on
 // v_mfma_f32_16x16x32_bf16 with the four waves splitting the hidden dimension (operands loaded
 // straight from global memory as 16-byte k-contiguous pieces); f32 rows (and logit-space
-// similarity) are swept once for eight others at a time on the vector ALU.  The probabilities of the siblings' and children's
+// similarity) are swept once for eight others at a time on the vector ALU (narrow ones for four, by each wave).  The probabilities of the siblings' and children's
 // tokens under the parent's distribution are gathered while the rows are still in flight; the sets
 // I_a and C_a, the distinct-token masses and all outputs then need only ballots and LDS.
 #include "common.h"
@@ -78,7 +78,12 @@ __device__ __forceinline__ f32x4 gram_tile_deep(const uint16_t* row, int k0, int
 // sweeps the row of a once per group of DG other rows and keeps a.x, x.x of each in registers, NT x 16 bytes of every
 // row per step.  Bound by the bytes a compute unit has in flight (each node reads all of its relatives' rows): the former
 // one-row-per-wave loop had one 4-byte load per lane and row in flight - 235 us for 120 nodes x 16384 logits, now 19.
-constexpr int DG = 8;
+// Narrow rows would spend their time on the 17 sums over eight waves and two barriers per group: up to NARROW elements (an
+// eighth where they are loaded one at a time) a wave takes a group of WG rows by itself.  Two trees of 64 nodes, cold caches,
+// with one row per wave, swept by the workgroup, swept by a wave: f32 x 64 6.1, 8.6, 5.6 us; x 512 15.0, 8.5, 5.6; x 1024 25.4, 8.2,
+// 6.3; bf16 x 72 6.4, 8.9, 6.4; x 1016 7.1, 8.5, 6.6.  Wider rows: f32 x 2048 37.0, 6.6; bf16 x 1976 the wave is slower in small trees
+// (40 nodes: 6.6 and 7.4).
+constexpr int DG = 8, WG = 4, NARROW = 1024;
 template <typename T> struct Piece;   // 16 bytes of a row, or one element of rows that are not 16-byte aligned
 template <> struct Piece<float> {
   static constexpr int N = 4;
@@ -93,32 +98,32 @@ template <> struct Piece<uint16_t> {
     for (int i = 0; i < 4; ++i) { x[2 * i] = __uint_as_float(w[i] << 16); x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
   }
 };
-// sums over this thread's share of the row: s[2 j] = a.x_j, s[2 j + 1] = x_j.x_j, s[2 DG] = a.a
-template <int NT, typename T>
-__device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[DG], int h, bool aligned, int tid, float (&s)[2 * DG + 1]) {
+// sums over this thread's share of the row (NT threads): s[2 j] = a.x_j, s[2 j + 1] = x_j.x_j, s[2 G] = a.a
+template <int G, int NT, typename T>
+__device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], int h, bool aligned, int tid, float (&s)[2 * G + 1]) {
   constexpr int N = Piece<T>::N;
 #pragma unroll
-  for (int j = 0; j < 2 * DG + 1; ++j) s[j] = 0.f;
+  for (int j = 0; j < 2 * G + 1; ++j) s[j] = 0.f;
   if (aligned) {
 #pragma unroll 2
     for (int k = tid * N; k < h; k += NT * N) {   // h is a multiple of N
-      float av[N], xv[DG][N];
+      float av[N], xv[G][N];
       Piece<T>::get(a + k, av);
 #pragma unroll
-      for (int j = 0; j < DG; ++j) Piece<T>::get(x[j] + k, xv[j]);
+      for (int j = 0; j < G; ++j) Piece<T>::get(x[j] + k, xv[j]);
 #pragma unroll
       for (int c = 0; c < N; ++c) {
-        s[2 * DG] = fmaf(av[c], av[c], s[2 * DG]);
+        s[2 * G] = fmaf(av[c], av[c], s[2 * G]);
 #pragma unroll
-        for (int j = 0; j < DG; ++j) { s[2 * j] = fmaf(av[c], xv[j][c], s[2 * j]); s[2 * j + 1] = fmaf(xv[j][c], xv[j][c], s[2 * j + 1]); }
+        for (int j = 0; j < G; ++j) { s[2 * j] = fmaf(av[c], xv[j][c], s[2 * j]); s[2 * j + 1] = fmaf(xv[j][c], xv[j][c], s[2 * j + 1]); }
       }
     }
   } else {
     for (int k = tid; k < h; k += NT) {
       const float av = load_f32(a + k);
-      s[2 * DG] = fmaf(av, av, s[2 * DG]);
+      s[2 * G] = fmaf(av, av, s[2 * G]);
 #pragma unroll
-      for (int j = 0; j < DG; ++j) {
+      for (int j = 0; j < G; ++j) {
         const float xv = load_f32(x[j] + k);
         s[2 * j] = fmaf(av, xv, s[2 * j]);
         s[2 * j + 1] = fmaf(xv, xv, s[2 * j + 1]);
@@ -129,7 +134,7 @@ __device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[DG], i
 
 constexpr int MAXO = 2 * MAXW;   // others of a node: parent + (siblings - 1) + children <= 1 + 63 + 64
 
-template <typename T, int NT>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
+template <typename T, int NT, bool NARROW_ROWS>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
 __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev_status) {
   __shared__ float gq[4][256];          // K-quarter partial Gram tiles; generic path: the waves' partial sums
   __shared__ float s_cos[MAXO];         // cos(a, other)
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
 
   const T* row_a = H + (int64_t)gi * h;
   bool mfma_done = false;
-  if constexpr (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2 && !NARROW_ROWS) {
     if ((h & 127) == 0) {
       mfma_done = true;
       const int l16 = lane & 15, g = lane >> 4;
@@ -283,32 +288,49 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
   }
   if (!mfma_done) {
     gather_q();
-    float* part = &gq[0][0];   // [NT / 64 waves][2 DG + 1]
-    static_assert(NT / 64 * (2 * DG + 1) <= 1024, "partial sums fit");
     const bool aligned = (h * sizeof(T)) % 16 == 0 && ((uintptr_t)H & 15) == 0;
-    for (int o0 = 0; o0 < n_other; o0 += DG) {
-      const T* x[DG];
+    if constexpr (NARROW_ROWS) {
+      for (int o0 = WG * wave; o0 < n_other; o0 += NT / 64 * WG) {
+        const T* x[WG];
 #pragma unroll
-      for (int j = 0; j < DG; ++j)   // past the end: the last one again
-        x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
-      float s[2 * DG + 1];
-      dot_group<NT>(row_a, x, h, aligned, tid, s);
-      if (o0 > 0) __syncthreads();   // the previous group's sums have been consumed
+        for (int j = 0; j < WG; ++j)   // past the end: the last one again
+          x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
+        float s[2 * WG + 1];
+        dot_group<WG, 64>(row_a, x, h, aligned, lane, s);
+        const float aa = wave_sum(s[2 * WG]);
 #pragma unroll
-      for (int j = 0; j < 2 * DG + 1; ++j) {
-        const float t = wave_sum(s[j]);
-        if (lane == 0) part[wave * (2 * DG + 1) + j] = t;
-      }
-      __syncthreads();
-      if (tid < DG && o0 + tid < n_other) {
-        float ax = 0.f, xx = 0.f, aa = 0.f;
-        for (int w = 0; w < NT / 64; ++w) {
-          const float* q = part + w * (2 * DG + 1);
-          ax += q[2 * tid];
-          xx += q[2 * tid + 1];
-          aa += q[2 * DG];
+        for (int j = 0; j < WG; ++j) {
+          const float ax = wave_sum(s[2 * j]), xx = wave_sum(s[2 * j + 1]);
+          if (lane == j && o0 + j < n_other) s_cos[o0 + j] = cos_from(ax, aa, xx);
         }
-        s_cos[o0 + tid] = cos_from(ax, aa, xx);
+      }
+    } else {
+      float* part = &gq[0][0];   // [NT / 64 waves][2 DG + 1]
+      static_assert(NT / 64 * (2 * DG + 1) <= 1024, "partial sums fit");
+      for (int o0 = 0; o0 < n_other; o0 += DG) {
+        const T* x[DG];
+#pragma unroll
+        for (int j = 0; j < DG; ++j)   // past the end: the last one again
+          x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
+        float s[2 * DG + 1];
+        dot_group<DG, NT>(row_a, x, h, aligned, tid, s);
+        if (o0 > 0) __syncthreads();   // the previous group's sums have been consumed
+#pragma unroll
+        for (int j = 0; j < 2 * DG + 1; ++j) {
+          const float t = wave_sum(s[j]);
+          if (lane == 0) part[wave * (2 * DG + 1) + j] = t;
+        }
+        __syncthreads();
+        if (tid < DG && o0 + tid < n_other) {
+          float ax = 0.f, xx = 0.f, aa = 0.f;
+          for (int w = 0; w < NT / 64; ++w) {
+            const float* q = part + w * (2 * DG + 1);
+            ax += q[2 * tid];
+            xx += q[2 * tid + 1];
+            aa += q[2 * DG];
+          }
+          s_cos[o0 + tid] = cos_from(ax, aa, xx);
+        }
       }
     }
   }
@@ -367,7 +389,12 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
 hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   KernelTimer t(ctx, CASCADE_K_ACCEPT);
   dim3 grid(ctx->lim.max_nodes_per_tree, a->n_prompts);
-  if (a->h_dtype == CASCADE_BF16) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<uint16_t, 256>), grid, dim3(256), 0, ctx->stream, *a, ctx->dev_status);
-  else CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<float, 512>), grid, dim3(512), 0, ctx->stream, *a, ctx->dev_status);
+  const bool bf16 = a->h_dtype == CASCADE_BF16, mfma = bf16 && a->hidden % 128 == 0;
+  const bool aligned = (a->hidden * (bf16 ? 2 : 4)) % 16 == 0 && ((uintptr_t)a->h_cond & 15) == 0;
+  const bool narrow = !mfma && a->hidden <= (aligned ? NARROW : NARROW / 8);
+#define CASCADE_LAUNCH_ACCEPT(T, NT, N) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, N>), grid, dim3(NT), 0, ctx->stream, *a, ctx->dev_status)
+  if (bf16) { if (narrow) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, true); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, false); }
+  else { if (narrow) CASCADE_LAUNCH_ACCEPT(float, 512, true); else CASCADE_LAUNCH_ACCEPT(float, 512, false); }
+#undef CASCADE_LAUNCH_ACCEPT
   return hipGetLastError();
 }

@@ -1,6 +1,8 @@
 """Acceptance on feature rows that do not go through the matrix cores (f32 of any width, bf16 widths that are no multiple
-of 128): the others of a node are swept eight at a time, so nodes with 1 to 60 relatives and widths around the
-workgroup's stride (512 threads x 4 floats) and not divisible by a 16-byte piece are compared with the checker.
+of 128): the others of a node are swept eight at a time by the workgroup, or four at a time by each wave where rows are
+narrow, so nodes with 1 to 60 relatives and widths around the workgroup's stride (512 threads x 4 floats), around the
+narrow rows' limit (1024 elements, 128 where a row cannot be read 16 bytes at a time) and not divisible by a 16-byte
+piece are compared with the checker.
 
 Cosines are float32 dot products in some order: off by at most h 2^-24 sum|a||b| / (|a||b|) <= h 2^-24, the quotient adds a
 few 2^-24; set sizes are exact because the constructed cosines stay 1e-3 away from the thresholds."""
@@ -15,7 +17,7 @@ from paper_2605_07230_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype,hidden", [("f32", 1), ("f32", 99), ("f32", 516), ("f32", 2048), ("f32", 2052), ("f32", 5000), ("bf16", 136), ("bf16", 4104)])
+@pytest.mark.parametrize("dtype,hidden", [("f32", 1), ("f32", 99), ("f32", 129), ("f32", 260), ("f32", 516), ("f32", 1024), ("f32", 1028), ("f32", 2048), ("f32", 2052), ("f32", 5000), ("bf16", 136), ("bf16", 1016), ("bf16", 1032), ("bf16", 4104)])
 @pytest.mark.parametrize("kids", [1, 7, 8, 17, 60])
 def test_acceptance_on_generic_rows(dtype, hidden, kids):
     rng = np.random.default_rng(hidden * 64 + kids)
