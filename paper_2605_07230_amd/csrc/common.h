@@ -21,6 +21,7 @@ struct cascade_ctx {
   size_t attn_ws_bytes;
   char* hpack_ws;         // hidden states repacked into MFMA operand order, cond then uncond
   size_t hpack_ws_bytes;
+  char* select_ws;        // select_path: counters (zero between calls) and chunk sums of prompts shared by several workgroups
   // optional per-kernel timing with HIP events on the ctx stream (cascade_set_kernel_timing)
   bool timing;
   hipEvent_t* ev;         // [CASCADE_K_COUNT][TIMING_RING][2], created on first enable
@@ -28,6 +29,10 @@ struct cascade_ctx {
 };
 
 enum { TIMING_RING = 2048 };
+
+// prompts whose vocabulary several workgroups of select_path share (a counter and the sums of all 256-entry chunks each)
+enum { SELECT_MAX_SHARED = 128 };
+constexpr size_t SELECT_WS_BYTES = SELECT_MAX_SHARED * (sizeof(int) + CASCADE_MAX_VOCAB / 256 * sizeof(float));
 
 // Per-kernel timing: when it is on, a launch goes through hipExtLaunchKernelGGL with a start and a stop
 // event taken from the context's ring, which receive the dispatch's own begin / end timestamps (no

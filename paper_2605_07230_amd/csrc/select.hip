@@ -1,4 +1,4 @@
-// select_path kernel for gfx950: one workgroup per prompt.
+// select_path kernel for gfx950: as many workgroups per prompt as its row has passes of 4096 entries, where the chip has room.
 //
 // SEQUENTIAL (Alg. 2 as printed): wave 0 holds the per-node scalars of the whole tree in registers
 // (one node per lane per 64-node chunk).  The children of the current node are found with one
@@ -35,26 +35,32 @@ __device__ __forceinline__ Try try_node(float q, float mi, float mc, float up, f
   return r;
 }
 
-// NT = threads; TCH = 64-node chunks of the tree held in registers by the walking wave
-// (Tn <= 64 * TCH); CPW = 256-entry vocabulary chunks each wave keeps in registers
-// (V <= 256 * (NT / 64) * CPW)
-template <int NT, int TCH, int CPW>
-__global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_status) {
-  constexpr int SEL_THREADS = NT, SEL_WAVES = NT / 64;
+// Where the workgroups of one prompt meet: the sums of their vocabulary chunks and a counter that is zero between calls.
+struct SelectShare {
+  int* arrived;     // [prompts]
+  float* sums;      // [prompts][MAXCHUNKS]
+};
+
+// TCH = 64-node chunks of the tree held in registers by the walking wave (Tn <= 64 * TCH); CPW = 256-entry vocabulary chunks
+// that each of the eight waves sums per pass
+template <int TCH, int CPW>
+__global__ __launch_bounds__(512) void select_kernel(select_args a, SelectShare share, int* dev_status) {
+  constexpr int SEL_THREADS = 512, SEL_WAVES = 8, PASS = SEL_WAVES * CPW;
+  __shared__ int s_tok[CASCADE_MAX_DEPTH];   // tokens of the accepted path
   __shared__ int s_path[CASCADE_MAX_DEPTH];
   __shared__ int s_tried[CASCADE_MAX_WIDTH];
   __shared__ int s_len, s_cur, s_ntried, s_best;
   __shared__ float s_tvd;
   __shared__ float s_chunk[MAXCHUNKS];
-  __shared__ float s_total, s_base;
-  __shared__ int s_cstar, s_lastkept;
+  __shared__ float s_total;
+  __shared__ int s_last;
   // LONGEST only
   __shared__ int s_par[CASCADE_MAX_TREE];
   __shared__ float s_ntvd[CASCADE_MAX_TREE];
   __shared__ unsigned char s_alive[CASCADE_MAX_TREE], s_ready[CASCADE_MAX_TREE], s_depth[CASCADE_MAX_TREE], s_haschild[CASCADE_MAX_TREE];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.x;
+  const int b = blockIdx.y, parts = gridDim.x;
   const int lo = a.node_off[b], Tn = min(a.node_off[b + 1] - lo, 64 * TCH);
   // a tree larger than the launch was sized for is walked over its first 64 * TCH nodes only, and flagged
   if (tid == 0 && a.node_off[b + 1] - lo > 64 * TCH) atomicOr(dev_status, CASCADE_FLAG_TREE_SIZE);
@@ -121,19 +127,39 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
         }
         if (accepted < 0) break;
         if (len >= maxd) { if (lane == 0) atomicOr(dev_status, CASCADE_FLAG_DEPTH); break; }
-        if (lane == 0) s_path[len] = accepted;
+        int at = tok[0];   // (of the accepted node's chunk)
+#pragma unroll
+        for (int c = 1; c < TCH; ++c) at = (accepted >> 6) == c ? tok[c] : at;
+        at = __builtin_amdgcn_readlane(at, accepted & 63);
+        if (lane == 0) { s_path[len] = accepted; s_tok[len] = at; }
         ++len;
         cur = accepted;
       }
       if (lane == 0) { s_len = len; s_cur = cur; s_ntried = ntried; s_tvd = tvd; }
     }
   } else {
-    // top-down recurrence over the tree, one level per round
-    for (int i = tid; i < Tn; i += SEL_THREADS) {
-      int pi = a.parent[lo + i];
-      if (i == 0) pi = -1;
-      else if (pi < 0 || pi >= i) { atomicOr(dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // orphan: never reached
-      s_par[i] = pi;
+    // top-down recurrence over the tree, one level per round; every value a round needs is requested before the first one
+    // (a load inside a round costs it a trip to memory: 119 nodes and nine rounds x 33088 entries 10.1 -> 9.4 us)
+    constexpr int SLOTS = 64 * TCH / SEL_THREADS > 0 ? 64 * TCH / SEL_THREADS : 1;   // nodes of a thread
+    int par[SLOTS];
+    float qv[SLOTS], mi[SLOTS], mc[SLOTS], up[SLOTS];
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      const int i = tid + k * SEL_THREADS, at = lo + max(min(i, Tn - 1), 0);
+      par[k] = -1;
+      qv[k] = mi[k] = mc[k] = up[k] = 0.f;
+      if (k * SEL_THREADS < Tn) {
+        par[k] = a.parent[at];
+        qv[k] = a.q_tok[at];
+        mi[k] = a.m_int[at];
+        mc[k] = a.m_conv[at];
+        up[k] = a.u[at];
+        if (a.draft_prob) up[k] *= a.draft_prob[at];
+      }
+      if (i >= Tn) continue;
+      if (i == 0) par[k] = -1;
+      else if (par[k] < 0 || par[k] >= i) { atomicOr(dev_status, CASCADE_FLAG_PARENT); par[k] = -1; }   // orphan: never reached
+      s_par[i] = par[k];
       s_alive[i] = i == 0;
       s_ready[i] = i == 0;
       s_depth[i] = 0;
@@ -142,26 +168,26 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
     }
     if (tid == 0) s_best = -1;
     __syncthreads();
-    for (int i = tid; i < Tn; i += SEL_THREADS)
-      if (s_par[i] >= 0) s_haschild[s_par[i]] = 1;
-    for (int round = 0; round < maxd; ++round) {
-      bool can[(CASCADE_MAX_TREE + SEL_THREADS - 1) / SEL_THREADS];
 #pragma unroll
-      for (int k = 0; k < (CASCADE_MAX_TREE + SEL_THREADS - 1) / SEL_THREADS; ++k) {
+    for (int k = 0; k < SLOTS; ++k)
+      if (tid + k * SEL_THREADS < Tn && par[k] >= 0) s_haschild[par[k]] = 1;
+    for (int round = 0; round < maxd; ++round) {
+      bool can[SLOTS];
+#pragma unroll
+      for (int k = 0; k < SLOTS; ++k) {
         const int i = tid + k * SEL_THREADS;
-        can[k] = i < Tn && !s_ready[i] && s_par[i] >= 0 && s_ready[s_par[i]];
+        can[k] = i < Tn && !s_ready[i] && par[k] >= 0 && s_ready[par[k]];
       }
       __syncthreads();
 #pragma unroll
-      for (int k = 0; k < (CASCADE_MAX_TREE + SEL_THREADS - 1) / SEL_THREADS; ++k) {
+      for (int k = 0; k < SLOTS; ++k) {
         const int i = tid + k * SEL_THREADS;
         if (can[k]) {
-          const int pi = s_par[i];
+          const int pi = par[k];
           float t = s_ntvd[pi];
           bool alive = false;
           if (s_alive[pi]) {
-            const float up = a.u[lo + i] * (a.draft_prob ? a.draft_prob[lo + i] : 1.f);
-            const Try r = try_node(a.q_tok[lo + i], a.m_int[lo + i], a.m_conv[lo + i], up, t, eps);
+            const Try r = try_node(qv[k], mi[k], mc[k], up[k], t, eps);
             t = r.tvd;
             alive = r.pass;
           }
@@ -195,7 +221,7 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
       s_tvd = first_dead >= 0 ? s_ntvd[first_dead] : s_ntvd[x];
       s_ntried = first_dead >= 0 ? 1 : 0;
       if (first_dead >= 0) s_tried[0] = a.token[lo + first_dead];
-      for (int d = len - 1, y = x; d >= 0; --d) { s_path[d] = y; y = s_par[y]; }
+      for (int d = len - 1, y = x; d >= 0; --d) { s_path[d] = y; s_tok[d] = a.token[lo + y]; y = s_par[y]; }
     }
   }
   __syncthreads();
@@ -205,160 +231,196 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
   const int V = a.vocab;
   const float* Lr = a.logits + (int64_t)(lo + cur) * V;
   const float thr = a.row_thr[lo + cur], lse = a.row_lse[lo + cur];
-  const int nchunks = (V + 255) >> 8;
+  const int nchunks = (V + 255) >> 8;   // at most CPW per wave
   const bool vec = (V & 3) == 0;
   const float ub = a.u_bonus[b];
 
-  // every wave owns the chunks wave, wave + NW, ...; their logits are loaded in batches of 8 chunks, all loads of a batch in
-  // flight together: clamped into the row (entries past its end are masked in chunk_vals), because a guard around every
-  // load made every chunk wait for the one before.  With a single batch (CPW == 8) the registers are kept, and the crossing
-  // chunk is resolved by its owner without a second trip to memory.  Latency-bound: 60 nodes x 16384 entries 9.0 -> 7.6 us,
-  // x 65536 12.9 -> 11.4, four 256-node trees x 65536 16.1 -> 14.5.  Sixteen chunks in registers instead of two batches were
-  // slower (65536 entries: 13.6 and 17.3): a lone workgroup runs through straight-line code that it has to fetch first.
-  constexpr int NBATCH = CPW / 8;
-  auto load_chunk = [&](int c) -> f32x4 {
-    const int e0 = c * 256 + lane * 4;
-    if (vec) return *(const f32x4*)(Lr + min(e0, V - 4));
-    f32x4 v;
+  // Chunk sums.  A pass of a workgroup covers PASS chunks, CPW per wave; all loads of a pass are in flight together: clamped
+  // into the row (entries past its end are masked), because a guard around every load made every chunk wait for the one
+  // before.  What bounds this part is the chain of instructions of a wave (a dependent one issues every 8 cycles) and, in long
+  // rows, the exponentials of the one compute unit: the scans of a pass advance side by side without branches, the rejected
+  // tokens are visited once per pass by the wave that owns them, and the passes of a prompt are dealt to `parts` workgroups.
+  // Each of those walks the tree by itself (nothing is exchanged before the sums), leaves its sums in memory and counts itself
+  // in; the one that arrives last goes on, the others are done, so no workgroup ever waits for another.
+  const int ban = lane < ntried ? s_tried[lane] : -1;   // lane e holds the e-th rejected token
+  const int n_pass = (nchunks + PASS - 1) / PASS;
+  auto sum_chunks = [&](int first, int step, bool use_ban, auto&& put) {
+#pragma unroll 1
+    for (int ps = first; ps < n_pass; ps += step) {
+      const int c0 = ps * PASS + wave;   // this wave's chunks: c0, c0 + SEL_WAVES, ...
+      f32x4 r[CPW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = Lr[min(e0 + i, V - 1)];
-    return v;
-  };
-  f32x4 gv[8];
-  auto load_batch = [&](int bt) {
-    if (vec) {
+      for (int ci = 0; ci < CPW; ++ci) {
+        const int e0 = (c0 + SEL_WAVES * ci) * 256 + 4 * lane;
+        if (vec) r[ci] = *(const f32x4*)(Lr + min(e0, V - 4));
+        else
 #pragma unroll
-      for (int ci = 0; ci < 8; ++ci) gv[ci] = *(const f32x4*)(Lr + min((wave + SEL_WAVES * (8 * bt + ci)) * 256 + lane * 4, V - 4));
-    } else {
-#pragma unroll
-      for (int ci = 0; ci < 8; ++ci) gv[ci] = load_chunk(wave + SEL_WAVES * (8 * bt + ci));
-    }
-  };
-  if (NBATCH == 1) load_batch(0);
-  // masses of the 4 entries a lane owns inside chunk c
-  // lane e holds the e-th rejected token; chunk_vals visits them with readlane (no LDS in the loop)
-  const int tried_reg = lane < ntried ? s_tried[lane] : -1;
-  auto chunk_vals = [&](int c, const f32x4& g4, bool use_ban, int l4, float ref, float r[4]) {
-    const int e0 = c * 256 + l4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = (g4[i] >= thr && e0 + i < V) ? __expf(g4[i] - ref) : 0.f;
-    if (use_ban) {
-      for (int e = 0; e < ntried; ++e) {
-        const int t = __builtin_amdgcn_readlane(tried_reg, e);
-        if ((t >> 8) == c && lane == ((t & 255) >> 2)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) if ((t & 3) == i) r[i] = 0.f;
-        }
+          for (int i = 0; i < 4; ++i) r[ci][i] = Lr[min(e0 + i, V - 1)];
       }
+#pragma unroll
+      for (int ci = 0; ci < CPW; ++ci)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float x = __expf(r[ci][i] - lse);
+          r[ci][i] = r[ci][i] >= thr ? x : 0.f;
+        }
+      if ((ps + 1) * PASS * 256 > V)   // the pass reaches past the row
+#pragma unroll
+        for (int ci = 0; ci < CPW; ++ci)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r[ci][i] = (c0 + SEL_WAVES * ci) * 256 + 4 * lane + i < V ? r[ci][i] : 0.f;
+      for (int e = 0; use_ban && e < ntried; ++e) {
+        const int t = __builtin_amdgcn_readlane(ban, e);
+        if (t >= 0 && t / (256 * PASS) == ps && ((t >> 8) & (SEL_WAVES - 1)) == wave)
+#pragma unroll
+          for (int ci = 0; ci < CPW; ++ci)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[ci][i] = (c0 + SEL_WAVES * ci) * 256 + 4 * lane + i == t ? 0.f : r[ci][i];
+      }
+      float cs[CPW];
+#pragma unroll
+      for (int ci = 0; ci < CPW; ++ci) cs[ci] = ((r[ci][0] + r[ci][1]) + r[ci][2]) + r[ci][3];
+      auto scan_step = [&](auto shift) {
+#pragma unroll
+        for (int ci = 0; ci < CPW; ++ci) cs[ci] += shift(cs[ci]);
+      };
+      scan_step([](float v) { return dpp_f32<0x111, 0xf>(0.f, v); });   // wave_sum's steps: lane 63 ends up with the total
+      scan_step([](float v) { return dpp_f32<0x112, 0xf>(0.f, v); });
+      scan_step([](float v) { return dpp_f32<0x114, 0xf>(0.f, v); });
+      scan_step([](float v) { return dpp_f32<0x118, 0xf>(0.f, v); });
+      scan_step([](float v) { return dpp_f32<0x142, 0xa>(0.f, v); });
+      scan_step([](float v) { return dpp_f32<0x143, 0xc>(0.f, v); });
+      if (lane == 63)
+#pragma unroll
+        for (int ci = 0; ci < CPW; ++ci) put(c0 + SEL_WAVES * ci, cs[ci]);   // chunks past the row: 0
     }
   };
+  auto to_lds = [&](int c, float x) { if (c < MAXCHUNKS) s_chunk[c] = x; };
 
-  bool use_ban = true;
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    // the masses and masks are recomputed per attempt: hoisted out of the loop they would need as many registers again
-    int l4 = 4 * lane;
-    float ref = lse;
-    asm volatile("" : "+v"(l4), "+v"(ref));
-    for (int bt = 0; bt < NBATCH; ++bt) {
-      if (NBATCH > 1) load_batch(bt);
-#pragma unroll
-      for (int ci = 0; ci < 8; ++ci) {
-        const int c = wave + SEL_WAVES * (8 * bt + ci);
-        if (c < nchunks) {
-          float r[4];
-          chunk_vals(c, gv[ci], use_ban, l4, ref, r);
-          const float cs = wave_sum(((r[0] + r[1]) + r[2]) + r[3]);
-          if (lane == 0) s_chunk[c] = cs;
-        }
-      }
-    }
+  float cs[4];   // wave 0: lane l owns chunks 4 l .. 4 l + 3
+  if (parts > 1) {
+    // Sums and counter pass through memory that all XCDs see (agent-scope accesses go past their L2s), so no cache has to be
+    // written back; the wait puts every wave's sums there before the workgroup counts itself in.
+    float* shared = share.sums + (size_t)b * MAXCHUNKS;
+    sum_chunks(blockIdx.x, parts, true, [&](int c, float x) {
+      if (c < nchunks) __hip_atomic_store(shared + c, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (wave == 0) {
-      // lane l owns chunks 4l .. 4l+3
-      float cs[4], loc = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        cs[i] = 4 * lane + i < nchunks ? s_chunk[4 * lane + i] : 0.f;
-        loc += cs[i];
+      int n = 0;
+      if (lane == 0) n = __hip_atomic_fetch_add(share.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = __builtin_amdgcn_readfirstlane(n) == parts - 1;
+      if (lane == 0) {
+        s_last = last;
+        if (last) __hip_atomic_store(share.arrived + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
       }
-      const float incl = wave_scan_incl_f(loc);
-      const float total = readlane_f(incl, 63);
-      const float target = ub * total;
-      float run = incl - loc;
-      int cand = 0x7fffffff;
-      float cbase = 0.f;
+      if (last)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (cand == 0x7fffffff && cs[i] > 0.f && run + cs[i] > target) { cand = 4 * lane + i; cbase = run; }
-        run += cs[i];
-      }
-      const int best = wave_min_i(cand);
-      if (best == 0x7fffffff) {
-        // rounding kept the running sum at or below the target: take the last chunk that holds mass
-        int lastc = -1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (cs[i] > 0.f) lastc = 4 * lane + i;
-        lastc = wave_max_i(lastc);
-        if (lane == 0) { s_cstar = lastc; s_base = 0.f; s_lastkept = 1; }
-      } else if (cand == best) {
-        s_cstar = best;
-        s_base = cbase;
-        s_lastkept = 0;
-      }
-      if (lane == 0) s_total = total;
+        for (int i = 0; i < 4; ++i)
+          cs[i] = 4 * lane + i < nchunks ? __hip_atomic_load(shared + 4 * lane + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
     }
+  } else {
+    sum_chunks(0, 1, true, to_lds);
     __syncthreads();
-    if (s_total > 0.f || attempt == 1) break;
-    use_ban = false;   // every kept entry was removed: fall back to the unfiltered row
+    if (wave == 0)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cs[i] = 4 * lane + i < nchunks ? s_chunk[4 * lane + i] : 0.f;
+  }
+  // wave 0 of the workgroup that goes on
+  float total = 0.f, base = 0.f;
+  int cstar = -1;
+  bool lastkept = false;
+  auto find_chunk = [&]() {   // the chunk in which the running sum crosses the target
+    const float loc = ((0.f + cs[0]) + cs[1]) + cs[2] + cs[3];
+    const float incl = wave_scan_incl_f(loc);
+    total = readlane_f(incl, 63);
+    const float target = ub * total;
+    float run = incl - loc;
+    int cand = 0x7fffffff;
+    float cbase = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (cand == 0x7fffffff && cs[i] > 0.f && run + cs[i] > target) { cand = 4 * lane + i; cbase = run; }
+      run += cs[i];
+    }
+    cstar = wave_min_i(cand);
+    lastkept = cstar == 0x7fffffff;
+    if (lastkept) {
+      // rounding kept the running sum at or below the target: take the last chunk that holds mass
+      int lastc = -1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) if (cs[i] > 0.f) lastc = 4 * lane + i;
+      cstar = wave_max_i(lastc);
+      base = 0.f;
+    } else {
+      base = readlane_f(cbase, __ffsll((long long)__ballot(cand == cstar)) - 1);
+    }
+  };
+  const bool mine = wave == 0 && (parts == 1 || s_last);   // (s_last was written by this very wave)
+  if (mine) {
+    find_chunk();
+    if (lane == 0) s_total = total;
+  }
+  __syncthreads();
+  if (parts > 1 && !s_last) return;
+  bool use_ban = true;
+  if (!(s_total > 0.f)) {   // every kept entry was removed: the unfiltered row, which this workgroup sums by itself
+    use_ban = false;
+    sum_chunks(0, 1, false, to_lds);
     __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cs[i] = 4 * lane + i < nchunks ? s_chunk[4 * lane + i] : 0.f;
+      find_chunk();
+    }
   }
 
-  {
-    const int cstar = s_cstar;
-    const bool ok = s_total > 0.f && cstar >= 0;
-    if (!ok && tid == 0) a.emitted[(int64_t)b * (a.max_depth + 1) + len] = -1;
-    if (ok && wave == cstar % SEL_WAVES) {   // the owner of the crossing chunk finishes
-      const float target = ub * s_total;
-      float r[4];
-      f32x4 g4 = gv[0];
-      if (NBATCH > 1) g4 = load_chunk(cstar);
-      else
-#pragma unroll
-        for (int ci = 1; ci < 8; ++ci)
-          if (wave + SEL_WAVES * ci == cstar) g4 = gv[ci];
-      chunk_vals(cstar, g4, use_ban, 4 * lane, lse, r);
-      const float p0 = r[0], p1 = p0 + r[1], p2 = p1 + r[2], p3 = p2 + r[3];
-      const float incl = wave_scan_incl_f(p3);
-      const float run = s_base + (incl - p3);
-      int cand = 0x7fffffff;
+  if (wave == 0) {
+    int x = -1;
+    if (total > 0.f && cstar >= 0) {
+      const float target = ub * total;
       const int e0 = cstar * 256 + lane * 4;
-      if (!s_lastkept) {
-        if (r[0] > 0.f && run + p0 > target) cand = e0;
-        else if (r[1] > 0.f && run + p1 > target) cand = e0 + 1;
-        else if (r[2] > 0.f && run + p2 > target) cand = e0 + 2;
-        else if (r[3] > 0.f && run + p3 > target) cand = e0 + 3;
+      float m[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float g = Lr[min(e0 + i, V - 1)], p = __expf(g - lse);
+        m[i] = (g >= thr && e0 + i < V) ? p : 0.f;
       }
-      const int best = wave_min_i(cand);
-      int x = best;
-      if (best == 0x7fffffff) {
+      for (int e = 0; use_ban && e < ntried; ++e) {
+        const int t = __builtin_amdgcn_readlane(ban, e);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = e0 + i == t ? 0.f : m[i];
+      }
+      const float p0 = m[0], p1 = p0 + m[1], p2 = p1 + m[2], p3 = p2 + m[3];
+      const float incl = wave_scan_incl_f(p3);
+      const float run = base + (incl - p3);
+      int cand = 0x7fffffff;
+      if (!lastkept) {
+        if (m[0] > 0.f && run + p0 > target) cand = e0;
+        else if (m[1] > 0.f && run + p1 > target) cand = e0 + 1;
+        else if (m[2] > 0.f && run + p2 > target) cand = e0 + 2;
+        else if (m[3] > 0.f && run + p3 > target) cand = e0 + 3;
+      }
+      x = wave_min_i(cand);
+      if (x == 0x7fffffff) {
         int last = -1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) if (r[i] > 0.f) last = e0 + i;
+        for (int i = 0; i < 4; ++i) if (m[i] > 0.f) last = e0 + i;
         x = wave_max_i(last);
       }
-      if (lane == 0) a.emitted[(int64_t)b * (a.max_depth + 1) + len] = x;
     }
-  }
-  for (int d = tid; d < a.max_depth; d += SEL_THREADS)
-    a.path_nodes[(int64_t)b * a.max_depth + d] = d < len ? s_path[d] : -1;
-  for (int d = tid; d <= a.max_depth; d += SEL_THREADS) {
-    if (d < len) a.emitted[(int64_t)b * (a.max_depth + 1) + d] = a.token[lo + s_path[d]];
-    else if (d > len) a.emitted[(int64_t)b * (a.max_depth + 1) + d] = -1;
-  }
-  if (tid == 0) {
-    a.accept_len[b] = len;
-    a.terminal[b] = cur;
-    a.tvd_used[b] = s_tvd;
+    if (lane == 0) {
+      a.emitted[(int64_t)b * (a.max_depth + 1) + len] = x;
+      a.accept_len[b] = len;
+      a.terminal[b] = cur;
+      a.tvd_used[b] = s_tvd;
+    }
+  } else if (wave == 1) {
+    for (int d = lane; d <= a.max_depth; d += 64) {
+      if (d < a.max_depth) a.path_nodes[(int64_t)b * a.max_depth + d] = d < len ? s_path[d] : -1;
+      if (d != len) a.emitted[(int64_t)b * (a.max_depth + 1) + d] = d < len ? s_tok[d] : -1;
+    }
   }
 }
 
@@ -366,11 +428,22 @@ __global__ __launch_bounds__(NT) void select_kernel(select_args a, int* dev_stat
 
 hipError_t launch_select(cascade_ctx* ctx, const select_args* a) {
   KernelTimer t(ctx, CASCADE_K_SELECT);
-  const bool small_tree = ctx->lim.max_nodes_per_tree <= 256, small_vocab = a->vocab <= 16384;
-  dim3 grid(a->n_prompts);
-  if (small_tree && small_vocab) CASCADE_TIMED_LAUNCH(t, (select_kernel<512, 4, 8>), grid, dim3(512), 0, ctx->stream, *a, ctx->dev_status);
-  else if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<1024, 4, 16>), grid, dim3(1024), 0, ctx->stream, *a, ctx->dev_status);
-  else if (small_vocab) CASCADE_TIMED_LAUNCH(t, (select_kernel<512, 16, 8>), grid, dim3(512), 0, ctx->stream, *a, ctx->dev_status);
-  else CASCADE_TIMED_LAUNCH(t, (select_kernel<1024, 16, 16>), grid, dim3(1024), 0, ctx->stream, *a, ctx->dev_status);
+  SelectShare share = {(int*)ctx->select_ws, (float*)(ctx->select_ws + SELECT_MAX_SHARED * sizeof(int))};
+  const bool small_tree = ctx->lim.max_nodes_per_tree <= 256;
+  // One pass of 4096 entries per workgroup while the chip has a compute unit for each: a row's exponentials take a lone
+  // compute unit 1 us per 16384 entries, the meeting of the workgroups 1.5 us.  In a step, with one workgroup per prompt and as
+  // built now: 15 nodes x 4096 entries 5.7 -> 4.9 us, 60 x 16384 9.0 -> 6.4, 60 x 65536 13.3 -> 6.7, four trees of 256 x 65536
+  // 15.0 -> 8.3.  More prompts than half the compute units fill the chip by themselves.
+  const int pass = 4096, n_pass = (a->vocab + pass - 1) / pass;
+  int parts = a->n_prompts <= SELECT_MAX_SHARED ? ctx->n_cu / a->n_prompts : 1;
+  parts = parts < 1 ? 1 : (parts < n_pass ? parts : n_pass);
+  dim3 grid(parts, a->n_prompts);
+  if (parts > 1 || n_pass == 1) {
+    if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<4, 2>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
+    else CASCADE_TIMED_LAUNCH(t, (select_kernel<16, 2>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
+  } else {
+    if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<4, 8>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
+    else CASCADE_TIMED_LAUNCH(t, (select_kernel<16, 8>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
+  }
   return hipGetLastError();
 }
