@@ -1,6 +1,14 @@
 // kv_commit: append the root and the accepted path of every row's tree to that row's prefix cache,
 // for all layers (Preliminaries: accepted tokens are appended to the prefix).  A pure gather /
-// scatter of 16-byte pieces; one workgroup per (row, path slot, layer).
+// scatter of 16-byte pieces.
+//
+// One workgroup per (row, layer, keys or values, 2 KiB of a node row) copies all of the row's slots: the row's lookups are
+// three trips to memory (prompt, lengths and tree; accepted length and path; the data), made once for all slots with the path
+// in the lanes of a wave.  Bound by the copy: 47 MB (8 pairs of rows, 30 layers, 32 heads x 128) 15.4 -> 11.8 us, against 9.4 at
+// the rate of a large copy.  One workgroup per (row, slot, layer) made two thirds of the launched ones find out by three
+// dependent trips that their slot was empty, and dirty lines that stay in the L2s are written back after the last
+// workgroup has ended: streaming (non-temporal) stores alone are worth 2 us.  Streaming loads cost 6; four or eight pieces of a
+// thread in flight 1 (few slots have that many).
 #include "common.h"
 
 namespace {
@@ -12,24 +20,30 @@ struct CommitParams {
   int* dev_status;
   int row_vec;       // 16-byte pieces per node row (n_kv_heads * head_dim * elem / 16)
   int head_vec;      // 16-byte pieces per head
+  int part_vec;      // 16-byte pieces of a node row that one workgroup copies
   long long sl, sr, sh, sp;   // cache strides in 16-byte pieces
   long long tree_layer_vec;   // 16-byte pieces per layer of k_tree / v_tree
 };
 
-__global__ __launch_bounds__(256) void kv_commit_kernel(CommitParams p) {
-  const kv_commit_args& a = p.a;
-  const int slots = a.max_depth + 1;
-  const int s = blockIdx.x / slots, j = blockIdx.x % slots, layer = blockIdx.y;
-  const int tid = threadIdx.x;
-  const bool reporter = (j == 0 && layer == 0 && tid == 0);
+constexpr int COMMIT_THREADS = 256, COMMIT_FLIGHT = 2;
 
-  const int b = a.row_prompt[s];
-  const int P = a.prefix_len[s];
+__global__ __launch_bounds__(COMMIT_THREADS) void kv_commit_kernel(CommitParams p) {
+  __shared__ int s_node[CASCADE_MAX_DEPTH + 1];   // tree node of every slot, -1: nothing to copy
+  const kv_commit_args& a = p.a;
+  const int s = blockIdx.x, layer = blockIdx.y, part = blockIdx.z >> 1;
+  const bool values = blockIdx.z & 1;
+  const int tid = threadIdx.x;
+  const bool reporter = layer == 0 && blockIdx.z == 0 && tid == 0;
+
+  const int b = a.row_prompt[s], P = a.prefix_len[s];
+  const int base = a.node_off[s], n_tree = a.node_off[s + 1] - base;
   if (b < 0 || b >= a.n_prompts) {
     if (reporter) { atomicOr(p.dev_status, CASCADE_FLAG_PATH); a.prefix_len_out[s] = P; }
     return;
   }
-  int n_acc = a.accept_len[b];
+  const int n_acc = a.accept_len[b];
+  int node = 0;      // slot tid: the root, then the path
+  if (tid > 0 && tid <= a.max_depth) node = a.path_nodes[(long long)b * a.max_depth + tid - 1];
   if (n_acc < 0 || n_acc > a.max_depth) {
     if (reporter) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); a.prefix_len_out[s] = P; }
     return;
@@ -39,24 +53,36 @@ __global__ __launch_bounds__(256) void kv_commit_kernel(CommitParams p) {
     return;
   }
   if (reporter) a.prefix_len_out[s] = P + 1 + n_acc;
-  if (j > n_acc) return;
-  const int base = a.node_off[s], n_tree = a.node_off[s + 1] - base;
-  const int node = (j == 0) ? 0 : a.path_nodes[(long long)b * a.max_depth + (j - 1)];
-  if (node < 0 || node >= n_tree || base < 0 || base + node >= a.n_nodes_total) {
-    if (layer == 0 && tid == 0) atomicOr(p.dev_status, CASCADE_FLAG_PATH);
-    return;
+  if (tid <= n_acc) {   // at most CASCADE_MAX_DEPTH + 1 slots
+    if (node < 0 || node >= n_tree || base < 0 || base + node >= a.n_nodes_total) {
+      if (layer == 0 && blockIdx.z == 0) atomicOr(p.dev_status, CASCADE_FLAG_PATH);
+      node = -1;
+    }
+    s_node[tid] = node;
   }
-  const long long src_off = (long long)layer * p.tree_layer_vec + (long long)(base + node) * p.row_vec;
-  const long long dst_off = (long long)layer * p.sl + (long long)s * p.sr + (long long)(P + j) * p.sp;
-  const u32x4* ks = (const u32x4*)a.k_tree + src_off;
-  const u32x4* vs = (const u32x4*)a.v_tree + src_off;
-  u32x4* kd = (u32x4*)a.k_cache + dst_off;
-  u32x4* vd = (u32x4*)a.v_cache + dst_off;
-  for (int i = tid; i < p.row_vec; i += 256) {
-    const int head = i / p.head_vec, within = i - head * p.head_vec;
-    const u32x4 kx = ks[i], vx = vs[i];
-    kd[(long long)head * p.sh + within] = kx;
-    vd[(long long)head * p.sh + within] = vx;
+  __syncthreads();
+  const u32x4* src = (const u32x4*)(values ? a.v_tree : a.k_tree) + (long long)layer * p.tree_layer_vec + (long long)base * p.row_vec;
+  u32x4* dst = (u32x4*)(values ? a.v_cache : a.k_cache) + (long long)layer * p.sl + (long long)s * p.sr + (long long)P * p.sp;
+  const int v0 = part * p.part_vec, n_vec = min(p.part_vec, p.row_vec - v0), total = (1 + n_acc) * n_vec;   // n_vec >= 1
+  for (int i0 = tid; i0 < total; i0 += COMMIT_THREADS * COMMIT_FLIGHT) {
+    u32x4 x[COMMIT_FLIGHT];
+    long long to[COMMIT_FLIGHT];
+#pragma unroll
+    for (int u = 0; u < COMMIT_FLIGHT; ++u) {
+      const unsigned i = i0 + u * COMMIT_THREADS;
+      to[u] = -1;
+      if ((int)i < total) {
+        const unsigned slot = i / (unsigned)n_vec, v = v0 + i - slot * n_vec, head = v / (unsigned)p.head_vec;
+        const int nd = s_node[slot];
+        if (nd >= 0) {
+          x[u] = src[(long long)nd * p.row_vec + v];
+          to[u] = (long long)slot * p.sp + (long long)head * p.sh + (v - head * p.head_vec);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < COMMIT_FLIGHT; ++u)
+      if (to[u] >= 0) __builtin_nontemporal_store(x[u], dst + to[u]);
   }
 }
 
@@ -74,8 +100,11 @@ hipError_t launch_kv_commit(cascade_ctx* ctx, const kv_commit_args* a) {
   p.sh = a->cache_stride_head * e / 16;
   p.sp = a->cache_stride_pos * e / 16;
   p.tree_layer_vec = (long long)a->n_nodes_total * p.row_vec;
-  dim3 grid((unsigned)(a->n_rows * (a->max_depth + 1)), (unsigned)a->n_layers);
+  // 2 KiB of every node row per workgroup: 47 MB (30 layers x 16 rows x 8 KiB) 11.8 us with parts of 2 or 4 KiB, 12.7 with whole rows
+  p.part_vec = p.row_vec < 128 ? p.row_vec : 128;
+  const int parts = (p.row_vec + p.part_vec - 1) / p.part_vec;
+  dim3 grid((unsigned)a->n_rows, (unsigned)a->n_layers, 2u * parts);
   KernelTimer t(ctx, CASCADE_K_COMMIT);
-  CASCADE_TIMED_LAUNCH(t, kv_commit_kernel, grid, dim3(256), 0, ctx->stream, p);
+  CASCADE_TIMED_LAUNCH(t, kv_commit_kernel, grid, dim3(COMMIT_THREADS), 0, ctx->stream, p);
   return hipGetLastError();
 }
