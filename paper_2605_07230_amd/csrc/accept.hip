@@ -98,15 +98,15 @@ template <> struct Piece<uint16_t> {
     for (int i = 0; i < 4; ++i) { x[2 * i] = __uint_as_float(w[i] << 16); x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
   }
 };
-// sums over this thread's share of the row (NT threads): s[2 j] = a.x_j, s[2 j + 1] = x_j.x_j, s[2 G] = a.a
+// sums over this thread's share of elements h0 .. h - 1 of the row (NT threads): s[2 j] = a.x_j, s[2 j + 1] = x_j.x_j, s[2 G] = a.a
 template <int G, int NT, typename T>
-__device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], int h, bool aligned, int tid, float (&s)[2 * G + 1]) {
+__device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], int h0, int h, bool aligned, int tid, float (&s)[2 * G + 1]) {
   constexpr int N = Piece<T>::N;
 #pragma unroll
   for (int j = 0; j < 2 * G + 1; ++j) s[j] = 0.f;
   if (aligned) {
 #pragma unroll 2
-    for (int k = tid * N; k < h; k += NT * N) {   // h is a multiple of N
+    for (int k = h0 + tid * N; k < h; k += NT * N) {   // h0 and h are multiples of N
       float av[N], xv[G][N];
       Piece<T>::get(a + k, av);
 #pragma unroll
@@ -119,7 +119,7 @@ __device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], in
       }
     }
   } else {
-    for (int k = tid; k < h; k += NT) {
+    for (int k = h0 + tid; k < h; k += NT) {
       const float av = load_f32(a + k);
       s[2 * G] = fmaf(av, av, s[2 * G]);
 #pragma unroll
@@ -134,9 +134,16 @@ __device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], in
 
 constexpr int MAXO = 2 * MAXW;   // others of a node: parent + (siblings - 1) + children <= 1 + 63 + 64
 
+// Where the workgroups of one node meet (wide rows): a counter that is zero between calls, and the partial sums.
+struct AcceptShare {
+  int* arrived;                 // [nodes]
+  unsigned long long* sums;     // [nodes][parts][MAXO + 1]: a.x and x.x of every other row, a.a
+};
+
 template <typename T, int NT, bool NARROW_ROWS>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
-__global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev_status) {
-  __shared__ float gq[4][256];          // K-quarter partial Gram tiles; generic path: the waves' partial sums
+__global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptShare share, int* dev_status) {
+  constexpr int NWV = NT / 64;
+  __shared__ float gq[NWV][256];        // the waves' partial Gram tiles over their parts of K; generic path: their partial sums
   __shared__ float s_cos[MAXO];         // cos(a, other)
   __shared__ int s_other[MAXO];         // node index of every other row: parent, siblings (without a), children
   __shared__ int s_stok[MAXW], s_ctok[MAXW];   // tokens of the siblings (by rank, a included) and of the children
@@ -144,12 +151,12 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
   __shared__ float s_sq[MAXW], s_cq[MAXW];     // their probabilities under the parent's distribution
   __shared__ int s_ks, s_kc, s_rank;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.y, node = blockIdx.x;
+  const int b = blockIdx.z, node = blockIdx.y, n_grid = gridDim.y;
   const int lo = a.node_off[b], Tn = a.node_off[b + 1] - lo;
-  if (node == 0 && Tn > (int)gridDim.x) {
+  if (node == 0 && Tn > n_grid) {
     // the launch was sized for smaller trees: the nodes beyond it are flagged and written as zeros
     if (tid == 0) atomicOr(dev_status, CASCADE_FLAG_TREE_SIZE);
-    for (int j = (int)gridDim.x + tid; j < Tn && lo + j < a.n_nodes_total; j += NT) {
+    for (int j = n_grid + tid; j < Tn && lo + j < a.n_nodes_total; j += NT) {
       a.q_tok[lo + j] = 0.f; a.m_int[lo + j] = 0.f; a.cos_parent[lo + j] = 0.f; a.n_int[lo + j] = 0;
       a.m_conv[lo + j] = 0.f; a.n_conv[lo + j] = 0;
     }
@@ -257,15 +264,15 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
     if ((h & 127) == 0) {
       mfma_done = true;
       const int l16 = lane & 15, g = lane >> 4;
-      const int kq = h / 4;   // a multiple of 32
+      const int kq = h / NWV;   // a multiple of 32
       for (int blk = 0; blk * 15 < n_other; ++blk) {
         // tile rows: 0 = a, 1..15 = others 15 blk .. 15 blk + 14 (clamped: extra rows repeat the last one)
         const int o = 15 * blk + l16 - 1;
         const uint16_t* ra = l16 == 0 ? (const uint16_t*)row_a
                                       : (const uint16_t*)(H + (int64_t)(lo + s_other[min(o, n_other - 1)]) * h);
         f32x4 acc;
-        if (kq == 1024) {   // hidden = 4096: the whole quarter row in flight at once
-          acc = gram_tile_deep<32>(ra, wave * kq, g, [&]() { if (blk == 0) request_q(); });
+        if (h == 4096) {   // the wave's whole part in flight at once
+          acc = gram_tile_deep<128 / NWV>(ra, wave * kq, g, [&]() { if (blk == 0) request_q(); });
           if (blk == 0) finish_q();
         } else {
           acc = gram_tile(ra, ra, true, wave * kq, (wave + 1) * kq, g);
@@ -278,9 +285,9 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
         if (tid >= 1 && tid < 16 && 15 * blk + tid - 1 < n_other) {
           // row 0 of the tile: a . x_j ; diagonal: |x_j|^2 ; entry (0, 0): |a|^2
           const int j = tid;
-          const float ax = ((gq[0][j] + gq[1][j]) + gq[2][j]) + gq[3][j];
-          const float xx = ((gq[0][17 * j] + gq[1][17 * j]) + gq[2][17 * j]) + gq[3][17 * j];
-          const float aa = ((gq[0][0] + gq[1][0]) + gq[2][0]) + gq[3][0];
+          float ax = gq[0][j], xx = gq[0][17 * j], aa = gq[0][0];
+#pragma unroll
+          for (int w = 1; w < NWV; ++w) { ax += gq[w][j]; xx += gq[w][17 * j]; aa += gq[w][0]; }
           s_cos[15 * blk + j - 1] = cos_from(ax, aa, xx);
         }
       }
@@ -296,7 +303,7 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
         for (int j = 0; j < WG; ++j)   // past the end: the last one again
           x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
         float s[2 * WG + 1];
-        dot_group<WG, 64>(row_a, x, h, aligned, lane, s);
+        dot_group<WG, 64>(row_a, x, 0, h, aligned, lane, s);
         const float aa = wave_sum(s[2 * WG]);
 #pragma unroll
         for (int j = 0; j < WG; ++j) {
@@ -305,31 +312,63 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
         }
       }
     } else {
-      float* part = &gq[0][0];   // [NT / 64 waves][2 DG + 1]
-      static_assert(NT / 64 * (2 * DG + 1) <= 1024, "partial sums fit");
+      float* part = &gq[0][0];   // [NWV waves][2 DG + 1]
+      static_assert(NWV * (2 * DG + 1) <= NWV * 256, "partial sums fit");
+      // Wide rows: gridDim.x workgroups, dealt to different XCDs, take the same part of every node's elements, leave their sums in memory that all XCDs see
+      // (agent-scope accesses go past their L2s) and count themselves in; the one that arrives last adds the parts up in their
+      // order and goes on, the others are done.  No workgroup ever waits for another.
+      const int parts = gridDim.x, width = ((h + parts - 1) / parts + 63) & ~63;
+      const int h0 = min((int)blockIdx.x * width, h), h1 = min(h0 + width, h);
+      unsigned long long* const shared = share.sums + (gi * parts + blockIdx.x) * (MAXO + 1);
+      auto pair = [](float x, float y) { return (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32); };
       for (int o0 = 0; o0 < n_other; o0 += DG) {
         const T* x[DG];
 #pragma unroll
         for (int j = 0; j < DG; ++j)   // past the end: the last one again
           x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
         float s[2 * DG + 1];
-        dot_group<DG, NT>(row_a, x, h, aligned, tid, s);
+        dot_group<DG, NT>(row_a, x, h0, h1, aligned, tid, s);
         if (o0 > 0) __syncthreads();   // the previous group's sums have been consumed
 #pragma unroll
-        for (int j = 0; j < 2 * DG + 1; ++j) {
-          const float t = wave_sum(s[j]);
-          if (lane == 0) part[wave * (2 * DG + 1) + j] = t;
-        }
+        for (int j = 0; j < 2 * DG + 1; ++j) s[j] = wave_sum(s[j]);
+        if (lane == 0)
+#pragma unroll
+          for (int j = 0; j < 2 * DG + 1; ++j) part[wave * (2 * DG + 1) + j] = s[j];
         __syncthreads();
         if (tid < DG && o0 + tid < n_other) {
           float ax = 0.f, xx = 0.f, aa = 0.f;
-          for (int w = 0; w < NT / 64; ++w) {
+          for (int w = 0; w < NWV; ++w) {
             const float* q = part + w * (2 * DG + 1);
             ax += q[2 * tid];
             xx += q[2 * tid + 1];
             aa += q[2 * DG];
           }
-          s_cos[o0 + tid] = cos_from(ax, aa, xx);
+          if (parts == 1) s_cos[o0 + tid] = cos_from(ax, aa, xx);
+          else {
+            __hip_atomic_store(shared + o0 + tid, pair(ax, xx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (o0 + tid == 0) __hip_atomic_store(shared + MAXO, pair(aa, 0.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+      if (parts > 1) {
+        __shared__ int s_before;
+        if (wave == 0) {   // the wave that stored the sums
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          if (lane == 0) s_before = __hip_atomic_fetch_add(share.arrived + gi, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        if (s_before != parts - 1) return;
+        if (tid == 0) __hip_atomic_store(share.arrived + gi, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
+        if (tid < n_other) {
+          float ax = 0.f, xx = 0.f, aa = 0.f;
+          for (int q = 0; q < parts; ++q) {
+            const unsigned long long* from = share.sums + (gi * parts + q) * (MAXO + 1);
+            const unsigned long long v = __hip_atomic_load(from + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            aa += __uint_as_float((unsigned)__hip_atomic_load(from + MAXO, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            ax += __uint_as_float((unsigned)v);
+            xx += __uint_as_float((unsigned)(v >> 32));
+          }
+          s_cos[tid] = cos_from(ax, aa, xx);
         }
       }
     }
@@ -388,11 +427,24 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, int* dev
 
 hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   KernelTimer t(ctx, CASCADE_K_ACCEPT);
-  dim3 grid(ctx->lim.max_nodes_per_tree, a->n_prompts);
+  dim3 grid(1, ctx->lim.max_nodes_per_tree, a->n_prompts);
   const bool bf16 = a->h_dtype == CASCADE_BF16, mfma = bf16 && a->hidden % 128 == 0;
   const bool aligned = (a->hidden * (bf16 ? 2 : 4)) % 16 == 0 && ((uintptr_t)a->h_cond & 15) == 0;
   const bool narrow = !mfma && a->hidden <= (aligned ? NARROW : NARROW / 8);
-#define CASCADE_LAUNCH_ACCEPT(T, NT, N) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, N>), grid, dim3(NT), 0, ctx->stream, *a, ctx->dev_status)
+  // Rows of 16 KiB and more that the vector ALU sweeps: a node with many relatives reads 20 of them and more, through one compute
+  // unit.  Parts of at least 8 KiB, two workgroups per compute unit (what its registers hold).  120 nodes x 16384 floats: 22.3 us
+  // whole (the median node 8.4), 17.6 in two parts, 15.5 in four, 20 in eight (two rounds).
+  AcceptShare share = {(int*)ctx->accept_ws, (unsigned long long*)(ctx->attn_ws)};
+  int parts = 1;
+  if (!mfma && !narrow && a->n_nodes_total <= ctx->lim.max_nodes_total) {
+    const int64_t by_bytes = (int64_t)a->hidden * (bf16 ? 2 : 4) / 8192, by_room = 2 * ctx->n_cu / a->n_nodes_total;
+    const int64_t by_space = ctx->attn_ws_bytes / ((int64_t)a->n_nodes_total * (MAXO + 1) * 8);   // the partials of attention are dead by now
+    const int64_t n = by_bytes < by_room ? by_bytes : by_room, m = n < by_space ? n : by_space;
+    parts = m < 1 ? 1 : (m > 8 ? 8 : (int)m);
+  }
+  grid.x = parts;
+  // (Gram tiles on eight waves: 462 nodes 10.2 -> 12.1 us, 1024 nodes 18 -> 23.6, fewer nodes the same)
+#define CASCADE_LAUNCH_ACCEPT(T, NT, N) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, N>), grid, dim3(NT), 0, ctx->stream, *a, share, ctx->dev_status)
   if (bf16) { if (narrow) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, true); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, false); }
   else { if (narrow) CASCADE_LAUNCH_ACCEPT(float, 512, true); else CASCADE_LAUNCH_ACCEPT(float, 512, false); }
 #undef CASCADE_LAUNCH_ACCEPT

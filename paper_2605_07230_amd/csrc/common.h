@@ -22,6 +22,7 @@ struct cascade_ctx {
   char* hpack_ws;         // hidden states repacked into MFMA operand order, cond then uncond
   size_t hpack_ws_bytes;
   char* select_ws;        // select_path: counters (zero between calls) and chunk sums of prompts shared by several workgroups
+  char* accept_ws;        // cascade_accept: a counter per node, zero between calls
   // optional per-kernel timing with HIP events on the ctx stream (cascade_set_kernel_timing)
   bool timing;
   hipEvent_t* ev;         // [CASCADE_K_COUNT][TIMING_RING][2], created on first enable
