@@ -175,6 +175,11 @@ __global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__
 // lane l's 16 bytes at 16 l, so bank conflicts are avoided by WHICH piece a lane fetches: slot q of row r holds piece
 // q ^ ((r >> 1) & 7), and the 16 rows that a fragment read touches together land in 16 different 16-byte slots.  Packed
 // weights (contiguous 1 KiB operand blocks) are 4 us faster than row-major ones at 16384 x 4096.
+// Weights are streamed (nt): a step reads them once, or once per row tile at the same time, and everything else it touches
+// would be displaced from the caches by them.  Steps over weights that the caches do not hold yet: 60 rows x 16384 28.9 ->
+// 25.9 us, 60 x 65536 103.8 -> 92.7 (5.8 TB/s), 60 guidance pairs, row-major 40.7 -> 38.1, and the kernels after it find
+// their rows again (whole step of 60 x 16384: 66 -> 58).  The same 134 MB called again and again with nothing in between would
+// be kept by the last-level cache otherwise (23.5 us, streamed 26); other layers' weights lie between two steps of a model.
 // Measured against the kernels this replaced (64 x 64 tiles, operands loaded to registers, hidden 4096; us, without the
 // packing pass of 4 us that they needed): 60 rows x 16384: 30.2 -> 27.4; 60 x 65536: 110 -> 101 (5.3 TB/s);
 // 120 x 16384: 45 -> 35; 230 x 16384: 75 -> 45; 60 guidance pairs, row-major weights: 63 -> 37.
@@ -188,7 +193,8 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   static_assert(WM * WN * KW == 8 && KS % KW == 0 && KS % 4 == 0 && (!CFG || AM == 2), "eight waves; guidance pairs are a wave's two row blocks");
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NA = BM / 32, NBLK = NA + BN / 32, STAGE = NBLK * KS * 1024;
   constexpr int LPW = NBLK * KS / 8, SPW = KS / KW;
-  static_assert(NBLK * KS % 8 == 0, "every wave requests the same number of 1 KiB chunks");
+  constexpr int LPA = NA * KS / 8;   // a wave's requests of a stage: LPA of rows, then of weights
+  static_assert(NA * KS % 8 == 0 && NBLK * KS % 8 == 0, "every wave requests the same number of 1 KiB chunks");
   extern __shared__ __align__(1024) char ring_lds[];   // [NST stages][NBLK blocks][KS KiB]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -199,16 +205,18 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   const int logical = xcd * (nwg >> 3) + min(xcd, nwg & 7) + (blockIdx.x >> 3);
   const int nt = logical / n_mtiles, mt = logical % n_mtiles;
 
-  // loader: chunk id = LPW wave + i of a stage: block id / KS, KiB id % KS of it (one k16 step of packed operands, or
-  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece)
+  // loader: request i of a wave is chunk id of a stage: block id / KS, KiB id % KS of it (one k16 step of packed operands, or
+  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece).  Which requests are weights is
+  // known at compile time: they are streaming (nt) loads, see above.
+  auto chunk = [&](int i) { return i < LPA ? wave * LPA + i : NA * KS + wave * (LPW - LPA) + (i - LPA); };
   unsigned voff[LPW];
   const char* src[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    const int id = wave * LPW + i, blk = id / KS, q = id % KS;
+    const int id = chunk(i), blk = id / KS, q = id % KS;
     const char* base;
     int row0, rows;
-    if (blk < NA) {
+    if (i < LPA) {
       base = (const char*)((CFG && (blk & 1)) ? p.h_uncond : p.h_cond);
       row0 = CFG ? mt * (BM / 2) + 32 * (blk >> 1) : mt * BM + 32 * blk;
       rows = p.n_nodes;
@@ -217,7 +225,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       row0 = p.col0 + nt * BN + 32 * (blk - NA);
       rows = p.vocab;
     }
-    if (PW && blk >= NA) {
+    if (PW && i >= LPA) {
       src[i] = base + ((int64_t)min(row0 / 32, rows / 32 - 1) * (K / 16) + q) * 1024;   // columns past the end: clamped, never stored
       voff[i] = 16u * lane;
     } else {
@@ -226,20 +234,21 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       voff[i] = (unsigned)(min(row0 + lr, rows - 1) - first) * (unsigned)(2 * K) + 16u * (unsigned)((lane & 7) ^ ((lr >> 1) & 7));
     }
   }
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)ring_lds) + wave * LPW * 1024;
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)ring_lds);
   u32x4 held[DIRECT ? 1 : LPW];   // (ordinary loads) the stage on its way
   auto store_held = [&](int slot) {   // complete before the next barrier, which waits for the wave's LDS operations
 #pragma unroll
-    for (int i = 0; i < (DIRECT ? 0 : LPW); ++i) *(u32x4*)(ring_lds + (wave * LPW + i) * 1024 + slot * STAGE + 16 * lane) = held[i];
+    for (int i = 0; i < (DIRECT ? 0 : LPW); ++i) *(u32x4*)(ring_lds + chunk(i) * 1024 + slot * STAGE + 16 * lane) = held[i];
   };
   auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
     const int tc = min(t, n_stages - 1);
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
-      const char* g = src[i] + (int64_t)tc * ((PW && (wave * LPW + i) / KS >= NA) ? KS * 1024 : KS * 32);
+      const char* g = src[i] + (int64_t)tc * ((PW && i >= LPA) ? KS * 1024 : KS * 32);
       if constexpr (!DIRECT) { __builtin_memcpy(&held[i], g + voff[i], 16); continue; }
-      const unsigned l = lds0 + slot * STAGE + i * 1024;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
+      const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
+      if (i < LPA) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
+      else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
     }
   };
   const int kw = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
@@ -404,7 +413,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
   const int last = n_half - 1;
-  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd).  h may run past the end:
+  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd, streamed like the ring kernel's: 1 % at 256 to 1024 rows x 65536).  h may run past the end:
   // clamped, that data is never multiplied.  M0 carries the LDS address of the wave's 1 KiB block;
   // each lane's 16 bytes land at 16 * lane behind it.
   auto request = [&](int h, int buf, int i) {
@@ -413,7 +422,8 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
     const char* g = src[i & 1] + ((int64_t)min(h, last) * HS + ks) * 1024;
     const int slot = (i & 1) ? 8 + wave : (HALF ? (wave & 3) : wave);
     const unsigned l = lds0 + buf * HBYTES + (ks * 16 + slot) * 1024;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
+    if (i & 1) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
   };
   // A wave's own loads of the next half-stage have landed when at most the 2 x 4 later ones are
   // outstanding; its LDS reads are complete at lgkmcnt(0).
