@@ -506,11 +506,18 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     if (tc < n_pt && (tc + 1) * KT <= P) {
       // a whole tile of the prefix: nothing to clamp, the per-lane offsets are constants
       const char* src = (is_v ? vc : kc) + (int64_t)tc * KT * cache_pitch_b;
+      if (stream) {
 #pragma unroll
-      for (int i = 0; i < CPW; ++i) {
-        const unsigned l = ldst + i * 1024;
-        if (stream) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
-        else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
+        for (int i = 0; i < CPW; ++i) {
+          const unsigned l = ldst + i * 1024;
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+          const unsigned l = ldst + i * 1024;
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
+        }
       }
     } else {
       const bool tree_tile = tc >= n_pt;
