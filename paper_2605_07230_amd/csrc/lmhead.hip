@@ -564,8 +564,13 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
   const int incl = wave_scan_incl_i(loc);
   if (lane == 63) s_wsum[wave] = incl;
   __syncthreads();
-  int before = incl - loc;
-  for (int w = 0; w < wave; ++w) before += s_wsum[w];
+  // lane l holds the sum of waves 0 .. l % 16
+  int upto = s_wsum[lane & 15];
+  upto += dpp_i32<0x111, 0xf>(0, upto);
+  upto += dpp_i32<0x112, 0xf>(0, upto);
+  upto += dpp_i32<0x114, 0xf>(0, upto);
+  upto += dpp_i32<0x118, 0xf>(0, upto);
+  int before = incl - loc + (wave > 0 ? __builtin_amdgcn_readlane(upto, __builtin_amdgcn_readfirstlane(wave - 1) & 15) : 0);
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
     if (before < k && before + hb[i] >= k) { *s_bin = NB - 1 - (BPT * tid + i); *s_above = before; }
@@ -584,16 +589,20 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // still arriving.  Any non-decreasing bin function keeps the selection exact: with `above` entries in the bins
 // over bin B and above < k <= above + hist[B], the k-th largest is the (k - above)-th largest of bin B.  A
 // second sweep over the registers re-evaluates the same fused multiply-add and files every entry of bin B or
-// higher (some k + a few dozen of them) into a small per-thread list in LDS; the candidates of bin B are then
-// ranked exactly by their integer keys, and only the listed entries see an exponential.
+// higher (some k + a few dozen of them) into a list of its wave in LDS, by ballots; the candidates of bin B are then
+// ranked exactly by their integer keys, and only the listed entries see an exponential - two rounds of a wave's lanes
+// for k = 2000, where one list per thread took as many as the fullest of 64 lists (6 to 8), and rows whose kept entries crowd
+// into some threads fell back.  What bounds a row once it is in registers is the instructions of its 16 waves and the
+// barriers between the stages.  60 rows x 16384 6.6 -> 6.0 us, 462 x 16384 15.3 -> 14.1, 343 x 33088 28.7 -> 21.8, 1024 x 65536
+// 76.6 -> 74.0.  (Two workgroups per compute unit, at 64 registers: 462 x 16384 16.3 us, spilled from 24576 entries on.)
 // Rows the fast path does not fit (degenerate or non-finite sample range, k-th largest in the lowest bin, more
-// than RS_CAND candidates, a thread with more than RS_CAP listed entries) take the radix rounds: slow, exact.
-constexpr int RS_CAP = 12;      // listed entries per thread
+// than RS_CAND candidates, a wave with more than RS_CAP - 64 listed entries) take the radix rounds: slow, exact.
+constexpr int RS_CAP = 768;     // listed entries per wave
 constexpr int RS_CAND = 1024;   // candidates ranked by counting
 constexpr int RS_PRE_OFFSET = 80 * 1024;   // 80 KiB prefetch buffer behind the structure below (1 KiB aligned)
 struct RowStatsSmem {
   int hist1[4096], hist2[1024], hist3[1024];
-  float priv[RS_CAP * 1024];    // entry j of thread t at [j * 1024 + t]
+  float list[16 * RS_CAP];      // entry j of wave w at [w * RS_CAP + j]
   float cand[RS_CAND];
   float f_rng[32], f_max[16], f_sum[16];
   int s_wsum[16];
@@ -747,13 +756,11 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     mx = wave_max(mx);
     if (lane == 0) sm.f_max[wave] = mx;
     __syncthreads();                       // maxima and every atomic of the sweep
-    mx = sm.f_max[0];
-#pragma unroll
-    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sm.f_max[w]);
 
     float thr = -INFINITY, se = 0.f;
     bool done = false;
-    int cnt = 0, B = 0, n_c = 0, k = p.top_k;
+    int n_list = 0, B = 0, n_c = 0, k = p.top_k;   // n_list: entries listed by this wave
+    float* const list = sm.list + wave * RS_CAP;
     if (fast) {
       find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       B = sm.s_bin;
@@ -761,26 +768,33 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
       k -= sm.s_above;                     // rank of the k-th largest inside bin B, 1 = largest
       if (B > 0 && n_c <= RS_CAND) {       // workgroup-uniform
         const float Bf = (float)B;
+        int most = 0;
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
-          if (fmaf(x[i], bs, bc) >= Bf) {  // bin(x) >= B (B >= 1: the clamp at 0 plays no part; the one at 4095 cannot matter)
-            if (cnt < RS_CAP) sm.priv[cnt * 1024 + tid] = x[i];
-            ++cnt;
-          }
+          const bool hit = fmaf(x[i], bs, bc) >= Bf;   // bin(x) >= B (B >= 1: the clamp at 0 plays no part; the one at 4095 cannot matter)
+          const unsigned long long m = __ballot(hit);
+          const int at = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_list));
+          if (hit) list[at] = x[i];
+          n_list += __popcll(m);
+          most = max(most, n_list);
+          n_list = min(n_list, RS_CAP - 64);           // room for the next 64
           if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        if (cnt > RS_CAP) sm.flag = 1;
+        if (most > RS_CAP - 64 && lane == 0) sm.flag = 1;
         __syncthreads();
         done = sm.flag == 0;
       }
     }
     // The registers are free (the rounds below re-read the row): the next row arrives during this row's tail.
     if (next < p.n_nodes) load_row(next);
+    mx = sm.f_max[0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sm.f_max[w]);
     if (done) {
       // listed entries: above bin B -> kept; in bin B -> candidate
       const float B1f = (float)(B + 1);
-      for (int j = 0; j < cnt; ++j) {
-        const float xv = sm.priv[j * 1024 + tid];
+      for (int j = lane; j < n_list; j += 64) {
+        const float xv = list[j];
         if (B < 4095 && fmaf(xv, bs, bc) >= B1f) se += __expf(xv - mx);
         else sm.cand[atomicAdd(&sm.n_cand, 1)] = xv;
       }
