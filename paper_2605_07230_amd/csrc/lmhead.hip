@@ -24,6 +24,7 @@ struct LmParams {
   int col0;                 // first vocabulary column of the launch
   float cfg_scale, temperature;
   int top_k;
+  bool stream_w;            // weights are loaded past the caches
 };
 
 // ------------------------------------------------------------------------------------------ f32
@@ -175,11 +176,10 @@ __global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__
 // lane l's 16 bytes at 16 l, so bank conflicts are avoided by WHICH piece a lane fetches: slot q of row r holds piece
 // q ^ ((r >> 1) & 7), and the 16 rows that a fragment read touches together land in 16 different 16-byte slots.  Packed
 // weights (contiguous 1 KiB operand blocks) are 4 us faster than row-major ones at 16384 x 4096.
-// Weights are streamed (nt): a step reads them once, or once per row tile at the same time, and everything else it touches
+// Large weights are streamed (nt): a step reads them once, or once per row tile at the same time, and everything else it touches
 // would be displaced from the caches by them.  Steps over weights that the caches do not hold yet: 60 rows x 16384 28.9 ->
 // 25.9 us, 60 x 65536 103.8 -> 92.7 (5.8 TB/s), 60 guidance pairs, row-major 40.7 -> 38.1, and the kernels after it find
-// their rows again (whole step of 60 x 16384: 66 -> 58).  The same 134 MB called again and again with nothing in between would
-// be kept by the last-level cache otherwise (23.5 us, streamed 26); other layers' weights lie between two steps of a model.
+// their rows again (whole step of 60 x 16384: 66 -> 58).  LM_STREAM_BYTES says from which size on.
 // Measured against the kernels this replaced (64 x 64 tiles, operands loaded to registers, hidden 4096; us, without the
 // packing pass of 4 us that they needed): 60 rows x 16384: 30.2 -> 27.4; 60 x 65536: 110 -> 101 (5.3 TB/s);
 // 120 x 16384: 45 -> 35; 230 x 16384: 75 -> 45; 60 guidance pairs, row-major weights: 63 -> 37.
@@ -242,13 +242,27 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   };
   auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
     const int tc = min(t, n_stages - 1);
+    auto from = [&](int i) { return src[i] + (int64_t)tc * ((PW && i >= LPA) ? KS * 1024 : KS * 32); };
+    if constexpr (!DIRECT) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      const char* g = src[i] + (int64_t)tc * ((PW && i >= LPA) ? KS * 1024 : KS * 32);
-      if constexpr (!DIRECT) { __builtin_memcpy(&held[i], g + voff[i], 16); continue; }
+      for (int i = 0; i < LPW; ++i) __builtin_memcpy(&held[i], from(i) + voff[i], 16);
+      return;
+    }
+    auto load = [&](int i) {
       const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
-      if (i < LPA) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
-      else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(from(i)) : "memory");
+    };
+#pragma unroll
+    for (int i = 0; i < LPA; ++i) load(i);
+    if (p.stream_w) {
+#pragma unroll
+      for (int i = LPA; i < LPW; ++i) {
+        const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff[i]), "s"(from(i)) : "memory");
+      }
+    } else {
+#pragma unroll
+      for (int i = LPA; i < LPW; ++i) load(i);
     }
   };
   const int kw = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
@@ -413,7 +427,8 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
   const int last = n_half - 1;
-  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd, streamed like the ring kernel's: 1 % at 256 to 1024 rows x 65536).  h may run past the end:
+  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd).  Half tiles stream W like the ring
+  // kernel (480 rows x 16384 x 1024 to 4096: 25.9 -> 25.1 us, 40.7 -> 38.7, 69 -> 67), whole ones do not (400 rows x 65536 x 2048 122 -> 129).  h may run past the end:
   // clamped, that data is never multiplied.  M0 carries the LDS address of the wave's 1 KiB block;
   // each lane's 16 bytes land at 16 * lane behind it.
   auto request = [&](int h, int buf, int i) {
@@ -422,7 +437,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
     const char* g = src[i & 1] + ((int64_t)min(h, last) * HS + ks) * 1024;
     const int slot = (i & 1) ? 8 + wave : (HALF ? (wave & 3) : wave);
     const unsigned l = lds0 + buf * HBYTES + (ks * 16 + slot) * 1024;
-    if (i & 1) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
+    if (HALF && (i & 1)) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
   };
   // A wave's own loads of the next half-stage have landed when at most the 2 x 4 later ones are
@@ -874,6 +889,12 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   }
 }
 
+// Weights from this size on are streamed (see the ring kernel): a third of the last-level cache.  A step of 60 nodes whose
+// weights no cache holds, default policy and streamed: 8192 x 4096 (67 MB) 56.8 and 52.1 us, 16384 x 3072 (101 MB) 59 and 53, 16384 x
+// 4096 63 and 56, 40000 x 4096 111 and 100.  Three smaller matrices used in turn stay in the cache together: 4096 x 2048 38.0 and
+// 41.1, 8192 x 4096 49.5 and 52.2, but 16384 x 3072 57 and 53.
+constexpr int64_t LM_STREAM_BYTES = (int64_t)85 << 20;
+
 LmParams make_params(const lmhead_args* a) {
   LmParams p;
   p.h_cond = a->h_cond;
@@ -892,6 +913,7 @@ LmParams make_params(const lmhead_args* a) {
   p.cfg_scale = a->cfg_scale;
   p.temperature = a->temperature;
   p.top_k = a->top_k;
+  p.stream_w = a->dtype == CASCADE_BF16 && (int64_t)a->vocab * a->hidden * 2 >= LM_STREAM_BYTES;
   return p;
 }
 
