@@ -939,7 +939,7 @@ hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a) {
 }
 
 template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT = true>
-hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols) {
+hipError_t launch_ring_t(cascade_ctx* ctx, LmParams p, int n_cols) {
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NODES = CFG ? BM / 2 : BM;
   constexpr int RING = NST * (BM + BN) / 32 * KS * 1024, RED = KW > 1 ? 8 * AM * AN * 4096 : 0;
   constexpr int smem = RING > RED ? RING : RED;
@@ -952,6 +952,9 @@ hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols) {
     attr_done = true;
   }
   const int n_mtiles = (p.n_nodes + NODES - 1) / NODES;
+  // three row tiles and more that share a column of weights are bound by the matrix cores: 343 pairs x 33088 x 2048 the same
+  // over cold weights (122 us), 116 against 122 where the cache holds them
+  p.stream_w = p.stream_w && n_mtiles <= 2;
   KernelTimer t(ctx, CASCADE_K_LMHEAD);
   CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
