@@ -864,6 +864,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams
 // one key row per lane), V goes through a wave-private LDS region only to be read back transposed.
 // No workgroup barrier inside the tile loop; the eight (m, l, O) partials are merged through LDS at
 // the end.  Keys and values are read by every query block of a (row, kv head) - from L2.
+// What bounds it is the chain of one wave: lookups, queries, its tile, the merge.  Parents in the lanes of the wave that owns a
+// tree tile, no division where heads are not grouped and no barrier before the merge: 2 rows x 312 keys, 60 nodes 11.4 -> 10.4 us.
 template <int D>
 __global__ __launch_bounds__(512) void attn_bf16_qsplit_kernel(AttnParams p) {
   constexpr int NWV = 8, NT = 512;
@@ -875,8 +877,6 @@ __global__ __launch_bounds__(512) void attn_bf16_qsplit_kernel(AttnParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
   uint16_t* vt = (uint16_t*)smem_raw + (size_t)wave * KT * VP;                         // this wave's V tile
-  int* s_parent = (int*)(smem_raw + (size_t)NWV * KT * VP * sizeof(uint16_t));         // [128]
-  unsigned long long* s_anc = (unsigned long long*)(s_parent + 128);                   // [2 tree tiles][16 rows]
 
   // the query blocks of a (row, kv head) share an L2
   const unsigned nx = gridDim.x, ny = gridDim.y;
@@ -925,50 +925,54 @@ __global__ __launch_bounds__(512) void attn_bf16_qsplit_kernel(AttnParams p) {
       vr[it] = *(const u32x4*)(vsrc + (int64_t)min(key, last) * pitch + 8 * dc);
     }
   };
-  for (int i = tid; i < T; i += NT) {
-    int pi = p.parent[lo + i];
-    if (pi >= i || pi < -1 || (i == 0 && pi != -1) || (i > 0 && pi < 0)) {
-      atomicOr(p.dev_status, CASCADE_FLAG_PARENT);
-      pi = (i == 0) ? -1 : 0;
-    }
-    s_parent[i] = pi;
+  // The tree tile that this wave owns, if any (there are at most two, in consecutive waves): the wave takes the parents of the
+  // whole tree into its lanes and climbs there, so nothing is staged and no barrier stands in front of the tile loop.
+  const int t_tree = n_pt + ((wave - n_pt) & (NWV - 1));
+  const bool owns_tree = t_tree < nt;
+  int pa[2] = {-1, -1};
+  if (owns_tree) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) pa[j] = p.parent[lo + min(64 * j + lane, T - 1)];
   }
 
-  // the workgroup's 16 query rows (B operand of S^T): lane = (query l16, d group g)
+  // the workgroup's 16 query rows (B operand of S^T): lane = (query l16, d group g); rows past the end repeat the last one,
+  // masked and never stored
   Frag8 qf[KS];
-  const int qr = row0 + l16;
-  const bool q_ok = qr < M;
-  const int qi = q_ok ? qr % T : 0, qh = q_ok ? qr / T : 0;
+  const bool q_ok = row0 + l16 < M;
+  const int qr = min(row0 + l16, M - 1);
+  const int qh = G == 1 ? 0 : qr / T, qi = qr - qh * T;
   const int64_t rowg = (int64_t)(lo + qi) * p.n_heads + kvh * G + qh;
   {
     const uint16_t* qp = (const uint16_t*)p.q + rowg * D + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (q_ok) qf[ks].u = *(const uint4*)(qp + 32 * ks);
-      else qf[ks].u = make_uint4(0, 0, 0, 0);
-    }
+    for (int ks = 0; ks < KS; ++ks) qf[ks].u = *(const uint4*)(qp + 32 * ks);
   }
   // The first tile is requested AFTER the parent and query loads: loads return in order, so the wait
-  // for the parent entry below then leaves the 32 tile loads in flight instead of draining them.
-  const bool has_keys = P > 0 || T > 0;   // T >= 1 for a row that reaches this point
-  if (wave < nt && has_keys) request_tile(wave);
-  __syncthreads();   // parent array complete
-  if (tid < 32) {
-    // ancestor-or-self bits of the (at most two) tree tiles for the 16 query rows
-    const int tt = tid >> 4, rr = row0 + (tid & 15), kbase = tt * KT;
-    unsigned long long wbits = 0ull;
-    if (rr < M && tt < n_tt) {
-      int a = rr % T, guard = 0;
-      while (a >= 0 && guard++ <= 128) {
-        const int rel = a - kbase;
-        if (rel < 0) break;
-        if (rel < 64) wbits |= 1ull << rel;
-        a = s_parent[a];
+  // for the parents below leaves the tile's loads in flight instead of draining them.
+  unsigned long long seen = 0ull;   // keys of the tree tile that query l16 sees: itself and its ancestors
+  if (wave < nt) {
+    request_tile(wave);
+    if (owns_tree) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int i = 64 * j + lane;
+        const bool bad = i < T && (i == 0 ? pa[j] != -1 : (pa[j] >= i || pa[j] < 0));
+        if (bad) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pa[j] = i == 0 ? -1 : 0; }   // keeps the climb finite
+      }
+      const int kbase = (t_tree - n_pt) * KT;
+      int a = q_ok ? qi : -1;
+      while (__any(a >= kbase)) {   // kbase >= 0; ancestors only get smaller
+        if (a >= kbase && a - kbase < 64) seen |= 1ull << (a - kbase);
+        const int at = 4 * (a & 63);
+        int up = __builtin_amdgcn_ds_bpermute(at, pa[0]);
+        if (T > 64) {
+          const int hi = __builtin_amdgcn_ds_bpermute(at, pa[1]);
+          up = a >= 64 ? hi : up;
+        }
+        a = a > 0 ? up : -1;
       }
     }
-    s_anc[tid] = wbits;
   }
-  __syncthreads();
 
   f32x4 ot[DB];
   float m_run = -INFINITY, l_run = 0.f;
@@ -1003,7 +1007,7 @@ __global__ __launch_bounds__(512) void attn_bf16_qsplit_kernel(AttnParams p) {
 
     unsigned long long valid;
     if (tree_tile) {
-      valid = s_anc[16 * (t - n_pt) + l16];
+      valid = seen;   // (the wave's only tree tile)
     } else {
       const int rem = klimit - kbase;
       valid = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
@@ -1235,7 +1239,7 @@ hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
 template <int D>
 hipError_t launch_qsplit_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int VP = D + 16;
-  const size_t smem = (size_t)8 * KT * VP * sizeof(uint16_t) + 128 * sizeof(int) + 32 * sizeof(unsigned long long);
+  const size_t smem = (size_t)8 * KT * VP * sizeof(uint16_t);
   static_assert(8 * 16 * (D + 4) * 4 + 8 * 16 * 2 * 4 <= 8 * KT * (D + 16) * 2, "merge buffers fit in the V tiles");
   static bool attr_done = false;
   if (!attr_done) {
