@@ -8,6 +8,10 @@
 // coalesced read of the drafter row, a workgroup sum and a rescale; an acceptance one read of the
 // new node's logits row.  All decisions are taken by every thread on the same broadcast scalars,
 // so control flow stays uniform.  The inverse CDF at the end runs over the same registers.
+// Bound by the chain of dependent trips to memory: the scalars of all nodes (and the drafter's probability of each node's
+// token) are fetched once, by a thread per node, and a child's drafter row is on its way while the child is tested.  In a step,
+// with a trip per tried child for each of these before: 60 nodes x 16384, four prompts 22.4 -> 15.7 us, 60 x 4096 10.7 -> 9.2,
+// 60 x 20480 50.6 -> 14.6 (also: a frame of its own up to 32768 entries), 60 x 65536 32.0 -> 25.7.
 #include "common.h"
 
 namespace {
@@ -36,6 +40,8 @@ template <int VQ, bool EXACT>
 __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, int* dev_status) {
   constexpr int SEG = 256 * VQ;
   __shared__ int s_child[CASCADE_MAX_WIDTH];
+  __shared__ int s_par[CASCADE_MAX_TREE], s_tok[CASCADE_MAX_TREE];                       // the tree's nodes
+  __shared__ float s_mi[CASCADE_MAX_TREE], s_mc[CASCADE_MAX_TREE], s_up[CASCADE_MAX_TREE];   // s_up: u times the drafter's probability
   __shared__ int s_path[CASCADE_MAX_DEPTH];
   __shared__ int s_m, s_x;
   __shared__ float s_q;
@@ -67,15 +73,41 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     }
   };
 
+  // the drafter row of a child, requested before it is known whether the child is rejected (frames of 8 and 16 vectors have no
+  // registers for it and read the row when they need it, twice)
+  constexpr bool AHEAD = VQ <= 4;
+  f32x4 pr[AHEAD ? VQ : 1];
+  auto load_draft = [&](int node) {
+    const float* prow = a.draft_dist + (int64_t)(lo + node) * V;
+#pragma unroll
+    for (int i = 0; i < (AHEAD ? VQ : 0); ++i) {
+      const int e = e_base + 256 * i;
+      pr[i] = *(const f32x4*)((const char*)prow + 4u * (unsigned)(EXACT ? e : min(e, V - 4)));
+      if (!EXACT && e >= V) pr[i] = f32x4{0.f, 0.f, 0.f, 0.f};   // f is 0 there as well
+    }
+  };
+
+  // Everything a tried child needs is fetched for all nodes at once: thread i is node i (a tree has at most 1024).
+  static_assert(CASCADE_MAX_TREE <= 64 * NW, "a thread per node");
+  if (tid < Tn) {
+    const int tok = a.token[lo + tid];
+    const float u = a.u[lo + tid];
+    s_par[tid] = a.parent[lo + tid];
+    s_mi[tid] = a.m_int[lo + tid];
+    s_mc[tid] = a.m_conv[lo + tid];
+    s_tok[tid] = tok;
+    s_up[tid] = u * (tok >= 0 && tok < V ? a.draft_dist[(int64_t)(lo + tid) * V + tok] : 1.f);
+  }
   int cur = 0, len = 0;
   float tvd = 0.f;
   load_target(0);
+  __syncthreads();
   while (true) {
     if (wave == 0) {   // ordered list of cur's children
       int k = 0;
       for (int base = (cur + 1) & ~63; base < Tn; base += 64) {
         const int j = base + lane;
-        const bool is = j < Tn && j > cur && a.parent[lo + j] == cur;
+        const bool is = j < Tn && j > cur && s_par[j] == cur;
         const unsigned long long m = __ballot(is);
         if (is) {
           const int idx = k + __popcll(m & ((1ull << lane) - 1ull));
@@ -92,9 +124,10 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     __syncthreads();
     const int m = s_m;
     int accepted = -1;
+    if (AHEAD && m > 0) load_draft(s_child[0]);
     for (int j = 0; j < m; ++j) {
       const int ch = s_child[j];
-      const int ta = a.token[lo + ch];
+      const int ta = s_tok[ch];
       const bool tok_ok = ta >= 0 && ta < V;
       const float* prow = a.draft_dist + (int64_t)(lo + ch) * V;
       if (tok_ok) {
@@ -113,22 +146,32 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
         s_q = 0.f;
       }
       __syncthreads();
-      const float px = tok_ok ? prow[ta] : 1.f;
-      const Try t = try_node(s_q, a.m_int[lo + ch], a.m_conv[lo + ch], a.u[lo + ch] * px, tvd, eps);
+      const Try t = try_node(s_q, s_mi[ch], s_mc[ch], s_up[ch], tvd, eps);
       tvd = t.tvd;
       if (t.pass) { accepted = ch; break; }
-      // rejected: f <- norm([f - p]_+), kept as it is when nothing would be left.  Two passes over the
-      // drafter row (the second one hits the cache) instead of a second register copy of f.
+      // rejected: f <- norm([f - p]_+), kept as it is when nothing would be left
       float loc = 0.f;
+      f32x4 left[AHEAD ? VQ : 1];
+      auto take_away = [&](int i, const f32x4& p4) {
+        f32x4 d;
 #pragma unroll
-      for (int i = 0; i < VQ; ++i) {
+        for (int c = 0; c < 4; ++c) d[c] = fmaxf(f[i][c] - p4[c], 0.f);
+        return d;
+      };
+      auto row_of = [&](int i) {
         const int e = e_base + 256 * i;
         f32x4 p4 = *(const f32x4*)((const char*)prow + 4u * (unsigned)(EXACT ? e : min(e, V - 4)));
         if (!EXACT && e >= V) p4 = f32x4{0.f, 0.f, 0.f, 0.f};   // f is 0 there as well
-        loc += ((fmaxf(f[i][0] - p4[0], 0.f) + fmaxf(f[i][1] - p4[1], 0.f)) + fmaxf(f[i][2] - p4[2], 0.f)) +
-               fmaxf(f[i][3] - p4[3], 0.f);
+        return p4;
+      };
+#pragma unroll
+      for (int i = 0; i < VQ; ++i) {
+        const f32x4 d = take_away(i, AHEAD ? pr[AHEAD ? i : 0] : row_of(i));
+        loc += ((d[0] + d[1]) + d[2]) + d[3];
+        if (AHEAD) left[AHEAD ? i : 0] = d;
         if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
+      if (AHEAD && j + 1 < m) load_draft(s_child[j + 1]);
       const float ws = wave_sum(loc);
       if (lane == 0) s_wsum[wave] = ws;
       __syncthreads();
@@ -138,11 +181,9 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
       if (Z > 0.f) {
         const float inv = 1.f / Z;
 #pragma unroll
-        for (int i = 0; i < VQ; ++i) {
-          const int e = e_base + 256 * i;
-          const f32x4 p4 = *(const f32x4*)((const char*)prow + 4u * (unsigned)(EXACT ? e : min(e, V - 4)));   // beyond V: f is 0 and stays 0
-#pragma unroll
-          for (int c = 0; c < 4; ++c) f[i][c] = fmaxf(f[i][c] - p4[c], 0.f) * inv;
+        for (int i = 0; i < VQ; ++i) {   // (the second read of the row hits the cache: no second register copy of f)
+          const f32x4 d = AHEAD ? left[AHEAD ? i : 0] : take_away(i, row_of(i));
+          f[i] = d * inv;
           if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -217,7 +258,7 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     a.path_nodes[(int64_t)b * a.max_depth + d] = d < len ? s_path[d] : -1;
   for (int d = tid; d <= a.max_depth; d += 1024) {
     int v = -1;
-    if (d < len) v = a.token[lo + s_path[d]];
+    if (d < len) v = s_tok[s_path[d]];
     else if (d == len) v = s_x;
     a.emitted[(int64_t)b * (a.max_depth + 1) + d] = v;
   }
@@ -238,6 +279,7 @@ hipError_t launch_select_residual(cascade_ctx* ctx, const select_args* a) {
   CASCADE_TIMED_LAUNCH(t, (select_residual_kernel<VQ, EX>), grid, dim3(1024), 0, ctx->stream, *a, ctx->dev_status)
   if (V <= 16 * 256) { if (V == 16 * 256) CASCADE_LAUNCH_RESIDUAL(1, true); else CASCADE_LAUNCH_RESIDUAL(1, false); }
   else if (V <= 16 * 1024) { if (V == 16 * 1024) CASCADE_LAUNCH_RESIDUAL(4, true); else CASCADE_LAUNCH_RESIDUAL(4, false); }
+  else if (V <= 16 * 2048) CASCADE_LAUNCH_RESIDUAL(8, false);
   else { if (V == 16 * 4096) CASCADE_LAUNCH_RESIDUAL(16, true); else CASCADE_LAUNCH_RESIDUAL(16, false); }
 #undef CASCADE_LAUNCH_RESIDUAL
   return hipGetLastError();
