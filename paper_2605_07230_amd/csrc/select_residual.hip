@@ -11,7 +11,8 @@
 // Bound by the chain of dependent trips to memory: the scalars of all nodes (and the drafter's probability of each node's
 // token) are fetched once, by a thread per node, and a child's drafter row is on its way while the child is tested.  In a step,
 // with a trip per tried child for each of these before: 60 nodes x 16384, four prompts 22.4 -> 15.7 us, 60 x 4096 10.7 -> 9.2,
-// 60 x 20480 50.6 -> 14.6 (also: a frame of its own up to 32768 entries), 60 x 65536 32.0 -> 25.7.
+// 60 x 20480 50.6 -> 14.6 (also: frames of its own up to 32768 and 49152
+// entries), 50 x 33088, two prompts 53.5 -> 26.2, 60 x 65536 32.0 -> 25.7.
 #include "common.h"
 
 namespace {
@@ -280,6 +281,7 @@ hipError_t launch_select_residual(cascade_ctx* ctx, const select_args* a) {
   if (V <= 16 * 256) { if (V == 16 * 256) CASCADE_LAUNCH_RESIDUAL(1, true); else CASCADE_LAUNCH_RESIDUAL(1, false); }
   else if (V <= 16 * 1024) { if (V == 16 * 1024) CASCADE_LAUNCH_RESIDUAL(4, true); else CASCADE_LAUNCH_RESIDUAL(4, false); }
   else if (V <= 16 * 2048) CASCADE_LAUNCH_RESIDUAL(8, false);
+  else if (V <= 16 * 3072) CASCADE_LAUNCH_RESIDUAL(12, false);
   else { if (V == 16 * 4096) CASCADE_LAUNCH_RESIDUAL(16, true); else CASCADE_LAUNCH_RESIDUAL(16, false); }
 #undef CASCADE_LAUNCH_RESIDUAL
   return hipGetLastError();

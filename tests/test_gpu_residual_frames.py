@@ -1,4 +1,4 @@
-"""The residual walk around its register frames (1, 4, 8 and 16 four-wide vectors per lane; 4096 to 65536 entries): rows that
+"""The residual walk around its register frames (1, 4, 8, 12 and 16 four-wide vectors per lane; 4096 to 65536 entries): rows that
 fill a frame, one vector more, a few entries, trees of one and several 64-node chunks.  Checked as in test_gpu_next."""
 import numpy as np
 import pytest
@@ -9,7 +9,7 @@ from paper_2605_07230_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab", [128, 4096, 4100, 12300, 16384, 16388, 32768, 32772])
+@pytest.mark.parametrize("vocab", [128, 4096, 4100, 12300, 16384, 16388, 32768, 32772, 49152, 49156])
 @pytest.mark.parametrize("sizes", [(3, 20), (65, 130)])
 def test_residual_walk_frames(vocab, sizes):
     for seed in range(20):
