@@ -21,6 +21,8 @@
  *    only inside cascade_create (one workspace, freed by cascade_destroy).
  *  - Asynchrony: every compute call enqueues kernels on the ctx stream and returns; it never
  *    synchronises the device.
+ *    The calls of a context share its workspace: they are ordered by its stream, and replays of graphs
+ *    captured from it have to be ordered with each other and with further calls.
  *  - Errors: 0 = CASCADE_OK, negative = cascade_status.  Errors detectable from host-visible
  *    arguments (null pointers, shapes, limits, dtype) are reported before anything is enqueued and
  *    leave outputs untouched.  HIP runtime failures give CASCADE_EHIP.  Preconditions on device

@@ -67,16 +67,18 @@ int cascade_create(cascade_ctx** out, const cascade_limits* lim, void* hip_strea
   c->attn_ws_bytes = align_up(attn, 256);
   // packed hidden states: two operands (cond, uncond), rows rounded up to 256, 2 bytes per element
   c->hpack_ws_bytes = align_up((size_t)2 * ((lim->max_nodes_total + 255) / 256 * 256) * lim->hidden * 2, 256);
-  c->ws_bytes = 256 + c->attn_ws_bytes + c->hpack_ws_bytes + SELECT_WS_BYTES + (size_t)lim->max_nodes_total * sizeof(int);
+  // cleared together: the status word and the counters, which are zero between calls (and the chunk sums between them)
+  const size_t accept_bytes = align_up((size_t)lim->max_nodes_total * sizeof(int), 256), cleared = 256 + SELECT_WS_BYTES + accept_bytes;
+  static_assert(SELECT_WS_BYTES % 256 == 0, "what follows stays aligned");
+  c->ws_bytes = cleared + c->attn_ws_bytes + c->hpack_ws_bytes;
   e = hipMalloc((void**)&c->ws, c->ws_bytes);
   if (e != hipSuccess) { delete c; (void)hipGetLastError(); return CASCADE_ENOMEM; }
   c->dev_status = (int*)c->ws;
-  c->attn_ws = c->ws + 256;
-  c->hpack_ws = c->attn_ws + c->attn_ws_bytes;
-  c->select_ws = c->hpack_ws + c->hpack_ws_bytes;
+  c->select_ws = c->ws + 256;
   c->accept_ws = c->select_ws + SELECT_WS_BYTES;
-  e = hipMemsetAsync(c->ws, 0, 256, c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->select_ws, 0, SELECT_WS_BYTES + (size_t)lim->max_nodes_total * sizeof(int), c->stream);
+  c->attn_ws = c->ws + cleared;
+  c->hpack_ws = c->attn_ws + c->attn_ws_bytes;
+  e = hipMemsetAsync(c->ws, 0, cleared, c->stream);
   if (e != hipSuccess) { (void)hipFree(c->ws); delete c; return hip_fail(e); }
   *out = c;
   return CASCADE_OK;
