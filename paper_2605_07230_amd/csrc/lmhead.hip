@@ -6,6 +6,8 @@
 // lmhead_bf16_ring_kernel takes rows and weights as they lie in memory (or packed weights) and comes in tiles from
 // 64 x 64 to 256 x 128; lmhead_bf16_tiled_kernel takes both operands packed and carries the large tiles of steps with
 // several hundred rows.  lm_plan chooses by estimated time, and gives the columns that do not fill a round a smaller tile.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
 #pragma unroll
     for (int i = 0; i < (DIRECT ? 0 : LPW); ++i) *(u32x4*)(ring_lds + chunk(i) * 1024 + slot * STAGE + 16 * lane) = held[i];
   };
-  auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
+  auto request = [&](int t, int slot, auto stream_w) {   // t past the end: clamped, that data is never multiplied
     const int tc = min(t, n_stages - 1);
     auto from = [&](int i) { return src[i] + (int64_t)tc * ((PW && i >= LPA) ? KS * 1024 : KS * 32); };
     if constexpr (!DIRECT) {
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
     };
 #pragma unroll
     for (int i = 0; i < LPA; ++i) load(i);
-    if (p.stream_w) {
+    if constexpr (decltype(stream_w)::value) {
 #pragma unroll
       for (int i = LPA; i < LPW; ++i) {
         const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
@@ -277,52 +279,56 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
     for (int j = 0; j < AN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll
-  for (int t = 0; t < NST - 1; ++t) { request(t, t); store_held(t); }
   // every sum over the hidden dimension is four chains, over the KW groups of waves and within a wave: one chain of 4096
   // terms is off by 3.7e-7 of the row (2-norm, against float64), two 2.5e-7, four 1.7e-7
   constexpr int CH = 4 / KW;
   f32x16 done[AM][AN];   // (CH > 1) the finished chains
-  int slot = 0, t = 0;
-  for (int c = 1; c <= CH; ++c) {
-    for (const int t_end = n_stages * c / CH; t < t_end; ++t) {
-      // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
-      // barrier: everybody's chunks are there and stage t - 1's slot is free
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
-      const int free_slot = slot == 0 ? NST - 1 : slot - 1;
-      request(t + NST - 1, free_slot);
-      if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
-      const char* st = ring_lds + slot * STAGE;
-      Frag8 a[SPW][AM], b[SPW][AN];
+  auto run = [&](auto stream_w) {   // (two loops without a branch in them; one loop that branches takes the same time)
 #pragma unroll
-      for (int ss = 0; ss < SPW; ++ss) {
-        const int s = kw * SPW + ss;
+    for (int t = 0; t < NST - 1; ++t) { request(t, t, stream_w); store_held(t); }
+    int slot = 0, t = 0;
+    for (int c = 1; c <= CH; ++c) {
+      for (const int t_end = n_stages * c / CH; t < t_end; ++t) {
+        // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
+        // barrier: everybody's chunks are there and stage t - 1's slot is free
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
+        const int free_slot = slot == 0 ? NST - 1 : slot - 1;
+        request(t + NST - 1, free_slot, stream_w);
+        if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
+        const char* st = ring_lds + slot * STAGE;
+        Frag8 a[SPW][AM], b[SPW][AN];
 #pragma unroll
-        for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
+        for (int ss = 0; ss < SPW; ++ss) {
+          const int s = kw * SPW + ss;
 #pragma unroll
-        for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
+          for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
+#pragma unroll
+          for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
+        }
+#pragma unroll
+        for (int ss = 0; ss < SPW; ++ss)
+#pragma unroll
+          for (int i = 0; i < AM; ++i)
+#pragma unroll
+            for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
+        store_held(free_slot);
+        slot = slot + 1 == NST ? 0 : slot + 1;
       }
-#pragma unroll
-      for (int ss = 0; ss < SPW; ++ss)
+      if (CH > 1)
 #pragma unroll
         for (int i = 0; i < AM; ++i)
 #pragma unroll
-          for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
-      store_held(free_slot);
-      slot = slot + 1 == NST ? 0 : slot + 1;
+          for (int j = 0; j < AN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
+              done[i][j][r] = x;
+              acc[i][j][r] = c < CH ? 0.f : x;
+            }
     }
-    if (CH > 1)
-#pragma unroll
-      for (int i = 0; i < AM; ++i)
-#pragma unroll
-        for (int j = 0; j < AN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
-            done[i][j][r] = x;
-            acc[i][j][r] = c < CH ? 0.f : x;
-          }
-  }
+  };
+  if (DIRECT && p.stream_w) run(std::true_type{});
+  else run(std::false_type{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
   // epilogue: accumulator (i, j), register r of lane (r32, half) is row 8 (r / 4) + 4 half + r % 4, column r32
