@@ -21,8 +21,11 @@
  *    only inside cascade_create (one workspace, freed by cascade_destroy).
  *  - Asynchrony: every compute call enqueues kernels on the ctx stream and returns; it never
  *    synchronises the device.
- *    The calls of a context share its workspace: they are ordered by its stream, and replays of graphs
- *    captured from it have to be ordered with each other and with further calls.
+ *    The calls of a context share its workspace and are ordered by its stream.  Replays of graphs captured
+ *    from it: tree_verify_attn (keys in parts) and lmhead_softmax_cfg (packed or mixed rows) use that
+ *    workspace, so replays that hold them have to be ordered with each other and with further such calls.
+ *    Captured cascade_accept, select_path, kv_commit and convergence_weights use none of it: their replays
+ *    may overlap with each other and with anything else.
  *  - Errors: 0 = CASCADE_OK, negative = cascade_status.  Errors detectable from host-visible
  *    arguments (null pointers, shapes, limits, dtype) are reported before anything is enqueued and
  *    leave outputs untouched.  HIP runtime failures give CASCADE_EHIP.  Preconditions on device

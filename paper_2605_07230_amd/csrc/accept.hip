@@ -133,6 +133,7 @@ __device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], in
 }
 
 constexpr int MAXO = 2 * MAXW;   // others of a node: parent + (siblings - 1) + children <= 1 + 63 + 64
+static_assert(MAXO + 1 == ACCEPT_SUMS, "the workspace is sized for these");
 
 // Where the workgroups of one node meet (wide rows): a counter that is zero between calls, and the partial sums.
 struct AcceptShare {
@@ -434,13 +435,13 @@ hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   // Rows of 16 KiB and more that the vector ALU sweeps: a node with many relatives reads 20 of them and more, through one compute
   // unit.  Parts of at least 8 KiB, two workgroups per compute unit (what its registers hold).  120 nodes x 16384 floats: 22.3 us
   // whole (the median node 8.4), 17.6 in two parts, 15.5 in four, 20 in eight (two rounds).
-  AcceptShare share = {(int*)ctx->accept_ws, (unsigned long long*)(ctx->attn_ws)};
+  AcceptShare share = {(int*)ctx->accept_ws, (unsigned long long*)ctx->accept_sums};
   int parts = 1;
-  if (!mfma && !narrow && a->n_nodes_total <= ctx->lim.max_nodes_total) {
-    const int64_t by_bytes = (int64_t)a->hidden * (bf16 ? 2 : 4) / 8192, by_room = 2 * ctx->n_cu / a->n_nodes_total;
-    const int64_t by_space = ctx->attn_ws_bytes / ((int64_t)a->n_nodes_total * (MAXO + 1) * 8);   // the partials of attention are dead by now
-    const int64_t n = by_bytes < by_room ? by_bytes : by_room, m = n < by_space ? n : by_space;
-    parts = m < 1 ? 1 : (m > 8 ? 8 : (int)m);
+  if (!mfma && !narrow) {
+    const int64_t by_bytes = (int64_t)a->hidden * (bf16 ? 2 : 4) / 8192, by_room = ACCEPT_PER_CU * ctx->n_cu / a->n_nodes_total;
+    const int64_t n = by_bytes < by_room ? by_bytes : by_room;
+    parts = n < 1 ? 1 : (n > 8 ? 8 : (int)n);
+    if (parts > 1 && recorded(ctx->stream)) parts = 1;
   }
   grid.x = parts;
   // (Gram tiles on eight waves: 462 nodes 10.2 -> 12.1 us, 1024 nodes 18 -> 23.6, fewer nodes the same)

@@ -70,7 +70,8 @@ int cascade_create(cascade_ctx** out, const cascade_limits* lim, void* hip_strea
   // cleared together: the status word and the counters, which are zero between calls (and the chunk sums between them)
   const size_t accept_bytes = align_up((size_t)lim->max_nodes_total * sizeof(int), 256), cleared = 256 + SELECT_WS_BYTES + accept_bytes;
   static_assert(SELECT_WS_BYTES % 256 == 0, "what follows stays aligned");
-  c->ws_bytes = cleared + c->attn_ws_bytes + c->hpack_ws_bytes;
+  const size_t sums_bytes = align_up((size_t)ACCEPT_PER_CU * c->n_cu * ACCEPT_SUMS * 8, 256);
+  c->ws_bytes = cleared + c->attn_ws_bytes + c->hpack_ws_bytes + sums_bytes;
   e = hipMalloc((void**)&c->ws, c->ws_bytes);
   if (e != hipSuccess) { delete c; (void)hipGetLastError(); return CASCADE_ENOMEM; }
   c->dev_status = (int*)c->ws;
@@ -78,6 +79,7 @@ int cascade_create(cascade_ctx** out, const cascade_limits* lim, void* hip_strea
   c->accept_ws = c->select_ws + SELECT_WS_BYTES;
   c->attn_ws = c->ws + cleared;
   c->hpack_ws = c->attn_ws + c->attn_ws_bytes;
+  c->accept_sums = c->hpack_ws + c->hpack_ws_bytes;
   e = hipMemsetAsync(c->ws, 0, cleared, c->stream);
   if (e != hipSuccess) { (void)hipFree(c->ws); delete c; return hip_fail(e); }
   *out = c;

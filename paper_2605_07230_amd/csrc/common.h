@@ -23,6 +23,7 @@ struct cascade_ctx {
   size_t hpack_ws_bytes;
   char* select_ws;        // select_path: counters (zero between calls) and chunk sums of prompts shared by several workgroups
   char* accept_ws;        // cascade_accept: a counter per node, zero between calls
+  char* accept_sums;      // cascade_accept: what the workgroups of shared nodes leave for each other
   // optional per-kernel timing with HIP events on the ctx stream (cascade_set_kernel_timing)
   bool timing;
   hipEvent_t* ev;         // [CASCADE_K_COUNT][TIMING_RING][2], created on first enable
@@ -34,6 +35,17 @@ enum { TIMING_RING = 2048 };
 // prompts whose vocabulary several workgroups of select_path share (a counter and the sums of all 256-entry chunks each)
 enum { SELECT_MAX_SHARED = 128 };
 constexpr size_t SELECT_WS_BYTES = SELECT_MAX_SHARED * (sizeof(int) + CASCADE_MAX_VOCAB / 256 * sizeof(float));
+// sums that one workgroup of a shared node leaves in cascade_accept (two floats each), workgroups per compute unit that share nodes
+enum { ACCEPT_SUMS = 2 * CASCADE_MAX_WIDTH + 1, ACCEPT_PER_CU = 2 };
+
+// Whether calls on the stream are being recorded into a graph.  Replays are ordered by their own streams, not by the context's,
+// so a recorded call must not meet in memory that other calls of the context use: it runs with one workgroup per prompt or node.
+inline bool recorded(hipStream_t stream) {
+  if (!stream) return false;   // the default stream is never captured, and asking about it is an error while another one is
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
+  return status != hipStreamCaptureStatusNone;
+}
 
 // Per-kernel timing: when it is on, a launch goes through hipExtLaunchKernelGGL with a start and a stop
 // event taken from the context's ring, which receive the dispatch's own begin / end timestamps (no

@@ -437,6 +437,7 @@ hipError_t launch_select(cascade_ctx* ctx, const select_args* a) {
   const int pass = 4096, n_pass = (a->vocab + pass - 1) / pass;
   int parts = a->n_prompts <= SELECT_MAX_SHARED ? ctx->n_cu / a->n_prompts : 1;
   parts = parts < 1 ? 1 : (parts < n_pass ? parts : n_pass);
+  if (parts > 1 && recorded(ctx->stream)) parts = 1;
   dim3 grid(parts, a->n_prompts);
   if (parts > 1 || n_pass == 1) {
     if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<4, 2>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
