@@ -231,7 +231,7 @@ __global__ __launch_bounds__(512) void select_kernel(select_args a, SelectShare 
   const int V = a.vocab;
   const float* Lr = a.logits + (int64_t)(lo + cur) * V;
   const float thr = a.row_thr[lo + cur], lse = a.row_lse[lo + cur];
-  const int nchunks = (V + 255) >> 8;   // at most CPW per wave
+  const int nchunks = (V + 255) >> 8;
   const bool vec = (V & 3) == 0;
   const float ub = a.u_bonus[b];
 
@@ -298,6 +298,7 @@ __global__ __launch_bounds__(512) void select_kernel(select_args a, SelectShare 
   auto to_lds = [&](int c, float x) { if (c < MAXCHUNKS) s_chunk[c] = x; };
 
   float cs[4];   // wave 0: lane l owns chunks 4 l .. 4 l + 3
+  bool last = parts == 1;   // wave 0: this workgroup goes on
   if (parts > 1) {
     // Sums and counter pass through memory that all XCDs see (agent-scope accesses go past their L2s), so no cache has to be
     // written back; the wait puts every wave's sums there before the workgroup counts itself in.
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(512) void select_kernel(select_args a, SelectShare 
     if (wave == 0) {
       int n = 0;
       if (lane == 0) n = __hip_atomic_fetch_add(share.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const bool last = __builtin_amdgcn_readfirstlane(n) == parts - 1;
+      last = __builtin_amdgcn_readfirstlane(n) == parts - 1;
       if (lane == 0) {
         s_last = last;
         if (last) __hip_atomic_store(share.arrived + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
@@ -357,8 +358,7 @@ __global__ __launch_bounds__(512) void select_kernel(select_args a, SelectShare 
       base = readlane_f(cbase, __ffsll((long long)__ballot(cand == cstar)) - 1);
     }
   };
-  const bool mine = wave == 0 && (parts == 1 || s_last);   // (s_last was written by this very wave)
-  if (mine) {
+  if (wave == 0 && last) {
     find_chunk();
     if (lane == 0) s_total = total;
   }
@@ -430,21 +430,23 @@ hipError_t launch_select(cascade_ctx* ctx, const select_args* a) {
   KernelTimer t(ctx, CASCADE_K_SELECT);
   SelectShare share = {(int*)ctx->select_ws, (float*)(ctx->select_ws + SELECT_MAX_SHARED * sizeof(int))};
   const bool small_tree = ctx->lim.max_nodes_per_tree <= 256;
-  // One pass of 4096 entries per workgroup while the chip has a compute unit for each: a row's exponentials take a lone
-  // compute unit 1 us per 16384 entries, the meeting of the workgroups 1.5 us.  In a step, with one workgroup per prompt and as
-  // built now: 15 nodes x 4096 entries 5.7 -> 4.9 us, 60 x 16384 9.0 -> 6.4, 60 x 65536 13.3 -> 6.7, four trees of 256 x 65536
-  // 15.0 -> 8.3.  More prompts than half the compute units fill the chip by themselves.
+  // Passes of 4096 entries, dealt to up to two workgroups per compute unit: a row's exponentials take a lone compute unit 1 us per
+  // 16384 entries, the meeting of the workgroups 1.5 us.  In a step, with one workgroup per prompt and as built now: 60 nodes x
+  // 16384 entries 9.0 -> 6.4 us, 60 x 65536 13.3 -> 6.7, four trees of 256 x 65536 15.0 -> 8.3.  Trees of 12 nodes, walk alone:
+  // 48 prompts x 65536 12.4 -> 8.3, 100 x 33088 9.4 -> 8.4, 100 x 65536 13.4 -> 10.4 (with one workgroup per compute unit, two
+  // parts: 10.3 and 14.5).  More than 128 prompts fill the chip by themselves.
   const int pass = 4096, n_pass = (a->vocab + pass - 1) / pass;
-  int parts = a->n_prompts <= SELECT_MAX_SHARED ? ctx->n_cu / a->n_prompts : 1;
+  int parts = a->n_prompts <= SELECT_MAX_SHARED ? 2 * ctx->n_cu / a->n_prompts : 1;
   parts = parts < 1 ? 1 : (parts < n_pass ? parts : n_pass);
   if (parts > 1 && recorded(ctx->stream)) parts = 1;
+  // A lone workgroup takes up to eight chunks per wave and pass, and as many in every pass as it can: 33088 entries are 130 chunks, 17
+  // per wave, three passes of six (200 prompts: 9.9 us, with eight 11.4).
+  const int per_wave = ((a->vocab + 255) / 256 + 7) / 8, alone = (per_wave + 7) / 8, cpw = parts > 1 || n_pass == 1 ? 2 : ((per_wave + alone - 1) / alone <= 6 ? 6 : 8);
   dim3 grid(parts, a->n_prompts);
-  if (parts > 1 || n_pass == 1) {
-    if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<4, 2>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
-    else CASCADE_TIMED_LAUNCH(t, (select_kernel<16, 2>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
-  } else {
-    if (small_tree) CASCADE_TIMED_LAUNCH(t, (select_kernel<4, 8>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
-    else CASCADE_TIMED_LAUNCH(t, (select_kernel<16, 8>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status);
-  }
+#define CASCADE_LAUNCH_SELECT(TCH, CPW) CASCADE_TIMED_LAUNCH(t, (select_kernel<TCH, CPW>), grid, dim3(512), 0, ctx->stream, *a, share, ctx->dev_status)
+  if (cpw == 2) { if (small_tree) CASCADE_LAUNCH_SELECT(4, 2); else CASCADE_LAUNCH_SELECT(16, 2); }
+  else if (cpw == 6) { if (small_tree) CASCADE_LAUNCH_SELECT(4, 6); else CASCADE_LAUNCH_SELECT(16, 6); }
+  else { if (small_tree) CASCADE_LAUNCH_SELECT(4, 8); else CASCADE_LAUNCH_SELECT(16, 8); }
+#undef CASCADE_LAUNCH_SELECT
   return hipGetLastError();
 }

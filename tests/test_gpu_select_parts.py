@@ -22,11 +22,12 @@ def test_passes_of_a_row(vocab, mode):
     edges._check(inp, ref, vocab, sizes, mode)
 
 
-@pytest.mark.parametrize("prompts", [127, 128, 129])    # 2 workgroups of a prompt, 2, 1
-def test_many_prompts(prompts):
-    vocab, sizes = 20000, (3,) * prompts
+@pytest.mark.parametrize("prompts", [127, 128, 129])    # 4 workgroups of a prompt, 4, 1
+@pytest.mark.parametrize("vocab", [16384, 16388, 20000, 24580, 33088, 65532])    # alone, passes x chunks per wave: 1 x 8, 2 x 6, 2 x 6, 2 x 8, 3 x 6, 4 x 8
+def test_many_prompts(prompts, vocab):
+    sizes = (3,) * prompts
     inp, ref = next(r for r in (edges._inputs(vocab, sizes, False, binding.WALK_SEQUENTIAL, seed) for seed in range(40)) if r is not None)
-    print(f"[select] prompts={prompts}", flush=True)
+    print(f"[select] prompts={prompts} vocab={vocab}", flush=True)
     edges._check(inp, ref, vocab, sizes, binding.WALK_SEQUENTIAL)
 
 
