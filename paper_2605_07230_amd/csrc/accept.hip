@@ -1,7 +1,7 @@
 // cascade_accept kernel for gfx950 (Sec. 4.1 cosine similarity of target hidden states; Eq. 1
 // interchangeable set; Eq. 2 convergence set; Eq. 3 aggregated mass).
 //
-// One workgroup per node a.  Everything a needs is the cosine of its own feature row against its
+// One workgroup per node a (several where its rows are wide and do not go through the matrix cores).  Everything a needs is the cosine of its own feature row against its
 // parent, its siblings and its children: one row against at most 1 + 63 + 64 others.  The others
 // are taken in blocks of 15; with a as the 16th row, one 16 x 16 Gram tile per block gives every
 // a . x (row of a) and every |x|^2 (diagonal) at once.  For bf16 hidden states the tile runs on
@@ -77,7 +77,8 @@ __device__ __forceinline__ f32x4 gram_tile_deep(const uint16_t* row, int k0, int
 // Rows that do not go through the matrix cores (f32; bf16 of a width that is no multiple of 128): the whole workgroup
 // sweeps the row of a once per group of DG other rows and keeps a.x, x.x of each in registers, NT x 16 bytes of every
 // row per step.  Bound by the bytes a compute unit has in flight (each node reads all of its relatives' rows): the former
-// one-row-per-wave loop had one 4-byte load per lane and row in flight - 235 us for 120 nodes x 16384 logits, now 19.
+// one-row-per-wave loop had one 4-byte load per lane and row in flight - 235 us for 120 nodes x 16384 logits, 19-22 so (and
+// less in parts, see launch_accept).
 // Narrow rows would spend their time on the 17 sums over eight waves and two barriers per group: up to NARROW elements (an
 // eighth where they are loaded one at a time) a wave takes a group of WG rows by itself.  Two trees of 64 nodes, cold caches,
 // with one row per wave, swept by the workgroup, swept by a wave: f32 x 64 6.1, 8.6, 5.6 us; x 512 15.0, 8.5, 5.6; x 1024 25.4, 8.2,
@@ -317,9 +318,14 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptSh
       static_assert(NWV * (2 * DG + 1) <= NWV * 256, "partial sums fit");
       // Wide rows: gridDim.x workgroups, dealt to different XCDs, take the same part of every node's elements, leave their sums in memory that all XCDs see
       // (agent-scope accesses go past their L2s) and count themselves in; the one that arrives last adds the parts up in their
-      // order and goes on, the others are done.  No workgroup ever waits for another.
-      const int parts = gridDim.x, width = ((h + parts - 1) / parts + 63) & ~63;
-      const int h0 = min((int)blockIdx.x * width, h), h1 = min(h0 + width, h);
+      // order and goes on, the others are done.  No workgroup ever waits for another.  A node whose relatives fit one sweep of rows
+      // below 16384 elements saves less than the meeting takes: one of its workgroups does it alone (15 and 40 nodes x 8192 floats,
+      // no family of more than eight: 6.9 and 7.4 us, 7.7 and 7.8 with a meeting).
+      const int launched = gridDim.x;
+      const bool alone = n_other <= DG && h < 16384;
+      if (alone && (int)blockIdx.x != (node * launched >> 3) % launched) return;   // (the one: spread over the XCDs)
+      const int parts = alone ? 1 : launched, width = ((h + parts - 1) / parts + 63) & ~63;
+      const int h0 = alone ? 0 : min((int)blockIdx.x * width, h), h1 = min(h0 + width, h);
       unsigned long long* const shared = share.sums + (gi * parts + blockIdx.x) * (MAXO + 1);
       auto pair = [](float x, float y) { return (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32); };
       for (int o0 = 0; o0 < n_other; o0 += DG) {
@@ -432,15 +438,17 @@ hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   const bool bf16 = a->h_dtype == CASCADE_BF16, mfma = bf16 && a->hidden % 128 == 0;
   const bool aligned = (a->hidden * (bf16 ? 2 : 4)) % 16 == 0 && ((uintptr_t)a->h_cond & 15) == 0;
   const bool narrow = !mfma && a->hidden <= (aligned ? NARROW : NARROW / 8);
-  // Rows of 16 KiB and more that the vector ALU sweeps: a node with many relatives reads 20 of them and more, through one compute
-  // unit.  Parts of at least 8 KiB, two workgroups per compute unit (what its registers hold).  120 nodes x 16384 floats: 22.3 us
-  // whole (the median node 8.4), 17.6 in two parts, 15.5 in four, 20 in eight (two rounds).
+  // Wide rows that the vector ALU sweeps: a node with many relatives reads 20 of them and more, through one compute unit.  Parts of
+  // at least 8 KiB of rows of 8192 elements and more (16 KiB from 16384 floats on), two workgroups per compute unit (what its
+  // registers hold), and 2, 4 or 8 of them, so that an XCD holds one part of every row.  f32, one tree: 60 nodes x 4096 8.5 us
+  // whole, 8.8 in two parts; 60 x 8192 11.3 whole, 10.9 in two, 10.0 in four; 60 x 16384 16.5 whole, 11.0 in four, 11.9 in
+  // eight; 120 x 16384 16.3 whole, 11.6-12.0 in four; 80 x 33088 26.6, 14.3 in four, 15.1 in six; 96 x 65536 44.4 whole, 20.7 in four, 24.8 in five.
   AcceptShare share = {(int*)ctx->accept_ws, (unsigned long long*)ctx->accept_sums};
   int parts = 1;
   if (!mfma && !narrow) {
-    const int64_t by_bytes = (int64_t)a->hidden * (bf16 ? 2 : 4) / 8192, by_room = ACCEPT_PER_CU * ctx->n_cu / a->n_nodes_total;
-    const int64_t n = by_bytes < by_room ? by_bytes : by_room;
-    parts = n < 1 ? 1 : (n > 8 ? 8 : (int)n);
+    const int by_bytes = (int64_t)a->hidden * (bf16 ? 2 : 4) / 8192, by_room = ACCEPT_PER_CU * ctx->n_cu / a->n_nodes_total;
+    const int by_width = a->hidden < 8192 ? 1 : (a->hidden < 32768 ? 4 : 8);
+    while (2 * parts <= by_width && 2 * parts <= by_bytes && 2 * parts <= by_room) parts *= 2;
     if (parts > 1 && recorded(ctx->stream)) parts = 1;
   }
   grid.x = parts;
