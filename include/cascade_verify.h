@@ -255,6 +255,8 @@ int lmhead_softmax_cfg(cascade_ctx* ctx, const lmhead_args* args);
  * 128 x 64, 64 x 256, 128 x 128, 256 x 128 rows x columns), 5 and 6 of the one that takes them packed (128 x 256,
  * 256 x 256), -1 for ordinary loads; columns from rest_column on, if that is below vocab, run in rest_tile. */
 int cascade_projection_tiles(const cascade_ctx* ctx, const lmhead_args* args, int32_t* tile, int32_t* rest_tile, int32_t* rest_column);
+/* Whether those tiles load the weights past the caches (1) or not (0), likewise. */
+int cascade_projection_streams(const cascade_ctx* ctx, const lmhead_args* args, int32_t* streams, int32_t* rest_streams);
 
 /* ---------------------------------------------------------------------------------------------
  * cascade_accept — what the relaxed acceptance rule needs at every non-root node a with parent p

@@ -27,7 +27,7 @@ OK, EINVAL, ESHAPE, EDTYPE, ENOMEM, EHIP, ETREE = 0, -1, -2, -3, -4, -5, -6
 EXPORTS = ["cascade_create", "cascade_destroy", "cascade_strerror", "cascade_device_status", "cascade_workspace_bytes",
            "cascade_set_kernel_timing", "cascade_read_kernel_timing", "cascade_measure_hbm_read",
            "cascade_measure_mfma_bf16", "cascade_pack_lmhead_w", "tree_verify_attn", "tree_verify_attn_static",
-           "lmhead_softmax_cfg", "cascade_attention_cut", "cascade_projection_tiles", "cascade_accept", "select_path", "kv_commit", "convergence_weights"]
+           "lmhead_softmax_cfg", "cascade_attention_cut", "cascade_projection_tiles", "cascade_projection_streams", "cascade_accept", "select_path", "kv_commit", "convergence_weights"]
 
 _vp, _i32, _i64, _f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
 
@@ -117,6 +117,8 @@ def load_library() -> C.CDLL:
     lib.cascade_attention_cut.restype = C.c_int
     lib.cascade_projection_tiles.argtypes = [_vp, C.POINTER(lmhead_args)] + [C.POINTER(_i32)] * 3
     lib.cascade_projection_tiles.restype = C.c_int
+    lib.cascade_projection_streams.argtypes = [_vp, C.POINTER(lmhead_args)] + [C.POINTER(_i32)] * 2
+    lib.cascade_projection_streams.restype = C.c_int
     for name, st in (("tree_verify_attn", tree_attn_args), ("lmhead_softmax_cfg", lmhead_args),
                      ("cascade_accept", accept_args), ("select_path", select_args), ("kv_commit", kv_commit_args),
                      ("convergence_weights", conv_weight_args)):
@@ -250,11 +252,24 @@ def attention_cut(*, n_rows, n_nodes_total, max_nodes_per_tree, max_prefix_len, 
     return rows.value, parts.value
 
 
-def projection_tiles(*, n_nodes, hidden, vocab, guided, w_layout: int = W_ROWMAJOR, cfg_mix: int = CFG_MIX_LOGITS, ctx: Optional[Context] = None):
-    """(tile, tile of the rest, first column of the rest) of a bf16 call of these sizes on aligned buffers."""
+def _projection_args(n_nodes, hidden, vocab, guided, w_layout, cfg_mix) -> lmhead_args:
     a = lmhead_args()
     a.dtype, a.n_nodes, a.hidden, a.vocab, a.w_layout, a.cfg_mix = BF16, n_nodes, hidden, vocab, w_layout, cfg_mix
     a.h_uncond = 16 if guided else None    # an aligned address, not read
+    return a
+
+
+def projection_streams(*, n_nodes, hidden, vocab, guided, w_layout: int = W_ROWMAJOR, cfg_mix: int = CFG_MIX_LOGITS, ctx: Optional[Context] = None):
+    """Whether the tiles of projection_tiles load the weights past the caches: (the tile, that of the rest)."""
+    a = _projection_args(n_nodes, hidden, vocab, guided, w_layout, cfg_mix)
+    main, rest = _i32(), _i32()
+    _check(load_library().cascade_projection_streams(ctx.handle if ctx else None, C.byref(a), C.byref(main), C.byref(rest)))
+    return bool(main.value), bool(rest.value)
+
+
+def projection_tiles(*, n_nodes, hidden, vocab, guided, w_layout: int = W_ROWMAJOR, cfg_mix: int = CFG_MIX_LOGITS, ctx: Optional[Context] = None):
+    """(tile, tile of the rest, first column of the rest) of a bf16 call of these sizes on aligned buffers."""
+    a = _projection_args(n_nodes, hidden, vocab, guided, w_layout, cfg_mix)
     tile, rest, column = _i32(), _i32(), _i32()
     _check(load_library().cascade_projection_tiles(ctx.handle if ctx else None, C.byref(a), C.byref(tile), C.byref(rest), C.byref(column)))
     return tile.value, rest.value, column.value

@@ -320,6 +320,14 @@ int cascade_projection_tiles(const cascade_ctx* ctx, const lmhead_args* a, int32
   return CASCADE_OK;
 }
 
+int cascade_projection_streams(const cascade_ctx* ctx, const lmhead_args* a, int32_t* streams, int32_t* rest_streams) {
+  if (!a || !streams || !rest_streams) return CASCADE_EINVAL;
+  if (a->dtype != CASCADE_BF16) return CASCADE_EDTYPE;
+  if (a->n_nodes <= 0 || a->hidden <= 0 || a->vocab <= 0) return CASCADE_EINVAL;
+  plan_lmhead_streams(a, ctx ? ctx->n_cu : 256, streams, rest_streams);
+  return CASCADE_OK;
+}
+
 int cascade_pack_lmhead_w(cascade_ctx* ctx, const void* w, int32_t vocab, int32_t hidden, void* w_packed) {
   if (!ctx || !w || !w_packed || w == w_packed) return CASCADE_EINVAL;
   if (vocab <= 0 || hidden <= 0) return CASCADE_EINVAL;

@@ -85,6 +85,7 @@ void plan_tree_attn_bf16(const tree_attn_args* a, int n_cu, size_t ws_bytes, int
 hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a);
 hipError_t launch_lmhead_bf16(cascade_ctx* ctx, const lmhead_args* a);
 void plan_lmhead_bf16(const lmhead_args* a, int n_cu, int32_t* tile, int32_t* rest_tile, int32_t* rest_column);
+void plan_lmhead_streams(const lmhead_args* a, int n_cu, int32_t* streams, int32_t* rest_streams);
 hipError_t launch_row_stats(cascade_ctx* ctx, const lmhead_args* a);
 hipError_t launch_pack_w(cascade_ctx* ctx, const void* w, int vocab, int hidden, void* w_packed);
 hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a);

@@ -6,8 +6,6 @@
 // lmhead_bf16_ring_kernel takes rows and weights as they lie in memory (or packed weights) and comes in tiles from
 // 64 x 64 to 256 x 128; lmhead_bf16_tiled_kernel takes both operands packed and carries the large tiles of steps with
 // several hundred rows.  lm_plan chooses by estimated time, and gives the columns that do not fill a round a smaller tile.
-#include <type_traits>
-
 #include "common.h"
 
 namespace {
@@ -26,7 +24,6 @@ struct LmParams {
   int col0;                 // first vocabulary column of the launch
   float cfg_scale, temperature;
   int top_k;
-  bool stream_w;            // weights are loaded past the caches
 };
 
 // ------------------------------------------------------------------------------------------ f32
@@ -181,7 +178,9 @@ __global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__
 // Large weights are streamed (nt): a step reads them once, or once per row tile at the same time, and everything else it touches
 // would be displaced from the caches by them.  Steps over weights that the caches do not hold yet: 60 rows x 16384 28.9 ->
 // 25.9 us, 60 x 65536 103.8 -> 92.7 (5.8 TB/s), 60 guidance pairs, row-major 40.7 -> 38.1, and the kernels after it find
-// their rows again (whole step of 60 x 16384: 66 -> 58).  LM_STREAM_BYTES says from which size on.
+// their rows again (whole step of 60 x 16384: 66 -> 58).  lm_streams says which launches do.  They are instances of their own:
+// two loops in one kernel, or one that chooses at every request, made the launches that do not stream 2-8 % slower
+// (512 rows x 16384 x 4096 74.7 -> 79.5 us, 300 x 8192 x 2048 24.4 -> 25.1, 686 row-major rows x 16384 x 4096 123 -> 131).
 // Measured against the kernels this replaced (64 x 64 tiles, operands loaded to registers, hidden 4096; us, without the
 // packing pass of 4 us that they needed): 60 rows x 16384: 30.2 -> 27.4; 60 x 65536: 110 -> 101 (5.3 TB/s);
 // 120 x 16384: 45 -> 35; 230 x 16384: 75 -> 45; 60 guidance pairs, row-major weights: 63 -> 37.
@@ -190,13 +189,13 @@ __global__ __launch_bounds__(256) void mix_rows_kernel(const uint4* __restrict__
 // slots (so the stages are twice as long).  60 rows x 16384 x 4096: 26 us aligned, 38 with rows at 8 bytes past a boundary,
 // 47 with packed weights 2 bytes past one (36 in the register-staged kernel); 60 pairs, row-major: 36, 62, 78 (93); 230 rows:
 // 44, 58, 78 (109).
-template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT>
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT, bool STREAM>
 __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n_mtiles) {
   static_assert(WM * WN * KW == 8 && KS % KW == 0 && KS % 4 == 0 && (!CFG || AM == 2), "eight waves; guidance pairs are a wave's two row blocks");
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NA = BM / 32, NBLK = NA + BN / 32, STAGE = NBLK * KS * 1024;
   constexpr int LPW = NBLK * KS / 8, SPW = KS / KW;
-  constexpr int LPA = NA * KS / 8;   // a wave's requests of a stage: LPA of rows, then of weights
-  static_assert(NA * KS % 8 == 0 && NBLK * KS % 8 == 0, "every wave requests the same number of 1 KiB chunks");
+  constexpr int LPA = NA * KS / 8;   // (STREAM) a wave's requests of a stage: LPA of rows, then of weights
+  static_assert(NA * KS % 8 == 0 && NBLK * KS % 8 == 0 && (DIRECT || !STREAM), "every wave requests the same number of 1 KiB chunks");
   extern __shared__ __align__(1024) char ring_lds[];   // [NST stages][NBLK blocks][KS KiB]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -208,9 +207,10 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   const int nt = logical / n_mtiles, mt = logical % n_mtiles;
 
   // loader: request i of a wave is chunk id of a stage: block id / KS, KiB id % KS of it (one k16 step of packed operands, or
-  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece).  Which requests are weights is
-  // known at compile time: they are streaming (nt) loads, see above.
-  auto chunk = [&](int i) { return i < LPA ? wave * LPA + i : NA * KS + wave * (LPW - LPA) + (i - LPA); };
+  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece).  Consecutive chunks, unless the weights are
+  // streamed: then which requests are weights is known at compile time.
+  auto chunk = [&](int i) { return !STREAM ? wave * LPW + i : (i < LPA ? wave * LPA + i : NA * KS + wave * (LPW - LPA) + (i - LPA)); };
+  auto weights = [&](int i) { return STREAM ? i >= LPA : chunk(i) / KS >= NA; };
   unsigned voff[LPW];
   const char* src[LPW];
 #pragma unroll
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
     const int id = chunk(i), blk = id / KS, q = id % KS;
     const char* base;
     int row0, rows;
-    if (i < LPA) {
+    if (!weights(i)) {
       base = (const char*)((CFG && (blk & 1)) ? p.h_uncond : p.h_cond);
       row0 = CFG ? mt * (BM / 2) + 32 * (blk >> 1) : mt * BM + 32 * blk;
       rows = p.n_nodes;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
       row0 = p.col0 + nt * BN + 32 * (blk - NA);
       rows = p.vocab;
     }
-    if (PW && i >= LPA) {
+    if (PW && weights(i)) {
       src[i] = base + ((int64_t)min(row0 / 32, rows / 32 - 1) * (K / 16) + q) * 1024;   // columns past the end: clamped, never stored
       voff[i] = 16u * lane;
     } else {
@@ -242,29 +242,15 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
 #pragma unroll
     for (int i = 0; i < (DIRECT ? 0 : LPW); ++i) *(u32x4*)(ring_lds + chunk(i) * 1024 + slot * STAGE + 16 * lane) = held[i];
   };
-  auto request = [&](int t, int slot, auto stream_w) {   // t past the end: clamped, that data is never multiplied
+  auto request = [&](int t, int slot) {   // t past the end: clamped, that data is never multiplied
     const int tc = min(t, n_stages - 1);
-    auto from = [&](int i) { return src[i] + (int64_t)tc * ((PW && i >= LPA) ? KS * 1024 : KS * 32); };
-    if constexpr (!DIRECT) {
 #pragma unroll
-      for (int i = 0; i < LPW; ++i) __builtin_memcpy(&held[i], from(i) + voff[i], 16);
-      return;
-    }
-    auto load = [&](int i) {
+    for (int i = 0; i < LPW; ++i) {
+      const char* g = src[i] + (int64_t)tc * ((PW && weights(i)) ? KS * 1024 : KS * 32);
+      if constexpr (!DIRECT) { __builtin_memcpy(&held[i], g + voff[i], 16); continue; }
       const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(from(i)) : "memory");
-    };
-#pragma unroll
-    for (int i = 0; i < LPA; ++i) load(i);
-    if constexpr (decltype(stream_w)::value) {
-#pragma unroll
-      for (int i = LPA; i < LPW; ++i) {
-        const unsigned l = lds0 + slot * STAGE + chunk(i) * 1024;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff[i]), "s"(from(i)) : "memory");
-      }
-    } else {
-#pragma unroll
-      for (int i = LPA; i < LPW; ++i) load(i);
+      if (STREAM && i >= LPA) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
+      else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff[i]), "s"(g) : "memory");
     }
   };
   const int kw = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
@@ -283,52 +269,48 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   // terms is off by 3.7e-7 of the row (2-norm, against float64), two 2.5e-7, four 1.7e-7
   constexpr int CH = 4 / KW;
   f32x16 done[AM][AN];   // (CH > 1) the finished chains
-  auto run = [&](auto stream_w) {   // (two loops without a branch in them; one loop that branches takes the same time)
 #pragma unroll
-    for (int t = 0; t < NST - 1; ++t) { request(t, t, stream_w); store_held(t); }
-    int slot = 0, t = 0;
-    for (int c = 1; c <= CH; ++c) {
-      for (const int t_end = n_stages * c / CH; t < t_end; ++t) {
-        // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
-        // barrier: everybody's chunks are there and stage t - 1's slot is free
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
-        const int free_slot = slot == 0 ? NST - 1 : slot - 1;
-        request(t + NST - 1, free_slot, stream_w);
-        if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
-        const char* st = ring_lds + slot * STAGE;
-        Frag8 a[SPW][AM], b[SPW][AN];
+  for (int t = 0; t < NST - 1; ++t) { request(t, t); store_held(t); }
+  int slot = 0, t = 0;
+  for (int c = 1; c <= CH; ++c) {
+    for (const int t_end = n_stages * c / CH; t < t_end; ++t) {
+      // own chunks of stage t landed (the NST - 2 later stages may be in flight), own LDS reads of stage t - 1 done; bare
+      // barrier: everybody's chunks are there and stage t - 1's slot is free
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPW * (NST - 2)) : "memory");
+      const int free_slot = slot == 0 ? NST - 1 : slot - 1;
+      request(t + NST - 1, free_slot);
+      if (!DIRECT) __builtin_amdgcn_sched_barrier(0);   // left alone, each load sinks to the store of its value
+      const char* st = ring_lds + slot * STAGE;
+      Frag8 a[SPW][AM], b[SPW][AN];
 #pragma unroll
-        for (int ss = 0; ss < SPW; ++ss) {
-          const int s = kw * SPW + ss;
+      for (int ss = 0; ss < SPW; ++ss) {
+        const int s = kw * SPW + ss;
 #pragma unroll
-          for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
+        for (int i = 0; i < AM; ++i) a[ss][i].n = *(const u32x4*)(st + (AM * wm + i) * KS * 1024 + rows_at(s));
 #pragma unroll
-          for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
-        }
-#pragma unroll
-        for (int ss = 0; ss < SPW; ++ss)
-#pragma unroll
-          for (int i = 0; i < AM; ++i)
-#pragma unroll
-            for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
-        store_held(free_slot);
-        slot = slot + 1 == NST ? 0 : slot + 1;
+        for (int j = 0; j < AN; ++j) b[ss][j].n = *(const u32x4*)(st + (NA + AN * wn + j) * KS * 1024 + (PW ? packed_at(s) : rows_at(s)));
       }
-      if (CH > 1)
+#pragma unroll
+      for (int ss = 0; ss < SPW; ++ss)
 #pragma unroll
         for (int i = 0; i < AM; ++i)
 #pragma unroll
-          for (int j = 0; j < AN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
-              done[i][j][r] = x;
-              acc[i][j][r] = c < CH ? 0.f : x;
-            }
+          for (int j = 0; j < AN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ss][i].v, b[ss][j].v, acc[i][j], 0, 0, 0);
+      store_held(free_slot);
+      slot = slot + 1 == NST ? 0 : slot + 1;
     }
-  };
-  if (DIRECT && p.stream_w) run(std::true_type{});
-  else run(std::false_type{});
+    if (CH > 1)
+#pragma unroll
+      for (int i = 0; i < AM; ++i)
+#pragma unroll
+        for (int j = 0; j < AN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = c > 1 ? done[i][j][r] + acc[i][j][r] : acc[i][j][r];
+            done[i][j][r] = x;
+            acc[i][j][r] = c < CH ? 0.f : x;
+          }
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped extra requests must not outlive the workgroup's LDS
 
   // epilogue: accumulator (i, j), register r of lane (r32, half) is row 8 (r / 4) + 4 half + r % 4, column r32
@@ -895,12 +877,6 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   }
 }
 
-// Weights from this size on are streamed (see the ring kernel): a third of the last-level cache.  A step of 60 nodes whose
-// weights no cache holds, default policy and streamed: 8192 x 4096 (67 MB) 56.8 and 52.1 us, 16384 x 3072 (101 MB) 59 and 53, 16384 x
-// 4096 63 and 56, 40000 x 4096 111 and 100.  Three smaller matrices used in turn stay in the cache together: 4096 x 2048 38.0 and
-// 41.1, 8192 x 4096 49.5 and 52.2, but 16384 x 3072 57 and 53.
-constexpr int64_t LM_STREAM_BYTES = (int64_t)85 << 20;
-
 LmParams make_params(const lmhead_args* a) {
   LmParams p;
   p.h_cond = a->h_cond;
@@ -919,7 +895,6 @@ LmParams make_params(const lmhead_args* a) {
   p.cfg_scale = a->cfg_scale;
   p.temperature = a->temperature;
   p.top_k = a->top_k;
-  p.stream_w = a->dtype == CASCADE_BF16 && (int64_t)a->vocab * a->hidden * 2 >= LM_STREAM_BYTES;
   return p;
 }
 
@@ -944,13 +919,13 @@ hipError_t launch_lmhead_f32(cascade_ctx* ctx, const lmhead_args* a) {
   return hipGetLastError();
 }
 
-template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT = true>
-hipError_t launch_ring_t(cascade_ctx* ctx, LmParams p, int n_cols) {
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW, bool DIRECT, bool STREAM>
+hipError_t launch_ring_k(cascade_ctx* ctx, const LmParams& p, int n_cols) {
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NODES = CFG ? BM / 2 : BM;
   constexpr int RING = NST * (BM + BN) / 32 * KS * 1024, RED = KW > 1 ? 8 * AM * AN * 4096 : 0;
   constexpr int smem = RING > RED ? RING : RED;
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-  auto kern = lmhead_bf16_ring_kernel<AM, AN, WM, WN, KW, KS, NST, CFG, PW, DIRECT>;
+  auto kern = lmhead_bf16_ring_kernel<AM, AN, WM, WN, KW, KS, NST, CFG, PW, DIRECT, STREAM>;
   static bool attr_done = false;   // one flag per template instance
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
@@ -958,24 +933,26 @@ hipError_t launch_ring_t(cascade_ctx* ctx, LmParams p, int n_cols) {
     attr_done = true;
   }
   const int n_mtiles = (p.n_nodes + NODES - 1) / NODES;
-  // three row tiles and more that share a column of weights are bound by the matrix cores: 343 pairs x 33088 x 2048 the same
-  // over cold weights (122 us), 116 against 122 where the cache holds them
-  p.stream_w = p.stream_w && n_mtiles <= 2;
   KernelTimer t(ctx, CASCADE_K_LMHEAD);
   CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + BN - 1) / BN * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
 }
+template <int AM, int AN, int WM, int WN, int KW, int KS, int NST, bool CFG, bool PW>
+hipError_t launch_ring_t(cascade_ctx* ctx, const LmParams& p, int n_cols, bool stream) {
+  return stream ? launch_ring_k<AM, AN, WM, WN, KW, KS, NST, CFG, PW, true, true>(ctx, p, n_cols)
+                : launch_ring_k<AM, AN, WM, WN, KW, KS, NST, CFG, PW, true, false>(ctx, p, n_cols);
+}
 constexpr int LM_UNALIGNED = -1;   // ordinary loads: 64 x 64 or 128 x 128
 template <bool CFG, bool PW>
-hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols) {
+hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols, bool stream) {
   switch (tile) {
-    case 0: return launch_ring_t<2, 1, 1, 2, 4, 4, 6, CFG, PW>(ctx, p, n_cols);
-    case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p, n_cols);
-    case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p, n_cols);
-    case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p, n_cols);
-    case LM_UNALIGNED: return p.n_nodes * (CFG ? 2 : 1) <= 64 ? launch_ring_t<2, 1, 1, 2, 4, 8, 2, CFG, PW, false>(ctx, p, n_cols)
-                                                              : launch_ring_t<2, 2, 2, 2, 2, 8, 2, CFG, PW, false>(ctx, p, n_cols);
-    default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p, n_cols);
+    case 0: return launch_ring_t<2, 1, 1, 2, 4, 4, 6, CFG, PW>(ctx, p, n_cols, stream);
+    case 1: return launch_ring_t<2, 2, 2, 1, 4, 4, 4, CFG, PW>(ctx, p, n_cols, stream);
+    case 2: return launch_ring_t<2, 2, 1, 4, 2, 4, 3, CFG, PW>(ctx, p, n_cols, stream);
+    case 3: return launch_ring_t<2, 2, 2, 2, 2, 4, 4, CFG, PW>(ctx, p, n_cols, stream);
+    case LM_UNALIGNED: return p.n_nodes * (CFG ? 2 : 1) <= 64 ? launch_ring_k<2, 1, 1, 2, 4, 8, 2, CFG, PW, false, false>(ctx, p, n_cols)
+                                                              : launch_ring_k<2, 2, 2, 2, 2, 8, 2, CFG, PW, false, false>(ctx, p, n_cols);
+    default: return launch_ring_t<2, 2, 4, 2, 1, 4, 3, CFG, PW>(ctx, p, n_cols, stream);
   }
 }
 
@@ -990,6 +967,25 @@ struct LmTile {
 constexpr LmTile LM_TILES[7] = {{64, 64, 17.6f, 1.f, 0.83f}, {128, 64, 26.8f, 1.f, 0.64f}, {64, 256, 46.5f, 0.91f, 1.f}, {128, 128, 41.f, 0.83f, 0.8f},
                                 {256, 128, 72.f, 0.77f, 0.9f}, {128, 256, 68.5f, 0.87f, 0.77f}, {256, 256, 115.4f, 0.66f, 0.58f}};
 constexpr int LM_RING_TILES = 5;
+
+// Weights from this size on are streamed (see the ring kernel): a third of the last-level cache.  A step of 60 nodes whose
+// weights no cache holds, default policy and streamed: 8192 x 4096 (67 MB) 56.8 and 52.1 us, 16384 x 3072 (101 MB) 59 and 53, 16384 x
+// 4096 63 and 56, 40000 x 4096 111 and 100.  Three smaller matrices used in turn stay in the cache together: 4096 x 2048 38.0 and
+// 41.1, 8192 x 4096 49.5 and 52.2, but 16384 x 3072 57 and 53.
+// The rule counts on the layers of a model that pass between two projections.  The projection alone, default policy and
+// streamed, behind a copy of 1 GiB: 60 x 16384 x 4096 38.4 and 27.1 us, 120 x 33088 x 2048 (128 x 128) 64.2 and 51.8, 256 x 65536 x 4096
+// (256 x 128) 163 and 147; over copies of the weights in turn, of which the cache keeps some: 25.7 and 24.4, 51.3 and 50.2, 152
+// and 155.  A caller that repeats it on one matrix of at most 256 MB with nothing between finds that in the cache only without
+// streaming: 60 x 16384 x 4096 23 and 24 us, 120 x 16384 x 4096 26 and 33, 60 pairs x 33088 x 2048 row-major 23 and 35.
+constexpr int64_t LM_STREAM_BYTES = (int64_t)85 << 20;
+
+// Whether a launch of tiles over `rows` rows streams its weights.  Three row tiles and more that share a column of weights are
+// bound by the matrix cores: 343 pairs x 33088 x 2048 the same over cold weights (122 us), 116 against 122 where the cache holds them.
+bool lm_streams(int tile, int rows, int vocab, int hidden) {
+  if (tile == 5) return true;
+  return tile >= 0 && tile < LM_RING_TILES && (rows + LM_TILES[tile].rows - 1) / LM_TILES[tile].rows <= 2 &&
+         (int64_t)vocab * hidden * 2 >= LM_STREAM_BYTES;
+}
 
 // Time of the tiles of a launch over n_cols columns: rounds over the compute units.
 float lm_rounds_us(const LmTile& tile, int rows, int n_cols, int hidden, int n_cu) {
@@ -1064,9 +1060,10 @@ LmPlan lm_choose(const lmhead_args* a, int n_cu) {
 
 // one launch over columns [p.col0, p.col0 + n_cols)
 hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cfg, bool packed_w, int n_cols) {
+  const bool stream = lm_streams(tile, p.n_nodes * (cfg ? 2 : 1), p.vocab, p.hidden);
   if (tile < LM_RING_TILES) {
-    if (packed_w) return cfg ? launch_ring<true, true>(ctx, p, tile, n_cols) : launch_ring<false, true>(ctx, p, tile, n_cols);
-    return cfg ? launch_ring<true, false>(ctx, p, tile, n_cols) : launch_ring<false, false>(ctx, p, tile, n_cols);
+    if (packed_w) return cfg ? launch_ring<true, true>(ctx, p, tile, n_cols, stream) : launch_ring<false, true>(ctx, p, tile, n_cols, stream);
+    return cfg ? launch_ring<true, false>(ctx, p, tile, n_cols, stream) : launch_ring<false, false>(ctx, p, tile, n_cols, stream);
   }
   const bool half = tile == 5;
   const int nodes_per_tile = (cfg || half) ? 128 : 256, n_mtiles = (p.n_nodes + nodes_per_tile - 1) / nodes_per_tile;
@@ -1082,6 +1079,13 @@ hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cf
   KernelTimer t(ctx, CASCADE_K_LMHEAD);
   CASCADE_TIMED_LAUNCH(t, kern, dim3((n_cols + 255) / 256 * n_mtiles), dim3(512), smem, ctx->stream, p, n_mtiles);
   return hipGetLastError();
+}
+
+void plan_lmhead_streams(const lmhead_args* a, int n_cu, int32_t* streams, int32_t* rest_streams) {
+  const LmPlan plan = lm_choose(a, n_cu);
+  const int rows = a->n_nodes * (a->h_uncond != nullptr && !lm_premix(a) ? 2 : 1);
+  *streams = lm_streams(plan.main, rows, a->vocab, a->hidden);
+  *rest_streams = lm_streams(plan.rest, rows, a->vocab, a->hidden);
 }
 
 void plan_lmhead_bf16(const lmhead_args* a, int n_cu, int32_t* tile, int32_t* rest_tile, int32_t* rest_column) {

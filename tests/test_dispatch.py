@@ -13,6 +13,12 @@ def _tiles(n, vocab, hidden, mode, packed):
                                     cfg_mix=binding.CFG_MIX_HIDDEN if mode == "mixed" else binding.CFG_MIX_LOGITS)
 
 
+def _streams(n, vocab, hidden, mode, packed):
+    return binding.projection_streams(n_nodes=n, hidden=hidden, vocab=vocab, guided=mode != "plain",
+                                      w_layout=binding.W_PACKED32 if packed else binding.W_ROWMAJOR,
+                                      cfg_mix=binding.CFG_MIX_HIDDEN if mode == "mixed" else binding.CFG_MIX_LOGITS)
+
+
 def _marked(test, names):
     return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == names)
 
@@ -28,6 +34,20 @@ def test_every_projection_kernel_is_tested():
         pairs = mode == "pairs" or (mode == "mixed" and not packed)
         reached |= {(tile, pairs, packed), (rest, pairs, packed)}
     assert reached == {(t, c, p) for t in range(5) for c in (False, True) for p in (False, True)} | {(5, False, True), (6, False, True), (6, True, True)}
+
+
+def test_both_ways_of_loading_weights_are_tested_in_every_tile():
+    reached = set()     # (tile, rows in pairs, packed weights, streamed)
+    for shapes in (tiles.SHAPES, tiles.STREAMED):
+        for r, vocab, hidden in shapes:
+            for mode in ("plain", "pairs", "mixed"):
+                for packed in (True, False):
+                    n = max(1, r // 2) if mode == "pairs" else r
+                    pairs = mode == "pairs" or (mode == "mixed" and not packed)
+                    used = zip(_tiles(n, vocab, hidden, mode, packed)[:2], _streams(n, vocab, hidden, mode, packed))
+                    reached |= {(tile, pairs, packed, streamed) for tile, streamed in used}
+    ring = {(t, c, p, s) for t in range(5) for c in (False, True) for p in (False, True) for s in (False, True)}
+    assert ring <= reached and {s for t, _, _, s in reached if t == 5} == {True} and {s for t, _, _, s in reached if t == 6} <= {False}
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
@@ -47,4 +67,5 @@ def test_queries_refuse_what_they_do_not_describe():
     assert lib.cascade_attention_cut(None, a, n, n) == binding.EDTYPE and lib.cascade_projection_tiles(None, b, n, n, n) == binding.EDTYPE
     a.dtype = b.dtype = binding.BF16
     assert lib.cascade_attention_cut(None, a, n, n) == binding.EINVAL and lib.cascade_projection_tiles(None, b, n, n, n) == binding.EINVAL
+    assert lib.cascade_projection_streams(None, b, n, n) == binding.EINVAL and lib.cascade_projection_streams(None, None, n, n) == binding.EINVAL
     assert lib.cascade_attention_cut(None, None, n, n) == binding.EINVAL and lib.cascade_projection_tiles(None, None, n, n, n) == binding.EINVAL

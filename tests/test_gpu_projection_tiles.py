@@ -30,6 +30,18 @@ def test_projection_tiles(rows, vocab, hidden, mode, packed):
     _check(max(1, rows // 2) if mode == "pairs" else rows, vocab, hidden, mode, packed)
 
 
+# the same with weights that are loaded past the caches (85 MiB and more, at most two row tiles): every tile of the ring kernel, for
+# pairs or not, packed or row-major weights, and 128 x 256 (mixed rows; tests/test_dispatch.py counts these too)
+STREAMED = [(33, 16384, 2816), (61, 16384, 2816), (120, 16384, 2816), (60, 65472, 768), (200, 16448, 2816), (200, 65472, 768), (300, 16384, 2816)]
+
+
+@pytest.mark.parametrize("rows,vocab,hidden", STREAMED)
+@pytest.mark.parametrize("mode", ["plain", "pairs", "mixed"])
+@pytest.mark.parametrize("packed", [True, False])
+def test_projection_tiles_with_streamed_weights(rows, vocab, hidden, mode, packed):
+    _check(max(1, rows // 2) if mode == "pairs" else rows, vocab, hidden, mode, packed)
+
+
 # the large tiles, with one row in the last of them, at hidden sizes of one, three and five rounds of their rings (and the
 # 256 x 128 ring tile at as many): nodes, vocabulary, hidden, mode, tile
 @pytest.mark.parametrize("n,vocab,hidden,mode,tile", [

@@ -108,17 +108,19 @@ def _check_lds_direct(name, body, direct):
 
 
 def test_ring_projection_m0_and_waits(tmp_path):
-    """Every instance of the ring projection: five tiles and, with ordinary loads, two, for pairs or not and packed weights or
-    not.  With LDS-direct loads two to five stages stay in flight, so the loop holds no wait for ALL outstanding loads."""
+    """Every instance of the ring projection: five tiles with streamed and with plain weights and, with ordinary loads, two, for
+    pairs or not and packed weights or not.  With LDS-direct loads two to five stages stay in flight, so the loop holds no wait for ALL outstanding loads."""
     _, text = _kernel_stats("lmhead.hip", tmp_path)
     bodies = _bodies(text, "lmhead_bf16_ring_kernel")
-    assert len(bodies) == 28
+    assert len(bodies) == 48
     for name, body in bodies:
-        direct = "ELb1EEEv" in name
+        direct, stream = "ELb1ELb" in name[name.index("EEEv") - 10:], "ELb1EEEv" in name
         _check_lds_direct(name, body, direct)
         loop = body[body.index("Loop Header"):body.rindex("vmcnt(0)")]      # up to the drain behind it
         assert "s_barrier" in loop and "v_mfma_f32_32x32x16_bf16" in loop, name
         assert not direct or "vmcnt(0)" not in loop, name
+        streamed = len(re.findall(r"global_load_lds_dwordx4 .* nt$", body, flags=re.M))
+        assert 0 < streamed < body.count("global_load_lds_dwordx4") if stream else streamed == 0, name
 
 
 def test_row_cut_attention_m0(tmp_path):
