@@ -380,9 +380,9 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
 // HALF (no guidance only): 128-row tiles for steps whose 256-row tiles would leave compute units idle - a wave owns
 // 2 x 2 accumulators; the tile has four H blocks per k16 step, eight per half-stage: wave w requests block w % 4 of
 // step w / 4, so every wave issues three loads per half-stage (one H, two W) and the wait counts stay uniform.
-template <bool CFG, bool HALF>
+template <bool CFG, bool HALF, bool STREAM>
 __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int n_mtiles) {
-  static_assert(!(CFG && HALF), "half tiles exist for the plain projection only");
+  static_assert(!(CFG && HALF) && (HALF || !STREAM), "half tiles exist for the plain projection only, and only they stream");
   constexpr int NI = HALF ? 2 : 4;   // row blocks per wave
   extern __shared__ u32x4 lds[];     // [4 half-stages][2 k16 steps][16 blocks: 8 H then 8 W][64 lanes]
   constexpr int NBUF = 4, HS = 2, HBYTES = HS * 16 * 1024;
@@ -392,9 +392,10 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   const int KS = p.hidden / 16, n_half = KS / HS;
   const unsigned lane_off = 16u * lane;                        // byte offset of this lane's 16-byte piece in a block
 
-  int logical = blockIdx.x;
-  const int nwg = gridDim.x;
-  if ((nwg & 7) == 0) logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+  // the row tiles of a column share an XCD's L2, as in the ring kernel and for any grid: streamed weights that every XCD fetched
+  // for its own row tile came from HBM each time (400 rows x 33024 x 4096, 516 tiles: 249 us, so 180; with plain weights 223 and 182)
+  const int nwg = gridDim.x, xcd = blockIdx.x & 7;
+  const int logical = xcd * (nwg >> 3) + min(xcd, nwg & 7) + (blockIdx.x >> 3);
   const int nt = logical / n_mtiles, mt = logical % n_mtiles;
 
   // loader: per k16 step a wave copies block wave (H) and block wave + 8 (W); both base pointers are scalars
@@ -415,8 +416,8 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
   }
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
   const int last = n_half - 1;
-  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd).  Half tiles stream W like the ring
-  // kernel (480 rows x 16384 x 1024 to 4096: 25.9 -> 25.1 us, 40.7 -> 38.7, 69 -> 67), whole ones do not (400 rows x 65536 x 2048 122 -> 129).  h may run past the end:
+  // request i of a half-stage: k16 step i / 2, H (i even) or W (i odd).  Half tiles may stream W like the ring
+  // kernel (see lm_streams), whole ones do not (400 rows x 65536 x 2048 122 -> 129).  h may run past the end:
   // clamped, that data is never multiplied.  M0 carries the LDS address of the wave's 1 KiB block;
   // each lane's 16 bytes land at 16 * lane behind it.
   auto request = [&](int h, int buf, int i) {
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(512) void lmhead_bf16_tiled_kernel(LmParams p, int 
     const char* g = src[i & 1] + ((int64_t)min(h, last) * HS + ks) * 1024;
     const int slot = (i & 1) ? 8 + wave : (HALF ? (wave & 3) : wave);
     const unsigned l = lds0 + buf * HBYTES + (ks * 16 + slot) * 1024;
-    if (HALF && (i & 1)) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
+    if (STREAM && (i & 1)) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(lane_off), "s"(g) : "memory");
   };
   // A wave's own loads of the next half-stage have landed when at most the 2 x 4 later ones are
@@ -979,12 +980,15 @@ constexpr int LM_RING_TILES = 5;
 // streaming: 60 x 16384 x 4096 23 and 24 us, 120 x 16384 x 4096 26 and 33, 60 pairs x 33088 x 2048 row-major 23 and 35.
 constexpr int64_t LM_STREAM_BYTES = (int64_t)85 << 20;
 
-// Whether a launch of tiles over `rows` rows streams its weights.  Three row tiles and more that share a column of weights are
-// bound by the matrix cores: 343 pairs x 33088 x 2048 the same over cold weights (122 us), 116 against 122 where the cache holds them.
+// Whether a launch of tiles over `rows` rows streams its weights.  In the ring kernel, three row tiles and more that share a column
+// of weights are bound by the matrix cores: 343 pairs x 33088 x 2048 the same over cold weights (122 us), 116 against 122 where the
+// cache holds them.  128 x 256 tiles stream for any number of them: behind a copy of 1 GiB 300 rows x 16384 x 4096 69.7 -> 61.5 us, 480 x 16384 x 4096
+// 71.2 -> 66.0, 480 x 65536 x 2048 152 -> 142; over copies in turn 400 x 33088 x 4096 146.4 -> 143.1, 256 x 65536 x 4096 157.3 -> 153.7,
+// 200 x 65536 x 2048 80.9 -> 85.1.  Smaller weights, not streamed and streamed: 300 x 20480 x 2048 over copies in turn 38.0 and 38.7,
+// repeated 34.9 and 38.5.
 bool lm_streams(int tile, int rows, int vocab, int hidden) {
-  if (tile == 5) return true;
-  return tile >= 0 && tile < LM_RING_TILES && (rows + LM_TILES[tile].rows - 1) / LM_TILES[tile].rows <= 2 &&
-         (int64_t)vocab * hidden * 2 >= LM_STREAM_BYTES;
+  if (tile < 0 || tile > 5 || (int64_t)vocab * hidden * 2 < LM_STREAM_BYTES) return false;
+  return tile == 5 || (rows + LM_TILES[tile].rows - 1) / LM_TILES[tile].rows <= 2;
 }
 
 // Time of the tiles of a launch over n_cols columns: rounds over the compute units.
@@ -1068,9 +1072,11 @@ hipError_t launch_lm_tile(cascade_ctx* ctx, const LmParams& p, int tile, bool cf
   const bool half = tile == 5;
   const int nodes_per_tile = (cfg || half) ? 128 : 256, n_mtiles = (p.n_nodes + nodes_per_tile - 1) / nodes_per_tile;
   const size_t smem = (size_t)4 * 32 * 1024;   // ring of four 32 KiB half-stages
-  static bool attr_done[3] = {false, false, false};
-  auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false> : (half ? lmhead_bf16_tiled_kernel<false, true> : lmhead_bf16_tiled_kernel<false, false>);
-  const int which = cfg ? 0 : (half ? 1 : 2);
+  static bool attr_done[4] = {false, false, false, false};
+  auto kern = cfg ? lmhead_bf16_tiled_kernel<true, false, false>
+                  : (half ? (stream ? lmhead_bf16_tiled_kernel<false, true, true> : lmhead_bf16_tiled_kernel<false, true, false>)
+                          : lmhead_bf16_tiled_kernel<false, false, false>);
+  const int which = cfg ? 0 : (half ? 1 + stream : 3);
   if (!attr_done[which]) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;

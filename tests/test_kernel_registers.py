@@ -39,7 +39,7 @@ def test_tiled_projection_m0_and_waits(tmp_path):
     its main loop must not contain a wait for ALL outstanding loads."""
     _, text = _kernel_stats("lmhead.hip", tmp_path)
     bodies = re.findall(r"^(_ZN\S*lmhead_bf16_tiled_kernel\S*):[^\n]*\n(.*?)s_endpgm", text, flags=re.S | re.M)
-    assert len(bodies) == 3          # guidance pairs, plain rows, plain rows in 128-row tiles
+    assert len(bodies) == 4          # guidance pairs, plain rows, plain rows in 128-row tiles with plain and with streamed weights
     for name, body in bodies:
         m0 = [l.strip() for l in body.splitlines() if re.search(r"\bm0\b", l)]
         assert m0 and all(l.startswith("s_mov_b32 m0,") for l in m0), (name, m0[:5])
