@@ -597,7 +597,9 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // ranked exactly by their integer keys, and only the listed entries see an exponential - two rounds of a wave's lanes
 // for k = 2000, where one list per thread took as many as the fullest of 64 lists (6 to 8), and rows whose kept entries crowd
 // into some threads fell back.  What bounds a row once it is in registers is the instructions of its 16 waves and the
-// barriers between the stages.  60 rows x 16384 6.6 -> 6.0 us, 462 x 16384 15.3 -> 14.1, 343 x 33088 28.7 -> 21.8, 1024 x 65536
+// barriers between the stages; values that a wave has no hit among, most of them for small k, cost it a comparison and a branch
+// (700 x 65536 with k = 50 47.4 us with a list per thread, 50.9 with a ballot and a count for every value, 45 so).  60 rows x 16384 6.6 ->
+// 6.0 us, 462 x 16384 15.3 -> 14.1, 300 x 33088 with k = 8000, where lists per thread overflowed, 0.27 of the time, 1024 x 65536
 // 76.6 -> 74.0.  (Two workgroups per compute unit, at 64 registers: 462 x 16384 16.3 us, spilled from 24576 entries on.)
 // Rows the fast path does not fit (degenerate or non-finite sample range, k-th largest in the lowest bin, more
 // than RS_CAND candidates, a wave with more than RS_CAP - 64 listed entries) take the radix rounds: slow, exact.
@@ -760,6 +762,9 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     mx = wave_max(mx);
     if (lane == 0) sm.f_max[wave] = mx;
     __syncthreads();                       // maxima and every atomic of the sweep
+    mx = sm.f_max[0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sm.f_max[w]);
 
     float thr = -INFINITY, se = 0.f;
     bool done = false;
@@ -777,11 +782,13 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
         for (int i = 0; i < VPT; ++i) {
           const bool hit = fmaf(x[i], bs, bc) >= Bf;   // bin(x) >= B (B >= 1: the clamp at 0 plays no part; the one at 4095 cannot matter)
           const unsigned long long m = __ballot(hit);
-          const int at = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_list));
-          if (hit) list[at] = x[i];
-          n_list += __popcll(m);
-          most = max(most, n_list);
-          n_list = min(n_list, RS_CAP - 64);           // room for the next 64
+          if (m) {
+            const int at = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_list));
+            if (hit) list[at] = x[i];
+            n_list += __popcll(m);
+            most = max(most, n_list);
+            n_list = min(n_list, RS_CAP - 64);         // room for the next 64
+          }
           if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
         if (most > RS_CAP - 64 && lane == 0) sm.flag = 1;
@@ -791,9 +798,6 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     }
     // The registers are free (the rounds below re-read the row): the next row arrives during this row's tail.
     if (next < p.n_nodes) load_row(next);
-    mx = sm.f_max[0];
-#pragma unroll
-    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sm.f_max[w]);
     if (done) {
       // listed entries: above bin B -> kept; in bin B -> candidate
       const float B1f = (float)(B + 1);
