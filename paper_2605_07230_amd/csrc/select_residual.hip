@@ -8,11 +8,13 @@
 // coalesced read of the drafter row, a workgroup sum and a rescale; an acceptance one read of the
 // new node's logits row.  All decisions are taken by every thread on the same broadcast scalars,
 // so control flow stays uniform.  The inverse CDF at the end runs over the same registers.
-// Bound by the chain of dependent trips to memory: the scalars of all nodes (and the drafter's probability of each node's
-// token) are fetched once, by a thread per node, and a child's drafter row is on its way while the child is tested.  In a step,
-// with a trip per tried child for each of these before: 60 nodes x 16384, four prompts 22.4 -> 15.7 us, 60 x 4096 10.7 -> 9.2,
-// 60 x 20480 50.6 -> 14.6 (also: frames of its own up to 32768 and 49152
-// entries), 50 x 33088, two prompts 53.5 -> 26.2, 60 x 65536 32.0 -> 25.7.
+// Bound by the chain of dependent trips to memory: the scalars of all nodes (and, but for the widest frame, the drafter's
+// probability of each node's token) are fetched once, by a thread per node, and the drafter row of a rejected child's sibling is on
+// its way while the child's residual is summed.  In a step, with a trip per tried child for each of these before: 60 nodes x 16384,
+// four prompts 22.4 -> 15.6 us, 60 x 4096 10.7 -> 9.2, 60 x 20480 50.6 -> 14.6 (also: frames of its own up to 32768 and
+// 49152 entries), 50 x 33088, two prompts 53.5 -> 26.2.  The row of a node's first child is not requested before its test:
+// chains of eight accepted first children 9.7 -> 8.9 us (1000 entries), 13.0 -> 12.5 (8192), 13.7 -> 12.8 (16384), with a row for each of
+// them 10.5, 15.9 and 15.0.
 #include "common.h"
 
 namespace {
@@ -42,7 +44,7 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
   constexpr int SEG = 256 * VQ;
   __shared__ int s_child[CASCADE_MAX_WIDTH];
   __shared__ int s_par[CASCADE_MAX_TREE], s_tok[CASCADE_MAX_TREE];                       // the tree's nodes
-  __shared__ float s_mi[CASCADE_MAX_TREE], s_mc[CASCADE_MAX_TREE], s_up[CASCADE_MAX_TREE];   // s_up: u times the drafter's probability
+  __shared__ float s_mi[CASCADE_MAX_TREE], s_mc[CASCADE_MAX_TREE], s_up[CASCADE_MAX_TREE];   // s_up: u, times the drafter's probability (GATHER)
   __shared__ int s_path[CASCADE_MAX_DEPTH];
   __shared__ int s_m, s_x;
   __shared__ float s_q;
@@ -74,17 +76,17 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     }
   };
 
-  // the drafter row of a child, requested before it is known whether the child is rejected (frames of 8 and 16 vectors have no
-  // registers for it and read the row when they need it, twice)
-  constexpr bool AHEAD = VQ <= 4;
+  // AHEAD: the drafter row of a child is requested before it is known whether the child is rejected (frames of 8 vectors and more
+  // have no registers for it and read the row when they need it, twice).  GATHER: probabilities of all tokens at once; 250
+  // nodes x 65536 are as many lines and pages (16 prompts 43.0 -> 46.8 us, with one at a time 41.6).
+  constexpr bool AHEAD = VQ <= 4, GATHER = VQ < 16;
   f32x4 pr[AHEAD ? VQ : 1];
   auto load_draft = [&](int node) {
     const float* prow = a.draft_dist + (int64_t)(lo + node) * V;
 #pragma unroll
     for (int i = 0; i < (AHEAD ? VQ : 0); ++i) {
       const int e = e_base + 256 * i;
-      pr[i] = *(const f32x4*)((const char*)prow + 4u * (unsigned)(EXACT ? e : min(e, V - 4)));
-      if (!EXACT && e >= V) pr[i] = f32x4{0.f, 0.f, 0.f, 0.f};   // f is 0 there as well
+      pr[i] = *(const f32x4*)((const char*)prow + 4u * (unsigned)(EXACT ? e : min(e, V - 4)));   // (a select on it would wait for it here)
     }
   };
 
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     s_mi[tid] = a.m_int[lo + tid];
     s_mc[tid] = a.m_conv[lo + tid];
     s_tok[tid] = tok;
-    s_up[tid] = u * (tok >= 0 && tok < V ? a.draft_dist[(int64_t)(lo + tid) * V + tok] : 1.f);
+    s_up[tid] = GATHER && tok >= 0 && tok < V ? u * a.draft_dist[(int64_t)(lo + tid) * V + tok] : u;
   }
   int cur = 0, len = 0;
   float tvd = 0.f;
@@ -125,7 +127,6 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
     __syncthreads();
     const int m = s_m;
     int accepted = -1;
-    if (AHEAD && m > 0) load_draft(s_child[0]);
     for (int j = 0; j < m; ++j) {
       const int ch = s_child[j];
       const int ta = s_tok[ch];
@@ -146,11 +147,13 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
         atomicOr(dev_status, CASCADE_FLAG_TOKEN);
         s_q = 0.f;
       }
+      const float px = !GATHER && tok_ok ? prow[ta] : 1.f;
       __syncthreads();
-      const Try t = try_node(s_q, s_mi[ch], s_mc[ch], s_up[ch], tvd, eps);
+      const Try t = try_node(s_q, s_mi[ch], s_mc[ch], s_up[ch] * px, tvd, eps);
       tvd = t.tvd;
       if (t.pass) { accepted = ch; break; }
       // rejected: f <- norm([f - p]_+), kept as it is when nothing would be left
+      if (AHEAD && j == 0) load_draft(ch);
       float loc = 0.f;
       f32x4 left[AHEAD ? VQ : 1];
       auto take_away = [&](int i, const f32x4& p4) {
@@ -167,7 +170,8 @@ __global__ __launch_bounds__(1024) void select_residual_kernel(select_args a, in
       };
 #pragma unroll
       for (int i = 0; i < VQ; ++i) {
-        const f32x4 d = take_away(i, AHEAD ? pr[AHEAD ? i : 0] : row_of(i));
+        f32x4 d = take_away(i, AHEAD ? pr[AHEAD ? i : 0] : row_of(i));
+        if (AHEAD && !EXACT && e_base + 256 * i >= V) d = f32x4{0.f, 0.f, 0.f, 0.f};   // past the row: f is 0 and stays 0
         loc += ((d[0] + d[1]) + d[2]) + d[3];
         if (AHEAD) left[AHEAD ? i : 0] = d;
         if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
