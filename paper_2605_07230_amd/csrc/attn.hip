@@ -407,12 +407,12 @@ __device__ __forceinline__ float rows4_max_raw(float v) {
 // DIRECT = false: keys and values that do not start on a 16-byte boundary, or positions more than 64 MiB apart.  LDS-direct
 // loads are counted on for aligned addresses only and take 32-bit offsets inside a tile; ordinary loads with 64-bit addresses
 // take any.  They pass through registers and are stored to the same places at the end of the step that requested them.
-template <int D, int NS, int NQ, int NW, bool WHOLE, bool FINE, bool DIRECT>
+template <int D, int NS, int NQ, int NW, bool WHOLE, bool FINE, bool DIRECT, bool STREAM>
 __device__ __forceinline__ void ring_body(const AttnParams& p) {
   using GM = RingGeom<D>;
   constexpr int NT = 64 * NW, RW = 16 * NQ * NW;
   constexpr int KS = D / 32, DB = D / 16;
-  static_assert(!(WHOLE && FINE), "the 256-row kernel lets the reference lag");
+  static_assert(!(WHOLE && FINE) && (DIRECT || !STREAM), "the 256-row kernel lets the reference lag; LDS-direct loads stream");
   constexpr int LW = GM::CPT % NW == 0 ? NW : 4;   // waves that load: all, or the first four when the chunks do not divide
   constexpr int CPW = GM::CPT / LW;     // chunks of K (and of V) a loading wave fetches per tile
   constexpr int LPI = 2 * CPW;          // LDS-direct loads a wave issues per iteration
@@ -485,10 +485,13 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     for (int i = 0; i < (DIRECT ? 0 : CPW); ++i)
       *(u32x4*)(smem_raw + (is_v ? NS * GM::TILE : 0) + stage * GM::TILE + (CPW * wave + i) * 1024 + 16 * lane) = held[is_v][i];
   };
-  // A prefix that one workgroup per (row, kv head) reads, once, is streamed: 16 rows of 100-600 keys 39.6 -> 35.9 us and 3 us off
-  // the step behind it, 8 rows 1 us off the step.  With keys in parts (2 rows of 1289 keys) and 256-row workgroups (8 rows of
-  // 4200) it changes nothing; prefixes that several query blocks read meet in an L2 and stay with the default policy.
-  const bool stream = !WHOLE && p.n_sb == 1 && p.n_split == 1;
+  // STREAM: a prefix that one workgroup per (row, kv head) reads, once, is streamed: 16 rows of 100-600 keys 39.6 -> 35.9 us and 3 us
+  // off the step behind it, 8 rows 1 us off the step.  With keys in parts (2 rows of 1289 keys) and 256-row workgroups (8 rows of
+  // 4200) it changes nothing; prefixes that several query blocks read meet in an L2 and stay with the default policy.  The rule
+  // counts on the other layers of a model between two steps: attention alone behind a copy of 1 GiB, 8 rows of 1289 keys, 60 nodes
+  // 61 -> 40 us, 16 of 312 keys 40 -> 34; repeated on the same prefixes, which the last-level cache then keeps, 32.6 -> 36 and 26.1 -> 26.5.
+  // Instances of their own: chosen at every request it made the others up to 4 % slower (4 rows of 1289 keys, 119 nodes, head_dim 64:
+  // 25.3 -> 26.2).
   auto request = [&](int tk, int stage, bool is_v) {
     if (LW < NW && wave >= LW) return;
     const int tc = min(tk, t_end - 1);
@@ -506,18 +509,11 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
     if (tc < n_pt && (tc + 1) * KT <= P) {
       // a whole tile of the prefix: nothing to clamp, the per-lane offsets are constants
       const char* src = (is_v ? vc : kc) + (int64_t)tc * KT * cache_pitch_b;
-      if (stream) {
 #pragma unroll
-        for (int i = 0; i < CPW; ++i) {
-          const unsigned l = ldst + i * 1024;
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < CPW; ++i) {
-          const unsigned l = ldst + i * 1024;
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
-        }
+      for (int i = 0; i < CPW; ++i) {
+        const unsigned l = ldst + i * 1024;
+        if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
+        else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(is_v ? ld_vfull[i] : ld_kfull[i]), "s"(src) : "memory");
       }
     } else {
       const bool tree_tile = tc >= n_pt;
@@ -845,7 +841,7 @@ __device__ __forceinline__ void ring_body(const AttnParams& p) {
 }
 
 template <int D, int NS>
-__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { ring_body<D, NS, 2, 8, true, false, true>(p); }
+__global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { ring_body<D, NS, 2, 8, true, false, true, false>(p); }
 
 // 64 (4 waves), 80 (5), 96 (6) or, with two query blocks per wave, 128 rows per workgroup: two workgroups share a compute
 // unit (two-deep rings, 64 KiB) and cover each other's waits.  One workgroup as large as the row's tree reads every key once:
@@ -853,8 +849,8 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_ring_kernel(AttnParams p) { 
 // the same or slower at every shape.  Against the kernels this replaced, in a step (us): 16 rows of 113-680 keys, 40-80
 // nodes: 46 -> 37; 10 rows of 107-1619 keys, 8 kv heads of 4: 54 -> 34; 8 rows of 140-680 keys: 25 -> 22; 2 rows of 4200 keys
 // and 256 nodes, keys in four parts: 65 -> 59 with the merge; 2 rows of 1289 keys, four parts: 23 -> 21.
-template <int D, int NS, int NQ, int NW, int OCC, bool FINE, bool DIRECT>
-__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false, FINE, DIRECT>(p); }
+template <int D, int NS, int NQ, int NW, int OCC, bool FINE, bool DIRECT, bool STREAM>
+__global__ __launch_bounds__(64 * NW, OCC) void attn_bf16_rows_kernel(AttnParams p) { ring_body<D, NS, NQ, NW, false, FINE, DIRECT, STREAM>(p); }
 
 // ---------------------------------------------------------------------- bf16, few query rows
 // When a step has so few (row, kv head) pairs and keys that the chain of tiles of one workgroup is what takes the time,
@@ -1215,25 +1211,32 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
 }
 
 // 16 NQ NW query rows per workgroup, keys split p.n_split ways (partials, then the merge kernel)
-template <int D, int NQ, int NW, int OCC, bool FINE, bool DIRECT>
-hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
+template <int D, int NQ, int NW, int OCC, bool FINE, bool DIRECT, bool STREAM>
+hipError_t launch_rows_k(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
   constexpr int NS = 2, RW = 16 * NQ * NW;
   constexpr int smem = 2 * NS * RingGeom<D>::TILE + CASCADE_MAX_TREE * (int)sizeof(int) + 2 * RW * (int)sizeof(unsigned long long);
+  auto kern = attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, FINE, DIRECT, STREAM>;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, FINE, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   {
     KernelTimer t(ctx, CASCADE_K_ATTN);
-    CASCADE_TIMED_LAUNCH(t, (attn_bf16_rows_kernel<D, NS, NQ, NW, OCC, FINE, DIRECT>), grid, dim3(64 * NW), smem, ctx->stream, p);
+    CASCADE_TIMED_LAUNCH(t, kern, grid, dim3(64 * NW), smem, ctx->stream, p);
   }
   if (p.n_split > 1) {
     KernelTimer t(ctx, CASCADE_K_ATTN_MERGE);
     CASCADE_TIMED_LAUNCH(t, (attn_merge_kernel<D>), dim3((p.n_rows_total + (1024 / D) - 1) / (1024 / D)), dim3(256), 0, ctx->stream, p);
   }
   return hipGetLastError();
+}
+// a prefix that one workgroup reads, once, is streamed (see ring_body)
+template <int D, int NQ, int NW, int OCC, bool FINE>
+hipError_t launch_rows_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
+  return p.n_sb == 1 && p.n_split == 1 ? launch_rows_k<D, NQ, NW, OCC, FINE, true, true>(ctx, p, grid)
+                                       : launch_rows_k<D, NQ, NW, OCC, FINE, true, false>(ctx, p, grid);
 }
 
 template <int D>
@@ -1321,10 +1324,10 @@ bool attn_fine(const tree_attn_args* a, int group, int n_split, int n_cu) {
 template <int D, bool FINE>
 hipError_t launch_rows(cascade_ctx* ctx, const AttnParams& p, int shape, dim3 grid) {
   switch (shape) {
-    case 0: return launch_rows_t<D, 1, 4, 2, FINE, true>(ctx, p, grid);
-    case 1: return launch_rows_t<D, 1, 5, 3, FINE, true>(ctx, p, grid);
-    case 2: return launch_rows_t<D, 1, 6, 3, FINE, true>(ctx, p, grid);
-    default: return launch_rows_t<D, 2, 4, 2, FINE, true>(ctx, p, grid);
+    case 0: return launch_rows_t<D, 1, 4, 2, FINE>(ctx, p, grid);
+    case 1: return launch_rows_t<D, 1, 5, 3, FINE>(ctx, p, grid);
+    case 2: return launch_rows_t<D, 1, 6, 3, FINE>(ctx, p, grid);
+    default: return launch_rows_t<D, 2, 4, 2, FINE>(ctx, p, grid);
   }
 }
 
@@ -1332,7 +1335,7 @@ template <int D>
 hipError_t launch_bf16_t(cascade_ctx* ctx, const AttnParams& p, int shape, bool fine, bool direct, dim3 grid) {
   if (shape == ATTN_RING) return launch_ring_t<D>(ctx, p, grid);
   if (shape == ATTN_QSPLIT) return launch_qsplit_t<D>(ctx, p, grid);
-  if (!direct) return shape == 0 ? launch_rows_t<D, 1, 4, 2, true, false>(ctx, p, grid) : launch_rows_t<D, 1, 8, 2, true, false>(ctx, p, grid);
+  if (!direct) return shape == 0 ? launch_rows_k<D, 1, 4, 2, true, false, false>(ctx, p, grid) : launch_rows_k<D, 1, 8, 2, true, false, false>(ctx, p, grid);
   return fine ? launch_rows<D, true>(ctx, p, shape, grid) : launch_rows<D, false>(ctx, p, shape, grid);
 }
 

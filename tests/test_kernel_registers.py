@@ -124,12 +124,14 @@ def test_ring_projection_m0_and_waits(tmp_path):
 
 
 def test_row_cut_attention_m0(tmp_path):
-    """Every instance of the smaller attention cuts: four at two head widths with the running or the tile's maximum, and two
-    with ordinary loads.  Their rings are two deep: a tile is waited for whole, one barrier each."""
+    """Every instance of the smaller attention cuts: four at two head widths with the running or the tile's maximum, prefixes
+    streamed or not, and two with ordinary loads.  Their rings are two deep: a tile is waited for whole, one barrier each."""
     _, text = _kernel_stats("attn.hip", tmp_path)
     bodies = _bodies(text, "attn_bf16_rows_kernel")
-    assert len(bodies) == 20
+    assert len(bodies) == 36
     for name, body in bodies:
-        _check_lds_direct(name, body, "ELb1EEEv" in name)
+        _check_lds_direct(name, body, "ELb1ELb" in name[name.index("EEEv") - 10:])
+        streamed = len(re.findall(r"global_load_lds_dwordx4 .* nt$", body, flags=re.M))
+        assert 0 < streamed < body.count("global_load_lds_dwordx4") if "ELb1EEEv" in name else streamed == 0, name
         loop = body[body.index("=>This Loop Header: Depth=1"):body.rindex("vmcnt(0)")]
         assert loop.count("s_barrier") == 2, name
