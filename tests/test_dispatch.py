@@ -52,13 +52,15 @@ def test_both_ways_of_loading_weights_are_tested_in_every_tile():
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_every_attention_cut_is_tested(head_dim):
-    reached = set()
+    reached, loads = set(), set()
     for name, (kv_heads, group, sizes, prefix) in cuts.CASES.items():
         cut = binding.attention_cut(n_rows=len(sizes), n_nodes_total=sum(sizes), max_nodes_per_tree=max(sizes), max_prefix_len=max(prefix),
                                     n_heads=kv_heads * group, n_kv_heads=kv_heads, head_dim=head_dim)
         assert cut == cuts.CUTS[name][head_dim == 128], name
         reached.add((cut[0], cut[1] > 1))
+        loads.add((cut[0], cut[1] == 1 and max(sizes) * group <= cut[0]))    # one block and one part: the prefix is streamed
     assert {r for r, _ in reached} == {16, 64, 80, 96, 128, 256} and {(64, True), (64, False), (128, True), (128, False)} <= reached
+    assert {(rows, streamed) for rows in (64, 80, 96, 128) for streamed in (True, False)} <= loads
 
 
 def test_queries_refuse_what_they_do_not_describe():

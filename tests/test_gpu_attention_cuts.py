@@ -36,6 +36,18 @@ CASES = {   # kv heads, query heads per kv head, tree sizes, prefix lengths (cut
     "256 rows": (32, 1, [256, 255, 130, 200, 140, 199, 250, 256], [70, 1, 0, 64, 65, 130, 200, 31]),
     "query split": (2, 1, [20, 17], [400, 63]),
     "query split, one node": (1, 1, [1], [0]),
+    # the cuts above with several blocks of query rows or several parts where they had one (prefixes are not streamed then), and
+    # with fewer or more workgroups (the tile's own maximum, or the running one)
+    "64 rows, grouped heads, full chip": (8, 4, [80, 80, 66, 3, 80, 79, 41, 1, 80], [24, 0, 64, 65, 1, 20, 70, 13, 5]),
+    "80 rows, grouped heads, several blocks": (16, 2, [70] * 8 + [69], [24, 0, 24, 1, 20, 24, 13, 5, 24]),
+    "80 rows, grouped heads, few workgroups": (8, 4, [40] * 15 + [39], [24, 0, 24, 1, 20, 24, 13, 5, 24, 24, 7, 23, 19, 24, 2, 24]),
+    "80 rows, one block, few workgroups": (16, 2, [33, 40, 5, 33, 40, 40, 21, 1, 40, 38, 40, 40], [24, 0, 64, 65, 1, 20, 70, 13, 5, 24, 24, 7]),
+    "96 rows, grouped heads, several blocks": (8, 4, [70] * 8 + [69], [24, 0, 24, 1, 20, 24, 13, 5, 24]),
+    "96 rows, keys in parts": (8, 1, [90] * 5 + [89], [513, 90, 400, 64, 0, 130]),
+    "96 rows, few workgroups": (32, 1, [90, 96, 81, 3, 64, 95], [24, 0, 64, 65, 1, 20]),
+    "128 rows, grouped heads, several blocks": (8, 4, [60] * 15 + [59], [24, 0, 24, 1, 20, 24, 13, 5, 24, 24, 7, 23, 19, 24, 2, 24]),
+    "128 rows, one block, few workgroups": (32, 1, [15, 20, 7, 15, 20, 19, 3, 20, 15, 20, 1, 20], [24, 0, 64, 65, 1, 20, 70, 13, 5, 24, 24, 7]),
+    "128 rows, grouped heads, keys in parts": (16, 2, [60, 64, 33, 60, 60, 21, 64, 64], [2000, 1300, 64, 1900, 2000, 7, 1000, 2000]),
 }
 
 # (query rows per workgroup, parts of the keys) that 256 compute units choose, at head_dim 64 and 128
@@ -44,13 +56,20 @@ CUTS = {
     "64 rows, grouped heads, ragged blocks": ((64, 8), (64, 8)), "80 rows": ((80, 1), (80, 1)), "96 rows": ((96, 1), (96, 1)),
     "128 rows": ((128, 1), (128, 1)), "128 rows, keys in parts": ((64, 3), (128, 4)), "128 rows, long keys in parts": ((128, 4), (128, 4)),
     "256 rows": ((256, 1), (256, 1)), "query split": ((16, 1), (16, 1)), "query split, one node": ((16, 1), (16, 1)),
+    "64 rows, grouped heads, full chip": ((64, 1), (64, 1)), "80 rows, grouped heads, several blocks": ((80, 1), (80, 1)),
+    "80 rows, grouped heads, few workgroups": ((80, 1), (80, 1)), "80 rows, one block, few workgroups": ((80, 1), (80, 1)),
+    "96 rows, grouped heads, several blocks": ((96, 1), (96, 1)), "96 rows, keys in parts": ((96, 4), (96, 4)), "96 rows, few workgroups": ((96, 1), (96, 1)),
+    "128 rows, grouped heads, several blocks": ((64, 1), (128, 1)), "128 rows, one block, few workgroups": ((64, 1), (128, 1)),
+    "128 rows, grouped heads, keys in parts": ((128, 3), (128, 3)),
 }
+FULL_CHIP = ("256 rows", "128 rows, keys in parts", "128 rows, long keys in parts", "64 rows, grouped heads, full chip",
+             "80 rows, grouped heads, several blocks", "96 rows, grouped heads, several blocks")
 
 
 @pytest.mark.parametrize("name", CASES)
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_attention_cuts(name, head_dim):
-    full_chip = name in ("256 rows", "128 rows, keys in parts", "128 rows, long keys in parts") or (head_dim == 128 and name in ("80 rows", "96 rows", "128 rows"))
+    full_chip = name in FULL_CHIP or (head_dim == 128 and name in ("80 rows", "96 rows", "128 rows"))
     _check(head_dim, *CASES[name], further=(1.17 if name == "256 rows" else 1.08) if full_chip else 1.003)
 
 
