@@ -1282,7 +1282,10 @@ constexpr float ATTN_NARROW[ATTN_N_SHAPES] = {0.75f, 0.75f, 0.75f, 0.83f, 0.62f,
 // 107-1619 keys, 8 kv heads of 4: 64 rows 40 (34), 128 rows in two splits 43 (38).  With cold caches, query split and 64 rows: 8 rows
 // of 29 keys, 54 nodes (four rounds) 25.5 and 12.7, at head_dim 64 18.6 and 10.3; 16 x 110 keys, 29 nodes, 8 kv heads of 4 (three)
 // 24.7 and 13.7; 64 rows in four, eight and sixteen parts: 2 x 1269 keys, 29 nodes, 8 heads 18.6, 18.4, 21.0.  Over 72 steps
-// (1-16 rows, 24-4200 keys, 15-256 nodes) the cut chosen is 2.5 % behind the fastest in the mean.
+// (1-16 rows, 24-4200 keys, 15-256 nodes) the cut chosen was 2.5 % behind the fastest in the mean when the costs were fitted; over
+// 340 others (the same ranges, 32 or 8 kv heads, both head widths, inputs from HBM) it is 4.3 % behind.  At worst: 96 rows in
+// several blocks (8 rows x 700 keys, 119 nodes, 8 kv heads of 4: 48.5 us, 64 rows 32.3; x 2400 keys 111 and 68) and 128 rows for
+// 16 rows of 60 nodes at head_dim 64 (700 keys: 31.9 us, 64 rows 24.2).
 float attn_estimate_us(int shape, const tree_attn_args* a, int group, int n_split, int n_cu) {
   const AttnShape& sh = ATTN_SHAPES[shape];
   const int M = a->max_nodes_per_tree * group, n_sb = (M + sh.rows - 1) / sh.rows;

@@ -964,7 +964,8 @@ hipError_t launch_ring(cascade_ctx* ctx, const LmParams& p, int tile, int n_cols
 // Tiles of the projection: ring kernel 0-4, tiled kernel 5 (128 x 256, plain rows only) and 6 (256 x 256).  us = one tile
 // on every compute unit, hidden 4096, the weight stream aside; a last round that fills few units costs `few` of that plus
 // the filled share of the rest (the clock rises when units idle), a tile of padding rows only `pad` (zeros draw less
-// power).  Fitted to 100 sizes (16-1024 rows, 16384-65536 columns, plain, pairs and row-major weights), all seven tiles each.
+// power).  Fitted to 100 sizes (16-1024 rows, 16384-65536 columns, plain, pairs and row-major weights), all seven tiles each, before
+// weights were streamed; see lm_estimate_us for how well they choose since.
 struct LmTile {
   int rows, cols;
   float us, few, pad;
@@ -1003,8 +1004,10 @@ float lm_rounds_us(const LmTile& tile, int rows, int n_cols, int hidden, int n_c
   const float rounds = (float)(tiles / n_cu) + (last > 0.f ? tile.few + (1.f - tile.few) * last : 0.f);
   return rounds * tile.us * (tile.pad + (1.f - tile.pad) * used) * (hidden / 4096.f);
 }
-// Estimated time of the whole projection: that, and the weight stream at 6.2 TB/s, which overlap only partly.  Over those
-// sizes the single tile chosen is 1.2 % behind the fastest one in the mean.
+// Estimated time of the whole projection: that, and the weight stream at 6.2 TB/s, which overlap only partly.  Over 250
+// sizes (16-800 rows, 16384-65536 columns, hidden 2048 and 4096, weights from HBM, streamed where lm_streams says so) a single tile, where one is
+// chosen, is 1.0 % behind the fastest one in the mean, at worst 23 % (90 rows x 49152 x 2048: 54.3 us in 128 x 64, 44.0 in 128 x 256;
+// 16 pairs of row-major rows x 49152 x 2048 48.5 in 64 x 256, 39.3 in 64 x 64).
 float lm_estimate_us(float a, int vocab, int hidden) {
   const float b = (float)vocab * hidden * 2.f / 6.2e6f;
   return sqrtf(a * a + b * b);
@@ -1013,9 +1016,9 @@ float lm_estimate_us(float a, int vocab, int hidden) {
 // How a projection is cut: columns [0, split) in tiles of one shape, [split, vocab) in tiles of another (split = vocab: one
 // launch).  A last round that fills few compute units costs as much as a full one, so the columns that fill whole rounds
 // take the large tile and the rest a smaller one in a second launch: 686 rows (guidance pairs) x 33088 x 2048 are 777
-// tiles of 256 x 128, four rounds of 256 units (133 us); 768 of them and 55 of 64 x 64: 122 us.  Over those 100 sizes the
-// cut that is chosen is 5 % faster than the fastest single tile in the mean, 29 % at 461 rows x 33024 (193 -> 137 us),
-// and at worst 14 % behind it (850 rows x 24000: 235 us in 128 x 256 against 207 in 256 x 128).
+// tiles of 256 x 128, four rounds of 256 units (133 us); 768 of them and 55 of 64 x 64: 122 us.  Where columns are cut (71 of
+// those 250 sizes) that is 10 % faster than the fastest single tile in the mean, 27 % at best and 4 % slower at worst (300 pairs x
+// 33024 x 2048: 103.9 us, 100.3 in 256 x 256).
 struct LmPlan {
   int main, rest, split;
   float us;

@@ -1,8 +1,8 @@
 """Acceptance on wide rows that several workgroups share: around the widths at which there are more parts (8192 elements: four of
-floats, two of bf16, 16384: four, 32768: eight) and the node counts that limit them (256, 128, 64), widths whose last part is short, rows that 16-byte loads cannot read, nodes beside
-each other that meet and that are done by one workgroup (one sweep of less than 16384 elements); called on one context with
-other widths in turn (the counters of arrival are zero between calls).  Gram tiles beside them, at hidden sizes of one and
-several steps per wave.
+floats, two of bf16, 16384: four, 32768: eight) and the node counts that limit them (256, 128, 64), widths whose last part is
+short, rows that 16-byte loads cannot read, nodes beside each other that meet and that are done by one workgroup (one sweep of
+less than 16384 elements); called on one context with other widths in turn (the counters of arrival are zero between calls).
+Gram tiles beside them, at hidden sizes of one and several steps per wave.
 Cosines are off by at most (h + 16) 2^-24, as in test_gpu_accept_widths; bf16 products are exact in float32, their sums are not."""
 import numpy as np
 import pytest
