@@ -194,7 +194,12 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   static_assert(WM * WN * KW == 8 && KS % KW == 0 && KS % 4 == 0 && (!CFG || AM == 2), "eight waves; guidance pairs are a wave's two row blocks");
   constexpr int BM = 32 * AM * WM, BN = 32 * AN * WN, NA = BM / 32, NBLK = NA + BN / 32, STAGE = NBLK * KS * 1024;
   constexpr int LPW = NBLK * KS / 8, SPW = KS / KW;
-  constexpr int LPA = NA * KS / 8;   // (STREAM) a wave's requests of a stage: LPA of rows, then of weights
+  // DEALT: a wave's requests of a stage are LPA chunks of rows, then chunks of weights.  Streamed weights need that, 256 x 128 tiles
+  // take it: with consecutive chunks some waves request nothing but weights, and all wait for them (343 pairs x 33088 x 2048
+  // packed 122.0 us, dealt 116.5, 500 pairs 157.8 and 152.6, 450 pairs x 49152 x 2048 row-major 225.3 and 217.5).  The smaller tiles
+  // do not: 64 x 64 over 8192 x 4096 gets up to 10 % slower.
+  constexpr bool DEALT = STREAM || WM == 4;
+  constexpr int LPA = NA * KS / 8;
   static_assert(NA * KS % 8 == 0 && NBLK * KS % 8 == 0 && (DIRECT || !STREAM), "every wave requests the same number of 1 KiB chunks");
   extern __shared__ __align__(1024) char ring_lds[];   // [NST stages][NBLK blocks][KS KiB]
   const int tid = threadIdx.x, lane = tid & 63;
@@ -207,10 +212,10 @@ __global__ __launch_bounds__(512) void lmhead_bf16_ring_kernel(LmParams p, int n
   const int nt = logical / n_mtiles, mt = logical % n_mtiles;
 
   // loader: request i of a wave is chunk id of a stage: block id / KS, KiB id % KS of it (one k16 step of packed operands, or
-  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece).  Consecutive chunks, unless the weights are
-  // streamed: then which requests are weights is known at compile time.
-  auto chunk = [&](int i) { return !STREAM ? wave * LPW + i : (i < LPA ? wave * LPA + i : NA * KS + wave * (LPW - LPA) + (i - LPA)); };
-  auto weights = [&](int i) { return STREAM ? i >= LPA : chunk(i) / KS >= NA; };
+  // eight rows x 128 bytes of row-major ones, four of which make a 32-row x 64-column piece).  Where they are dealt, which requests are
+  // weights is known at compile time.
+  auto chunk = [&](int i) { return !DEALT ? wave * LPW + i : (i < LPA ? wave * LPA + i : NA * KS + wave * (LPW - LPA) + (i - LPA)); };
+  auto weights = [&](int i) { return DEALT ? i >= LPA : chunk(i) / KS >= NA; };
   unsigned voff[LPW];
   const char* src[LPW];
 #pragma unroll
