@@ -559,10 +559,10 @@ __device__ __forceinline__ float key_f32(uint32_t k) {
 // 19..10 among the keys of the chosen bin, then 1024 bins of bits 9..0.  After each round a scan
 // from the top bin finds the bin that holds the k-th largest and how many keys lie above it.
 // (A row whose entries all share one bin, e.g. all equal, serialises on one LDS address: slow, exact.)
-template <int BPT>   // bins per thread; the workgroup's 1024 threads cover 1024 * BPT bins, highest first
+template <int NB, int NT>   // bins (the workgroup's NT threads take NB / NT each, highest first)
 __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int tid, int lane, int wave, int* s_wsum, int* s_bin,
                                                   int* s_above) {
-  constexpr int NB = 1024 * BPT;
+  constexpr int BPT = NB / NT;
   int hb[BPT], loc = 0;
 #pragma unroll
   for (int i = 0; i < BPT; ++i) {
@@ -588,7 +588,7 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
   __syncthreads();
 }
 
-// Row statistics.  One workgroup of 1024 threads per row; the row lives in registers (VPT values per thread,
+// Row statistics.  One workgroup of NT = 1024 or 512 threads per row; the row lives in registers (VPT values per thread,
 // loaded 16 bytes at a time when the row allows it).
 //
 // Fast path (top-k active): the order-preserving radix rounds above put sign, exponent and three mantissa bits
@@ -608,12 +608,12 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // 76.6 -> 74.0.  (Two workgroups per compute unit, at 64 registers: 462 x 16384 16.3 us, spilled from 24576 entries on.)
 // Rows the fast path does not fit (degenerate or non-finite sample range, k-th largest in the lowest bin, more
 // than RS_CAND candidates, a wave with more than RS_CAP - 64 listed entries) take the radix rounds: slow, exact.
-constexpr int RS_CAP = 768;     // listed entries per wave
+constexpr int RS_LIST = 12288;  // listed entries, dealt evenly to the waves of a workgroup
 constexpr int RS_CAND = 1024;   // candidates ranked by counting
 constexpr int RS_PRE_OFFSET = 80 * 1024;   // 80 KiB prefetch buffer behind the structure below (1 KiB aligned)
 struct RowStatsSmem {
   int hist1[4096], hist2[1024], hist3[1024];
-  float list[16 * RS_CAP];      // entry j of wave w at [w * RS_CAP + j]
+  float list[RS_LIST];          // wave after wave
   float cand[RS_CAND];
   float f_rng[32], f_max[16], f_sum[16];
   int s_wsum[16];
@@ -624,12 +624,14 @@ struct RowStatsSmem {
 // Workgroups are persistent: workgroup b takes rows b, b + gridDim.x, ...; the loads of its next row are issued
 // as soon as the registers of the current one are no longer needed, so that they overlap the row's tail (list
 // processing, candidate ranking, reductions).
-// VPT = values per thread: 4, 8, 16, 24, 32, 40, 48 or 64 (rows that are not 16-byte aligned: 4, 16 or 64), the smallest
-// that holds the row.  A chunk that the row does not fill files only its real entries: 33088 entries in a 65536-entry
+// VPT = values per thread: 4, 8, 16, 24, 32, 40, 48 or 64 (rows that are not 16-byte aligned: 4, 16 or 64; NT = 512: 8, 16, 32 or 48),
+// the smallest that holds the row.  A chunk that the row does not fill files only its real entries: 33088 entries in a 65536-entry
 // frame used to send 32448 padding entries through LDS atomics on one bin, one after the other (78 us for 343 rows, now
 // 22; 46 -> 10 us for 200 x 24000).
-template <int VPT, bool VEC>   // VEC: rows start on 16-byte boundaries and V is a multiple of 4
-__global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
+// NT = 512: two rows on a compute unit, each with half of its waves and registers; while one row is loaded, the other is searched.
+template <int VPT, bool VEC, int NT>   // VEC: rows start on 16-byte boundaries and V is a multiple of 4
+__global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
+  constexpr int NW = NT / 64, RS_CAP = RS_LIST / NW;   // waves, listed entries of one
   extern __shared__ __align__(1024) char rs_smem_raw[];
   RowStatsSmem& sm = *(RowStatsSmem*)rs_smem_raw;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -637,21 +639,21 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
   const bool topk = p.top_k > 0 && p.top_k < V;
   constexpr int NCH = VPT / 4;
   // chunks that the row fills for sure (it did not fit the next smaller frame)
-  constexpr int SURE = VEC ? (VPT == 64 ? 12 : (VPT == 16 ? 2 : (VPT >= 24 ? NCH - 2 : (VPT == 8 ? 1 : 0)))) : (VPT == 64 ? 4 : (VPT == 16 ? 1 : 0));
+  constexpr int SURE = NT == 512 ? NCH - 4 : VEC ? (VPT == 64 ? 12 : (VPT == 16 ? 2 : (VPT >= 24 ? NCH - 2 : (VPT == 8 ? 1 : 0)))) : (VPT == 64 ? 4 : (VPT == 16 ? 1 : 0));
   // Long rows: the last NPRE 16 KiB chunks of the NEXT row are fetched into LDS (LDS-direct loads, no registers
   // needed) while the current row's registers are still in use - HBM would otherwise idle between the end of a
   // row's loads and the moment its registers are free.  A thread reads back exactly the 16 bytes its own lane
   // fetched, so no barrier is involved.
-  constexpr int NPRE = (VEC && VPT == 64) ? 5 : 0;
+  constexpr int NPRE = (VEC && NT == 1024 && VPT == 64) ? 5 : 0;
   constexpr int NREG = NCH - NPRE;   // chunks loaded into registers
   float* const pre = (float*)(rs_smem_raw + RS_PRE_OFFSET);
   const unsigned pre_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)pre) + 1024u * (unsigned)__builtin_amdgcn_readfirstlane(wave);
-  // Chunk jj of this thread, element c, is vocabulary entry 4 (tid + 1024 jj) + c: chunks 0 .. NREG-1 are loaded
+  // Chunk jj of this thread, element c, is vocabulary entry 4 (tid + NT jj) + c: chunks 0 .. NREG-1 are loaded
   // into registers (and swept in the order they arrive; chunk 0, always inside the row, is the sample), chunks
   // NREG .. NCH-1 come from LDS and are swept last.  Entries past V are masked to -inf before use.  Every load
   // is unconditional (addresses clamped into the row): all of them are in flight at once.
   auto mch = [](int jj) { return jj; };
-  const bool whole = V == VPT * 1024;   // workgroup-uniform: a full row needs no masking
+  const bool whole = V == VPT * NT;   // workgroup-uniform: a full row needs no masking
   float x[VPT];
   // (The thread index is passed through an empty asm so that the per-chunk offsets and masks below are recomputed
   // where they are used instead of being kept in registers across the whole row loop.)
@@ -662,12 +664,12 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     if (VEC) {
 #pragma unroll
       for (int jj = 0; jj < NREG; ++jj) {
-        const float4 q = *(const float4*)(g + 4u * (unsigned)min(4 * (t + 1024 * mch(jj)), V - 4));
+        const float4 q = *(const float4*)(g + 4u * (unsigned)min(4 * (t + NT * mch(jj)), V - 4));
         x[4 * jj] = q.x; x[4 * jj + 1] = q.y; x[4 * jj + 2] = q.z; x[4 * jj + 3] = q.w;
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < VPT; ++i) x[i] = *(const float*)(g + 4u * (unsigned)min(4 * (t + 1024 * (i >> 2)) + (i & 3), V - 1));
+      for (int i = 0; i < VPT; ++i) x[i] = *(const float*)(g + 4u * (unsigned)min(4 * (t + NT * (i >> 2)) + (i & 3), V - 1));
     }
   };
   auto prefetch_row = [&](int row) {   // chunks NREG .. NCH-1 -> LDS, lane l's 16 bytes at 16 l behind M0
@@ -676,7 +678,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     asm volatile("" : "+v"(t));
 #pragma unroll
     for (int m = 0; m < NPRE; ++m) {
-      const unsigned voff = 4u * (unsigned)min(4 * (t + 1024 * (NREG + m)), V - 4);
+      const unsigned voff = 4u * (unsigned)min(4 * (t + NT * (NREG + m)), V - 4);
       const unsigned l = pre_lds + 16384u * m;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(g) : "memory");
     }
@@ -688,7 +690,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
 #pragma unroll
       for (int jj = jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + 1024 * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
+        for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + NT * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
     }
   };
   int row = blockIdx.x;
@@ -700,7 +702,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     const int next = row + gridDim.x;
     mask_chunks(0, NREG);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sm.hist1[tid + 1024 * i] = 0;
+    for (int i = 0; i < 4096 / NT; ++i) sm.hist1[tid + NT * i] = 0;
     if (tid == 0) { sm.n_cand = 0; sm.flag = 0; }
 
     // ---- range of the sample (first chunk of every thread)
@@ -714,7 +716,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     __syncthreads();
     smax = sm.f_rng[0]; smin = sm.f_rng[16];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) { smax = fmaxf(smax, sm.f_rng[w]); smin = fminf(smin, sm.f_rng[16 + w]); }
+    for (int w = 1; w < NW; ++w) { smax = fmaxf(smax, sm.f_rng[w]); smin = fminf(smin, sm.f_rng[16 + w]); }
     const float bs = 4096.f / (smax - smin), bc = -smin * bs;
     // usable: finite positive scale and offset (rules out equal, infinite or NaN sample bounds)
     const bool fast = topk && bs > 0.f && bs < INFINITY && fabsf(bc) < INFINITY;
@@ -739,8 +741,8 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
         asm volatile("" : "+v"(t));
 #pragma unroll
         for (int jj = jj0; jj < jj1; ++jj) {
-          if (jj < SURE || 4096 * (jj + 1) <= V) chunk(jj, always);   // workgroup-uniform
-          else chunk(jj, [&](int c) { return 4 * (t + 1024 * jj) + c < V; });
+          if (jj < SURE || 4 * NT * (jj + 1) <= V) chunk(jj, always);   // workgroup-uniform
+          else chunk(jj, [&](int c) { return 4 * (t + NT * jj) + c < V; });
         }
       } else {
 #pragma unroll
@@ -769,14 +771,14 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     __syncthreads();                       // maxima and every atomic of the sweep
     mx = sm.f_max[0];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sm.f_max[w]);
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sm.f_max[w]);
 
     float thr = -INFINITY, se = 0.f;
     bool done = false;
     int n_list = 0, B = 0, n_c = 0, k = p.top_k;   // n_list: entries listed by this wave
     float* const list = sm.list + wave * RS_CAP;
     if (fast) {
-      find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
+      find_bin_from_top<4096, NT>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       B = sm.s_bin;
       n_c = sm.hist1[B];
       k -= sm.s_above;                     // rank of the k-th largest inside bin B, 1 = largest
@@ -819,8 +821,8 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
       }
       __syncthreads();
       // exact k-th largest of the n_c candidates by counting (ties: lower list index first); wave w ranks
-      // candidates w, w + 16, ..., its lanes share the comparisons
-      for (int i = wave; i < n_c; i += 16) {
+      // candidates w, w + NW, ..., its lanes share the comparisons
+      for (int i = wave; i < n_c; i += NW) {
         const uint32_t ki = f32_key(sm.cand[i]);
         int rank = 0;
         for (int j = lane; j < n_c; j += 64) {
@@ -833,7 +835,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
       __syncthreads();
       thr = sm.s_thr;
       const uint32_t tk = f32_key(thr);
-      for (int i = tid; i < n_c; i += 1024) {
+      for (int i = tid; i < n_c; i += NT) {
         const float xi = sm.cand[i];
         if (f32_key(xi) >= tk) se += __expf(xi - mx);
       }
@@ -843,35 +845,35 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
       const float* g = p.logits + (int64_t)row * V;
       __syncthreads();
 #pragma unroll
-      for (int i = 0; i < 4; ++i) sm.hist1[tid + 1024 * i] = 0;
-      sm.hist2[tid] = 0;
-      sm.hist3[tid] = 0;
+      for (int i = 0; i < 4096 / NT; ++i) sm.hist1[tid + NT * i] = 0;
+#pragma unroll
+      for (int i = 0; i < 1024 / NT; ++i) sm.hist2[tid + NT * i] = sm.hist3[tid + NT * i] = 0;
       __syncthreads();
       k = p.top_k;
-      for (int v = tid; v < V; v += 1024) atomicAdd(&sm.hist1[f32_key(g[v]) >> 20], 1);
+      for (int v = tid; v < V; v += NT) atomicAdd(&sm.hist1[f32_key(g[v]) >> 20], 1);
       __syncthreads();
-      find_bin_from_top<4>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
+      find_bin_from_top<4096, NT>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       const uint32_t b1 = (uint32_t)sm.s_bin;
       k -= sm.s_above;
       __syncthreads();   // s_bin / s_above are rewritten by the next round
-      for (int v = tid; v < V; v += 1024) {
+      for (int v = tid; v < V; v += NT) {
         const uint32_t key = f32_key(g[v]);
         if ((key >> 20) == b1) atomicAdd(&sm.hist2[(key >> 10) & 1023u], 1);
       }
       __syncthreads();
-      find_bin_from_top<1>(sm.hist2, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
+      find_bin_from_top<1024, NT>(sm.hist2, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       const uint32_t b12 = (b1 << 10) | (uint32_t)sm.s_bin;
       k -= sm.s_above;
       __syncthreads();
-      for (int v = tid; v < V; v += 1024) {
+      for (int v = tid; v < V; v += NT) {
         const uint32_t key = f32_key(g[v]);
         if ((key >> 10) == b12) atomicAdd(&sm.hist3[key & 1023u], 1);
       }
       __syncthreads();
-      find_bin_from_top<1>(sm.hist3, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
+      find_bin_from_top<1024, NT>(sm.hist3, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       const uint32_t thr_key = (b12 << 10) | (uint32_t)sm.s_bin;
       thr = key_f32(thr_key);
-      for (int v = tid; v < V; v += 1024) {
+      for (int v = tid; v < V; v += NT) {
         const float xv = g[v];
         if (f32_key(xv) >= thr_key) se += __expf(xv - mx);
       }
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(1024) void row_stats_kernel(LmParams p) {
     __syncthreads();
     if (tid == 0) {
       float tot = 0.f;
-      for (int w = 0; w < 16; ++w) tot += sm.f_sum[w];
+      for (int w = 0; w < NW; ++w) tot += sm.f_sum[w];
       p.row_max[row] = mx;
       p.row_thr[row] = thr;
       p.row_lse[row] = mx + logf(tot);
@@ -1164,20 +1166,22 @@ hipError_t launch_pack_w(cascade_ctx* ctx, const void* w, int vocab, int hidden,
   return hipGetLastError();
 }
 
-template <int VPT, bool VEC>
+template <int VPT, bool VEC, int NT>
 hipError_t launch_row_stats_t(cascade_ctx* ctx, const LmParams& p) {
+  constexpr int PER_CU = 1024 / NT;
   static_assert(sizeof(RowStatsSmem) <= RS_PRE_OFFSET, "the prefetch buffer starts behind the structure");
-  const size_t smem = (VEC && VPT == 64) ? RS_PRE_OFFSET + 80 * 1024 : sizeof(RowStatsSmem);
+  static_assert(PER_CU * sizeof(RowStatsSmem) <= 160 * 1024, "LDS of a compute unit");
+  const size_t smem = (VEC && NT == 1024 && VPT == 64) ? RS_PRE_OFFSET + 80 * 1024 : sizeof(RowStatsSmem);
   static bool attr_done = false;   // one flag per template instance
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)row_stats_kernel<VPT, VEC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    hipError_t e = hipFuncSetAttribute((const void*)row_stats_kernel<VPT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   KernelTimer t(ctx, CASCADE_K_ROW_STATS);
-  // one workgroup per compute unit at most (its 1024 threads hold a row in registers), each walking its share of the rows
-  const int grid = p.n_nodes < ctx->n_cu ? p.n_nodes : ctx->n_cu;
-  CASCADE_TIMED_LAUNCH(t, (row_stats_kernel<VPT, VEC>), dim3(grid), dim3(1024), smem, ctx->stream, p);
+  // as many workgroups as the compute units hold (128 registers for each of 1024 threads), each walking its share of the rows
+  const int most = PER_CU * ctx->n_cu, grid = p.n_nodes < most ? p.n_nodes : most;
+  CASCADE_TIMED_LAUNCH(t, (row_stats_kernel<VPT, VEC, NT>), dim3(grid), dim3(NT), smem, ctx->stream, p);
   return hipGetLastError();
 }
 
@@ -1186,14 +1190,23 @@ hipError_t launch_row_stats(cascade_ctx* ctx, const lmhead_args* a) {
   const int V = a->vocab;
   // 16-byte loads need every row to start on a 16-byte boundary
   const bool vec = V % 4 == 0 && ((uintptr_t)a->logits & 15u) == 0;
-  if (!vec) return V <= 4096 ? launch_row_stats_t<4, false>(ctx, p) : (V <= 16384 ? launch_row_stats_t<16, false>(ctx, p) : launch_row_stats_t<64, false>(ctx, p));
+  if (!vec) return V <= 4096 ? launch_row_stats_t<4, false, 1024>(ctx, p) : (V <= 16384 ? launch_row_stats_t<16, false, 1024>(ctx, p) : launch_row_stats_t<64, false, 1024>(ctx, p));
+  // More rows than compute units: two on each at a time, 512 threads for a row.  1024 threads for one at a time and so, us: 280 rows x 4096
+  // 8.3 and 6.4, x 8192 9.3 and 6.8, x 16384 12.4 and 9.7; 400 x 16384 13.3 and 10.3, x 24576 16.6 and 12.9; 1024 x 8192 18.2 and
+  // 13.1, x 16384 25.4 and 19.2, x 24576 33.1 and 23.8.  Fewer rows have the whole compute unit (60 x 16384 6.2 us, 6.8 in 512
+  // threads), and wider ones are bound by its instructions (400 x 33088 22.1 and 21.6, and registers are spilled).
+  if (a->n_nodes > ctx->n_cu && V <= 24576) {
+    if (V <= 4096) return launch_row_stats_t<8, true, 512>(ctx, p);
+    if (V <= 8192) return launch_row_stats_t<16, true, 512>(ctx, p);
+    return V <= 16384 ? launch_row_stats_t<32, true, 512>(ctx, p) : launch_row_stats_t<48, true, 512>(ctx, p);
+  }
   switch ((V + 8191) / 8192) {
-    case 1: return V <= 4096 ? launch_row_stats_t<4, true>(ctx, p) : launch_row_stats_t<8, true>(ctx, p);
-    case 2: return launch_row_stats_t<16, true>(ctx, p);
-    case 3: return launch_row_stats_t<24, true>(ctx, p);
-    case 4: return launch_row_stats_t<32, true>(ctx, p);
-    case 5: return launch_row_stats_t<40, true>(ctx, p);
-    case 6: return launch_row_stats_t<48, true>(ctx, p);
-    default: return launch_row_stats_t<64, true>(ctx, p);
+    case 1: return V <= 4096 ? launch_row_stats_t<4, true, 1024>(ctx, p) : launch_row_stats_t<8, true, 1024>(ctx, p);
+    case 2: return launch_row_stats_t<16, true, 1024>(ctx, p);
+    case 3: return launch_row_stats_t<24, true, 1024>(ctx, p);
+    case 4: return launch_row_stats_t<32, true, 1024>(ctx, p);
+    case 5: return launch_row_stats_t<40, true, 1024>(ctx, p);
+    case 6: return launch_row_stats_t<48, true, 1024>(ctx, p);
+    default: return launch_row_stats_t<64, true, 1024>(ctx, p);
   }
 }

@@ -81,7 +81,7 @@ def test_row_statistics_prefetch_uses_m0_only_for_its_loads(tmp_path):
     """The long-row statistics kernel prefetches part of the next row with LDS-direct loads (M0 set by hand,
     the compiler is not told): nothing else in that kernel may touch M0."""
     _, text = _kernel_stats("lmhead.hip", tmp_path)
-    bodies = re.findall(r"^(_ZN\S*row_stats_kernelILi64ELb1E\S*):[^\n]*\n(.*?)\.amdhsa_kernel", text, flags=re.S | re.M)
+    bodies = re.findall(r"^(_ZN\S*row_stats_kernelILi64ELb1ELi1024E\S*):[^\n]*\n(.*?)\.amdhsa_kernel", text, flags=re.S | re.M)
     assert len(bodies) == 1
     name, body = bodies[0]
     m0 = [l.strip() for l in body.splitlines() if re.search(r"\bm0\b", l)]
