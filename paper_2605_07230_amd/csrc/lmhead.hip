@@ -24,6 +24,7 @@ struct LmParams {
   int col0;                 // first vocabulary column of the launch
   float cfg_scale, temperature;
   int top_k;
+  int sample_rank;          // row statistics: entries of the sample at and above the cut
 };
 
 // ------------------------------------------------------------------------------------------ f32
@@ -606,17 +607,23 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // (700 x 65536 with k = 50 47.4 us with a list per thread, 50.9 with a ballot and a count for every value, 45 so).  60 rows x 16384 6.6 ->
 // 6.0 us, 462 x 16384 15.3 -> 14.1, 300 x 33088 with k = 8000, where lists per thread overflowed, 0.27 of the time, 1024 x 65536
 // 76.6 -> 74.0.  (Two workgroups per compute unit, at 64 registers: 462 x 16384 16.3 us, spilled from 24576 entries on.)
+// CUT, rows of more than 32768 entries: counting every entry in LDS is most of the work there.  The entries of the sample alone are counted,
+// while the rest of the row arrives, and give a value that somewhat more than k entries of the row will reach; the one sweep lists
+// those, and the bins are filled from the lists.  Any cut that at least k entries reach keeps the selection exact; where fewer do, or a
+// list is full, every entry is counted after all.  So that the sample stands for the row, each wave begins elsewhere.
+// 1024 rows x 65536 71.1 -> 65.7 us (see launch_row_stats_long for where it pays).
 // Rows the fast path does not fit (degenerate or non-finite sample range, k-th largest in the lowest bin, more
 // than RS_CAND candidates, a wave with more than RS_CAP - 64 listed entries) take the radix rounds: slow, exact.
 constexpr int RS_LIST = 12288;  // listed entries, dealt evenly to the waves of a workgroup
 constexpr int RS_CAND = 1024;   // candidates ranked by counting
 constexpr int RS_PRE_OFFSET = 80 * 1024;   // 80 KiB prefetch buffer behind the structure below (1 KiB aligned)
+
 struct RowStatsSmem {
   int hist1[4096], hist2[1024], hist3[1024];
   float list[RS_LIST];          // wave after wave
   float cand[RS_CAND];
   float f_rng[32], f_max[16], f_sum[16];
-  int s_wsum[16];
+  int s_wsum[16], n_listed[16];
   int s_bin, s_above, n_cand, flag;
   float s_thr;
 };
@@ -629,7 +636,7 @@ struct RowStatsSmem {
 // frame used to send 32448 padding entries through LDS atomics on one bin, one after the other (78 us for 343 rows, now
 // 22; 46 -> 10 us for 200 x 24000).
 // NT = 512: two rows on a compute unit, each with half of its waves and registers; while one row is loaded, the other is searched.
-template <int VPT, bool VEC, int NT>   // VEC: rows start on 16-byte boundaries and V is a multiple of 4
+template <int VPT, bool VEC, int NT, bool CUT>   // VEC: rows start on 16-byte boundaries and V is a multiple of 4
 __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
   constexpr int NW = NT / 64, RS_CAP = RS_LIST / NW;   // waves, listed entries of one
   extern __shared__ __align__(1024) char rs_smem_raw[];
@@ -638,6 +645,9 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
   const int V = p.vocab;
   const bool topk = p.top_k > 0 && p.top_k < V;
   constexpr int NCH = VPT / 4;
+  // CUT: wave w begins w / NW of the way through the whole chunks
+  static_assert(!CUT || VEC, "the first load of every wave lies in the row");
+  const int rot = CUT ? __builtin_amdgcn_readfirstlane(wave) * (V / (4 * NT)) / NW : 0;
   // chunks that the row fills for sure (it did not fit the next smaller frame)
   constexpr int SURE = NT == 512 ? NCH - 4 : VEC ? (VPT == 64 ? 12 : (VPT == 16 ? 2 : (VPT >= 24 ? NCH - 2 : (VPT == 8 ? 1 : 0)))) : (VPT == 64 ? 4 : (VPT == 16 ? 1 : 0));
   // Long rows: the last NPRE 16 KiB chunks of the NEXT row are fetched into LDS (LDS-direct loads, no registers
@@ -652,7 +662,7 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
   // into registers (and swept in the order they arrive; chunk 0, always inside the row, is the sample), chunks
   // NREG .. NCH-1 come from LDS and are swept last.  Entries past V are masked to -inf before use.  Every load
   // is unconditional (addresses clamped into the row): all of them are in flight at once.
-  auto mch = [](int jj) { return jj; };
+  auto mch = [&](int jj) { return !CUT ? jj : (jj + rot < NCH ? jj + rot : jj + rot - NCH); };   // chunk that slot jj holds
   const bool whole = V == VPT * NT;   // workgroup-uniform: a full row needs no masking
   float x[VPT];
   // (The thread index is passed through an empty asm so that the per-chunk offsets and masks below are recomputed
@@ -678,7 +688,7 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
     asm volatile("" : "+v"(t));
 #pragma unroll
     for (int m = 0; m < NPRE; ++m) {
-      const unsigned voff = 4u * (unsigned)min(4 * (t + NT * (NREG + m)), V - 4);
+      const unsigned voff = 4u * (unsigned)min(4 * (t + NT * mch(NREG + m)), V - 4);
       const unsigned l = pre_lds + 16384u * m;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(g) : "memory");
     }
@@ -688,9 +698,10 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
       int t = tid;
       asm volatile("" : "+v"(t));
 #pragma unroll
-      for (int jj = jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
+      for (int jj = CUT || jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
+        if (!CUT || 4 * NT * (mch(jj) + 1) > V)   // (a branch of the wave)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + NT * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
+          for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + NT * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
     }
   };
   int row = blockIdx.x;
@@ -741,15 +752,51 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
         asm volatile("" : "+v"(t));
 #pragma unroll
         for (int jj = jj0; jj < jj1; ++jj) {
-          if (jj < SURE || 4 * NT * (jj + 1) <= V) chunk(jj, always);   // workgroup-uniform
-          else chunk(jj, [&](int c) { return 4 * (t + NT * jj) + c < V; });
+          if ((!CUT && jj < SURE) || 4 * NT * (mch(jj) + 1) <= V) chunk(jj, always);   // uniform in a wave
+          else chunk(jj, [&](int c) { return 4 * (t + NT * mch(jj)) + c < V; });
         }
       } else {
 #pragma unroll
         for (int i = 4 * jj0; i < 4 * jj1; ++i) mx = fmaxf(mx, x[i]);
       }
     };
-    sweep(0, NREG);
+    // ---- the cut: the value that p.sample_rank entries of the sample reach
+    float cut = 0.f;
+    bool cutting = false;   // workgroup-uniform
+    int n_list = 0, most = 0;   // entries listed by this wave
+    float* const list = sm.list + wave * RS_CAP;
+    // values i0 .. i1 - 1 of this thread that pass go to its wave's list
+    auto file = [&](int i0, int i1, auto&& passes) {
+#pragma unroll
+      for (int i = i0; i < i1; ++i) {
+        const bool hit = passes(x[i]);
+        const unsigned long long m = __ballot(hit);
+        if (m) {
+          const int at = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_list));
+          if (hit) list[at] = x[i];
+          n_list += __popcll(m);
+          most = max(most, n_list);
+          n_list = min(n_list, RS_CAP - 64);         // room for the next 64
+        }
+        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if (CUT && fast) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) atomicAdd(&sm.hist1[(int)__builtin_amdgcn_fmed3f(fmaf(x[c], bs, bc), 0.f, 4095.f)], 1);
+      __syncthreads();
+      find_bin_from_top<4096, NT>(sm.hist1, p.sample_rank, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
+      const int Bs = sm.s_bin;
+      cutting = Bs > 0;
+      cut = ((float)Bs - bc) / bs;
+#pragma unroll
+      for (int i = 0; i < 4096 / NT; ++i) sm.hist1[tid + NT * i] = 0;
+    }
+    auto first_sweep = [&](int jj0, int jj1) {
+      if (CUT && cutting) file(4 * jj0, 4 * jj1, [&](float v) { return v >= cut; });
+      else sweep(jj0, jj1);
+    };
+    first_sweep(0, NREG);
     if (NPRE > 0) {
       // every load of this row that went to registers has been waited for; the LDS-direct ones were issued before
       // them and complete in order - waited for explicitly all the same
@@ -762,44 +809,56 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
         x[4 * (NREG + m)] = q.x; x[4 * (NREG + m) + 1] = q.y; x[4 * (NREG + m) + 2] = q.z; x[4 * (NREG + m) + 3] = q.w;
       }
       mask_chunks(NREG, NCH);
-      sweep(NREG, NCH);
+      first_sweep(NREG, NCH);
       // the values are in registers (the sweep consumed them): the buffer can take the next row's chunks
       if (next < p.n_nodes) prefetch_row(next);
     }
-    mx = wave_max(mx);
-    if (lane == 0) sm.f_max[wave] = mx;
-    __syncthreads();                       // maxima and every atomic of the sweep
-    mx = sm.f_max[0];
+    if (CUT && cutting)
+      for (int j = lane; j < n_list; j += 64) mx = fmaxf(mx, list[j]);
+    auto row_max = [&]() {
+      mx = wave_max(mx);
+      if (lane == 0) {
+        sm.f_max[wave] = mx;
+        sm.n_listed[wave] = most > RS_CAP - 64 ? -(1 << 20) : n_list;
+      }
+      __syncthreads();                       // maxima, lists and every atomic of the sweep
+      mx = sm.f_max[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sm.f_max[w]);
+      for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sm.f_max[w]);
+    };
+    row_max();
+    if (CUT && cutting) {
+      int total = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) total += sm.n_listed[w];
+      if (total >= p.top_k) {
+        for (int j = lane; j < n_list; j += 64) atomicAdd(&sm.hist1[(int)__builtin_amdgcn_fmed3f(fmaf(list[j], bs, bc), 0.f, 4095.f)], 1);
+        __syncthreads();
+      } else {   // the sample was misleading, or a list is full: every entry is looked at, as in narrower rows
+        __syncthreads();   // everyone has read the counts and maxima that are written again
+        cutting = false;
+        n_list = most = 0;
+        mx = -INFINITY;
+        sweep(0, NCH);
+        row_max();
+      }
+    }
 
     float thr = -INFINITY, se = 0.f;
     bool done = false;
-    int n_list = 0, B = 0, n_c = 0, k = p.top_k;   // n_list: entries listed by this wave
-    float* const list = sm.list + wave * RS_CAP;
+    int B = 0, n_c = 0, k = p.top_k;
     if (fast) {
       find_bin_from_top<4096, NT>(sm.hist1, k, tid, lane, wave, sm.s_wsum, &sm.s_bin, &sm.s_above);
       B = sm.s_bin;
       n_c = sm.hist1[B];
       k -= sm.s_above;                     // rank of the k-th largest inside bin B, 1 = largest
       if (B > 0 && n_c <= RS_CAND) {       // workgroup-uniform
-        const float Bf = (float)B;
-        int most = 0;
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          const bool hit = fmaf(x[i], bs, bc) >= Bf;   // bin(x) >= B (B >= 1: the clamp at 0 plays no part; the one at 4095 cannot matter)
-          const unsigned long long m = __ballot(hit);
-          if (m) {
-            const int at = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)n_list));
-            if (hit) list[at] = x[i];
-            n_list += __popcll(m);
-            most = max(most, n_list);
-            n_list = min(n_list, RS_CAP - 64);         // room for the next 64
-          }
-          if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        if (!cutting) {
+          const float Bf = (float)B;
+          file(0, VPT, [&](float v) { return fmaf(v, bs, bc) >= Bf; });   // bin(x) >= B (B >= 1: the clamp at 0 plays no part; the one at 4095 cannot matter)
+          if (most > RS_CAP - 64 && lane == 0) sm.flag = 1;
+          __syncthreads();
         }
-        if (most > RS_CAP - 64 && lane == 0) sm.flag = 1;
-        __syncthreads();
         done = sm.flag == 0;
       }
     }
@@ -812,12 +871,12 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
     // The registers are free (the rounds below re-read the row): the next row arrives during this row's tail.
     if (next < p.n_nodes) load_row(next);
     if (done) {
-      // listed entries: above bin B -> kept; in bin B -> candidate
-      const float B1f = (float)(B + 1);
+      // listed entries: above bin B -> kept; in bin B -> candidate; below (where there was a cut) -> not kept
+      const float Bf = (float)B, B1f = (float)(B + 1);
       for (int j = lane; j < n_list; j += 64) {
-        const float xv = list[j];
-        if (B < 4095 && fmaf(xv, bs, bc) >= B1f) se += __expf(xv - mx);
-        else sm.cand[atomicAdd(&sm.n_cand, 1)] = xv;
+        const float xv = list[j], t = fmaf(xv, bs, bc);
+        if (B < 4095 && t >= B1f) se += __expf(xv - mx);
+        else if (t >= Bf) sm.cand[atomicAdd(&sm.n_cand, 1)] = xv;
       }
       __syncthreads();
       // exact k-th largest of the n_c candidates by counting (ties: lower list index first); wave w ranks
@@ -909,6 +968,7 @@ LmParams make_params(const lmhead_args* a) {
   p.cfg_scale = a->cfg_scale;
   p.temperature = a->temperature;
   p.top_k = a->top_k;
+  p.sample_rank = 0;
   return p;
 }
 
@@ -1166,23 +1226,35 @@ hipError_t launch_pack_w(cascade_ctx* ctx, const void* w, int vocab, int hidden,
   return hipGetLastError();
 }
 
-template <int VPT, bool VEC, int NT>
+template <int VPT, bool VEC, int NT, bool CUT = false>
 hipError_t launch_row_stats_t(cascade_ctx* ctx, const LmParams& p) {
   constexpr int PER_CU = 1024 / NT;
   static_assert(sizeof(RowStatsSmem) <= RS_PRE_OFFSET, "the prefetch buffer starts behind the structure");
   static_assert(PER_CU * sizeof(RowStatsSmem) <= 160 * 1024, "LDS of a compute unit");
   const size_t smem = (VEC && NT == 1024 && VPT == 64) ? RS_PRE_OFFSET + 80 * 1024 : sizeof(RowStatsSmem);
+  auto kern = row_stats_kernel<VPT, VEC, NT, CUT>;
   static bool attr_done = false;   // one flag per template instance
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)row_stats_kernel<VPT, VEC, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   KernelTimer t(ctx, CASCADE_K_ROW_STATS);
   // as many workgroups as the compute units hold (128 registers for each of 1024 threads), each walking its share of the rows
   const int most = PER_CU * ctx->n_cu, grid = p.n_nodes < most ? p.n_nodes : most;
-  CASCADE_TIMED_LAUNCH(t, (row_stats_kernel<VPT, VEC, NT>), dim3(grid), dim3(NT), smem, ctx->stream, p);
+  CASCADE_TIMED_LAUNCH(t, kern, dim3(grid), dim3(NT), smem, ctx->stream, p);
   return hipGetLastError();
+}
+// Rows of more than 32768 entries, with a cut where it pays.  Every entry counted and a cut, us: 60 rows x 49152 10.6 and 10.3, x 65536 13.5 and
+// 12.8; 400 x 33088 22.0 and 21.0, x 57344 33.0 and 30.0; 1024 x 65536 71.1 and 65.7; but 60 x 33088 9.3 and 9.8, where the search in
+// the sample takes longer than the counting, and with long lists 60 x 65536 with k = 8000 14.7 and 14.9, 400 such rows 38.8 and 41.0.
+template <int VPT>
+hipError_t launch_row_stats_long(cascade_ctx* ctx, LmParams& p) {
+  // four standard deviations of a random sample's count above its mean; a tenth of the row is listed at most
+  const float mean = (float)p.top_k * 4096 / p.vocab, rank = mean + 4.f * sqrtf(mean) + 8.f;
+  const bool cut = (VPT > 40 || p.n_nodes >= 128) && p.top_k > 0 && rank <= 0.1f * 4096;
+  p.sample_rank = (int)rank;
+  return cut ? launch_row_stats_t<VPT, true, 1024, true>(ctx, p) : launch_row_stats_t<VPT, true, 1024, false>(ctx, p);
 }
 
 hipError_t launch_row_stats(cascade_ctx* ctx, const lmhead_args* a) {
@@ -1205,8 +1277,8 @@ hipError_t launch_row_stats(cascade_ctx* ctx, const lmhead_args* a) {
     case 2: return launch_row_stats_t<16, true, 1024>(ctx, p);
     case 3: return launch_row_stats_t<24, true, 1024>(ctx, p);
     case 4: return launch_row_stats_t<32, true, 1024>(ctx, p);
-    case 5: return launch_row_stats_t<40, true, 1024>(ctx, p);
-    case 6: return launch_row_stats_t<48, true, 1024>(ctx, p);
-    default: return launch_row_stats_t<64, true, 1024>(ctx, p);
+    case 5: return launch_row_stats_long<40>(ctx, p);
+    case 6: return launch_row_stats_long<48>(ctx, p);
+    default: return launch_row_stats_long<64>(ctx, p);
   }
 }
