@@ -56,11 +56,14 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // LDS.  Both products run on v_mfma_f32_16x16x4_f32 (one value per lane and operand, k = lane / 16 = g):
 //   S^T = K Q^T   lane (l16, g) loads 16 bytes at d = 16 ks + 4 g of key / query l16 and feeds element c of both to the
 //                 c-th product; the result holds keys 4 g + r of query l16;
-//   O^T = V^T P^T product r takes P^T straight from register r of that result, and key 4 g + r's value at d = 16 db + l16.
-// Nothing passes through LDS before the merge.  Latency-bound: the fixed part (row lookup, queries and
-// parents, barrier, merge) is 8.6 us of the 10.2 at 15 nodes x 8 heads x 64 and a 256-key prefix (48.5 us with one
-// workgroup per (node, head) and one key per thread); 8 instead of 16 waves, or the first tile requested before the
-// parent array is staged, change nothing.
+//   O^T = V^T P^T product r takes P^T straight from register r of that result, and element c of the 16 bytes of key 4 g + r's
+//                 value at d = 64 h + 4 l16: its row l16 stands for that d + c.
+// Nothing passes through LDS before the merge.  Bound by the trips to memory, one after the other (the row's place; queries, parents and
+// the first tile), by the 50 GB/s at which one compute unit receives keys and values that no cache near it holds (8 heads x 271 keys are 139 KB for
+// each of 8 units: 2.8 us), and by the tile that some wave has to do alone at the end.  15 nodes x 8 heads x 64, 256 keys: 10.6 us with
+// parents staged in LDS behind a barrier, values loaded four bytes at a time and sixteen parts read by every thread of the merge, now 9.7 (a step 28.3 and 26.9);
+// 60 nodes, 1000 keys 23.9 and 20.3-20.9, 200 nodes, 320 keys 14.9 and 13.2-14.5.  Two or three tiles of a wave side by side in 8 or 12 waves are
+// slower (10.1-10.4, 20.6-22.0).
 // DB = 16-wide blocks of head_dim; VEC: rows can be read 16 bytes at a time (otherwise element by element).
 template <int DB, int NW, bool VEC>
 __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_rows, int D) {
@@ -91,8 +94,8 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   if (s < 0) return;   // the grid is an upper bound of the number of blocks
   const int M = T * G;
   const int qr = min(16 * sb + l16, M - 1);   // rows past the end repeat the last one, never stored
-  const int qi = qr % T;
-  const int64_t q_row = (int64_t)(lo + qi) * p.n_heads + kvh * G + qr / T;
+  const int qh = G == 1 ? 0 : qr / T, qi = qr - qh * T;
+  const int64_t q_row = (int64_t)(lo + qi) * p.n_heads + kvh * G + qh;
   const int n_pt = (P + 15) / 16, nt = n_pt + (T + 15) / 16;
   auto load4 = [&](const float* row, int d) {
     if (VEC) return d < D ? *(const f32x4*)(row + d) : f32x4{0.f, 0.f, 0.f, 0.f};
@@ -107,8 +110,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   const float* vtr = (const float*)p.v_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
   const int64_t tree_pitch = (int64_t)p.n_kv_heads * D;
   // tile registers; keys past the end of the tile's source: clamped, masked below
-  f32x4 q[DB], ot[DB], k[DB];
-  float v[4][DB];
+  f32x4 q[DB], ot[DB], k[DB], v[4][DB / 4];
   auto request_k = [&](int t) {
     const bool tree = t >= n_pt;
     const int key = min(16 * (tree ? t - n_pt : t) + l16, (tree ? T : P) - 1);
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
       const int key = min(16 * (tree ? t - n_pt : t) + 4 * g + r, (tree ? T : P) - 1);
       const float* row = (tree ? vtr : vc) + (int64_t)key * (tree ? tree_pitch : p.sp);
 #pragma unroll
-      for (int db = 0; db < DB; ++db) v[r][db] = row[min(16 * db + l16, D - 1)];
+      for (int h = 0; h < DB / 4; ++h) v[r][h] = load4(row, 64 * h + 4 * l16);
     }
   };
 #pragma unroll
@@ -131,10 +133,27 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
     q[db] = load4((const float*)p.q + q_row * D, 16 * db + 4 * g);
     ot[db] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  for (int i = tid; i < T; i += 64 * NW) {
-    int pi = p.parent[lo + i];
-    if (pi >= i) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }   // keeps the climb finite; any negative parent ends it
-    if (i < CASCADE_MAX_TREE) s_parent[i] = pi;
+  // Trees of up to 128 nodes: every wave holds the parents in its lanes (like the query-split kernel), requested together with the
+  // queries and the first tiles.  Larger ones are staged, behind a barrier.
+  const bool in_lanes = T <= 128;
+  int pa[2] = {-1, -1};
+  if (in_lanes) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) pa[j] = p.parent[lo + min(64 * j + lane, T - 1)];
+  }
+  const int t0 = __builtin_amdgcn_readfirstlane(wave);
+  if (t0 < nt) { request_k(t0); request_v(t0); }
+  if (in_lanes) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (64 * j + lane < T && pa[j] >= 64 * j + lane) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pa[j] = -1; }   // keeps the climb finite; any negative parent ends it
+  } else {
+    for (int i = tid; i < T; i += 64 * NW) {
+      int pi = p.parent[lo + i];
+      if (pi >= i) { atomicOr(p.dev_status, CASCADE_FLAG_PARENT); pi = -1; }
+      if (i < CASCADE_MAX_TREE) s_parent[i] = pi;
+    }
+    __syncthreads();
   }
   // node a's parent: smaller than a, or negative.  Nothing but the array in LDS bounds a tree here; nodes past it read memory.
   auto parent_of = [&](int a) {
@@ -142,30 +161,46 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
     const int pi = p.parent[lo + a];
     return pi >= a ? -1 : pi;
   };
-  __syncthreads();
-  if (wave < nt) { request_k(wave); request_v(wave); }
-  float m = -INFINITY, l = 0.f;
-  for (int t = wave; t < nt; t += NW) {
-    const bool tree = t >= n_pt;
-    const int kb = 16 * (tree ? t - n_pt : t), last = (tree ? T : P) - 1;
-    // keys of the tile that query l16 sees
-    unsigned bits;
-    if (tree) {
-      bits = 0;
-      int a = qi, steps = 0;
-      while (a >= kb) {   // the node and its MAX_DEPTH nearest ancestors; a longer path is flagged
+  // keys of tile t that query l16 sees
+  auto seen = [&](int t) {
+    if (t < n_pt) {
+      const int left = P - 16 * t;
+      return left >= 16 ? 0xffffu : (1u << left) - 1u;
+    }
+    const int kb = 16 * (t - n_pt);
+    unsigned bits = 0;
+    int a = qi, steps = 0;
+    // the node and its MAX_DEPTH nearest ancestors; a longer path is flagged
+    if (in_lanes) {
+      while (__any(a >= kb)) {   // kb >= 0
+        if (a >= kb && ++steps > CASCADE_MAX_DEPTH + 1) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); a = -1; }
+        if (a >= kb && a - kb < 16) bits |= 1u << (a - kb);
+        int up = __builtin_amdgcn_ds_bpermute(4 * (a & 63), pa[0]);
+        if (T > 64) {
+          const int hi = __builtin_amdgcn_ds_bpermute(4 * (a & 63), pa[1]);
+          up = a >= 64 ? hi : up;
+        }
+        a = a >= kb ? up : a;
+      }
+    } else {
+      while (a >= kb) {
         if (++steps > CASCADE_MAX_DEPTH + 1) { atomicOr(p.dev_status, CASCADE_FLAG_DEPTH); break; }
         if (a - kb < 16) bits |= 1u << (a - kb);
         a = parent_of(a);
       }
-    } else {
-      bits = last - kb >= 15 ? 0xffffu : (1u << (last - kb + 1)) - 1u;
     }
+    return bits;
+  };
+  float m = -INFINITY, l = 0.f;
+  auto step = [&](int t, auto more) {   // more: another tile of the wave follows
+    constexpr bool MORE = decltype(more)::value;
+    const unsigned bits = seen(t);
     f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int c = 0; c < 4; ++c) st = __builtin_amdgcn_mfma_f32_16x16x4f32(k[db][c], q[db][c], st, 0, 0, 0);
+    if constexpr (MORE) request_k(t + NW);
     float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -190,7 +225,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int db = 0; db < DB; ++db) z = fmaf(v[r][db], 0.f, z);
+        for (int db = 0; db < DB; ++db) z = fmaf(v[r][db / 4][db % 4], 0.f, z);
       whole_keys = !__any(z != 0.f);
     }
 #pragma unroll
@@ -199,7 +234,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][db], st[r], ot[db], 0, 0, 0);
+        for (int r = 0; r < 4; ++r) ot[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][db / 4][db % 4], st[r], ot[db], 0, 0, 0);
     } else {
       for (int kg = 0; kg < 4; ++kg)
 #pragma unroll
@@ -207,40 +242,45 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
           const bool sees = (bits >> (4 * kg + r)) & 1u;
 #pragma unroll
           for (int db = 0; db < DB; ++db) {
-            const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? v[r][db] : 0.f, st[r], ot[db], 0, 0, 0);
+            const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x4f32(g == kg ? v[r][db / 4][db % 4] : 0.f, st[r], ot[db], 0, 0, 0);
 #pragma unroll
             for (int c = 0; c < 4; ++c) ot[db][c] = sees ? o[c] : ot[db][c];
           }
         }
     }
-    if (t + NW < nt) { request_k(t + NW); request_v(t + NW); }
-  }
-  // merge: lane (l16, g) holds d = 16 db + 4 g + c of query l16
+    if constexpr (MORE) request_v(t + NW);
+  };
+  int t = t0;
+  for (; t + NW < nt; t += NW) step(t, std::true_type{});
+  if (t < nt) step(t, std::false_type{});
+  // merge: lane (l16, g) holds d = 64 (db / 4) + 16 g + 4 c + db % 4 of query l16 (a value's 16 bytes feed four products)
   l = rows4_sum(l);
   float* mo = f32_smem + (wave * 16 + l16) * OP;
   float* ml = f32_smem + NW * 16 * OP;
 #pragma unroll
-  for (int db = 0; db < DB; ++db) *(f32x4*)(mo + 16 * db + 4 * g) = ot[db];
+  for (int h = 0; h < DB / 4; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) *(f32x4*)(mo + 64 * h + 16 * g + 4 * c) = f32x4{ot[4 * h][c], ot[4 * h + 1][c], ot[4 * h + 2][c], ot[4 * h + 3][c]};
   if (g == 0) {
     ml[(wave * 16 + l16) * 2] = m;
     ml[(wave * 16 + l16) * 2 + 1] = l;
   }
   __syncthreads();
+  // a wave finishes whole rows: lane w holds the factor of wave w's part
   const int rows = min(16, M - 16 * sb);
-  for (int e = tid; e < rows * D; e += 64 * NW) {
-    const int r = e / D, d = e % D, row = 16 * sb + r;
-    float mm = -INFINITY, o = 0.f, ll = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) mm = fmaxf(mm, ml[(w * 16 + r) * 2]);
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float f = fast_exp2(ml[(w * 16 + r) * 2] - mm);   // a wave without visible keys: 0
-      ll = fmaf(f, ml[(w * 16 + r) * 2 + 1], ll);
-      o = fmaf(f, f32_smem[(w * 16 + r) * OP + d], o);
-    }
+  for (int r = __builtin_amdgcn_readfirstlane(wave); r < rows; r += NW) {
+    const int row = 16 * sb + r, w = lane & 15;
+    const float mw = w < NW ? ml[(w * 16 + r) * 2] : -INFINITY, lw = w < NW ? ml[(w * 16 + r) * 2 + 1] : 0.f;
+    const float mm = wave_max(mw), f = fast_exp2(mw - mm);   // a wave without visible keys: 0
+    const float ll = wave_sum(lane < NW ? f * lw : 0.f);
     const int64_t rowg = (int64_t)(lo + row % T) * p.n_heads + kvh * G + row / T;
-    ((float*)p.out)[rowg * D + d] = o / ll;
-    if (d == 0 && p.lse) p.lse[rowg] = mm * LN2 + logf(ll);
+    for (int d = lane; d < D; d += 64) {
+      float o = 0.f;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) o = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), i)), f32_smem[(i * 16 + r) * OP + d], o);
+      ((float*)p.out)[rowg * D + d] = o / ll;
+    }
+    if (lane == 0 && p.lse) p.lse[rowg] = mm * LN2 + logf(ll);
   }
 }
 
@@ -1204,7 +1244,7 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
   // blocks of 16 query rows: at most one partly filled one per row of the batch
   dim3 grid((unsigned)((int64_t)a->n_nodes_total * p.group / 16 + a->n_rows), a->n_kv_heads);
   const bool vec = D % 4 == 0 && ((a->cache_stride_row | a->cache_stride_head | a->cache_stride_pos) & 3) == 0 &&
-                   (((uintptr_t)a->q | (uintptr_t)a->k_tree | (uintptr_t)a->k_cache) & 15) == 0;
+                   (((uintptr_t)a->q | (uintptr_t)a->k_tree | (uintptr_t)a->k_cache | (uintptr_t)a->v_tree | (uintptr_t)a->v_cache) & 15) == 0;
   if (D <= 64) return vec ? launch_f32_t<4, 16, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<4, 16, false>(ctx, p, grid, a->n_rows, D);
   if (D <= 128) return vec ? launch_f32_t<8, 8, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<8, 8, false>(ctx, p, grid, a->n_rows, D);
   return vec ? launch_f32_t<16, 4, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<16, 4, false>(ctx, p, grid, a->n_rows, D);
