@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Optional
 
 import torch
@@ -79,6 +80,27 @@ class conv_weight_args(C.Structure):
                 ("tau_seq", _f32), ("c", _f32), ("weights", _vp), ("cos_next", _vp)]
 
 
+# Argument records of the calls of a step are packed in one go: setting the fields of a ctypes structure one by one took most of a call's host
+# time (the four calls of a step of 15 nodes with their five launches: 28-29 us, now 22-27).
+_CODES = {_vp: "P", _i32: "i", C.c_int: "i", _i64: "q", _f32: "f"}
+
+
+class _Record:
+    def __init__(self, layout):
+        self.layout = layout
+        # native alignment, and "0P": up to the end of the structure
+        self.pack = struct.Struct("@" + "".join(_CODES[t] for _, t in layout._fields_) + "0P").pack
+        assert len(self.pack(*[0] * len(layout._fields_))) == C.sizeof(layout)
+
+    def __call__(self, *fields) -> bytes:
+        try:
+            return self.pack(*fields)
+        except (struct.error, OverflowError):    # ctypes converts more, and says what it does not
+            return bytes(self.layout(*fields))
+
+
+_TREE_ATTN, _LMHEAD, _ACCEPT, _SELECT, _COMMIT, _WEIGHTS = map(_Record, (tree_attn_args, lmhead_args, accept_args, select_args, kv_commit_args, conv_weight_args))
+
 _lib = None
 
 
@@ -125,6 +147,8 @@ def load_library() -> C.CDLL:
         fn = getattr(lib, name)
         fn.argtypes = [_vp, C.POINTER(st)]
         fn.restype = C.c_int
+        # the same entry point for a packed record
+        setattr(lib, name + "_record", C.CFUNCTYPE(C.c_int, _vp, C.c_char_p)((name, lib)))
     _lib = lib
     return lib
 
@@ -141,15 +165,27 @@ def _check(status: int) -> None:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else t.data_ptr()
+    return 0 if t is None else t.data_ptr()
+
+
+_data_ptr = torch.Tensor.data_ptr
+
+
+def _ptrs(*tensors):
+    try:
+        return tuple(map(_data_ptr, tensors))
+    except TypeError:    # None among them
+        return tuple(map(_ptr, tensors))
+
+
+_DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    return code
 
 
 class Context:
@@ -202,32 +238,28 @@ class Context:
         return out.value
 
 
-def _tree_attn_args(*, node_off, parent, prefix_len, q, k_tree, v_tree, k_cache, v_cache, out, lse, scale,
-                    max_nodes_per_tree, max_prefix_len) -> tree_attn_args:
-    a = tree_attn_args()
-    a.n_rows = prefix_len.numel()
-    a.node_off, a.parent, a.prefix_len = _ptr(node_off), _ptr(parent), _ptr(prefix_len)
-    a.n_nodes_total = q.shape[0]
-    a.max_nodes_per_tree, a.max_prefix_len = max_nodes_per_tree, max_prefix_len
-    a.dtype = _dtype_code(q)
-    a.n_heads, a.n_kv_heads, a.head_dim = q.shape[1], k_tree.shape[1], q.shape[2]
-    a.scale = scale
-    a.q, a.k_tree, a.v_tree = _ptr(q), _ptr(k_tree), _ptr(v_tree)
-    a.k_cache, a.v_cache = _ptr(k_cache), _ptr(v_cache)
+def _tree_attn_record(node_off, parent, prefix_len, q, k_tree, v_tree, k_cache, v_cache, out, lse, scale, max_nodes_per_tree,
+                      max_prefix_len) -> bytes:
+    shape = q.shape
     if k_cache is not None:
-        assert k_cache.stride() == v_cache.stride() and k_cache.stride(3) == 1
-        a.cache_stride_row, a.cache_stride_head, a.cache_stride_pos = k_cache.stride(0), k_cache.stride(1), k_cache.stride(2)
-    a.out, a.lse = _ptr(out), _ptr(lse)
-    return a
+        stride = k_cache.stride()
+        assert stride == v_cache.stride() and stride[3] == 1
+        row, head, pos = stride[0], stride[1], stride[2]
+    else:
+        row = head = pos = 0
+    return _TREE_ATTN(prefix_len.numel(), *_ptrs(node_off, parent, prefix_len), shape[0], max_nodes_per_tree, max_prefix_len, _dtype_code(q),
+                      shape[1], k_tree.shape[1], shape[2], scale, *_ptrs(q, k_tree, v_tree, k_cache, v_cache), row, head, pos, _ptr(out), _ptr(lse))
+
+
+def _tree_attn_args(**tensors) -> tree_attn_args:
+    return tree_attn_args.from_buffer_copy(_tree_attn_record(**tensors))
 
 
 def tree_verify_attn(ctx: Context, *, node_off, parent, prefix_len, q, k_tree, v_tree, k_cache, v_cache, out,
                      lse=None, scale: float = 0.0, max_nodes_per_tree: int, max_prefix_len: int) -> None:
     """q/out [N,Hq,D], k_tree/v_tree [N,Hkv,D], k_cache/v_cache [S,Hkv,P_cap,D] (last dim contiguous)."""
-    a = _tree_attn_args(node_off=node_off, parent=parent, prefix_len=prefix_len, q=q, k_tree=k_tree, v_tree=v_tree,
-                        k_cache=k_cache, v_cache=v_cache, out=out, lse=lse, scale=scale,
-                        max_nodes_per_tree=max_nodes_per_tree, max_prefix_len=max_prefix_len)
-    _check(ctx.lib.tree_verify_attn(ctx.handle, C.byref(a)))
+    _check(ctx.lib.tree_verify_attn_record(ctx.handle, _tree_attn_record(node_off, parent, prefix_len, q, k_tree, v_tree, k_cache, v_cache, out, lse, scale,
+                                                                         max_nodes_per_tree, max_prefix_len)))
 
 
 def tree_verify_attn_static(stream: Optional[torch.cuda.Stream] = None, *, node_off, parent, prefix_len, q, k_tree, v_tree,
@@ -285,74 +317,49 @@ def cascade_pack_lmhead_w(ctx: Context, w: torch.Tensor) -> torch.Tensor:
 
 def lmhead_softmax_cfg(ctx: Context, *, h_cond, h_uncond, w, cfg_scale, temperature, top_k, logits, row_max, row_thr, row_lse,
                        w_layout: int = W_ROWMAJOR, cfg_mix: int = CFG_MIX_LOGITS) -> None:
-    a = lmhead_args()
-    a.dtype = _dtype_code(w)
-    a.w_layout = w_layout
-    a.cfg_mix = cfg_mix
-    a.n_nodes, a.hidden, a.vocab = h_cond.shape[0], h_cond.shape[1], w.shape[0]
-    a.h_cond, a.h_uncond, a.w = _ptr(h_cond), _ptr(h_uncond), _ptr(w)
-    a.cfg_scale, a.temperature, a.top_k = cfg_scale, temperature, top_k
-    a.logits, a.row_max, a.row_thr, a.row_lse = _ptr(logits), _ptr(row_max), _ptr(row_thr), _ptr(row_lse)
-    _check(ctx.lib.lmhead_softmax_cfg(ctx.handle, C.byref(a)))
+    shape = h_cond.shape
+    _check(ctx.lib.lmhead_softmax_cfg_record(ctx.handle, _LMHEAD(
+        _dtype_code(w), shape[0], shape[1], w.shape[0], h_cond.data_ptr(), _ptr(h_uncond), w.data_ptr(), w_layout, cfg_scale, temperature, top_k, cfg_mix,
+        *_ptrs(logits, row_max, row_thr, row_lse))))
 
 
 def cascade_accept(ctx: Context, *, node_off, parent, token, h_cond, logits, row_thr, row_lse, tau_pos, tau_seq,
                    q_tok, m_int, m_conv, cos_parent, n_int, n_conv, feature_space: int = FEATURES_HIDDEN) -> None:
-    a = accept_args()
-    a.feature_space = feature_space
-    a.h_dtype = _dtype_code(h_cond)
-    a.n_prompts, a.n_nodes_total, a.hidden, a.vocab = node_off.numel() - 1, h_cond.shape[0], h_cond.shape[1], logits.shape[1]
-    a.node_off, a.parent, a.token, a.h_cond = _ptr(node_off), _ptr(parent), _ptr(token), _ptr(h_cond)
-    a.logits, a.row_thr, a.row_lse = _ptr(logits), _ptr(row_thr), _ptr(row_lse)
-    a.tau_pos, a.tau_seq = tau_pos, tau_seq
-    a.q_tok, a.m_int, a.m_conv, a.cos_parent = _ptr(q_tok), _ptr(m_int), _ptr(m_conv), _ptr(cos_parent)
-    a.n_int, a.n_conv = _ptr(n_int), _ptr(n_conv)
-    _check(ctx.lib.cascade_accept(ctx.handle, C.byref(a)))
+    shape = h_cond.shape
+    _check(ctx.lib.cascade_accept_record(ctx.handle, _ACCEPT(
+        _dtype_code(h_cond), node_off.numel() - 1, shape[0], shape[1], logits.shape[1],
+        *_ptrs(node_off, parent, token, h_cond, logits, row_thr, row_lse), tau_pos, tau_seq, *_ptrs(q_tok, m_int, m_conv, cos_parent, n_int, n_conv), feature_space)))
 
 
 def select_path(ctx: Context, *, node_off, parent, token, q_tok, m_int, m_conv, n_int, n_conv, draft_prob, u, u_bonus,
                 eps_tvd, logits, row_thr, row_lse, max_depth, mode, accept_len, path_nodes, emitted, terminal, tvd_used,
                 draft_dist=None) -> None:
-    a = select_args()
-    a.draft_dist = _ptr(draft_dist)
-    a.n_prompts, a.n_nodes_total, a.vocab, a.max_depth, a.mode = node_off.numel() - 1, token.numel(), logits.shape[1], max_depth, mode
-    a.node_off, a.parent, a.token = _ptr(node_off), _ptr(parent), _ptr(token)
-    a.q_tok, a.m_int, a.m_conv, a.n_int, a.n_conv = _ptr(q_tok), _ptr(m_int), _ptr(m_conv), _ptr(n_int), _ptr(n_conv)
-    a.draft_prob, a.u, a.u_bonus, a.eps_tvd = _ptr(draft_prob), _ptr(u), _ptr(u_bonus), eps_tvd
-    a.logits, a.row_thr, a.row_lse = _ptr(logits), _ptr(row_thr), _ptr(row_lse)
-    a.accept_len, a.path_nodes, a.emitted = _ptr(accept_len), _ptr(path_nodes), _ptr(emitted)
-    a.terminal, a.tvd_used = _ptr(terminal), _ptr(tvd_used)
-    _check(ctx.lib.select_path(ctx.handle, C.byref(a)))
+    _check(ctx.lib.select_path_record(ctx.handle, _SELECT(
+        node_off.numel() - 1, token.numel(), logits.shape[1], max_depth, mode, *_ptrs(node_off, parent, token, q_tok, m_int, m_conv, n_int, n_conv),
+        _ptr(draft_prob), _ptr(u), _ptr(u_bonus), eps_tvd, *_ptrs(logits, row_thr, row_lse, accept_len, path_nodes, emitted, terminal, tvd_used),
+        _ptr(draft_dist))))
 
 
 def kv_commit(ctx: Context, *, node_off, row_prompt, accept_len, path_nodes, k_tree, v_tree, k_cache, v_cache,
               prefix_len, prefix_len_out, n_prompts: Optional[int] = None) -> None:
     """k_tree/v_tree [L,N,Hkv,D]; k_cache/v_cache [L,S,Hkv,cap,D] (last dim contiguous); path_nodes [B,max_depth]."""
-    a = kv_commit_args()
-    a.n_rows, a.n_prompts = prefix_len.numel(), accept_len.numel() if n_prompts is None else n_prompts
-    a.node_off, a.row_prompt, a.accept_len, a.path_nodes = _ptr(node_off), _ptr(row_prompt), _ptr(accept_len), _ptr(path_nodes)
-    a.max_depth = path_nodes.shape[1] if path_nodes is not None else 0
-    a.n_nodes_total = k_tree.shape[1]
-    a.dtype = _dtype_code(k_tree)
-    a.n_layers, a.n_kv_heads, a.head_dim = k_tree.shape[0], k_tree.shape[2], k_tree.shape[3]
+    shape = k_tree.shape
+    stride = k_cache.stride()
     assert k_tree.is_contiguous() and v_tree.is_contiguous()
-    assert k_cache.stride() == v_cache.stride() and k_cache.stride(4) == 1
-    a.k_tree, a.v_tree, a.k_cache, a.v_cache = _ptr(k_tree), _ptr(v_tree), _ptr(k_cache), _ptr(v_cache)
-    a.cache_stride_layer, a.cache_stride_row, a.cache_stride_head, a.cache_stride_pos = k_cache.stride()[:4]
-    a.prefix_cap = k_cache.shape[3]
-    a.prefix_len, a.prefix_len_out = _ptr(prefix_len), _ptr(prefix_len_out)
-    _check(ctx.lib.kv_commit(ctx.handle, C.byref(a)))
+    assert stride == v_cache.stride() and stride[4] == 1
+    _check(ctx.lib.kv_commit_record(ctx.handle, _COMMIT(
+        prefix_len.numel(), accept_len.numel() if n_prompts is None else n_prompts, *_ptrs(node_off, row_prompt, accept_len, path_nodes),
+        path_nodes.shape[1] if path_nodes is not None else 0, shape[1], _dtype_code(k_tree), shape[0], shape[2], shape[3],
+        *_ptrs(k_tree, v_tree, k_cache, v_cache), stride[0], stride[1], stride[2], stride[3], k_cache.shape[3],
+        *_ptrs(prefix_len, prefix_len_out))))
 
 
 def convergence_weights(ctx: Context, *, features, tau_seq: float, c: float, weights, cos_next=None) -> None:
     """features [B, K, h] contiguous; weights / cos_next [B, K] float32."""
-    a = conv_weight_args()
     assert features.is_contiguous()
-    a.dtype = _dtype_code(features)
-    a.n_seqs, a.seq_len, a.hidden = features.shape
-    a.features, a.tau_seq, a.c = _ptr(features), tau_seq, c
-    a.weights, a.cos_next = _ptr(weights), _ptr(cos_next)
-    _check(ctx.lib.convergence_weights(ctx.handle, C.byref(a)))
+    seqs, length, hidden = features.shape
+    _check(ctx.lib.convergence_weights_record(ctx.handle, _WEIGHTS(_dtype_code(features), seqs, length, hidden, features.data_ptr(), tau_seq, c,
+                                                                   _ptr(weights), _ptr(cos_next))))
 
 
 # ------------------------------------------------------------------------------------------------
