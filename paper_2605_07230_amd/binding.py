@@ -173,9 +173,9 @@ _data_ptr = torch.Tensor.data_ptr
 
 def _ptrs(*tensors):
     try:
-        return tuple(map(_data_ptr, tensors))
+        return list(map(_data_ptr, tensors))
     except TypeError:    # None among them
-        return tuple(map(_ptr, tensors))
+        return list(map(_ptr, tensors))
 
 
 _DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
