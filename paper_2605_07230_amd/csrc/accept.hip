@@ -10,6 +10,8 @@
 // similarity) are swept once for eight others at a time on the vector ALU (narrow ones for four, by each wave).  The probabilities of the siblings' and children's
 // tokens under the parent's distribution are gathered while the rows are still in flight; the sets
 // I_a and C_a, the distinct-token masses and all outputs then need only ballots and LDS.
+#include <type_traits>
+
 #include "common.h"
 
 namespace {
@@ -33,33 +35,35 @@ union Frag8 {
   uint4 u;
 };
 
-// C[16x16] += A[16 rows][k] * B[16 rows][k]^T over k in [k0, k1), (k1 - k0) a multiple of 32;
-// rowa / rowb are this lane's row pointers, g its 8-wide k group
-__device__ __forceinline__ f32x4 gram_tile(const uint16_t* rowa, const uint16_t* rowb, bool same, int k0, int k1, int g) {
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+// Gram tile of 16 rows with themselves over k in [k0, k1), (k1 - k0) a multiple of 32; row is this lane's row, g its 8-wide k group.  Eight
+// steps' loads are issued together.  Lanes of rows that a tile does not have (live = false) load nothing: a tile holds 7 to 8 rows in the mean; their
+// entries of the result are not looked at.  In steps of four, every lane loading: 60 nodes x 2048 6.0 -> 4.8 us, x 5120 9.8 -> 6.3, four such
+// trees x 5120 11.2 -> 8.0 (steps of four, so: 5.2, 7.5, 8.8; of sixteen: 5.3, 7.6, 9.6).
+__device__ __forceinline__ f32x4 gram_tile(const uint16_t* row, bool live, int k0, int k1, int g) {
+  f32x4 acc[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto steps = [&](auto count, int k) {
+    constexpr int N = decltype(count)::value;
+    Frag8 f[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) f[s].u = make_uint4(0, 0, 0, 0);
+    if (live)
+#pragma unroll
+      for (int s = 0; s < N; ++s) f[s].u = *(const uint4*)(row + k + 32 * s + 8 * g);
+#pragma unroll
+    for (int s = 0; s < N; ++s) acc[s & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[s].v, f[s].v, acc[s & 3], 0, 0, 0);
+  };
   int k = k0;
-  for (; k + 128 <= k1; k += 128) {   // 4 MFMA steps per iteration, loads issued together
-    Frag8 fa[4], fb[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) fa[s].u = *(const uint4*)(rowa + k + 32 * s + 8 * g);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) fb[s].u = same ? fa[s].u : *(const uint4*)(rowb + k + 32 * s + 8 * g);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[s].v, fb[s].v, acc, 0, 0, 0);
-  }
-  for (; k < k1; k += 32) {
-    Frag8 fa, fb;
-    fa.u = *(const uint4*)(rowa + k + 8 * g);
-    fb.u = same ? fa.u : *(const uint4*)(rowb + k + 8 * g);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, fb.v, acc, 0, 0, 0);
-  }
-  return acc;
+  for (; k + 256 <= k1; k += 256) steps(std::integral_constant<int, 8>{}, k);
+  for (; k < k1; k += 32) steps(std::integral_constant<int, 1>{}, k);
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
 // The same Gram tile of one row set with itself over NS k-steps, all of the lane's NS 16-byte pieces
 // requested before the first multiplication (one round trip instead of NS / 4), side() issued
 // behind them (loads return in order, so what side() requests arrives after the rows), four
-// independent accumulator chains.
+// independent accumulator chains.  (Every lane loads: with the lanes of missing rows masked off 60 nodes x 4096 5.4 -> 5.7 us.)
 template <int NS, typename F>
 __device__ __forceinline__ f32x4 gram_tile_deep(const uint16_t* row, int k0, int g, F&& side) {
   Frag8 f[NS];
@@ -142,7 +146,11 @@ struct AcceptShare {
   unsigned long long* sums;     // [nodes][parts][MAXO + 1]: a.x and x.x of every other row, a.a
 };
 
-template <typename T, int NT, bool NARROW_ROWS>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
+// How a node's row is taken against the others: by the workgroup on the vector ALU, by single waves, or in Gram tiles (bf16 rows of a multiple of
+// 128; of 4096: the whole part of a wave in flight at once).  Kernels of their own: the less code stands in one, the sooner a cold launch is through it.
+enum AcceptRows { ROWS_SWEPT, ROWS_NARROW, ROWS_TILES, ROWS_TILES_4096 };
+
+template <typename T, int NT, AcceptRows HOW>   // NT threads; the Gram tiles of bf16 rows are laid out for 256
 __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptShare share, int* dev_status) {
   constexpr int NWV = NT / 64;
   __shared__ float gq[NWV][256];        // the waves' partial Gram tiles over their parts of K; generic path: their partial sums
@@ -261,44 +269,40 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptSh
   auto gather_q = [&]() { request_q(); finish_q(); };
 
   const T* row_a = H + (int64_t)gi * h;
-  bool mfma_done = false;
-  if constexpr (sizeof(T) == 2 && !NARROW_ROWS) {
-    if ((h & 127) == 0) {
-      mfma_done = true;
-      const int l16 = lane & 15, g = lane >> 4;
-      const int kq = h / NWV;   // a multiple of 32
-      for (int blk = 0; blk * 15 < n_other; ++blk) {
-        // tile rows: 0 = a, 1..15 = others 15 blk .. 15 blk + 14 (clamped: extra rows repeat the last one)
-        const int o = 15 * blk + l16 - 1;
-        const uint16_t* ra = l16 == 0 ? (const uint16_t*)row_a
-                                      : (const uint16_t*)(H + (int64_t)(lo + s_other[min(o, n_other - 1)]) * h);
-        f32x4 acc;
-        if (h == 4096) {   // the wave's whole part in flight at once
-          acc = gram_tile_deep<128 / NWV>(ra, wave * kq, g, [&]() { if (blk == 0) request_q(); });
-          if (blk == 0) finish_q();
-        } else {
-          acc = gram_tile(ra, ra, true, wave * kq, (wave + 1) * kq, g);
-          if (blk == 0) gather_q();
-        }
-        if (blk > 0) __syncthreads();   // the previous block's partial tiles have been consumed
+  if constexpr (HOW >= ROWS_TILES) {
+    const int l16 = lane & 15, g = lane >> 4;
+    const int kq = h / NWV;   // a multiple of 32
+    for (int blk = 0; blk * 15 < n_other; ++blk) {
+      // tile rows: 0 = a, 1..15 = others 15 blk .. 15 blk + 14 (clamped: extra rows repeat the last one)
+      const int o = 15 * blk + l16 - 1;
+      const uint16_t* ra = l16 == 0 ? (const uint16_t*)row_a
+                                    : (const uint16_t*)(H + (int64_t)(lo + s_other[min(o, n_other - 1)]) * h);
+      f32x4 acc;
+      if constexpr (HOW == ROWS_TILES_4096) {   // the wave's whole part in flight at once
+        acc = gram_tile_deep<128 / NWV>(ra, wave * kq, g, [&]() { if (blk == 0) request_q(); });
+      } else {
+        if (blk == 0) request_q();
+        acc = gram_tile(ra, l16 == 0 || o < n_other, wave * kq, (wave + 1) * kq, g);
+      }
+      if (blk == 0) finish_q();
+      if (blk > 0) __syncthreads();   // the previous block's partial tiles have been consumed
 #pragma unroll
-        for (int r = 0; r < 4; ++r) gq[wave][(4 * g + r) * 16 + l16] = acc[r];
-        __syncthreads();
-        if (tid >= 1 && tid < 16 && 15 * blk + tid - 1 < n_other) {
-          // row 0 of the tile: a . x_j ; diagonal: |x_j|^2 ; entry (0, 0): |a|^2
-          const int j = tid;
-          float ax = gq[0][j], xx = gq[0][17 * j], aa = gq[0][0];
+      for (int r = 0; r < 4; ++r) gq[wave][(4 * g + r) * 16 + l16] = acc[r];
+      __syncthreads();
+      if (tid >= 1 && tid < 16 && 15 * blk + tid - 1 < n_other) {
+        // row 0 of the tile: a . x_j ; diagonal: |x_j|^2 ; entry (0, 0): |a|^2
+        const int j = tid;
+        float ax = gq[0][j], xx = gq[0][17 * j], aa = gq[0][0];
 #pragma unroll
-          for (int w = 1; w < NWV; ++w) { ax += gq[w][j]; xx += gq[w][17 * j]; aa += gq[w][0]; }
-          s_cos[15 * blk + j - 1] = cos_from(ax, aa, xx);
-        }
+        for (int w = 1; w < NWV; ++w) { ax += gq[w][j]; xx += gq[w][17 * j]; aa += gq[w][0]; }
+        s_cos[15 * blk + j - 1] = cos_from(ax, aa, xx);
       }
     }
   }
-  if (!mfma_done) {
+  if constexpr (HOW < ROWS_TILES) {
     gather_q();
     const bool aligned = (h * sizeof(T)) % 16 == 0 && ((uintptr_t)H & 15) == 0;
-    if constexpr (NARROW_ROWS) {
+    if constexpr (HOW == ROWS_NARROW) {
       for (int o0 = WG * wave; o0 < n_other; o0 += NT / 64 * WG) {
         const T* x[WG];
 #pragma unroll
@@ -453,9 +457,10 @@ hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
   }
   grid.x = parts;
   // (Gram tiles on eight waves: 462 nodes 10.2 -> 12.1 us, 1024 nodes 18 -> 23.6, fewer nodes the same)
-#define CASCADE_LAUNCH_ACCEPT(T, NT, N) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, N>), grid, dim3(NT), 0, ctx->stream, *a, share, ctx->dev_status)
-  if (bf16) { if (narrow) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, true); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, false); }
-  else { if (narrow) CASCADE_LAUNCH_ACCEPT(float, 512, true); else CASCADE_LAUNCH_ACCEPT(float, 512, false); }
+#define CASCADE_LAUNCH_ACCEPT(T, NT, HOW) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, HOW>), grid, dim3(NT), 0, ctx->stream, *a, share, ctx->dev_status)
+  if (mfma) { if (a->hidden == 4096) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES_4096); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES); }
+  else if (bf16) { if (narrow) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_NARROW); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_SWEPT); }
+  else { if (narrow) CASCADE_LAUNCH_ACCEPT(float, 512, ROWS_NARROW); else CASCADE_LAUNCH_ACCEPT(float, 512, ROWS_SWEPT); }
 #undef CASCADE_LAUNCH_ACCEPT
   return hipGetLastError();
 }
