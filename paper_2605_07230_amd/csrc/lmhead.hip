@@ -1065,13 +1065,24 @@ bool lm_streams(int tile, int rows, int vocab, int hidden) {
   return tile == 5 || (rows + LM_TILES[tile].rows - 1) / LM_TILES[tile].rows <= 2;
 }
 
+// 256 x 128 tiles that stream their weights to one tile of mixed rows (up to 256), fitted again since they do: whole rounds take less, of that a part
+// whatever the hidden dimension (start and stores), and a round that is not full takes nearly as long.  Projection in 128 x 256 tiles, where each weight
+// is requested twice, which were taken, and so, us: 256 x 65536 x 4096 154.1 and 151.5, 184 rows 154.5 and 144.3, 130 rows 149.7 and 139.5, 200 x
+// 40000 x 4096 111.5 and 104.8, 200 x 65536 x 2048 88.1 and 87.9; with two tiles of rows the other way round, 400 x 36032 x 4096 154.5 and 161.4.
+// (Plain rows keep the costs they had.)
+constexpr LmTile LM_STREAMED_256X128 = {256, 128, 63.f, 0.937f, 0.9f};
+constexpr float LM_STREAMED_START_US = 8.f;
+
 // Time of the tiles of a launch over n_cols columns: rounds over the compute units.
-float lm_rounds_us(const LmTile& tile, int rows, int n_cols, int hidden, int n_cu) {
+float lm_rounds_us(int i, int rows, int n_cols, int vocab, int hidden, bool mixed, int n_cu) {
+  const bool streamed = i == 4 && mixed && rows <= 256 && lm_streams(i, rows, vocab, hidden);
+  const LmTile& tile = streamed ? LM_STREAMED_256X128 : LM_TILES[i];
+  const float start = streamed ? LM_STREAMED_START_US : 0.f;
   const int n_mtiles = (rows + tile.rows - 1) / tile.rows;
   const long tiles = (long)n_mtiles * ((n_cols + tile.cols - 1) / tile.cols);
   const float last = (float)(tiles % n_cu) / n_cu, used = (float)rows / ((float)n_mtiles * tile.rows);
   const float rounds = (float)(tiles / n_cu) + (last > 0.f ? tile.few + (1.f - tile.few) * last : 0.f);
-  return rounds * tile.us * (tile.pad + (1.f - tile.pad) * used) * (hidden / 4096.f);
+  return rounds * (start + (tile.us - start) * (hidden / 4096.f)) * (tile.pad + (1.f - tile.pad) * used);
 }
 // Estimated time of the whole projection: that, and the weight stream at 6.2 TB/s, which overlap only partly.  Over 250
 // sizes (16-800 rows, 16384-65536 columns, hidden 2048 and 4096, weights from HBM, streamed where lm_streams says so) a single tile, where one is
@@ -1108,14 +1119,14 @@ LmPlan lm_plan(const lmhead_args* a, bool packed_w, bool premix, bool cfg, int n
     if (!usable(i)) continue;
     const float pack = i >= LM_RING_TILES && !premix ? 4.f : 0.f;   // the tiled kernel needs its rows packed (the mix packs them on the way)
     const LmTile& t = LM_TILES[i];
-    const float whole = lm_estimate_us(lm_rounds_us(t, rows, V, a->hidden, n_cu), V, a->hidden) + pack;
+    const float whole = lm_estimate_us(lm_rounds_us(i, rows, V, V, a->hidden, premix, n_cu), V, a->hidden) + pack;
     if (whole < best.us) best = {i, i, V, whole};
     const int n_mtiles = (rows + t.rows - 1) / t.rows, n_ntiles = (V + t.cols - 1) / t.cols;
     const int full = (int)((long)n_mtiles * n_ntiles / n_cu) * n_cu / n_mtiles;   // column tiles in whole rounds
     if (full == 0 || full * t.cols >= V) continue;
     for (int j = 0; j < 7; ++j) {
       if (!usable(j) || (i < LM_RING_TILES && j >= LM_RING_TILES)) continue;
-      const float c = lm_rounds_us(t, rows, full * t.cols, a->hidden, n_cu) + lm_rounds_us(LM_TILES[j], rows, V - full * t.cols, a->hidden, n_cu);
+      const float c = lm_rounds_us(i, rows, full * t.cols, V, a->hidden, premix, n_cu) + lm_rounds_us(j, rows, V - full * t.cols, V, a->hidden, premix, n_cu);
       const float us = lm_estimate_us(c, V, a->hidden) + pack + LM_SECOND_LAUNCH_US;
       if (us < best.us) best = {i, j, full * t.cols, us};
     }
