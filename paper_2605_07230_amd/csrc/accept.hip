@@ -332,27 +332,28 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptSh
       const int h0 = alone ? 0 : min((int)blockIdx.x * width, h), h1 = min(h0 + width, h);
       unsigned long long* const shared = share.sums + (gi * parts + blockIdx.x) * (MAXO + 1);
       auto pair = [](float x, float y) { return (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32); };
-      for (int o0 = 0; o0 < n_other; o0 += DG) {
-        const T* x[DG];
+      auto group = [&](int o0, auto size) {   // others o0 .. o0 + G - 1
+        constexpr int G = decltype(size)::value;
+        const T* x[G];
 #pragma unroll
-        for (int j = 0; j < DG; ++j)   // past the end: the last one again
+        for (int j = 0; j < G; ++j)   // past the end: the last one again
           x[j] = H + (int64_t)(lo + __builtin_amdgcn_readfirstlane(s_other[min(o0 + j, n_other - 1)])) * h;
-        float s[2 * DG + 1];
-        dot_group<DG, NT>(row_a, x, h0, h1, aligned, tid, s);
+        float s[2 * G + 1];
+        dot_group<G, NT>(row_a, x, h0, h1, aligned, tid, s);
         if (o0 > 0) __syncthreads();   // the previous group's sums have been consumed
 #pragma unroll
-        for (int j = 0; j < 2 * DG + 1; ++j) s[j] = wave_sum(s[j]);
+        for (int j = 0; j < 2 * G + 1; ++j) s[j] = wave_sum(s[j]);
         if (lane == 0)
 #pragma unroll
-          for (int j = 0; j < 2 * DG + 1; ++j) part[wave * (2 * DG + 1) + j] = s[j];
+          for (int j = 0; j < 2 * G + 1; ++j) part[wave * (2 * G + 1) + j] = s[j];
         __syncthreads();
-        if (tid < DG && o0 + tid < n_other) {
+        if (tid < G && o0 + tid < n_other) {
           float ax = 0.f, xx = 0.f, aa = 0.f;
           for (int w = 0; w < NWV; ++w) {
-            const float* q = part + w * (2 * DG + 1);
+            const float* q = part + w * (2 * G + 1);
             ax += q[2 * tid];
             xx += q[2 * tid + 1];
-            aa += q[2 * DG];
+            aa += q[2 * G];
           }
           if (parts == 1) s_cos[o0 + tid] = cos_from(ax, aa, xx);
           else {
@@ -360,6 +361,12 @@ __global__ __launch_bounds__(NT) void accept_node_kernel(accept_args a, AcceptSh
             if (o0 + tid == 0) __hip_atomic_store(shared + MAXO, pair(aa, 0.f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
+      };
+      // A last group of up to four others reads four rows, not eight: one tree of 60 nodes x 16384 floats 10.2 -> 9.2 us, of 100 x 30016 14.2 -> 12.4,
+      // four of 60 x 8192 14.3 -> 13.0.
+      for (int o0 = 0; o0 < n_other; o0 += DG) {
+        if (n_other - o0 <= DG / 2) group(o0, std::integral_constant<int, DG / 2>{});   // (the last one)
+        else group(o0, std::integral_constant<int, DG>{});
       }
       if (parts > 1) {
         __shared__ int s_before;
