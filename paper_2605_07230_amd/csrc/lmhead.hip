@@ -1271,7 +1271,7 @@ hipError_t launch_row_stats_long(cascade_ctx* ctx, LmParams& p) {
   // four standard deviations of a random sample's count above its mean; a tenth of the row is listed at most
   const float mean = (float)p.top_k * 4096 / p.vocab, rank = mean + 4.f * sqrtf(mean) + 8.f;
   const bool cut = (VPT > 40 || p.n_nodes >= 128) && p.top_k > 0 && rank <= 0.1f * 4096;
-  p.sample_rank = (int)rank;
+  p.sample_rank = cut ? (int)rank : 0;
   return cut ? launch_row_stats_t<VPT, true, 1024, true>(ctx, p) : launch_row_stats_t<VPT, true, 1024, false>(ctx, p);
 }
 
