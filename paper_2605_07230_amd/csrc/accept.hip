@@ -140,6 +140,8 @@ __device__ __forceinline__ void dot_group(const T* a, const T* const (&x)[G], in
 constexpr int MAXO = 2 * MAXW;   // others of a node: parent + (siblings - 1) + children <= 1 + 63 + 64
 static_assert(MAXO + 1 == ACCEPT_SUMS, "the workspace is sized for these");
 
+constexpr unsigned CU_LDS = 160 << 10;   // of a compute unit, in bytes
+
 // Where the workgroups of one node meet (wide rows): a counter that is zero between calls, and the partial sums.
 struct AcceptShare {
   int* arrived;                 // [nodes]
@@ -463,8 +465,13 @@ hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
     if (parts > 1 && recorded(ctx->stream)) parts = 1;
   }
   grid.x = parts;
+  // Gram tiles of up to two nodes per compute unit: LDS is set aside so that two workgroups fit on one and no third, although the registers would
+  // hold three and more; the nodes then spread over the whole chip, where three on one unit end last.  462 nodes x 4096 of
+  // eight ragged trees 9.95 -> 8.25 us with the weights and rows warm; with cold rows, with equal trees and with few nodes the same within 2 %.  Beyond
+  // that many nodes three at a time hide more of the latency (1024 nodes 17.5, two at a time 17.8).
+  const unsigned apart = mfma && a->n_nodes_total <= 2 * ctx->n_cu ? CU_LDS / 3 : 0;   // beside the kernel's own, more than a third
   // (Gram tiles on eight waves: 462 nodes 10.2 -> 12.1 us, 1024 nodes 18 -> 23.6, fewer nodes the same)
-#define CASCADE_LAUNCH_ACCEPT(T, NT, HOW) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, HOW>), grid, dim3(NT), 0, ctx->stream, *a, share, ctx->dev_status)
+#define CASCADE_LAUNCH_ACCEPT(T, NT, HOW) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, HOW>), grid, dim3(NT), apart, ctx->stream, *a, share, ctx->dev_status)
   if (mfma) { if (a->hidden == 4096) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES_4096); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES); }
   else if (bf16) { if (narrow) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_NARROW); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_SWEPT); }
   else { if (narrow) CASCADE_LAUNCH_ACCEPT(float, 512, ROWS_NARROW); else CASCADE_LAUNCH_ACCEPT(float, 512, ROWS_SWEPT); }
