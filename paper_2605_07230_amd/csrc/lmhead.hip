@@ -794,7 +794,10 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
     }
     auto first_sweep = [&](int jj0, int jj1) {
       if (CUT && cutting) file(4 * jj0, 4 * jj1, [&](float v) { return v >= cut; });
-      else sweep(jj0, jj1);
+      else {
+        if (CUT && jj0 == 0) __syncthreads();   // the sweep counts into the bins that other waves have just cleared
+        sweep(jj0, jj1);
+      }
     };
     first_sweep(0, NREG);
     if (NPRE > 0) {

@@ -48,3 +48,66 @@ def test_rows_whose_sample_misleads(vocab, law):
         g = logits.double()
         ref = torch.logsumexp(g.masked_fill(g < kth.double()[:, None], -float("inf")), 1)
         assert torch.all((lse.double() - ref).abs() <= 1e-5 + 2.0 ** -23 * ref.abs()), k
+
+
+# entries that are not -inf, how many of them the sample holds, k
+FEW_FINITE = {"few": (128, 6, (20, 50)), "thousands": (2400, 100, (2000,))}
+
+
+def _delta(law, vocab, at, gen):
+    """What a misled row has added to the values of the ordinary ones."""
+    delta = torch.zeros(vocab, device="cuda")
+    if law in FEW_FINITE:
+        finite, sampled, _ = FEW_FINITE[law]
+        rest = torch.ones(vocab, dtype=torch.bool, device="cuda")
+        rest[at] = False
+        rest = torch.nonzero(rest).flatten()
+        keep = torch.cat([at[torch.randperm(len(at), device="cuda", generator=gen)[:sampled]],
+                          rest[torch.randperm(len(rest), device="cuda", generator=gen)[:finite - sampled]]])
+        delta[:] = -3e38      # twice that is -inf
+        delta[keep] = 0.0
+    elif law == "one_large":
+        delta[at[1234]] = 1e6
+    else:
+        delta[at] = 10.0 if law == "sample_high" else -10.0
+    return delta
+
+
+def _bins(row, at, k):
+    """The bins, of 4096 over the finite range of the sample, of the sample's entry that makes the cut and of the row's k-th largest."""
+    sample = row[at].double()
+    lo, hi = sample[sample > -float("inf")].min(), sample.max()
+    mean = k * 4096 / len(row)
+    rank = int(mean + 4 * mean ** 0.5 + 8)
+    return [int(torch.nan_to_num((torch.topk(x.double(), n).values[-1] - lo) * 4096 / (hi - lo), neginf=0.0).clamp(0, 4095)) for x, n in ((sample, rank), (row, k))]
+
+
+@pytest.mark.parametrize("vocab", [33088, 45060, 57344, 65532, 65536])
+@pytest.mark.parametrize("law", ["few", "thousands", "one_large", "sample_high", "sample_low"])
+def test_misled_and_ordinary_rows_in_turn(vocab, law):
+    """More rows than compute units, so that a workgroup takes a misled row and then an ordinary one, or the other way round.  "few",
+    "thousands" and "one_large" are samples whose cut lies in their lowest bin, which says nothing, while the k-th largest entry of the row does not."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 2 * units + 5
+    print(f"[row stats] vocab={vocab} rows={n} {law}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    at = _sampled(vocab)
+    w = torch.stack([torch.randn(vocab, device="cuda", generator=gen), _delta(law, vocab, at, gen)], dim=1)
+    rows = torch.arange(n, device="cuda")
+    misled = (rows + rows // units) % 2 == 0
+    h = torch.stack([torch.linspace(0.5, 2.0, n, device="cuda"), 2.0 * misled], dim=1)
+    ctx = binding.Context(max_rows=1, max_nodes_total=n, max_nodes_per_tree=1, max_prefix=0, n_heads=1, head_dim=64, hidden=2, vocab=vocab)
+    logits = torch.empty(n, vocab, device="cuda")
+    mx, thr, lse = (torch.full((n,), float("nan"), device="cuda") for _ in range(3))
+    for k in FEW_FINITE[law][2] if law in FEW_FINITE else (1,) if law == "one_large" else (50, 2000):
+        binding.lmhead_softmax_cfg(ctx, h_cond=h, h_uncond=None, w=w, cfg_scale=1.0, temperature=1.0, top_k=k, logits=logits, row_max=mx,
+                                   row_thr=thr, row_lse=lse)
+        if law in FEW_FINITE or law == "one_large":
+            sample_bin, row_bin = _bins(logits[0], at, k)
+            assert sample_bin == 0 < row_bin
+        kth = torch.topk(logits, k, dim=1).values[:, -1]
+        assert torch.equal(mx, logits.max(1).values) and torch.equal(thr, kth), k
+        g = logits.double()
+        ref = torch.logsumexp(g.masked_fill(g < kth.double()[:, None], -float("inf")), 1)
+        assert torch.all((lse.double() - ref).abs() <= 1e-5 + 2.0 ** -23 * ref.abs()), k

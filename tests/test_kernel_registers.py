@@ -89,6 +89,50 @@ def test_row_statistics_prefetch_uses_m0_only_for_its_loads(tmp_path):
         assert body.count("global_load_lds_dwordx4") >= 8 and "scratch_" not in body
 
 
+def _counts_behind_a_clearing(body):
+    """Pairs (clearing of a histogram, LDS count that is reached from it over some path without a barrier)."""
+    code, labels = [], {}
+    for line in body.replace(";;#ASMSTART\n\ts_waitcnt vmcnt(0)", "inline_wait").splitlines():
+        line = line.split(";")[0].strip()
+        if line.startswith(".LBB"):
+            labels[line.split(":")[0]] = len(code)
+        elif line and line[0] != ".":
+            code.append(line)
+    found = []
+    for at, clear in enumerate(code):
+        if not clear.startswith("ds_write2st64_b32"):
+            continue
+        seen, todo = set(), [at + 1]
+        while todo:
+            i = todo.pop()
+            if i in seen:
+                continue
+            seen.add(i)
+            op, *args = code[i].split()
+            if op in ("s_barrier", "s_endpgm", "inline_wait"):
+                continue
+            if op == "ds_add_u32":
+                found.append((clear, code[i]))
+                continue
+            if op.startswith(("s_cbranch", "s_branch")):
+                todo.append(labels[args[0]])
+            if op != "s_branch":
+                todo.append(i + 1)
+    return found
+
+
+def test_row_statistics_clear_and_count_with_a_barrier_between(tmp_path):
+    """Every thread clears its share of a histogram that all waves count into: no path of any instance leads from a clearing to a count but
+    over a barrier.  (The wait in front of the prefetched chunks ends a path: they are counted only where the chunks in front of it were.)"""
+    _, text = _kernel_stats("lmhead.hip", tmp_path)
+    bodies = re.findall(r"^(_ZN\S*row_stats_kernel\S*):[^\n]*\n(.*?)\.amdhsa_kernel", text, flags=re.S | re.M)
+    assert len(bodies) == 18
+    for name, body in bodies:
+        cut = "ELb1EEEv" in name
+        assert body.count("ds_write2st64_b32") >= (7 if cut else 5) and "ds_add_u32" in body, name
+        assert not _counts_behind_a_clearing(body), name
+
+
 LDS_DIRECT = {"s_waitcnt", "s_barrier", "s_mov_b32", "s_nop", "global_load_lds_dwordx4"}
 
 
