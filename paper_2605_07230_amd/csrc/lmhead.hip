@@ -1117,13 +1117,6 @@ LmPlan lm_plan(const lmhead_args* a, bool packed_w, bool premix, bool cfg, int n
     // but there every other tile is twice as close to the exact sums
     return i != 6 || (V % 256 == 0 && rows >= (cfg ? 512 : 257));
   };
-  // Few mixed rows whose streamed weights are one whole round of 128 x 256 tiles, or nearly: those, though most of their rows are padding.  64 x 256
-  // tiles and so, projection without its mix, us: 60 nodes x 65536 x 4096 91.2 and 87.2 (the step 137.7 and 136.2-137.5), 30 nodes 90.8 and 86.9
-  // (136.0 and 133.3), 16 nodes 89.0 and 85.8 (132.2 and 130.9); x 2048 50.0 and 49.2, the step the same; x 62016 (243 tiles) the same; 64 x
-  // 47296 74.8 and 82.9.
-  const int wide_tiles = (V + LM_TILES[5].cols - 1) / LM_TILES[5].cols;
-  if (premix && rows <= 64 && a->hidden >= 3072 && wide_tiles <= n_cu && wide_tiles * 100 >= n_cu * 97 && lm_streams(5, rows, V, a->hidden))
-    return {5, 5, V, lm_estimate_us(0.f, V, a->hidden)};
   LmPlan best = {0, 0, V, INFINITY};
   for (int i = 0; i < 7; ++i) {
     if (!usable(i)) continue;

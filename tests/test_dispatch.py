@@ -50,6 +50,14 @@ def test_both_ways_of_loading_weights_are_tested_in_every_tile():
     assert ring <= reached and {s for t, _, _, s in reached if t == 5} == {True, False} and {s for t, _, _, s in reached if t == 6} <= {False}
 
 
+@pytest.mark.parametrize("rows", [1, 33, 64])
+@pytest.mark.parametrize("vocab", [63552, 65536])
+@pytest.mark.parametrize("hidden", [3072, 4096, 5120])
+def test_few_mixed_rows_are_cut_like_plain_ones(rows, vocab, hidden):
+    """Up to 64 rows, mixed or not, fill one row tile of 64: what their weights divide into does not lead past the costs of the tiles."""
+    assert _tiles(rows, vocab, hidden, "mixed", True) == _tiles(rows, vocab, hidden, "plain", True) == (2, 2, vocab)
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_every_attention_cut_is_tested(head_dim):
     reached, loads = set(), set()
