@@ -465,11 +465,16 @@ hipError_t launch_accept(cascade_ctx* ctx, const accept_args* a) {
     if (parts > 1 && recorded(ctx->stream)) parts = 1;
   }
   grid.x = parts;
-  // Gram tiles of up to two nodes per compute unit: LDS is set aside so that two workgroups fit on one and no third, although the registers would
-  // hold three and more; the nodes then spread over the whole chip, where three on one unit end last.  462 nodes x 4096 of
-  // eight ragged trees 9.95 -> 8.25 us with the weights and rows warm; with cold rows, with equal trees and with few nodes the same within 2 %.  Beyond
-  // that many nodes three at a time hide more of the latency (1024 nodes 17.5, two at a time 17.8).
-  const unsigned apart = mfma && a->n_nodes_total <= 2 * ctx->n_cu ? CU_LDS / 3 : 0;   // beside the kernel's own, more than a third
+  // Rows of 4096, up to two nodes per compute unit: LDS is set aside so that two workgroups fit on one and no third, although the registers would
+  // hold three; the nodes then spread over the whole chip, where three on one unit end last.  Only where all workgroups of the launch
+  // could be resident at three per unit, those of nodes that a tree does not have included: more of them wait for places that are fewer so.
+  // Rows cold, registers' limit and so, us, means over eight sets of ragged trees of at most 512 nodes: 8 prompts x 40-80 nodes 12.4 and 11.6, 12 x 20-56 11.5
+  // and 10.7, 16 x 20-40 10.9 and 10.7, 4 x 60-140 12.0 and 11.9 (rows warm 10.7 and 10.6, 10.0 and 9.8, 9.5 and 9.8, 10.7 and 11.2); in contexts for trees
+  // twice as large 12 prompts 11.4 and 11.5, 16 prompts 11.2 and 12.6.  Beyond two nodes per unit three at a time hide more of the latency (1024 nodes 17.5, two
+  // at a time 17.8).  Other widths, whose kernel the registers let stand six times on a unit, are mostly slower so (2048: 16 x 20-40 8.5 and 9.5, 1536: 496
+  // nodes 8.5 and 11.4, 1152: 511 nodes 8.5 and 9.5).
+  const bool spread = mfma && a->hidden == 4096 && a->n_nodes_total <= 2 * ctx->n_cu && grid.y * grid.z <= 3u * ctx->n_cu;
+  const unsigned apart = spread ? CU_LDS / 3 : 0;   // beside the kernel's own, more than a third
   // (Gram tiles on eight waves: 462 nodes 10.2 -> 12.1 us, 1024 nodes 18 -> 23.6, fewer nodes the same)
 #define CASCADE_LAUNCH_ACCEPT(T, NT, HOW) CASCADE_TIMED_LAUNCH(t, (accept_node_kernel<T, NT, HOW>), grid, dim3(NT), apart, ctx->stream, *a, share, ctx->dev_status)
   if (mfma) { if (a->hidden == 4096) CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES_4096); else CASCADE_LAUNCH_ACCEPT(uint16_t, 256, ROWS_TILES); }
