@@ -595,7 +595,7 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // Fast path (top-k active): the order-preserving radix rounds above put sign, exponent and three mantissa bits
 // into the first digit, so a row of logits lands in a few dozen of its 4096 bins and the 65536 LDS atomics of
 // a long row serialise on them.  Instead the first round bins LINEARLY, bin(x) = clamp(int(x s + c), 0, 4095),
-// over the range of a 4096-entry sample of the row (each thread's first load), while the rest of the row is
+// over the range of a sample of the row (each thread's first load: 4096 entries, in 512 threads 2048), while the rest of the row is
 // still arriving.  Any non-decreasing bin function keeps the selection exact: with `above` entries in the bins
 // over bin B and above < k <= above + hist[B], the k-th largest is the (k - above)-th largest of bin B.  A
 // second sweep over the registers re-evaluates the same fused multiply-add and files every entry of bin B or
@@ -608,10 +608,13 @@ __device__ __forceinline__ void find_bin_from_top(const int* hist, int k, int ti
 // 6.0 us, 462 x 16384 15.3 -> 14.1, 300 x 33088 with k = 8000, where lists per thread overflowed, 0.27 of the time, 1024 x 65536
 // 76.6 -> 74.0.  (Two workgroups per compute unit, at 64 registers: 462 x 16384 16.3 us, spilled from 24576 entries on.)
 // CUT, rows of more than 32768 entries: counting every entry in LDS is most of the work there.  The entries of the sample alone are counted,
-// while the rest of the row arrives, and give a value that somewhat more than k entries of the row will reach; the one sweep lists
-// those, and the bins are filled from the lists.  Any cut that at least k entries reach keeps the selection exact; where fewer do, or a
-// list is full, every entry is counted after all.  So that the sample stands for the row, each wave begins elsewhere.
+// while the rest of the row arrives, and give a value that somewhat more than k entries of the row are expected to reach; the one sweep lists
+// those, and the bins are filled from the lists.  Any cut that at least k entries reach keeps the selection exact; where fewer do, a
+// list is full, or the sample's cut lies in its lowest bin, every entry is counted after all.
 // 1024 rows x 65536 71.1 -> 65.7 us (see launch_row_stats_long for where it pays).
+// Where there is a cut, and in the kernels of 512 threads, each wave begins elsewhere in the row (the sample is a run of 256 entries per wave), so that
+// the sample stands for rows whose entries are ordered as well: 1024 x 65536 of which one range of a quarter is finite 479 -> 60 us, 300 x 8192 falling
+// along the row, k = 5000, 25 -> 8 with samples from the row's beginning and so.
 // Rows the fast path does not fit (degenerate or non-finite sample range, k-th largest in the lowest bin, more
 // than RS_CAND candidates, a wave with more than RS_CAP - 64 listed entries) take the radix rounds: slow, exact.
 constexpr int RS_LIST = 12288;  // listed entries, dealt evenly to the waves of a workgroup
@@ -645,9 +648,9 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
   const int V = p.vocab;
   const bool topk = p.top_k > 0 && p.top_k < V;
   constexpr int NCH = VPT / 4;
-  // CUT: wave w begins w / NW of the way through the whole chunks
-  static_assert(!CUT || VEC, "the first load of every wave lies in the row");
-  const int rot = CUT ? __builtin_amdgcn_readfirstlane(wave) * (V / (4 * NT)) / NW : 0;
+  constexpr bool SPREAD = CUT || NT == 512;   // wave w begins w / NW of the way through the whole chunks
+  static_assert(!SPREAD || VEC, "the first load of every wave lies in the row");
+  const int rot = SPREAD ? __builtin_amdgcn_readfirstlane(wave) * (V / (4 * NT)) / NW : 0;
   // chunks that the row fills for sure (it did not fit the next smaller frame)
   constexpr int SURE = NT == 512 ? NCH - 4 : VEC ? (VPT == 64 ? 12 : (VPT == 16 ? 2 : (VPT >= 24 ? NCH - 2 : (VPT == 8 ? 1 : 0)))) : (VPT == 64 ? 4 : (VPT == 16 ? 1 : 0));
   // Long rows: the last NPRE 16 KiB chunks of the NEXT row are fetched into LDS (LDS-direct loads, no registers
@@ -658,11 +661,11 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
   constexpr int NREG = NCH - NPRE;   // chunks loaded into registers
   float* const pre = (float*)(rs_smem_raw + RS_PRE_OFFSET);
   const unsigned pre_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)pre) + 1024u * (unsigned)__builtin_amdgcn_readfirstlane(wave);
-  // Chunk jj of this thread, element c, is vocabulary entry 4 (tid + NT jj) + c: chunks 0 .. NREG-1 are loaded
-  // into registers (and swept in the order they arrive; chunk 0, always inside the row, is the sample), chunks
-  // NREG .. NCH-1 come from LDS and are swept last.  Entries past V are masked to -inf before use.  Every load
-  // is unconditional (addresses clamped into the row): all of them are in flight at once.
-  auto mch = [&](int jj) { return !CUT ? jj : (jj + rot < NCH ? jj + rot : jj + rot - NCH); };   // chunk that slot jj holds
+  // Slot jj of this thread, element c, holds vocabulary entry 4 (tid + NT mch(jj)) + c: chunk jj of the row, or, where samples are spread, the
+  // jj-th from the one that the thread's wave begins with, around the row's end.  Slots 0 .. NREG-1 are loaded into registers (and swept in the order they
+  // arrive; slot 0, always inside the row if that fills a chunk, is the sample), slots NREG .. NCH-1 come from LDS and are swept last.  Entries
+  // past V are masked to -inf before use.  Every load is unconditional (addresses clamped into the row): all of them are in flight at once.
+  auto mch = [&](int jj) { return !SPREAD ? jj : (jj + rot < NCH ? jj + rot : jj + rot - NCH); };   // chunk that slot jj holds
   const bool whole = V == VPT * NT;   // workgroup-uniform: a full row needs no masking
   float x[VPT];
   // (The thread index is passed through an empty asm so that the per-chunk offsets and masks below are recomputed
@@ -698,8 +701,8 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
       int t = tid;
       asm volatile("" : "+v"(t));
 #pragma unroll
-      for (int jj = CUT || jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
-        if (!CUT || 4 * NT * (mch(jj) + 1) > V)   // (a branch of the wave)
+      for (int jj = SPREAD || jj0 > SURE ? jj0 : SURE; jj < jj1; ++jj)
+        if (!SPREAD || 4 * NT * (mch(jj) + 1) > V)   // (a branch of the wave)
 #pragma unroll
           for (int c = 0; c < 4; ++c) x[4 * jj + c] = 4 * (t + NT * mch(jj)) + c < V ? x[4 * jj + c] : -INFINITY;
     }
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(NT, 4) void row_stats_kernel(LmParams p) {
         asm volatile("" : "+v"(t));
 #pragma unroll
         for (int jj = jj0; jj < jj1; ++jj) {
-          if ((!CUT && jj < SURE) || 4 * NT * (mch(jj) + 1) <= V) chunk(jj, always);   // uniform in a wave
+          if ((!SPREAD && jj < SURE) || 4 * NT * (mch(jj) + 1) <= V) chunk(jj, always);   // uniform in a wave
           else chunk(jj, [&](int c) { return 4 * (t + NT * mch(jj)) + c < V; });
         }
       } else {
@@ -1072,7 +1075,7 @@ bool lm_streams(int tile, int rows, int vocab, int hidden) {
 // whatever the hidden dimension (start and stores), and a round that is not full takes nearly as long.  Projection in 128 x 256 tiles, where each weight
 // is requested twice, which were taken, and so, us: 256 x 65536 x 4096 154.1 and 151.5, 184 rows 154.5 and 144.3, 130 rows 149.7 and 139.5, 200 x
 // 40000 x 4096 111.5 and 104.8, 200 x 65536 x 2048 88.1 and 87.9; with two tiles of rows the other way round, 400 x 36032 x 4096 154.5 and 161.4.
-// (Plain rows keep the costs they had.)
+// (Plain rows, for which 256 x 128 is up to 10 % faster as well, still take the old costs.)
 constexpr LmTile LM_STREAMED_256X128 = {256, 128, 63.f, 0.937f, 0.9f};
 constexpr float LM_STREAMED_START_US = 8.f;
 
@@ -1264,7 +1267,8 @@ hipError_t launch_row_stats_t(cascade_ctx* ctx, const LmParams& p) {
 // the sample takes longer than the counting, and with long lists 60 x 65536 with k = 8000 14.7 and 14.9, 400 such rows 38.8 and 41.0.
 template <int VPT>
 hipError_t launch_row_stats_long(cascade_ctx* ctx, LmParams& p) {
-  // four standard deviations of a random sample's count above its mean; a tenth of the row is listed at most
+  // The sample is sixteen runs of 256 entries.  If they stand for the row, the cut lets four standard deviations of a random sample's count more
+  // than k entries through; where neighbours are alike it may let through fewer, or too many for the lists (704 per wave).  A tenth of the row is asked for at most.
   const float mean = (float)p.top_k * 4096 / p.vocab, rank = mean + 4.f * sqrtf(mean) + 8.f;
   const bool cut = (VPT > 40 || p.n_nodes >= 128) && p.top_k > 0 && rank <= 0.1f * 4096;
   p.sample_rank = cut ? (int)rank : 0;
