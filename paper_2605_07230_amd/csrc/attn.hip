@@ -57,15 +57,17 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 //   S^T = K Q^T   lane (l16, g) loads 16 bytes at d = 16 ks + 4 g of key / query l16 and feeds element c of both to the
 //                 c-th product; the result holds keys 4 g + r of query l16;
 //   O^T = V^T P^T product r takes P^T straight from register r of that result, and element c of the 16 bytes of key 4 g + r's
-//                 value at d = 64 h + 4 l16: its row l16 stands for that d + c.
+//                 value at d = 64 h + 4 l16: its row l16 stands for that d + c (element loads: d = 16 db + l16).
 // Nothing passes through LDS before the merge.  Bound by the trips to memory, one after the other (the row's place; queries, parents and
 // the first tile), by the 50 GB/s at which one compute unit receives keys and values that no cache near it holds (8 heads x 271 keys are 139 KB for
 // each of 8 units: 2.8 us), and by the tile that some wave has to do alone at the end.  15 nodes x 8 heads x 64, 256 keys: 10.6 us with
 // parents staged in LDS behind a barrier, values loaded four bytes at a time and sixteen parts read by every thread of the merge, now 9.7 (a step 28.3 and 26.9);
 // 60 nodes, 1000 keys 23.9 and 20.3-20.9, 200 nodes, 320 keys 14.9 and 13.2-14.5.  Two or three tiles of a wave side by side in 8 or 12 waves are
 // slower (10.1-10.4, 20.6-22.0).
-// DB = 16-wide blocks of head_dim; VEC: rows can be read 16 bytes at a time (otherwise element by element).
-template <int DB, int NW, bool VEC>
+// DB = 16-wide blocks of head_dim; VEC, VEC_V: queries and keys, and values, can be read 16 bytes at a time (otherwise element by element, values of
+// neighbouring lanes side by side: two trees of 60 nodes x 4 heads x 70, 400 keys 29.7 us with four neighbouring elements per lane, 25.5 so; values alone off
+// the 16-byte grid, four trees of 60 nodes x 8 heads x 64, 1000 keys 54.5 with element loads for everything, 21.6 so).
+template <int DB, int NW, bool VEC, bool VEC_V>
 __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_rows, int D) {
   extern __shared__ __align__(16) float f32_smem[];   // [NW][16 queries][16 DB + 4] partial outputs, [NW][16][2] (m, l)
   __shared__ int s_parent[CASCADE_MAX_TREE];
@@ -110,6 +112,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   const float* vtr = (const float*)p.v_tree + ((int64_t)lo * p.n_kv_heads + kvh) * D;
   const int64_t tree_pitch = (int64_t)p.n_kv_heads * D;
   // tile registers; keys past the end of the tile's source: clamped, masked below
+  static_assert(VEC || !VEC_V, "load4 serves both");
   f32x4 q[DB], ot[DB], k[DB], v[4][DB / 4];
   auto request_k = [&](int t) {
     const bool tree = t >= n_pt;
@@ -125,7 +128,11 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
       const int key = min(16 * (tree ? t - n_pt : t) + 4 * g + r, (tree ? T : P) - 1);
       const float* row = (tree ? vtr : vc) + (int64_t)key * (tree ? tree_pitch : p.sp);
 #pragma unroll
-      for (int h = 0; h < DB / 4; ++h) v[r][h] = load4(row, 64 * h + 4 * l16);
+      for (int h = 0; h < DB / 4; ++h)
+        if (VEC_V) v[r][h] = load4(row, 64 * h + 4 * l16);
+        else
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[r][h][c] = row[min(64 * h + 16 * c + l16, D - 1)];
     }
   };
 #pragma unroll
@@ -253,14 +260,18 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p, int n_r
   int t = t0;
   for (; t + NW < nt; t += NW) step(t, std::true_type{});
   if (t < nt) step(t, std::false_type{});
-  // merge: lane (l16, g) holds d = 64 (db / 4) + 16 g + 4 c + db % 4 of query l16 (a value's 16 bytes feed four products)
+  // merge: lane (l16, g) holds d = 64 (db / 4) + 16 g + 4 c + db % 4 of query l16 (a value's 16 bytes feed four products; element
+  // loads: d = 16 db + 4 g + c)
   l = rows4_sum(l);
   float* mo = f32_smem + (wave * 16 + l16) * OP;
   float* ml = f32_smem + NW * 16 * OP;
 #pragma unroll
   for (int h = 0; h < DB / 4; ++h)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) *(f32x4*)(mo + 64 * h + 16 * g + 4 * c) = f32x4{ot[4 * h][c], ot[4 * h + 1][c], ot[4 * h + 2][c], ot[4 * h + 3][c]};
+    for (int c = 0; c < 4; ++c) {
+      if (VEC_V) *(f32x4*)(mo + 64 * h + 16 * g + 4 * c) = f32x4{ot[4 * h][c], ot[4 * h + 1][c], ot[4 * h + 2][c], ot[4 * h + 3][c]};
+      else *(f32x4*)(mo + 64 * h + 16 * c + 4 * g) = ot[4 * h + c];
+    }
   if (g == 0) {
     ml[(wave * 16 + l16) * 2] = m;
     ml[(wave * 16 + l16) * 2 + 1] = l;
@@ -1224,18 +1235,24 @@ hipError_t launch_ring_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid) {
 
 }  // namespace
 
-template <int DB, int NW, bool VEC>
-hipError_t launch_f32_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid, int n_rows, int D) {
+template <int DB, int NW, bool VEC, bool VEC_V>
+hipError_t launch_f32_k(cascade_ctx* ctx, const AttnParams& p, dim3 grid, int n_rows, int D) {
   constexpr int smem = (NW * 16 * (16 * DB + 4) + NW * 32) * 4;
+  auto kern = attn_f32_kernel<DB, NW, VEC, VEC_V>;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_f32_kernel<DB, NW, VEC>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   KernelTimer t(ctx, CASCADE_K_ATTN);
-  CASCADE_TIMED_LAUNCH(t, (attn_f32_kernel<DB, NW, VEC>), grid, dim3(64 * NW), smem, ctx->stream, p, n_rows, D);
+  CASCADE_TIMED_LAUNCH(t, kern, grid, dim3(64 * NW), smem, ctx->stream, p, n_rows, D);
   return hipGetLastError();
+}
+template <int DB, int NW>
+hipError_t launch_f32_t(cascade_ctx* ctx, const AttnParams& p, dim3 grid, int n_rows, int D, bool vec, bool vec_v) {
+  if (vec) return vec_v ? launch_f32_k<DB, NW, true, true>(ctx, p, grid, n_rows, D) : launch_f32_k<DB, NW, true, false>(ctx, p, grid, n_rows, D);
+  return launch_f32_k<DB, NW, false, false>(ctx, p, grid, n_rows, D);
 }
 
 hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
@@ -1244,10 +1261,11 @@ hipError_t launch_tree_attn_f32(cascade_ctx* ctx, const tree_attn_args* a) {
   // blocks of 16 query rows: at most one partly filled one per row of the batch
   dim3 grid((unsigned)((int64_t)a->n_nodes_total * p.group / 16 + a->n_rows), a->n_kv_heads);
   const bool vec = D % 4 == 0 && ((a->cache_stride_row | a->cache_stride_head | a->cache_stride_pos) & 3) == 0 &&
-                   (((uintptr_t)a->q | (uintptr_t)a->k_tree | (uintptr_t)a->k_cache | (uintptr_t)a->v_tree | (uintptr_t)a->v_cache) & 15) == 0;
-  if (D <= 64) return vec ? launch_f32_t<4, 16, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<4, 16, false>(ctx, p, grid, a->n_rows, D);
-  if (D <= 128) return vec ? launch_f32_t<8, 8, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<8, 8, false>(ctx, p, grid, a->n_rows, D);
-  return vec ? launch_f32_t<16, 4, true>(ctx, p, grid, a->n_rows, D) : launch_f32_t<16, 4, false>(ctx, p, grid, a->n_rows, D);
+                   (((uintptr_t)a->q | (uintptr_t)a->k_tree | (uintptr_t)a->k_cache) & 15) == 0;
+  const bool vec_v = (((uintptr_t)a->v_tree | (uintptr_t)a->v_cache) & 15) == 0;
+  if (D <= 64) return launch_f32_t<4, 16>(ctx, p, grid, a->n_rows, D, vec, vec_v);
+  if (D <= 128) return launch_f32_t<8, 8>(ctx, p, grid, a->n_rows, D, vec, vec_v);
+  return launch_f32_t<16, 4>(ctx, p, grid, a->n_rows, D, vec, vec_v);
 }
 
 // 16 NQ NW query rows per workgroup, keys split p.n_split ways (partials, then the merge kernel)
