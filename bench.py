@@ -42,30 +42,30 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 MEASURED_TRAFFIC_KIB = {
     ("stress_1024px", "accept"): (17655.2, 192.6),
-    ("stress_1024px", "attn"): (293578.1, 18432.0),
-    ("stress_1024px", "lmhead"): (394464.2, 262144.0),
+    ("stress_1024px", "attn"): (293580.6, 18432.0),
+    ("stress_1024px", "lmhead"): (393752.2, 262144.0),
     ("stress_1024px", "pack_h"): (8200.5, 8192.0),
-    ("stress_1024px", "row_stats"): (131220.6, 97.3),
-    ("stress_1024px", "select"): (713.5, 34.9),
-    ("janus_batched", "accept"): (7521.2, 83.8),
-    ("janus_batched", "attn"): (49278.1, 8118.0),
-    ("janus_batched", "lmhead"): (82066.0, 28864.0),
+    ("stress_1024px", "row_stats"): (131225.1, 97.9),
+    ("stress_1024px", "select"): (713.5, 34.8),
+    ("janus_batched", "accept"): (7521.2, 84.0),
+    ("janus_batched", "attn"): (49276.6, 8118.0),
+    ("janus_batched", "lmhead"): (82091.9, 28864.0),
     ("janus_batched", "pack_h"): (3616.5, 4096.0),
-    ("janus_batched", "row_stats"): (14527.5, 42.3),
-    ("janus_batched", "select"): (386.7, 18.4),
+    ("janus_batched", "row_stats"): (14543.0, 42.3),
+    ("janus_batched", "select"): (386.4, 18.4),
     ("janus_pro_7b", "accept"): (973.7, 11.2),
     ("janus_pro_7b", "attn"): (6515.1, 1080.0),
-    ("janus_pro_7b", "lmhead"): (67677.3, 3840.0),
+    ("janus_pro_7b", "lmhead"): (67672.8, 3840.0),
     ("janus_pro_7b", "pack_h"): (491.0, 480.0),
-    ("janus_pro_7b", "row_stats"): (1996.0, 5.6),
+    ("janus_pro_7b", "row_stats"): (2003.0, 5.6),
     ("janus_pro_7b", "select"): (77.0, 2.3),
     ("lumina_mgpt_7b_768", "accept"): (982.3, 11.2),
-    ("lumina_mgpt_7b_768", "attn"): (22197.1, 8160.0),
+    ("lumina_mgpt_7b_768", "attn"): (22196.8, 8160.0),
     ("lumina_mgpt_7b_768", "attn_merge"): (3975.5, 975.0),
-    ("lumina_mgpt_7b_768", "lmhead"): (267149.8, 15360.0),
-    ("lumina_mgpt_7b_768", "pack_h"): (488.5, 2048.0),
-    ("lumina_mgpt_7b_768", "row_stats"): (7827.0, 5.6),
-    ("lumina_mgpt_7b_768", "select"): (216.2, 8.7),
+    ("lumina_mgpt_7b_768", "lmhead"): (266775.1, 15360.0),
+    ("lumina_mgpt_7b_768", "pack_h"): (491.0, 480.0),
+    ("lumina_mgpt_7b_768", "row_stats"): (7830.5, 5.6),
+    ("lumina_mgpt_7b_768", "select"): (216.3, 8.7),
 }
 
 
